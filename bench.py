@@ -39,7 +39,7 @@ PEAK_ALU_TFLOPS = 78.6   # fp32 FMAs on the vector ALUs without the packed forms
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "hbm_traffic.json")
 KERNEL_SOURCES = {  # what the dominant kernel of each benchmark configuration is built from
     1: ["igemm_small.hip", "igemm_common.h", "conv_shape.h"],
-    2: ["igemm32_dma.hip", "igemm_conv.hip", "igemm_common.h", "lds_dma.h", "conv_shape.h"],
+    2: ["igemm32_split.hip", "igemm32_dma.hip", "igemm_conv.hip", "igemm_common.h", "lds_dma.h", "conv_shape.h"],
     3: ["igemm16_fast.hip", "igemm_conv.hip", "igemm_common.h", "lds_dma.h", "conv_shape.h"],
     4: ["igemm_small.hip", "igemm_common.h", "conv_shape.h"],
     5: ["igemm16_fast.hip", "igemm_conv.hip", "igemm_common.h", "lds_dma.h", "conv_shape.h"],

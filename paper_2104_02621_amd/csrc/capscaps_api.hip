@@ -129,7 +129,7 @@ int run(const void* input, const void* kernel, void* out, const ConvShape& s, in
             : path == CAPSCAPS_PATH_MFMA_TUNED16 ? capscaps::MfmaKernel::Tuned16
             : path == CAPSCAPS_PATH_MFMA_SMALL   ? capscaps::MfmaKernel::Small
                                                  : capscaps::MfmaKernel::Dma32;
-        const size_t need = own_choice ? capscaps::mfma_auto_workspace_bytes(s)
+        const size_t need = own_choice ? capscaps::mfma_kernel_workspace_bytes(s, capscaps::MfmaKernel::Auto)
                                        : capscaps::mfma_workspace_bytes(s);
         if (need > 0 && (workspace == nullptr || workspace_bytes < need))
             return CAPSCAPS_EWORKSPACE;
@@ -150,7 +150,7 @@ int status_from_hip(hipError_t err) { return hip_status(err); }
 
 size_t forward_workspace_bytes(const ConvShape& s)
 {
-    return choose_path(s) == CAPSCAPS_PATH_DIRECT ? 0 : mfma_auto_workspace_bytes(s);
+    return choose_path(s) == CAPSCAPS_PATH_DIRECT ? 0 : mfma_kernel_workspace_bytes(s, MfmaKernel::Auto);
 }
 
 bool forward_auto_repacks_kernel(const ConvShape& s) { return choose_path(s) != CAPSCAPS_PATH_DIRECT; }
@@ -295,12 +295,25 @@ int capscaps_conv_fwd_static(const void* input, const void* kernel, void* out, i
     ConvShape s;
     const int rc = fill_shape(s, N, H, W, C, M, kh, kw, stride, pad, D0, D1, D2, D3, dtype);
     if (rc != CAPSCAPS_OK) return rc;
-    // the scratch the library's own kernel choice needs must fit the fixed array
-    if (capscaps::forward_workspace_bytes(s) > (size_t)CAPSCAPS_STATIC_SCRATCH_BYTES)
-        return CAPSCAPS_ESCRATCH;
+    // the scratch must fit the fixed array: that of the library's own kernel choice, else that of
+    // a kernel that needs less (fp32 layers: the kernel tensor split into bf16 terms takes half as
+    // much again as repacked fp32 values, and larger tiles mean larger partial sums)
+    constexpr size_t room = CAPSCAPS_STATIC_SCRATCH_BYTES;
+    capscaps::MfmaKernel lean = capscaps::MfmaKernel::Auto;
+    if (capscaps::forward_workspace_bytes(s) > room) {
+        if (s.dtype != CAPSCAPS_FP32) return CAPSCAPS_ESCRATCH;
+        lean = capscaps::MfmaKernel::Generic;
+        if (capscaps::mfma_kernel_workspace_bytes(s, lean) > room) lean = capscaps::MfmaKernel::Small;
+        if (lean == capscaps::MfmaKernel::Small &&
+            (!capscaps::mfma_small_supported(s) || capscaps::mfma_kernel_workspace_bytes(s, lean) > room))
+            return CAPSCAPS_ESCRATCH;
+    }
     void* ws = nullptr;
     const int rs = scratch_of_current_device(&ws);
     if (rs != CAPSCAPS_OK) return rs;
+    if (lean != capscaps::MfmaKernel::Auto)
+        return hip_status(capscaps::launch_mfma(s, input, kernel, static_cast<float*>(out), ws,
+                                                static_cast<hipStream_t>(stream), lean));
     return run(input, kernel, out, s, CAPSCAPS_PATH_AUTO, ws, (size_t)CAPSCAPS_STATIC_SCRATCH_BYTES,
                static_cast<hipStream_t>(stream));
 }

@@ -85,7 +85,7 @@ bool mfma_dma32_supported(const ConvShape& s);
 bool mfma_small_supported(const ConvShape& s);
 size_t mfma_workspace_bytes(const ConvShape& s);  // enough for every MfmaKernel choice (with
                                                   // s.out16: for Auto, the only choice then)
-size_t mfma_auto_workspace_bytes(const ConvShape& s);  // for the kernel Auto resolves to only
+size_t mfma_kernel_workspace_bytes(const ConvShape& s, MfmaKernel which);  // for that kernel only
 hipError_t launch_mfma(const ConvShape& s, const void* in, const void* kernel, float* out,
                        void* workspace, hipStream_t stream, MfmaKernel which = MfmaKernel::Auto);
 

@@ -1,31 +1,27 @@
-// fp32 matrix-core kernel of the capsule convolution forward pass with direct-to-LDS copies.
-// Same implicit GEMM as the other igemm kernels (rows (pixel,d1), columns (m,d3),
-// K = (tap, c, d2); paper Algorithm 2).  It serves capsule rows of 3 floats (D2 a multiple of
-// 3: the 3x3x3 capsules of the paper's Fig. 2) as well as multiples of 4.
+// 16-bit matrix-core kernel of the capsule convolution forward pass, one tile row per lane, with
+// direct-to-LDS copies.  Same implicit GEMM as the other igemm kernels (rows (pixel,d1), columns
+// (m,d3), K = (tap, c, d2); paper Algorithm 2), for any D1 and D3: non-square and vector
+// capsules, which the 256x256-tile 16-bit kernel does not take, and 4x4 capsules.  This file
+// also holds the tile and split decisions of the fp32 kernel of the same row layout
+// (igemm32_split.hip).
 //
-// Unit of data movement: a 16-byte LDS slot holding CW = 3 or 4 consecutive d2 of one capsule
-// row ("chunk").  For CW = 3 the copy is a 12-byte buffer load, which the hardware places at
-// a 16-byte lane stride in LDS, so both cases read operands with one 16-byte LDS load per lane
-// and feed CW MFMA 32x32x2 instructions from it (element u of the lower and of the upper half
-// wave form the K pair of instruction u; the fourth float of a 3-float slot is never used).
+// Unit of data movement: a 16-byte LDS slot holding 8 consecutive d2 of one capsule row ("chunk");
+// lengths and offsets are counted in units of 4 bytes ("floats": a capsule row of 8, 16 or 32
+// halves is one of 4, 8 or 16 of them).  A chunk pair feeds one MFMA 32x32x16 per tile.
 //
 // Tile: 64*NW rows x 32*TN columns; wave w copies and contracts rows 64w..64w+63 (two MFMA
 // row tiles) against all TN column tiles.  Lane i of a wave copies row 64w+i: its byte offset,
 // with the out-of-range mark where the current tap falls into the padding, sits in one VGPR
 // and is refreshed once per stage from a per-lane bit mask over the taps; everything else
 // (tap, channel group, chunk) is a scalar offset.  K runs channel group outermost, tap inside,
-// 4 chunks per stage, ring of 3 LDS stages, one barrier per stage; the K loop can be split over
-// blocks (partial sums are reduced in a fixed order by the caller's reduce kernel).
+// 2 or 4 chunks per stage, ring of 3 or 4 LDS stages, one barrier per stage; the K loop can be
+// split over blocks (partial sums are reduced in a fixed order by the caller's reduce kernel).
 //
-// The same kernel serves 16-bit operands (one MFMA 32x32x16 per chunk pair and tile instead of CW
-// fp32 ones).  Capsule rows of 8, 16 or 32 halves are, in units of 4 bytes, rows of 4, 8 or 16
-// "floats": nothing else changes (any D1 and D3: non-square and vector capsules, which the
-// 256x256-tile 16-bit kernel does not take).  Rows of 4 halves (4x4 capsules) no 16-byte copy can
-// stage as they lie in memory: the 8 K values a 16-bit matrix instruction takes
-// per lane are the rows of two channels, 32 bytes apart.  A pre-pass (pair_channels_kernel, at
-// HBM speed) writes the input with channels paired, [pixel][c/2][d0][d1][c%2][d2]; in units of
-// 4 bytes that is an fp32 layer with half the channels and rows of 4 "floats", so every offset
-// and copy of this kernel stays as it is, and a chunk pair feeds one MFMA 32x32x16 per tile.
+// Rows of 4 halves (4x4 capsules) no 16-byte copy can stage as they lie in memory: the 8 K values
+// a 16-bit matrix instruction takes per lane are the rows of two channels, 32 bytes apart.  A
+// pre-pass (pair_channels_kernel, at HBM speed) writes the input with channels paired,
+// [pixel][c/2][d0][d1][c%2][d2]; that is a layer with half the channels and rows of 4 "floats", so
+// every offset and copy of this kernel stays as it is.
 #include <hip/hip_runtime.h>
 
 #include "igemm_common.h"
@@ -39,8 +35,7 @@ namespace {
 // under the others' MFMAs; they need capsule rows of at most 2 chunks.  With up to three column
 // tiles the kernel is compiled for four waves per SIMD (126 registers: the accumulators and a
 // small stage's operands) and takes a ring of three stages, so that four four-wave workgroups
-// share a CU (config 2: 0.877 -> 0.860 ms against three workgroups with a ring of four);
-// elsewhere the compiler's own register budget and the deeper ring of the small stages.
+// share a CU; elsewhere the compiler's own register budget and the deeper ring of the small stages.
 constexpr int waves_per_simd(int tn, int nw, int kch) { return nw == 4 && tn <= 3 && kch == 2 ? 4 : 1; }
 // The 16-bit-output variants are held to the waves per SIMD their fp32-output twins reach by
 // themselves (32 TN accumulator registers and about 30 others): left alone, the compiler reads
@@ -53,20 +48,14 @@ constexpr int waves_per_simd_out16(int tn, int nw, int kch)
 }
 constexpr int ring_depth(int kch, int tn, int nw) { return kch == 2 && waves_per_simd(tn, nw, kch) == 1 ? 4 : 3; }
 
-// Tag: f32_tag, or a 16-bit tag for capsule rows of 4 halves whose channels a pre-pass has paired
-// (pair_channels_kernel): a 16-byte chunk then holds the 8 K values (c, c+1) x d2 of one row, all
-// offsets are those of an fp32 layer with half the channels and rows of 4 floats, and a chunk pair
-// feeds one 16-bit MFMA 32x32x16 per tile instead of CW fp32 ones.
-// OUT16 (16-bit operands only): the output has the operands' type, rounded at the store.
-template <typename Tag, int CW, int TN, int NW, int KCH, bool OUT16 = false>
+// OUT16: the output has the operands' type, rounded at the store.
+template <typename Tag, int TN, int NW, int KCH, bool OUT16 = false>
 __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(OUT16 ? waves_per_simd_out16(TN, NW, KCH) : waves_per_simd(TN, NW, KCH)))) void igemm32_dma_kernel(const Dma32Params P)
 {
-    constexpr bool F32 = std::is_same<Tag, f32_tag>::value;
-    static_assert(!(F32 && OUT16), "fp32 operands have fp32 output");
     // a compile-time constant: with the choice made at run time the register allocator fails
     // to keep the copies' buffer descriptors in scalar registers
     constexpr int o16 = !OUT16 ? 0 : std::is_same<Tag, f16_tag>::value ? 2 : 1;
-    static_assert(F32 || CW == 4, "16-bit chunks are whole 16-byte slots");
+    constexpr int CW = 4;  // "floats" per chunk
     constexpr int NB = ring_depth(KCH, TN, NW);
     constexpr int BM = 64 * NW, BN = 32 * TN, BNL = (BN + 63) / 64 * 64, TM = 2;
     constexpr int A_BYTES = KCH * BM * 16, B_BYTES = KCH * BNL * 16;
@@ -244,23 +233,12 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(OUT16 ?
             for (int b = 0; b < TM; ++b)
                 ib[b] = *reinterpret_cast<const float4v*>(
                     stage + ((2 * t + h) * BM + 64 * wave + b * 32 + lr) * 16);
-            if constexpr (F32) {
 #pragma unroll
-                for (int u = 0; u < CW; ++u)
+            for (int a = 0; a < TN; ++a)
 #pragma unroll
-                    for (int a = 0; a < TN; ++a)
-#pragma unroll
-                        for (int b = 0; b < TM; ++b)
-                            acc[a][b] = __builtin_amdgcn_mfma_f32_32x32x2f32(ka[a][u], ib[b][u],
-                                                                             acc[a][b], 0, 0, 0);
-            } else {
-#pragma unroll
-                for (int a = 0; a < TN; ++a)
-#pragma unroll
-                    for (int b = 0; b < TM; ++b)
-                        Mma<Tag>::run(__builtin_bit_cast(chunk_t, ka[a]),
-                                      __builtin_bit_cast(chunk_t, ib[b]), acc[a][b]);
-            }
+                for (int b = 0; b < TM; ++b)
+                    Mma<Tag>::run(__builtin_bit_cast(chunk_t, ka[a]),
+                                  __builtin_bit_cast(chunk_t, ib[b]), acc[a][b]);
         }
     };
 
@@ -312,10 +290,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(OUT16 ?
                         const int m = j0 / P.D3, d3 = j0 - m * P.D3;
                         float4v v = {acc[a][b][4 * g], acc[a][b][4 * g + 1], acc[a][b][4 * g + 2],
                                      acc[a][b][4 * g + 3]};
-                        if constexpr (F32)
-                            *reinterpret_cast<float4v*>(out + orow_off + (long long)m * caps_out + d3) = v;
-                        else
-                            store4(out, orow_off + (long long)m * caps_out + d3, v, o16);
+                        store4(out, orow_off + (long long)m * caps_out + d3, v, o16);
                     }
                 } else {
 #pragma unroll
@@ -325,10 +300,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(OUT16 ?
                             // j / D3 by multiplication (exact while j * D3 < 2^32, which the host has checked)
                             const int m = P.d3_magic ? (int)__umulhi((unsigned)j, P.d3_magic) : j / P.D3;
                             const int d3 = j - m * P.D3;
-                            if constexpr (F32)
-                                out[orow_off + (long long)m * caps_out + d3] = acc[a][b][4 * g + u];
-                            else
-                                store1(out, orow_off + (long long)m * caps_out + d3, acc[a][b][4 * g + u], o16);
+                            store1(out, orow_off + (long long)m * caps_out + d3, acc[a][b][4 * g + u], o16);
                         }
                     }
                 }
@@ -337,11 +309,11 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(OUT16 ?
     }
 }
 
-template <typename Tag, int CW, int TN, int NW, int KCH, bool OUT16 = false>
+template <typename Tag, int TN, int NW, int KCH, bool OUT16 = false>
 hipError_t launch_kch(const Dma32Params& P, long long blocks, hipStream_t stream)
 {
     constexpr int BM = 64 * NW, BNL = (32 * TN + 63) / 64 * 64;
-    auto kern = igemm32_dma_kernel<Tag, CW, TN, NW, KCH, OUT16>;
+    auto kern = igemm32_dma_kernel<Tag, TN, NW, KCH, OUT16>;
     const size_t lds_bytes = (size_t)ring_depth(KCH, TN, NW) * KCH * (BM + BNL) * 16;
     static std::atomic<unsigned long long> lds_set{0};
     hipError_t err = set_dynamic_lds_once(reinterpret_cast<const void*>(kern), (int)lds_bytes, lds_set);
@@ -351,34 +323,28 @@ hipError_t launch_kch(const Dma32Params& P, long long blocks, hipStream_t stream
 }
 
 // 2-chunk stages where the column copies still divide over the waves; 16-bit output straight from
-// the kernel (16-bit operands) unless a split K loop leaves fp32 partial sums for the reduction
-template <typename Tag, int CW, int TN, int NW>
+// the kernel unless a split K loop leaves fp32 partial sums for the reduction
+template <typename Tag, int TN, int NW>
 hipError_t launch_one(const Dma32Params& P, long long blocks, hipStream_t stream)
 {
-    constexpr bool F32 = std::is_same<Tag, f32_tag>::value;
-    const bool o16 = !F32 && (P.out_mode >> 1) != 0 && P.nsplit == 1;
+    const bool o16 = (P.out_mode >> 1) != 0 && P.nsplit == 1;
     if constexpr ((2 * ((32 * TN + 63) / 64)) % NW == 0) {
-        if (P.kch == 2) {
-            if constexpr (!F32) {
-                if (o16) return launch_kch<Tag, CW, TN, NW, 2, true>(P, blocks, stream);
-            }
-            return launch_kch<Tag, CW, TN, NW, 2>(P, blocks, stream);
-        }
+        if (P.kch == 2)
+            return o16 ? launch_kch<Tag, TN, NW, 2, true>(P, blocks, stream)
+                       : launch_kch<Tag, TN, NW, 2>(P, blocks, stream);
     }
-    if constexpr (!F32) {
-        if (o16) return launch_kch<Tag, CW, TN, NW, 4, true>(P, blocks, stream);
-    }
-    return launch_kch<Tag, CW, TN, NW, 4>(P, blocks, stream);
+    return o16 ? launch_kch<Tag, TN, NW, 4, true>(P, blocks, stream)
+               : launch_kch<Tag, TN, NW, 4>(P, blocks, stream);
 }
 
-template <typename Tag, int CW, int NW>
+template <typename Tag, int NW>
 hipError_t launch_tn(const Dma32Params& P, int tn, long long blocks, hipStream_t stream)
 {
     switch (tn) {
-        case 1: return launch_one<Tag, CW, 1, NW>(P, blocks, stream);
-        case 2: return launch_one<Tag, CW, 2, NW>(P, blocks, stream);
-        case 3: return launch_one<Tag, CW, 3, NW>(P, blocks, stream);
-        default: return launch_one<Tag, CW, 4, NW>(P, blocks, stream);
+        case 1: return launch_one<Tag, 1, NW>(P, blocks, stream);
+        case 2: return launch_one<Tag, 2, NW>(P, blocks, stream);
+        case 3: return launch_one<Tag, 3, NW>(P, blocks, stream);
+        default: return launch_one<Tag, 4, NW>(P, blocks, stream);
     }
 }
 
@@ -435,6 +401,8 @@ bool igemm32_dma_eligible(const ConvShape& s)
     const long long bias = ((long long)(s.pad > 0 ? s.pad : 0) * s.W + (s.padw() > 0 ? s.padw() : 0)) *
                            s.C * s.D0 * s.D1 * s.D2 * es;
     if (images_spanned * img_bytes + bias >= (1LL << 31)) return false;
+    // (fp32 kernel: row numbers within the images a tile touches are 32-bit)
+    if (s.dtype == 0 && (hw + 256) * s.D1 >= (1LL << 31)) return false;
     const Dma32Plan pl = igemm32_dma_plan(s);
     // an output view is written by the kernel itself: no partial sums over a split K loop
     if (s.out_view && (pl.P.nsplit != 1 || s.out_sn < 0 || s.out_sx < 0 || s.out_sy < 0)) return false;
@@ -470,38 +438,56 @@ Dma32Plan igemm32_dma_plan(const ConvShape& s)
     P.D2C = cw ? D2 / cw : 1;
     const int KK = C * P.D2C;                   // chunks per row and tap
     pl.tn = P.cols <= 32 ? 1 : P.cols <= 64 ? 2 : P.cols <= 96 ? 3 : 4;
-    // four waves per block (256 rows) when that still fills the chip, else one (64 rows)
-    {
-        const int bn = 32 * pl.tn;
-        const long long big = (long long)ceil_div_ll(s.pixels() * s.D1, 256) * ((P.cols + bn - 1) / bn) * s.D0;
-        pl.nw = big >= 256 ? 4 : 1;
+    // (fp32: columns of a tile, see igemm32_split.hip; where four column tiles pad further than
+    // three, three)
+    int BN = 32 * pl.tn;
+    if (s.dtype == 0) {
+        auto columns = [&](int tn) { return igemm32_split_tile_columns(s.D3, tn); };
+        auto padded = [&](int tn) { return (P.cols + columns(tn) - 1) / columns(tn) * 32 * tn; };
+        pl.tn = 1;
+        while (pl.tn < 4 && P.cols > columns(pl.tn)) ++pl.tn;
+        if (pl.tn == 4 && padded(3) < padded(4)) pl.tn = 3;
+        BN = columns(pl.tn);
     }
-    // chunks per stage: 2 for the four-wave tile with wide column tiles and short capsule rows
-    // (measured on config 2: 0.955 ms against 0.987 ms), else 4
-    // (16-bit: 8-chunk stages, one workgroup per CU, measured 22 % slower than 4-chunk ones; 2-chunk
-    // stages 4 .. 5 % faster, as for fp32)
-    // (16-bit vector capsules, whose consecutive rows are different pixels: a lane's 4 chunks are
-    // one 64-byte run of memory; 11 .. 26 % faster than 2-chunk stages.  fp32: 2 % slower)
-    const int KCH = (pl.nw == 4 && pl.tn >= 3 && P.D2C <= 2 && !(s.dtype != 0 && s.D1 <= 2)) ? 2 : 4;
+    // four waves per block (256 rows) when that still fills the chip, else one (64 rows).  fp32: one
+    // wave where such tiles fill the chip twice over without a split K loop, else four waves and a
+    // split (64 channels of 4x4 capsules, 14x14 pixels: 98 tiles of 256 rows split 72 us, 64-row
+    // tiles 80 us; 196 tiles of 256 rows split 101 us, 784 64-row tiles 87 us)
+    {
+        const long long cols_d0 = (long long)((P.cols + BN - 1) / BN) * s.D0;
+        const long long big = (long long)ceil_div_ll(s.pixels() * s.D1, 256) * cols_d0;
+        pl.nw = big >= 256 ? 4 : 1;
+        if (s.dtype == 0 && (long long)ceil_div_ll(s.pixels() * s.D1, 64) * cols_d0 < 560) pl.nw = 4;
+    }
+    // 16-bit: chunks per stage: 2 for the four-wave tile with wide column tiles and short capsule
+    // rows (4 .. 5 % faster than 4; 8-chunk stages, one workgroup per CU, 22 % slower), else 4
+    // (vector capsules, whose consecutive rows are different pixels: a lane's 4 chunks are one
+    // 64-byte run of memory; 11 .. 26 % faster than 2-chunk stages).  fp32: 4
+    const int KCH = (s.dtype != 0 && pl.nw == 4 && pl.tn >= 3 && P.D2C <= 2 && !(s.dtype != 0 && s.D1 <= 2)) ? 2 : 4;
     P.kch = KCH;
     const int groups = (KK + KCH - 1) / KCH;
     pl.kqp = groups * KCH;
     P.nstages = groups * P.ntaps;
-    const int BN = 32 * pl.tn;
     P.col_tiles = (P.cols + BN - 1) / BN;
-    P.colsp = P.col_tiles * BN;
+    P.colsp = P.col_tiles * 32 * pl.tn;
     P.row_tiles = ceil_div_ll(P.rows, 64 * pl.nw);
     const long long tiles = (long long)P.row_tiles * P.col_tiles * s.D0;
     int nsplit = 1;
     if (tiles < 256) {
-        nsplit = ceil_div_ll(512, tiles);
+        nsplit = ceil_div_ll(s.dtype == 0 ? 256 : 512, tiles);
         if (nsplit > P.nstages) nsplit = P.nstages;
         if (nsplit > 64) nsplit = 64;
     }
     P.stages_per_split = (P.nstages + nsplit - 1) / nsplit;
+    if (s.dtype == 0) {  // a split begins at a whole K step
+        const int per = igemm32_split_period(cw);
+        P.stages_per_split = (P.stages_per_split + per - 1) / per * per;
+        P.ksteps = igemm32_split_ksteps(cw, P.nstages);
+    }
     P.nsplit = (P.nstages + P.stages_per_split - 1) / P.stages_per_split;
     pl.blocks = tiles * P.nsplit;
-    pl.repack_bytes = (size_t)s.D0 * P.nstages * KCH * P.colsp * 16;
+    pl.repack_bytes = s.dtype == 0 ? (size_t)s.D0 * P.ksteps * 6 * P.colsp * 16
+                                   : (size_t)s.D0 * P.nstages * KCH * P.colsp * 16;
     pl.partial_bytes = P.nsplit > 1 ? (size_t)P.nsplit * P.out_elems * sizeof(float) : 0;
     P.in_bytes = (long long)s.in_elems() * (s.dtype == 0 ? 4 : 2);
     P.kp_bytes = (long long)pl.repack_bytes;
@@ -522,8 +508,15 @@ Dma32Plan igemm32_dma_plan(const ConvShape& s)
 bool igemm32_dma_preferred(const ConvShape& s)
 {
     if (!igemm32_dma_eligible(s)) return false;
-    // measured on MI355X: 1.8x faster than the generic kernel on config 2 (many 256-row tiles);
-    // on problems so small that the K loop is split the generic kernel's 64x64 tiles win
+    // fp32: from 3e9 nominal FLOPs on this kernel beats the any-shape and the small-problem one,
+    // split K loop or not (16 .. 64 channels of 4x4 and 8x8 capsules, 25 to 98 tiles of 256 rows: 3.7
+    // GFLOP 48 against 57 us, 4.8 GFLOP 56 against 59, 7.4 GFLOP 72 against 104; 1.9 GFLOP 44 against
+    // 30 us); capsule rows of 3k floats, which the others load element by element, from 1.2e9
+    // (32 channels of 3x3x3 capsules, 1.5 GFLOP: 36 against 72 us)
+    if (s.dtype == 0) {
+        const double flops = 2.0 * (double)s.out_elems() * s.kh * s.kw * s.C * s.D2;
+        return flops >= (igemm32_dma_chunk_width(s) == 3 ? 1.2e9 : 3e9);
+    }
     // 16-bit: square capsules of 8 or 16 rows belong to the 256x256-tile kernel, which is 1.12 ..
     // 1.17x faster on whole column tiles (configs 3 and 5: 0.92 against 1.03 ms, 14.2 against
     // 16.6 ms) -- unless its 256-column tiles pad the columns much further than this kernel's
@@ -540,16 +533,12 @@ bool igemm32_dma_preferred(const ConvShape& s)
 hipError_t launch_igemm32_dma(const Dma32Plan& pl, hipStream_t stream)
 {
     if (pl.dtype == 1)
-        return pl.nw == 4 ? launch_tn<bf16_tag, 4, 4>(pl.P, pl.tn, pl.blocks, stream)
-                          : launch_tn<bf16_tag, 4, 1>(pl.P, pl.tn, pl.blocks, stream);
+        return pl.nw == 4 ? launch_tn<bf16_tag, 4>(pl.P, pl.tn, pl.blocks, stream)
+                          : launch_tn<bf16_tag, 1>(pl.P, pl.tn, pl.blocks, stream);
     if (pl.dtype == 2)
-        return pl.nw == 4 ? launch_tn<f16_tag, 4, 4>(pl.P, pl.tn, pl.blocks, stream)
-                          : launch_tn<f16_tag, 4, 1>(pl.P, pl.tn, pl.blocks, stream);
-    if (pl.cw == 3)
-        return pl.nw == 4 ? launch_tn<f32_tag, 3, 4>(pl.P, pl.tn, pl.blocks, stream)
-                          : launch_tn<f32_tag, 3, 1>(pl.P, pl.tn, pl.blocks, stream);
-    return pl.nw == 4 ? launch_tn<f32_tag, 4, 4>(pl.P, pl.tn, pl.blocks, stream)
-                      : launch_tn<f32_tag, 4, 1>(pl.P, pl.tn, pl.blocks, stream);
+        return pl.nw == 4 ? launch_tn<f16_tag, 4>(pl.P, pl.tn, pl.blocks, stream)
+                          : launch_tn<f16_tag, 1>(pl.P, pl.tn, pl.blocks, stream);
+    return launch_igemm32_split(pl, stream);
 }
 
 hipError_t launch_pair_channels(const void* src, void* dst, size_t pixels, int C,

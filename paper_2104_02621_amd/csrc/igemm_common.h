@@ -154,6 +154,7 @@ struct Dma32Params {
     int D2C;       // chunks per capsule row
     int kch;       // chunks per row and stage: 2 or 4
     int nstages;   // channel groups * taps
+    int ksteps;    // fp32: bf16 matrix instruction steps (16 K values) of the whole K loop
     int stages_per_split, nsplit;
     int row_tiles, col_tiles;
     // launch order: 0 = column tiles fastest, then row tiles, leading capsule index, K split;
@@ -176,6 +177,13 @@ Dma32Plan igemm32_dma_plan(const ConvShape& s);
 bool igemm32_dma_eligible(const ConvShape& s);   // the kernel can run the shape
 bool igemm32_dma_preferred(const ConvShape& s);  // ... and is the library's choice for it
 hipError_t launch_igemm32_dma(const Dma32Plan& pl, hipStream_t stream);
+// fp32 operands (igemm32_split.hip): the contraction on bf16 matrix instructions
+hipError_t launch_igemm32_split(const Dma32Plan& pl, hipStream_t stream);
+hipError_t launch_repack_split(const ConvShape& s, const Dma32Plan& pl, const void* kernel, void* kp,
+                               hipStream_t stream);
+int igemm32_split_period(int cw);
+int igemm32_split_ksteps(int cw, int stages);
+int igemm32_split_tile_columns(int D3, int tn);  // output columns of a tile
 // 16-bit operands: dst[pixel][c/2][d0][d1][c%2][4] = src[pixel][c][d0][d1][4] (8-byte units)
 hipError_t launch_pair_channels(const ConvShape& s, const void* src, void* dst, hipStream_t stream);
 // the same for any tensor [pixels][C][rows_per_capsule][4 halves]

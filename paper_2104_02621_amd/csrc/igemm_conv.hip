@@ -623,8 +623,9 @@ hipError_t launch_dma32(const ConvShape& s, const void* in, const void* kernel, 
         if (err != hipSuccess) return err;
         pl.P.in = paired;
     }
-    err = launch_repack(s, kernel, ws, s.dtype == 0 ? pl.cw : 8, pl.kqp, pl.P.colsp, pl.P.kch,
-                        pl.repack_bytes / 16, stream);
+    err = s.dtype == 0 ? launch_repack_split(s, pl, kernel, ws, stream)
+                       : launch_repack(s, kernel, ws, 8, pl.kqp, pl.P.colsp, pl.P.kch,
+                                       pl.repack_bytes / 16, stream);
     if (err != hipSuccess) return err;
     err = launch_igemm32_dma(pl, stream);
     if (err != hipSuccess) return err;
@@ -686,14 +687,8 @@ bool mfma_supported(const ConvShape& s) { return shape_supported(s); }
 size_t mfma_workspace_bytes(const ConvShape& s)
 {
     if (!shape_supported(s)) return 0;
-    if (s.out16 != 0) {
-        // 16-bit output is offered with the library's own kernel choice only
-        const MfmaKernel which = mfma_auto_kernel(s);
-        if (which == MfmaKernel::Dma32) return dma32_workspace_bytes(igemm32_dma_plan(s));
-        if (which == MfmaKernel::Small) return igemm_small_workspace_bytes(s);
-        const Plan pl = make_plan(s, which);
-        return ((pl.repack_bytes + 255) & ~(size_t)255) + pl.partial_bytes;
-    }
+    // 16-bit output is offered with the library's own kernel choice only
+    if (s.out16 != 0) return mfma_kernel_workspace_bytes(s, MfmaKernel::Auto);
     size_t need = 0;
     for (MfmaKernel which : {MfmaKernel::Generic, MfmaKernel::Tuned16}) {
         if (which == MfmaKernel::Tuned16 && !igemm16_fast_eligible(s)) continue;
@@ -709,14 +704,12 @@ size_t mfma_workspace_bytes(const ConvShape& s)
     return need;
 }
 
-size_t mfma_auto_workspace_bytes(const ConvShape& s)
+size_t mfma_kernel_workspace_bytes(const ConvShape& s, MfmaKernel which)
 {
     if (!shape_supported(s)) return 0;
-    const MfmaKernel which = mfma_auto_kernel(s);
+    if (which == MfmaKernel::Auto) which = mfma_auto_kernel(s);
     if (which == MfmaKernel::Small) return igemm_small_workspace_bytes(s);
-    if (which == MfmaKernel::Dma32) {
-        return dma32_workspace_bytes(igemm32_dma_plan(s));
-    }
+    if (which == MfmaKernel::Dma32) return dma32_workspace_bytes(igemm32_dma_plan(s));
     const Plan pl = make_plan(s, which);
     return ((pl.repack_bytes + 255) & ~(size_t)255) + pl.partial_bytes;
 }

@@ -1,0 +1,89 @@
+"""GPU parity of the fp32 kernel that contracts on the bf16 matrix instructions (every operand as
+the sum of three bf16 values): tile edges of every column-tile count and both chunk widths, whole and
+split K loops, and the values the decomposition cannot hold, which a workgroup recomputes on the
+fp32 instructions.  Needs an MI355X."""
+import numpy as np
+import pytest
+
+from paper_2104_02621_amd import capscaps as cc
+from paper_2104_02621_amd import workloads as wl
+from tests.gpu_util import run_gpu, to_device
+from tests.test_gpu_parity import full_compare, small
+
+pytestmark = pytest.mark.gpu
+
+# (N, H, W, C, M, kh, kw, stride, pad, D0, D1, D2, D3): column tiles of 1 .. 4 with the last one
+# ragged, capsule columns of 3 (stored by runs of three registers), 6 and 9 and not, K loops that
+# end inside a period of stages, 256-row and 64-row tiles
+SHAPES = [
+    (3, 7, 9, 5, 3, 3, 3, 1, 1, 3, 3, 3, 3),     # 9 columns: one tile of 10 capsules
+    (3, 7, 9, 5, 11, 3, 3, 1, 1, 1, 3, 3, 3),    # 33: two tiles' worth in 20 capsules
+    (2, 9, 8, 4, 27, 2, 3, 2, 1, 2, 2, 3, 3),    # 81: three, ragged
+    (2, 6, 7, 7, 43, 3, 1, 1, 0, 1, 3, 6, 3),    # 129: past 42 capsules of four tiles
+    (2, 8, 8, 3, 7, 3, 3, 1, 1, 1, 5, 12, 6),    # D3 = 6
+    (2, 8, 8, 3, 5, 3, 3, 1, 1, 1, 2, 4, 9),     # D3 = 9
+    (2, 8, 8, 3, 7, 3, 3, 1, 1, 1, 3, 3, 12),    # D3 = 12: a multiple of 4 as well
+    (4, 9, 9, 6, 9, 3, 3, 1, 1, 1, 4, 4, 4),     # 36
+    (2, 9, 9, 3, 25, 3, 3, 2, 2, 1, 8, 8, 4),    # 100: four tiles, two kernel stages in the ring
+    (2, 9, 9, 5, 17, 1, 1, 1, 0, 1, 4, 16, 5),   # 85, stored element by element
+    (1, 5, 5, 1, 1, 3, 3, 1, 0, 1, 1, 4, 4),     # a single row tile, nearly empty
+    (20, 24, 24, 3, 6, 3, 3, 1, 1, 1, 4, 3, 5),  # more than 560 tiles of 64 rows: one-wave tiles
+    (70, 33, 32, 2, 4, 3, 3, 1, 1, 1, 1, 4, 4),  # more than 256 tiles of 256 rows
+]
+
+
+@pytest.mark.parametrize("integers", [False, True], ids=["normal", "integers"])
+@pytest.mark.parametrize("shape", SHAPES, ids=["x".join(map(str, s)) for s in SHAPES])
+def test_split_kernel_matches_oracle(shape, integers):
+    w = small("split_" + "x".join(map(str, shape)), wl.FP32, *shape, seed=611)
+    full_compare(wl.integer_variant(w) if integers else w, cc.PATH_MFMA_TUNED32)
+
+
+def exact64(w, x, k):
+    from oracle import capsconv
+    with np.errstate(invalid="ignore", over="ignore"):
+        return capsconv.conv_fwd(x, k, w.stride, w.pad)
+
+
+SPECIAL = [(2, 9, 9, 4, 9, 3, 3, 1, 1, 1, 4, 4, 4), (2, 9, 9, 5, 9, 3, 3, 1, 1, 3, 3, 3, 3)]
+
+
+@pytest.mark.parametrize("value", [np.inf, -np.inf, np.nan, -3.4028235e38, 3.3961775e38])
+@pytest.mark.parametrize("shape", SPECIAL, ids=["4x4", "3x3x3"])
+@pytest.mark.parametrize("side", ["input", "kernel"])
+def test_values_bf16_cannot_hold(shape, value, side):
+    """One infinity, NaN or value that rounds to infinity in bf16: the results it does not reach are
+    untouched, those it reaches are what fp32 arithmetic gives."""
+    if side == "kernel":  # no padding: a matrix core multiplies a padding tap's zeros by the kernel
+        shape = shape[:8] + (0,) + shape[9:]
+    w = small("special", wl.FP32, *shape, seed=612)
+    x, k, _, _ = wl.generate(w)
+    x, k = x.copy(), k.copy()
+    k *= np.float32(0.125)  # a product with the largest fp32 value stays finite
+    x = np.clip(x, -1, 1)
+    (x if side == "input" else k).flat[37] = value
+    ref = exact64(w, x, k)
+    got = run_gpu(w, to_device(x, wl.FP32), to_device(k, wl.FP32), cc.PATH_MFMA_TUNED32).cpu().numpy()
+    assert np.array_equal(np.isnan(got), np.isnan(ref))
+    inf = np.isinf(ref)
+    assert np.array_equal(got[inf], ref[inf].astype(np.float32))
+    ok = np.isfinite(ref) & (np.abs(ref) < 3e38)
+    assert ok.any() and np.isfinite(got[ok]).all()
+    # fp32 sums of K <= 180 terms, relative to the largest result of the capsule's magnitude
+    scale = np.maximum(np.abs(ref[ok]), np.abs(ref[np.isfinite(ref) & (np.abs(ref) < 1e3)]).max())
+    assert (np.abs(got[ok] - ref[ok]) / scale).max() <= 180 * 2.0 ** -24
+
+
+@pytest.mark.parametrize("shape", SPECIAL, ids=["4x4", "3x3x3"])
+@pytest.mark.parametrize("scale", [1e-36, 3e-38, 1e-30, 1e30])
+def test_results_of_any_magnitude(shape, scale):
+    """The same relative error at every magnitude of the input (1e-36: the third bf16 term of most
+    values is below bf16's range)."""
+    w = small("magnitude", wl.FP32, *shape, seed=613)
+    x, k, _, _ = wl.generate(w)
+    x = (x.astype(np.float64) * scale).astype(np.float32)
+    ref = exact64(w, x, k)
+    got = run_gpu(w, to_device(x, wl.FP32), to_device(k, wl.FP32), cc.PATH_MFMA_TUNED32).cpu().numpy()
+    # products below 2^-126 are rounded to multiples of 2^-149
+    floor = 180 * 2.0 ** -149
+    assert np.abs(got - ref).max() <= 1e-5 * np.abs(ref).max() + floor
