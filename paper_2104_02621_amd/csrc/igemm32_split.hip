@@ -21,7 +21,7 @@
 // What the decomposition cannot represent is recomputed: infinities and NaNs (and values that
 // round to infinity in bf16) leave NaN in the sums they belong to, and operands below 2^-110 lose
 // bits of x3 to bf16's exponent range, which matters only to results that are as small.  A
-// workgroup that finds a result that is not finite, or not zero and below 2^-60, runs its K loop
+// workgroup that finds a result that is not finite, or not zero and below 2^-80, runs its K loop
 // again on the fp32 matrix instructions from the same LDS data (the input side lies there
 // unsplit; the kernel side's three values add up to the fp32 value exactly).
 //
@@ -42,6 +42,7 @@
 // can be split over blocks (partial sums are reduced in a fixed order by the caller's kernel).
 #include <hip/hip_runtime.h>
 
+#include "bf16_split.h"
 #include "igemm_common.h"
 #include "lds_dma.h"
 
@@ -59,37 +60,6 @@ constexpr int stage_period(int cw) { return cw == 3 ? 4 : 2; }
 // first operands of a stage are then read at its beginning, not at the end of the one before).
 constexpr int NBA = 3;
 constexpr int kernel_ring(int tn) { return tn == 4 ? 2 : 3; }
-
-// a pair of fp32 values as the sum of three pairs of bf16 values (the lower value in the lower
-// half of the word)
-typedef float float2v __attribute__((ext_vector_type(2)));
-typedef __bf16 bf16x2v __attribute__((ext_vector_type(2)));
-__device__ __forceinline__ unsigned round_pair(float lo, float hi)
-{
-    const float2v v = {lo, hi};
-    return __builtin_bit_cast(unsigned, __builtin_convertvector(v, bf16x2v));
-}
-__device__ __forceinline__ float low_half(unsigned w) { return __builtin_bit_cast(float, w << 16); }
-__device__ __forceinline__ float high_half(unsigned w) { return __builtin_bit_cast(float, w & 0xffff0000u); }
-// one of the two values of `pair` times -1, plus x: exact here, and one instruction where
-// unpacking the value and subtracting it are two
-__device__ __forceinline__ float minus_bf16(float x, unsigned pair, unsigned minus_one)
-{
-    return __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2v, pair),
-                                           __builtin_bit_cast(bf16x2v, minus_one), x, false);
-}
-// Copy of the first `lanes` lanes of a wave only (an exec mask; all lanes are active around it).
-__device__ __forceinline__ void copy_to_lds_16B_lanes(rsrc_t rs, unsigned lds_addr, unsigned voff,
-                                                      int soff, unsigned long long lanes)
-{
-    const int lds_s = __builtin_amdgcn_readfirstlane((int)lds_addr);
-    const int soff_s = __builtin_amdgcn_readfirstlane(soff);
-    asm volatile("s_mov_b32 m0, %0\n\ts_mov_b64 exec, %4\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds\n\t"
-                 "s_mov_b64 exec, -1"
-                 :
-                 : "s"(lds_s), "v"(voff), "s"(rs), "s"(soff_s), "s"(lanes)
-                 : "memory");
-}
 
 // Columns of a tile.  TRIPLE (D3 a multiple of 3): a lane's accumulator registers of one output row, 16
 // per column tile, hold whole runs of three consecutive columns, so that a capsule row is stored
@@ -272,9 +242,7 @@ void igemm32_split_kernel(const Dma32Params P)
 
     // ---- the K loop on the split values
     {
-        // the two halves of the minus_bf16 operand, opaque to the compiler
-        unsigned minus_lo = 0x0000bf80u, minus_hi = 0xbf800000u;
-        asm volatile("" : "+s"(minus_lo), "+s"(minus_hi));
+        const MinusOne one;
         // K values of one period, split: pairs per row tile and term
         unsigned iv[TM][3][WORDS];
         float lo[NPAIR], hi[NPAIR];  // the pairs being split: what the terms so far leave over
@@ -285,9 +253,9 @@ void igemm32_split_kernel(const Dma32Params P)
             if (k % 3 == 0)
                 w[k / 3][at] = round_pair(lo[p], hi[p]);
             else if (k % 3 == 1)
-                lo[p] = minus_bf16(lo[p], w[k / 3][at], minus_lo);
+                lo[p] = minus_bf16(lo[p], w[k / 3][at], one.lo);
             else
-                hi[p] = minus_bf16(hi[p], w[k / 3][at], minus_hi);
+                hi[p] = minus_bf16(hi[p], w[k / 3][at], one.hi);
         };
         auto take_input = [&](const char* slot) {
             float4v raw[TM][2];
@@ -362,12 +330,10 @@ void igemm32_split_kernel(const Dma32Params P)
                 static_for<GAPS>([&](auto I) {
                     constexpr int i = decltype(I)::value;
                     if constexpr (NMMA > 0) {
-                        // (kernel term, input term), smallest products first
-                        constexpr int KT[6] = {2, 1, 0, 1, 0, 0}, IT[6] = {0, 1, 2, 0, 1, 0};
                         constexpr int a = i / (6 * TM), u = i / TM % 6, b = i % TM;
-                        const unsigned(&w)[WORDS] = iv[b][IT[u]];
+                        const unsigned(&w)[WORDS] = iv[b][SPLIT_TERM_B[u]];
                         const chunk_t x = {w[W0], w[W0 + 1], w[W0 + 2], w[W0 + 3]};
-                        Mma<bf16_tag>::run(kb[a & 1][KT[u]], x, acc[a][b]);
+                        Mma<bf16_tag>::run(kb[a & 1][SPLIT_TERM_A[u]], x, acc[a][b]);
                         // operands of the next column tile, or of the next stage's first
                         constexpr int f = i % (6 * TM) - 1;
                         if constexpr (f >= 0 && f < 3) {
@@ -375,27 +341,24 @@ void igemm32_split_kernel(const Dma32Params P)
                                 kb[(a + 1) & 1][f] = read_kernel(smem + b_cur, a + 1, f);
                         }
                     }
-                    static_for<SLOTS + BPW>([&](auto J) {
-                        constexpr int j = decltype(J)::value;
-                        constexpr int at = j * NMMA / (SLOTS + BPW);
-                        if constexpr (at == i) {
-                            if constexpr (j < BPW) {
-                                if constexpr (fill) {
-                                    copy_b(lds0 + b_fill, std::integral_constant<int, j < BPW ? j : 0>{});
-                                    if constexpr (j == BPW - 1) kp_off += B_BYTES;
-                                }
-                                if constexpr (j == BPW - 1) begin_a();
-                            } else {
-                                copy_a(lds0 + a_cur, j - BPW);
-                                if constexpr (j == SLOTS + BPW - 1) advance_a();
+                    constexpr int NSIDE = SLOTS + BPW;
+                    constexpr int j0 = dealt_before(i, NSIDE, GAPS, 0), j1 = dealt_before(i + 1, NSIDE, GAPS, 0);
+                    static_for<j1 - j0>([&](auto J) {
+                        constexpr int j = j0 + decltype(J)::value;
+                        if constexpr (j < BPW) {
+                            if constexpr (fill) {
+                                copy_b(lds0 + b_fill, std::integral_constant<int, j < BPW ? j : 0>{});
+                                if constexpr (j == BPW - 1) kp_off += B_BYTES;
                             }
+                            if constexpr (j == BPW - 1) begin_a();
+                        } else {
+                            copy_a(lds0 + a_cur, j - BPW);
+                            if constexpr (j == SLOTS + BPW - 1) advance_a();
                         }
                     });
-                    static_for<NSTEP>([&](auto T) {
-                        constexpr int t = decltype(T)::value;
-                        constexpr int at = NMMA > 0 ? FIRST + t * (NMMA - FIRST) / NSTEP : 0;
-                        if constexpr (at == i) split_step(t % NPAIR, t / NPAIR, next);
-                    });
+                    constexpr int t0 = dealt_before(i, NSTEP, GAPS, FIRST), t1 = dealt_before(i + 1, NSTEP, GAPS, FIRST);
+#pragma unroll
+                    for (int t = t0; t < t1; ++t) split_step(t % NPAIR, t / NPAIR, next);
                     if constexpr (NMMA > 0) __builtin_amdgcn_sched_barrier(0);
                 });
                 if constexpr (AHEAD && has_step(next)) {
@@ -465,20 +428,12 @@ void igemm32_split_kernel(const Dma32Params P)
     };
 
     {
-        // results that are not finite, or not zero and below 2^-60?
-        float poison = 0.f;
-        unsigned small = 0xffffffffu;
+        SplitCheck check;
 #pragma unroll
         for (int a = 0; a < TN; ++a)
 #pragma unroll
-            for (int b = 0; b < TM; ++b)
-#pragma unroll
-                for (int r = 0; r < 16; ++r) {
-                    poison = fmaf(acc[a][b][r], 0.f, poison);  // NaN from an infinity or a NaN
-                    const unsigned m = 2 * __builtin_bit_cast(unsigned, acc[a][b][r]) - 1;  // 0: largest
-                    small = m < small ? m : small;
-                }
-        const bool redo = poison != 0.f || small < ((127u - 60u) << 24);
+            for (int b = 0; b < TM; ++b) check.take(acc[a][b]);
+        const bool redo = check.failed();
         __syncthreads();  // every wave's copies have landed: LDS is free
         if (lane == 0) reinterpret_cast<int*>(smem)[wave] = 0;
         const unsigned long long any = __builtin_amdgcn_ballot_w64(redo);

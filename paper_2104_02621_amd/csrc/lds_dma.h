@@ -75,4 +75,39 @@ __device__ __forceinline__ void copy_to_lds_dwords(rsrc_t rs, unsigned lds_addr,
                      : "memory");
 }
 
+// Copy by the lanes of a mask only (an exec mask inside the statement; all lanes are active around
+// it).
+__device__ __forceinline__ void copy_to_lds_16B_lanes(rsrc_t rs, unsigned lds_addr, unsigned voff,
+                                                      int soff, unsigned long long lanes)
+{
+    const int lds_s = __builtin_amdgcn_readfirstlane((int)lds_addr);
+    const int soff_s = __builtin_amdgcn_readfirstlane(soff);
+    asm volatile("s_mov_b32 m0, %0\n\ts_mov_b64 exec, %4\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds\n\t"
+                 "s_mov_b64 exec, -1"
+                 :
+                 : "s"(lds_s), "v"(voff), "s"(rs), "s"(soff_s), "s"(lanes)
+                 : "memory");
+}
+// Copy of DW = 3 or 4 dwords per lane to LDS address lds_base + IMM + 16 * lane, by the whole wave
+// or (HALF) by its first 32 lanes.
+template <int DW, bool HALF, int IMM>
+__device__ __forceinline__ void copy_to_lds_at(rsrc_t rs, unsigned lds_base, unsigned voff, int soff)
+{
+    static_assert(DW == 3 || DW == 4, "12- or 16-byte copies");
+    if constexpr (DW == 4 && !HALF)
+        asm volatile("s_add_u32 m0, %0, %4\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds"
+                     : : "s"(lds_base), "v"(voff), "s"(rs), "s"(soff), "i"(IMM) : "memory", "scc");
+    else if constexpr (DW == 4)
+        asm volatile("s_add_u32 m0, %0, %4\n\ts_mov_b64 exec, 0xffffffff\n\t"
+                     "buffer_load_dwordx4 %1, %2, %3 offen lds\n\ts_mov_b64 exec, -1"
+                     : : "s"(lds_base), "v"(voff), "s"(rs), "s"(soff), "i"(IMM) : "memory", "scc");
+    else if constexpr (!HALF)
+        asm volatile("s_add_u32 m0, %0, %4\n\ts_nop 0\n\tbuffer_load_dwordx3 %1, %2, %3 offen lds"
+                     : : "s"(lds_base), "v"(voff), "s"(rs), "s"(soff), "i"(IMM) : "memory", "scc");
+    else
+        asm volatile("s_add_u32 m0, %0, %4\n\ts_mov_b64 exec, 0xffffffff\n\t"
+                     "buffer_load_dwordx3 %1, %2, %3 offen lds\n\ts_mov_b64 exec, -1"
+                     : : "s"(lds_base), "v"(voff), "s"(rs), "s"(soff), "i"(IMM) : "memory", "scc");
+}
+
 }  // namespace capscaps

@@ -1,50 +1,57 @@
-// Kernel gradient of the capsule convolution for fp32 operands on the matrix cores: the same
-// per-tap GEMM as wgrad16.hip (rows (c,d2), columns (m,d3), K = (n,x,y,d1) over the output
-// pixels whose tap lies inside the image; the K_diff result of the paper's Algorithm 4 read as
-// the derivative of Algorithm 2's sum), for capsule heights D1 of 3, 4, 6, 8, 12 or 16 floats.
+// Kernel gradient of the capsule convolution for fp32 operands on the matrix cores: one GEMM per
+// window tap (rows (c,d2), columns (m,d3), K = (n,x,y,d1) over the output pixels whose tap lies
+// inside the image; the K_diff result of the paper's Algorithm 4 read as the derivative of
+// Algorithm 2's sum), for capsule heights D1 of 3, 4, 6, 8, 12 or 16 floats.
+//
+// Bound: the matrix rate.  As in igemm32_split.hip every fp32 value is the exact sum of three bf16
+// values (bf16_split.h) and six bf16 products take the place of one fp32 product: 192 instead of
+// 512 cycles per 32 x 32 tile and 16 K values; a workgroup whose sums are not finite, or not zero
+// and below 2^-80, takes them again on the fp32 instructions.  Both operands are split in
+// registers, so the tile is what decides: a workgroup is ONE wave with up to 96 x 96 of the result
+// (3 x 3 MFMA tiles: 54 matrix instructions beside 168 vector instructions of splitting per 16 K
+// values), with LDS of its own and no barrier.  Measured (N = 64, 32x32, 3x3, 32 -> 32 channels of
+// 3x3x3 capsules): 0.92 ms on the fp32 instructions with 128 x 96 tiles of two waves, 0.66 ms here
+// (error against 64-bit sums 1.05e-6 and 7.8e-7); 35 % of the cycles issue no matrix instruction
+// for LDS reads of single floats with bank conflicts, the splitting and the pixel walk of one wave.
+//
+// fp32 layers have few rows and columns per tap (32 channels of 3x3x3 capsules: 96 x 96) and a very
+// long K, so the K loop -- every tap's sequence of valid output pixels -- is cut into equal ranges
+// over the waves of the chip (partial sums to scratch, added in a fixed order by the shared
+// reduction kernel).
 //
 // Unless the capsules are square (see NAT below), a pre-pass writes capsule-transposed copies
 // It[n][h][w][c][d0][d2][d1] and Gt[n][x][y][m][d0][d3][d1], so the D1 contracted values of one
 // (pixel, row) are contiguous.
 // Data moves in 16-byte LDS slots of CW = 3 or 4 floats ("chunks", D1 = CW * D1C): a 12-byte
-// buffer load lands at a 16-byte lane stride in LDS, so both widths read operands with one
-// 16-byte LDS load per lane and feed CW MFMA 32x32x2 instructions from it (element u of the
-// lower and of the upper half wave form the K pair of instruction u).
-//
-// fp32 layers have few rows and columns per tap (config 2: 96 x 96) and a very long K, so the
-// tile is small -- 64*NW rows x 32*TN columns, wave w owning rows 64w..64w+63 against all
-// columns -- and the K loop is split over image ranges (partial sums to scratch, added in a
-// fixed order by the shared reduction kernel).  Lane i of a wave copies row 64w+i: a fixed
-// lane offset plus the scalar offset of the pixel.  A stage is 4 chunks = 4/D1C pixels; ring of
-// 3 LDS stages, one barrier per stage, several workgroups per CU overlap copies and MFMAs.
+// buffer load lands at a 16-byte lane stride in LDS.  A stage is 4 slots of every row and column
+// = 4/D1C pixels; the lower half wave takes the first half of the stage's K values, the upper the
+// second: 8 values (CW = 4), the K extent of one bf16 instruction, or 6 (CW = 3), so that four
+// stages make three instructions' worth.  A stage's values are read from LDS and split one stage
+// ahead of their use, between the matrix instructions of the stage before.
 #include <hip/hip_runtime.h>
 
+#include "bf16_split.h"
 #include "igemm_common.h"
 #include "lds_dma.h"
 
 namespace capscaps {
 namespace {
 
-// KCH chunks per row and stage (2 for the two-wave tile unless a capsule column is 4 chunks,
-// else 4), ring of NB stages:
-// small stages keep the LDS footprint of a workgroup low, so that two or more waves share each
-// SIMD and one wave's copies and scalar work run under another's MFMAs.
-constexpr int stage_chunks(int d1c, int nw) { return d1c == 4 || nw == 4 ? 4 : 2; }
-// waves per SIMD the kernel is compiled for: three where 168 registers hold the accumulators
-// of the column tiles and a small stage's operands, else two
-constexpr int waves_per_simd(int tn, int kch) { return tn <= 3 && kch == 2 ? 3 : 2; }
-// three stages where six two-wave workgroups are to share a CU (24 KB each; measured on config 2
-// against four stages and five workgroups: 0.98 against 1.07 ms), four for the other small stages
-constexpr int ring_depth(int kch, int tn) { return kch == 2 && waves_per_simd(tn, kch) == 2 ? 4 : 3; }
-
+constexpr int SLOTS = 4;  // per row or column and stage
+// stages the K loop's body covers (as in igemm32_split.hip)
+constexpr int stage_period(int cw) { return cw == 3 ? 4 : 2; }
+// Ring of LDS stages: three, or two where that lets eight waves share a CU (64 x 64 tiles: 16 KB).
+constexpr int ring_depth(int tm, int tn) { return tm == 2 && tn == 2 ? 2 : 3; }
+constexpr int lds_bytes_of(int tm, int tn) { return ring_depth(tm, tn) * SLOTS * 32 * (tm + tn) * 16; }
 
 struct Wgrad32Params {
-    const void* it;  // capsule-transposed input
-    const void* gt;  // capsule-transposed output gradient
+    const void* it;  // capsule-transposed input, or the input itself
+    const void* gt;  // capsule-transposed output gradient, or the output gradient itself
     float* out;      // dK, or partial sums [split][kernel elements]
     int N, H, W, C, M, kw, stride, pad, D0, D1, D2, D3, Ho, Wo;
     int D1C;         // chunks per capsule column: D1 = CW * D1C, D1C in {1, 2, 4}
     int rows, cols;  // C*D2, M*D3
+    int row_step, col_step;  // rows and columns of a tile
     int row_tiles, col_tiles, ntaps;
     int tiles;       // ntaps * D0 * row_tiles * col_tiles
     int natural;          // 1: it / gt are the input and the output gradient themselves
@@ -69,32 +76,32 @@ __global__ __launch_bounds__(256) void transpose_caps32_kernel(const float* __re
     dst[id] = src[(mat * A + a) * B + b];
 }
 
-// NAT: the operands are the tensors themselves (square capsules, D1 = D2 = D3) instead of the
-// capsule-transposed copies.  The copies are the same -- lane i then brings row (c, d1) with its
-// d2 values where the transposed tensor has row (c, d2) with its d1 values, at the same byte
-// offsets -- and the MFMA operands, single floats, are picked out of the slots one by one:
-// row (c, d2) at K index (pixel, d1) is element d2 of slot (pixel, c, d1).
-template <int CW, int TN, int NW, int KCH, bool NAT>
-__global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(waves_per_simd(TN, KCH)))) void wgrad32_kernel(const Wgrad32Params P)
+// NAT = 0: the operands are the capsule-transposed copies.  NAT = 1 (one chunk per capsule column)
+// or 2 (two or four): they are the tensors themselves (square capsules, D1 = D2 = D3).  The copies are the same -- lane i then brings row
+// (c, d1) with its d2 values where the transposed tensor has row (c, d2) with its d1 values, at the
+// same byte offsets -- and the values are picked out of the slots one by one: row (c, d2) at K
+// index (pixel, d1) is element d2 of slot (pixel, c, d1).
+template <int CW, int TM, int TN, int NAT>
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(TM + TN <= 4 ? 2 : 1)))
+void wgrad32_kernel(const Wgrad32Params P)
 {
-    constexpr int NB = ring_depth(KCH, TN);
-    constexpr int BM = 64 * NW, BN = 32 * TN, BNL = (BN + 63) / 64 * 64, TM = 2;
-    constexpr int A_BYTES = KCH * BM * 16, B_BYTES = KCH * BNL * 16;
-    constexpr int STAGE_BYTES = A_BYTES + B_BYTES;
-    constexpr int NBC = KCH * BNL / 64;  // column-side copies per stage, all waves
-    constexpr int BPW = NBC / NW;        // ... per wave
-    static_assert(NBC % NW == 0, "column copies divide evenly over the waves");
-    constexpr int NCOPY = KCH + BPW;     // copies per wave and stage
+    constexpr int PER = stage_period(CW), NB = ring_depth(TM, TN);
+    constexpr int RA = 32 * TM, RB = 32 * TN, TT = TM + TN;
+    constexpr int A_BYTES = SLOTS * RA * 16, B_BYTES = SLOTS * RB * 16, STAGE_BYTES = A_BYTES + B_BYTES;
+    constexpr int GA = (RA + 63) / 64, GB = (RB + 63) / 64;  // copies per slot
+    constexpr int NCOPY = SLOTS * (GA + GB);                 // ... per stage
+    constexpr int NPAIR = TT * CW;                           // pairs of values to split per stage
+    constexpr int WORDS = PER * CW;                          // pairs per tile and period
     constexpr int OOB = (int)0x80000000u;
-    // at a barrier the copies of the NB-2 most recent stages may still be in flight
-    constexpr int KEEP = (NB - 2) * NCOPY;
+    constexpr int NO_PIXEL = 0x7fffff00;  // no tensor range here is that long
+    constexpr int KEEP = (NB - 2) * NCOPY;  // copies that may be in flight when a stage begins
     static_assert(KEEP < 64, "vmcnt is a 6-bit counter");
     constexpr int VMCNT_KEEP = 0x0F70 | (KEEP & 15) | ((KEEP >> 4) << 14);
 
     extern __shared__ char smem[];
 
     // ---- which item: each XCD (workgroups are dealt to the 8 XCDs in turn) gets a contiguous
-    // range of items, image range slowest, so its resident workgroups read the same pixels
+    // range of items, pixel range slowest, so its resident workgroups read the same pixels
     long long item = blockIdx.x;
     {
         const long long per = P.items / 8;
@@ -111,7 +118,6 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(waves_p
     const int tp = tap / P.kw, tq = tap - tp * P.kw;
 
     const int lane = threadIdx.x & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int h = lane >> 5, lr = lane & 31;
 
     // ---- the pixels of this item.  Per image the output pixels whose tap (tp, tq) reads a
@@ -149,9 +155,8 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(waves_p
     const int i_rowjump = (s * P.W - (ny - 1) * s) * ipix, g_rowjump = (P.Wo - (ny - 1)) * gpix;
     const int i_imgjump = (P.H * P.W - nx * s * P.W) * ipix, g_imgjump = (P.Ho * P.Wo - nx * P.Wo) * gpix;
     // offsets are relative to image n0
-    int i_cur = (((x_lo + xs) * s - (P.pad - tp)) * P.W + ((y_lo + ys) * s - (P.pad - tq))) * ipix;
-    int g_cur = ((x_lo + xs) * P.Wo + y_lo + ys) * gpix;
-    int left = npix, yl = ny - ys, xl = nx - xs;
+    const int i_begin = (((x_lo + xs) * s - (P.pad - tp)) * P.W + ((y_lo + ys) * s - (P.pad - tq))) * ipix;
+    const int g_begin = ((x_lo + xs) * P.Wo + y_lo + ys) * gpix;
     const int n1 = n_last + 1;
 
     const char* it_base = static_cast<const char*>(P.it) + (long long)n0 * P.it_img_bytes;
@@ -161,207 +166,320 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(waves_p
     const unsigned lds0 = (unsigned)(size_t)(__attribute__((address_space(3))) char*)smem;
 
     // ---- per-lane constants: byte offset of the lane's row (column) within a pixel, or the
-    // out-of-range mark past the last row (column): those copy zeros
-    unsigned a_voff;
-    {
-        const int R = row_tile * BM + wave * 64 + lane;
+    // out-of-range mark past the last row (column) of the tile: those copy zeros
+    unsigned a_voff[GA], b_voff[GB];
+#pragma unroll
+    for (int u = 0; u < GA; ++u) {
+        const int rl = 64 * u + lane, R = row_tile * P.row_step + rl;
         const int c = R / P.D2, d2 = R - c * P.D2;
-        a_voff = R < P.rows ? (unsigned)((((c * P.D0 + d0) * P.D2 + d2) * P.D1) * 4) : (unsigned)OOB;
+        a_voff[u] = rl < P.row_step && R < P.rows ? (unsigned)((((c * P.D0 + d0) * P.D2 + d2) * P.D1) * 4)
+                                                  : (unsigned)OOB;
     }
-    unsigned b_voff[BPW];
 #pragma unroll
-    for (int j = 0; j < BPW; ++j) {
-        const int blk = wave * BPW + j;                 // chunk blk / (BNL/64), column block blk % ..
-        const int jl = (blk % (BNL / 64)) * 64 + lane;  // column within the tile
-        const int J = col_tile * BN + jl;
+    for (int u = 0; u < GB; ++u) {
+        const int jl = 64 * u + lane, J = col_tile * P.col_step + jl;
         const int m = J / P.D3, d3 = J - m * P.D3;
-        b_voff[j] = (jl < BN && J < P.cols)
-                        ? (unsigned)((((m * P.D0 + d0) * P.D3 + d3) * P.D1) * 4)
-                        : (unsigned)OOB;
+        b_voff[u] = jl < P.col_step && J < P.cols ? (unsigned)((((m * P.D0 + d0) * P.D3 + d3) * P.D1) * 4)
+                                                  : (unsigned)OOB;
     }
-
-    const int pps = KCH / P.D1C;                     // pixels per stage
-    const int d1c_shift = P.D1C == 1 ? 0 : P.D1C == 2 ? 1 : 2;
+    const int pps = NAT == 1 ? SLOTS : SLOTS / P.D1C;  // pixels per stage
     const int nstages = (npix + pps - 1) / pps;
-    const int nstages_pad = (nstages + NB - 1) / NB * NB;  // surplus stages contract zeros
 
-    // copies of the next stage (scalar pixel walk: the stage's pixels, each the next valid
-    // output pixel of the tap's rectangle, image after image; past the last one zero fill)
-    auto issue_stage = [&](int slot) {
-        const unsigned stage = lds0 + slot * STAGE_BYTES;
-        int i_soff[KCH], g_soff[KCH];
+    // Scalar pixel walk: a stage's pixels, each the next valid output pixel of the tap's rectangle,
+    // image after image; past the last one the out-of-range mark NO_PIXEL, which stays out of range
+    // without wrapping around when a lane's mark and a chunk's offset are added to it.  Three pieces
+    // of scalar instructions, written out: from C++ the compiler makes four times as many.
+    int left, yl, xl, i_cur, g_cur;
+    int i_soff[SLOTS], g_soff[SLOTS];
+    auto restart = [&]() {
+        left = npix;
+        yl = ny - ys;
+        xl = nx - xs;
+        i_cur = i_begin;
+        g_cur = g_begin;
 #pragma unroll
-        for (int j = 0; j < KCH; ++j) {
-            i_soff[j] = OOB;
-            g_soff[j] = OOB;
-            if (j < pps) {
-                if (left > 0) {
-                    i_soff[j] = i_cur;
-                    g_soff[j] = g_cur;
-                }
-                --left;
-                --yl;
-                if (yl != 0) {
-                    i_cur += i_step;
-                    g_cur += g_step;
-                } else {
-                    yl = ny;
-                    --xl;
-                    i_cur += i_rowjump;
-                    g_cur += g_rowjump;
-                    if (xl == 0) {
-                        xl = nx;
-                        i_cur += i_imgjump;
-                        g_cur += g_imgjump;
-                    }
-                }
-            }
+        for (int j = 0; j < SLOTS; ++j) i_soff[j] = g_soff[j] = NO_PIXEL;
+    };
+    int i_add, g_add, row_done;
+    auto walk = [&](int j, int piece) {
+        if (piece == 0) {
+            asm volatile("s_cmp_gt_i32 %2, 0\n\ts_cselect_b32 %0, %3, %5\n\ts_cselect_b32 %1, %4, %5\n\t"
+                         "s_sub_i32 %2, %2, 1"
+                         : "=&s"(i_soff[j]), "=&s"(g_soff[j]), "+s"(left)
+                         : "s"(i_cur), "s"(g_cur), "s"(NO_PIXEL) : "scc");
+        } else if (piece == 1) {
+            asm volatile("s_sub_i32 %0, %0, 1\n\ts_cmp_eq_u32 %0, 0\n\ts_cselect_b32 %1, %4, %5\n\t"
+                         "s_cselect_b32 %2, %6, %7\n\ts_cselect_b32 %0, %8, %0\n\ts_cselect_b32 %3, 1, 0"
+                         : "+s"(yl), "=&s"(i_add), "=&s"(g_add), "=&s"(row_done)
+                         : "s"(i_rowjump), "s"(i_step), "s"(g_rowjump), "s"(g_step), "s"(ny) : "scc");
+            asm volatile("s_add_i32 %0, %0, %3\n\ts_add_i32 %1, %1, %4\n\ts_sub_i32 %2, %2, %5"
+                         : "+s"(i_cur), "+s"(g_cur), "+s"(xl) : "s"(i_add), "s"(g_add), "s"(row_done) : "scc");
+        } else {
+            asm volatile("s_cmp_eq_u32 %0, 0\n\ts_cselect_b32 %1, %5, 0\n\ts_cselect_b32 %2, %6, 0\n\t"
+                         "s_cselect_b32 %0, %7, %0\n\ts_add_i32 %3, %3, %1\n\ts_add_i32 %4, %4, %2"
+                         : "+s"(xl), "=&s"(i_add), "=&s"(g_add), "+s"(i_cur), "+s"(g_cur)
+                         : "s"(i_imgjump), "s"(g_imgjump), "s"(nx) : "scc");
         }
+    };
+    constexpr int PIECES = 3;
+    auto walk_stage = [&]() {
 #pragma unroll
-        for (int q = 0; q < KCH; ++q) {
-            const int slot_px = q >> d1c_shift, part = q - (slot_px << d1c_shift);
-            int px = i_soff[0];
+        for (int j = 0; j < SLOTS; ++j)
+            if (j < pps)
 #pragma unroll
-            for (int k = 1; k < KCH; ++k) px = slot_px == k ? i_soff[k] : px;
-            copy_to_lds_dwords<CW>(rs_it, stage + (q * BM + 64 * wave) * 16, a_voff,
-                                   px == OOB ? OOB : px + part * CW * 4);
+                for (int k = 0; k < PIECES; ++k) walk(j, k);
+    };
+    // copy c (0 .. NCOPY-1) of the stage whose pixels have been walked, into the ring slot at `stage`
+    auto copy = [&](unsigned stage, auto C_) {
+        constexpr int c = decltype(C_)::value, q = c / (GA + GB), u = c % (GA + GB);
+        constexpr bool is_a = u < GA;
+        constexpr int g = is_a ? u : u - GA, R = is_a ? RA : RB;
+        constexpr bool half = 64 * g + 64 > R;  // the last 32 rows
+        const int(&soff)[SLOTS] = is_a ? i_soff : g_soff;
+        int so = soff[q];
+        if constexpr (NAT != 1) {  // slots of one pixel: its consecutive chunks
+            so = P.D1C == 1 ? so : P.D1C == 2 ? soff[q / 2] + (q % 2) * CW * 4 : soff[0] + q * CW * 4;
         }
-#pragma unroll
-        for (int j = 0; j < BPW; ++j) {
-            const int blk = wave * BPW + j;
-            const int q = blk / (BNL / 64);
-            const int slot_px = q >> d1c_shift, part = q - (slot_px << d1c_shift);
-            int px = g_soff[0];
-#pragma unroll
-            for (int k = 1; k < KCH; ++k) px = slot_px == k ? g_soff[k] : px;
-            copy_to_lds_dwords<CW>(rs_gt, stage + A_BYTES + blk * 1024, b_voff[j],
-                                   px == OOB ? OOB : px + part * CW * 4);
-        }
+        copy_to_lds_at<CW, half, (is_a ? 0 : A_BYTES) + (q * R + 64 * g) * 16>(
+            is_a ? rs_it : rs_gt, stage, is_a ? a_voff[g < GA ? g : 0] : b_voff[g < GB ? g : 0], so);
     };
 
     float16v acc[TN][TM];
+    auto clear_acc = [&]() {
 #pragma unroll
-    for (int a = 0; a < TN; ++a)
+        for (int a = 0; a < TN; ++a)
 #pragma unroll
-        for (int b = 0; b < TM; ++b)
+            for (int b = 0; b < TM; ++b)
 #pragma unroll
-            for (int r = 0; r < 16; ++r) acc[a][b][r] = 0.f;
+                for (int r = 0; r < 16; ++r) acc[a][b][r] = 0.f;
+    };
 
-    // row tiles of this wave that hold at least one real row (the others would multiply zeros)
-    bool row_tile_live[TM];
+    // ---- LDS offsets of this lane's values: tiles 0 .. TM-1 are row tiles, TM .. column tiles
+    unsigned rd[TT];
 #pragma unroll
-    for (int b = 0; b < TM; ++b) row_tile_live[b] = row_tile * BM + 64 * wave + b * 32 < P.rows;
-
-    // NAT: byte offsets of this lane's operands.  MFMA k-pair j takes K index 2j (lower half
-    // wave) and 2j+1 (upper half) of the stage's KCH*CW indices (pixel, d1).
-    constexpr int NPAIR = KCH * CW / 2;
-    int na_base[TM], nb_base[TN], na_k[NPAIR], nb_k[NPAIR];
-    if constexpr (NAT) {
-#pragma unroll
-        for (int b = 0; b < TM; ++b) {
-            const int rl = 64 * wave + 32 * b + lr;  // row within the tile
-            const int c_l = rl / P.D2, d2 = rl - c_l * P.D2;
-            const bool real = row_tile * BM + rl < P.rows;
-            na_base[b] = real ? ((d2 / CW) * BM + c_l * P.D1) * 16 + (d2 % CW) * 4 : 0;
-        }
-#pragma unroll
-        for (int a = 0; a < TN; ++a) {
-            const int jl = a * 32 + lr;  // column within the tile
-            const int m_l = jl / P.D3, d3 = jl - m_l * P.D3;
-            const bool real = col_tile * BN + jl < P.cols;
-            nb_base[a] = A_BYTES + (real ? ((d3 / CW) * BNL + m_l * P.D1) * 16 + (d3 % CW) * 4 : 0);
-        }
-#pragma unroll
-        for (int j = 0; j < NPAIR; ++j) {
-            const int k = 2 * j + h;
-            const int p = k / P.D1, d1 = k - p * P.D1;
-            na_k[j] = (p * P.D1C * BM + d1) * 16;
-            nb_k[j] = (p * P.D1C * BNL + d1) * 16;
+    for (int t = 0; t < TT; ++t) {
+        const int R = t < TM ? RA : RB, base = t < TM ? 0 : A_BYTES;
+        const int rl = 32 * (t < TM ? t : t - TM) + lr;
+        if constexpr (NAT) {
+            const int D = P.D2;  // = D1 = D3
+            const bool real = t < TM ? rl < P.row_step && row_tile * P.row_step + rl < P.rows
+                                     : rl < P.col_step && col_tile * P.col_step + rl < P.cols;
+            const int c_l = real ? rl / D : 0, d = real ? rl - c_l * D : 0;
+            // the half wave's first K index is (pixel, d1) = (2h, 0), (h, 0) or (0, 2 CW h)
+            const int k0 = NAT == 1 || P.D1C == 2 ? 2 * h * R : 2 * CW * h;
+            rd[t] = (unsigned)(base + (k0 + (d / CW) * R + c_l * D) * 16 + (d % CW) * 4);
+        } else {
+            rd[t] = (unsigned)(base + (2 * h * R + rl) * 16);
         }
     }
-
-    // A stage's operands are read from LDS in one go, the copies (and the scalar pixel walk) of
-    // a later stage are issued while those reads are on their way, then the stage's matrix
-    // instructions run: one LDS latency per stage is exposed instead of one per K pair
-    // (config 2: 1.05 -> 1.00 ms).
-    constexpr int NREAD = NAT ? NPAIR : KCH / 2;
-    float kb1[NAT ? NREAD : 1][TN], ia1[NAT ? NREAD : 1][TM];
-    float4v kb4[NAT ? 1 : NREAD][TN], ia4[NAT ? 1 : NREAD][TM];
-    auto read_stage = [&](int slot) {
-        const char* stage = smem + slot * STAGE_BYTES;
+    // value v (0 .. 2 CW - 1) of tile t of the stage at `slot`
+    auto read_one = [&](const char* slot, int t, int v) -> float {
+        const int R = t < TM ? RA : RB;
+        const int off = NAT == 1 ? (v / CW) * R + v % CW : v;
+        return *reinterpret_cast<const float*>(slot + rd[t] + off * 16);
+    };
+    auto read_chunk = [&](const char* slot, int t, int u) -> float4v {
+        return *reinterpret_cast<const float4v*>(slot + rd[t] + u * (t < TM ? RA : RB) * 16);
+    };
+    // all values of a tile, as pairs
+    auto take_tile = [&](const char* slot, int t, float* lo, float* hi) {
         if constexpr (NAT) {
 #pragma unroll
-            for (int j = 0; j < NPAIR; ++j) {
-#pragma unroll
-                for (int a = 0; a < TN; ++a)
-                    kb1[j][a] = *reinterpret_cast<const float*>(stage + nb_base[a] + nb_k[j]);
-#pragma unroll
-                for (int b = 0; b < TM; ++b)
-                    ia1[j][b] = *reinterpret_cast<const float*>(stage + na_base[b] + na_k[j]);
+            for (int i = 0; i < CW; ++i) {
+                lo[i] = read_one(slot, t, 2 * i);
+                hi[i] = read_one(slot, t, 2 * i + 1);
             }
         } else {
+            const float4v raw[2] = {read_chunk(slot, t, 0), read_chunk(slot, t, 1)};
 #pragma unroll
-            for (int t = 0; t < KCH / 2; ++t) {
-                // lanes 0..31 take chunk 2t, lanes 32..63 chunk 2t+1
-#pragma unroll
-                for (int a = 0; a < TN; ++a)
-                    kb4[t][a] = *reinterpret_cast<const float4v*>(
-                        stage + A_BYTES + ((2 * t + h) * BNL + a * 32 + lr) * 16);
-#pragma unroll
-                for (int b = 0; b < TM; ++b)
-                    ia4[t][b] = *reinterpret_cast<const float4v*>(
-                        stage + ((2 * t + h) * BM + 64 * wave + b * 32 + lr) * 16);
+            for (int i = 0; i < CW; ++i) {
+                lo[i] = raw[2 * i / CW][2 * i % CW];
+                hi[i] = raw[(2 * i + 1) / CW][(2 * i + 1) % CW];
             }
         }
     };
-    auto multiply_stage = [&]() {
-        if constexpr (NAT) {
+
+    // ---- the K loop on the split values
+    {
+        const MinusOne one;
+        unsigned iv[TT][3][WORDS];   // split values of one period: pairs per tile and term
+        float lo[NPAIR], hi[NPAIR];  // the pairs being split: what the terms so far leave over
+        // The bf16 instructions drop what lies far below the accumulator's last bit toward minus
+        // infinity: 2^-9 of that bit on average, but always the same way, which over the long K of
+        // a kernel gradient adds up (K = 262144: to more than all the rounding).  So the sums are
+        // taken with alternating sign: every FLIP stages the accumulators and the row operand
+        // change sign, every other range begins with the other sign, and the dropped parts cancel.
+        constexpr int FLIP = 48;  // a multiple of both periods
+        unsigned sign = split & 1 ? 0x80000000u : 0u;  // of the row values being split
+        // step `k` (0 .. 6) of splitting pair `p` of a stage at place `pos` of the period
+        auto split_step = [&](int p, int k, int pos) {
+            unsigned(&w)[3][WORDS] = iv[p / CW];
+            const int at = pos * CW + p % CW;
+            if (k == 0 && p / CW < TM) {
+                lo[p] = __builtin_bit_cast(float, __builtin_bit_cast(unsigned, lo[p]) ^ sign);
+                hi[p] = __builtin_bit_cast(float, __builtin_bit_cast(unsigned, hi[p]) ^ sign);
+            }
+            if (k % 3 == 0) {
+                w[k / 3][at] = round_pair(lo[p], hi[p]);
+                asm volatile("" : "+v"(w[k / 3][at]));  // (stays in the gap it is dealt to)
+            } else if (k % 3 == 1) {
+                lo[p] = minus_bf16(lo[p], w[k / 3][at], one.lo);
+                asm volatile("" : "+v"(lo[p]));
+            } else {
+                hi[p] = minus_bf16(hi[p], w[k / 3][at], one.hi);
+                asm volatile("" : "+v"(hi[p]));
+            }
+        };
+        // matrix instruction n of a period (stays in its place, like the splitting)
+        auto multiply = [&](auto N_) {
+            constexpr int n = decltype(N_)::value, NM = TN * TM * SPLIT_PRODUCTS;
+            constexpr int i = n % NM, W0 = n / NM * 4;  // (W0: the K step's first pair)
+            constexpr int b = i % TM, a = i / TM % TN, u = i / (TM * TN);
+            const unsigned(&wk)[WORDS] = iv[TM + a][SPLIT_TERM_A[u]];
+            const unsigned(&wi)[WORDS] = iv[b][SPLIT_TERM_B[u]];
+            const chunk_t kf = {wk[W0], wk[W0 + 1], wk[W0 + 2], wk[W0 + 3]};
+            const chunk_t xf = {wi[W0], wi[W0 + 1], wi[W0 + 2], wi[W0 + 3]};
+            asm volatile("" : "+a"(acc[a][b]));
+            Mma<bf16_tag>::run(kf, xf, acc[a][b]);
+            asm volatile("" : "+a"(acc[a][b]));
+        };
+        if constexpr (CW == 3) {  // the first period's first stage multiplies zeros
 #pragma unroll
-            for (int j = 0; j < NPAIR; ++j)
+            for (int t = 0; t < TT; ++t)
 #pragma unroll
-                for (int b = 0; b < TM; ++b) {
-                    if (!row_tile_live[b]) continue;  // wave-uniform
+                for (int k = 0; k < 3; ++k)
 #pragma unroll
-                    for (int a = 0; a < TN; ++a)
-                        acc[a][b] = __builtin_amdgcn_mfma_f32_32x32x2f32(kb1[j][a], ia1[j][b],
-                                                                         acc[a][b], 0, 0, 0);
-                }
-        } else {
-#pragma unroll
-            for (int t = 0; t < KCH / 2; ++t)
-#pragma unroll
-                for (int b = 0; b < TM; ++b) {
-                    if (!row_tile_live[b]) continue;  // wave-uniform
-#pragma unroll
-                    for (int u = 0; u < CW; ++u)
-#pragma unroll
-                        for (int a = 0; a < TN; ++a)
-                            acc[a][b] = __builtin_amdgcn_mfma_f32_32x32x2f32(
-                                kb4[t][a][u], ia4[t][b][u], acc[a][b], 0, 0, 0);
-                }
+                    for (int i = 8; i < 12; ++i) iv[t][k][i] = 0;
         }
-    };
-
-    // ---- prologue: NB-1 stages in flight, the first one landed
-    static_for<NB - 1>([&](auto S0) { issue_stage(decltype(S0)::value); });
-    __builtin_amdgcn_s_waitcnt(VMCNT_KEEP);
-    __syncthreads();
-
-    // ---- main loop: copy stage s+NB-1 into the slot read in iteration s-1, contract stage s
-    for (int st = 0; st < nstages_pad; st += NB) {
-        static_for<NB>([&](auto SLOT) {
-            constexpr int slot = decltype(SLOT)::value;
-            read_stage(slot);
-            issue_stage((slot + NB - 1) % NB);
-            multiply_stage();
-            // this wave's copies of the next stage have landed, its reads of this stage are
-            // done; after the barrier both hold for every wave
-            __builtin_amdgcn_s_waitcnt(VMCNT_KEEP & 0xF0FF);
-            __syncthreads();
+        clear_acc();
+        restart();
+        // prologue: NB stages in flight, the first landed, read and split; its slot is free then
+        static_for<NB>([&](auto S0) {
+            walk_stage();
+            static_for<NCOPY>([&](auto C_) { copy(lds0 + decltype(S0)::value * STAGE_BYTES, C_); });
         });
+        {
+            constexpr int keep0 = (NB - 1) * NCOPY;
+            static_assert(keep0 < 64, "vmcnt is a 6-bit counter");
+            __builtin_amdgcn_s_waitcnt(0x0F70 | (keep0 & 15) | ((keep0 >> 4) << 14));
+        }
+        asm volatile("" ::: "memory");
+#pragma unroll
+        for (int t = 0; t < TT; ++t) take_tile(smem, t, lo + t * CW, hi + t * CW);
+#pragma unroll
+        for (int k = 0; k < 7; ++k)
+#pragma unroll
+            for (int p = 0; p < NPAIR; ++p) split_step(p, k, 0);
+        __builtin_amdgcn_s_waitcnt(VMCNT_KEEP & 0xF0FF);  // stage 1 has landed, the reads are done
+        asm volatile("" ::: "memory");
+        unsigned cur = 0;  // ring slot of this stage: free, takes the stage NB ahead
+        int to_flip = FLIP;
+        for (int st = 0; st < nstages; st += PER) {
+            if (to_flip == 0) {
+                to_flip = FLIP;
+                sign ^= 0x80000000u;
+#pragma unroll
+                for (int a = 0; a < TN; ++a)
+#pragma unroll
+                    for (int b = 0; b < TM; ++b) acc[a][b] = -acc[a][b];
+                // the row values of the stage at hand are split already (CW = 3: as are those of the
+                // K step at hand)
+#pragma unroll
+                for (int b = 0; b < TM; ++b)
+#pragma unroll
+                    for (int t = 0; t < 3; ++t)
+#pragma unroll
+                        for (int i = 0; i < WORDS; ++i)
+                            if (i < CW || (CW == 3 && i >= 8)) iv[b][t][i] ^= 0x80008000u;
+            }
+            to_flip -= PER;
+            static_for<PER>([&](auto POS) {
+                constexpr int pos = decltype(POS)::value, next = (pos + 1) % PER;
+                // matrix instructions [first, last) of the period's: those of one K step (CW = 4), or
+                // a quarter of three K steps', which begin when the second stage is split and end
+                // in the next period's first stage
+                constexpr int NM = TN * TM * SPLIT_PRODUCTS, quarter = (pos + 3) % 4;
+                constexpr int first = CW == 4 ? pos * NM : quarter * 3 * NM / 4;
+                constexpr int last = CW == 4 ? first + NM : (quarter + 1) * 3 * NM / 4;
+                constexpr int NMMA = last - first;
+                const unsigned nxt = cur + STAGE_BYTES == NB * STAGE_BYTES ? 0 : cur + STAGE_BYTES;
+#pragma unroll
+                for (int t = 0; t < TT; ++t) take_tile(smem + nxt, t, lo + t * CW, hi + t * CW);
+                // side operations, dealt out over the gaps after the matrix instructions: the
+                // pixel walk and the copies of the stage NB ahead, the next stage's splitting
+                constexpr int NSTEP = 7 * NPAIR, GAPS = NMMA;
+                constexpr int FIRST = NMMA / 6;  // the values need time to arrive
+                constexpr int NWALK = SLOTS * PIECES, NSIDE = NWALK + NCOPY;
+                static_for<GAPS>([&](auto I) {
+                    constexpr int i = decltype(I)::value;
+                    multiply(std::integral_constant<int, first + i>{});
+                    constexpr int j0 = dealt_before(i, NSIDE, GAPS, 0), j1 = dealt_before(i + 1, NSIDE, GAPS, 0);
+                    static_for<j1 - j0>([&](auto J) {
+                        constexpr int j = j0 + decltype(J)::value;
+                        if constexpr (j < NWALK) {
+                            if (j / PIECES < pps) walk(j / PIECES, j % PIECES);
+                        } else {
+                            copy(lds0 + cur, std::integral_constant<int, j < NWALK ? 0 : j - NWALK>{});
+                        }
+                    });
+                    constexpr int t0 = dealt_before(i, NSTEP, GAPS, FIRST), t1 = dealt_before(i + 1, NSTEP, GAPS, FIRST);
+#pragma unroll
+                    for (int t = t0; t < t1; ++t) split_step(t % NPAIR, t / NPAIR, next);
+                    __builtin_amdgcn_sched_barrier(0);
+                });
+                // the copies of the stage after the next have landed, the reads are done
+                __builtin_amdgcn_s_waitcnt(VMCNT_KEEP & 0xF0FF);
+                asm volatile("" ::: "memory");
+                cur = nxt;
+            });
+        }
+        // the copies of the surplus stages still write (zeros) into this workgroup's LDS
+        __builtin_amdgcn_s_waitcnt(0x0F70);
+        if constexpr (CW == 3) {  // the last period's last quarter
+            constexpr int NM3 = 3 * TN * TM * SPLIT_PRODUCTS, begin = 3 * NM3 / 4;
+            static_for<NM3 - begin>([&](auto I) { multiply(std::integral_constant<int, begin + decltype(I)::value>{}); });
+        }
+        if (sign != 0) {
+#pragma unroll
+            for (int a = 0; a < TN; ++a)
+#pragma unroll
+                for (int b = 0; b < TM; ++b) acc[a][b] = -acc[a][b];
+        }
     }
-    // the copies of the surplus stages still write (zeros) into this workgroup's LDS
-    __builtin_amdgcn_s_waitcnt(0x0F70);
+
+    // ---- the same sums on the fp32 matrix instructions, one stage at a time
+    auto contract_exact = [&]() {
+        clear_acc();
+        restart();
+        for (int st = 0; st < nstages; ++st) {
+            walk_stage();
+            static_for<NCOPY>([&](auto C_) { copy(lds0, C_); });
+            __builtin_amdgcn_s_waitcnt(0x0F70);
+            asm volatile("" ::: "memory");
+            float lo[NPAIR], hi[NPAIR];
+#pragma unroll
+            for (int t = 0; t < TT; ++t) take_tile(smem, t, lo + t * CW, hi + t * CW);
+#pragma unroll
+            for (int i = 0; i < CW; ++i)
+#pragma unroll
+                for (int a = 0; a < TN; ++a)
+#pragma unroll
+                    for (int b = 0; b < TM; ++b) {
+                        acc[a][b] = __builtin_amdgcn_mfma_f32_32x32x2f32(lo[(TM + a) * CW + i], lo[b * CW + i], acc[a][b], 0, 0, 0);
+                        acc[a][b] = __builtin_amdgcn_mfma_f32_32x32x2f32(hi[(TM + a) * CW + i], hi[b * CW + i], acc[a][b], 0, 0, 0);
+                    }
+            __builtin_amdgcn_s_waitcnt(0xC07F);
+            asm volatile("" ::: "memory");
+        }
+    };
+    {
+        SplitCheck check;
+#pragma unroll
+        for (int a = 0; a < TN; ++a)
+#pragma unroll
+            for (int b = 0; b < TM; ++b) check.take(acc[a][b]);
+        if (__builtin_amdgcn_ballot_w64(check.failed()) != 0) contract_exact();
+    }
 
     // ---- epilogue: lane (h, lr) of tile (a, b) holds in registers 4g..4g+3 the columns
     // 8g + 4h + 0..3 of the tile for row lr of the tile
@@ -370,8 +488,8 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(waves_p
     const bool st4 = (P.D3 & 3) == 0;
 #pragma unroll
     for (int b = 0; b < TM; ++b) {
-        const int R = row_tile * BM + 64 * wave + b * 32 + lr;
-        if (R >= P.rows) continue;
+        const int rl = b * 32 + lr, R = row_tile * P.row_step + rl;
+        if (rl >= P.row_step || R >= P.rows) continue;
         const int c = R / P.D2, d2 = R - c * P.D2;
         float* orow = out + ((long long)tap * P.C + c) * P.M * caps +
                       ((long long)d0 * P.D2 + d2) * P.D3;
@@ -379,9 +497,9 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(waves_p
         for (int a = 0; a < TN; ++a) {
 #pragma unroll
             for (int g = 0; g < 4; ++g) {
-                const int j0 = col_tile * BN + a * 32 + 8 * g + 4 * h;
+                const int jl = a * 32 + 8 * g + 4 * h, j0 = col_tile * P.col_step + jl;
                 if (st4) {
-                    if (j0 < P.cols) {
+                    if (jl < P.col_step && j0 < P.cols) {
                         const int m = j0 / P.D3, d3 = j0 - m * P.D3;
                         float4v v = {acc[a][b][4 * g], acc[a][b][4 * g + 1], acc[a][b][4 * g + 2],
                                      acc[a][b][4 * g + 3]};
@@ -391,7 +509,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(waves_p
 #pragma unroll
                     for (int u = 0; u < 4; ++u) {
                         const int j = j0 + u;
-                        if (j < P.cols) {
+                        if (jl + u < P.col_step && j < P.cols) {
                             // j / D3 by multiplication (exact while j * D3 < 2^32, which the host has checked)
                             const int m = P.d3_magic ? (int)__umulhi((unsigned)j, P.d3_magic) : j / P.D3;
                             const int d3 = j - m * P.D3;
@@ -406,7 +524,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(waves_p
 
 struct Wgrad32Plan {
     Wgrad32Params P;
-    int cw, tn, nw;
+    int cw, tn, tm;
     size_t it_bytes, gt_bytes, partial_bytes;
 };
 
@@ -424,16 +542,36 @@ int chunk_width(const ConvShape& s)
     return 0;
 }
 
-// Fewest ranges such that the images one range touches (N/nsplit + 3) stay below 2^31 bytes;
+// Fewest ranges such that the images one range touches (N/nsplit + 3) stay below 0x7fffff00 bytes;
 // 0 if a single image is already too large for that.
 long long split_lower_bound(const ConvShape& s)
 {
     const long long it_img = (long long)s.H * s.W * s.C * s.D0 * s.D1 * s.D2 * 4;
     const long long gt_img = (long long)s.Ho * s.Wo * s.M * s.D0 * s.D1 * s.D3 * 4;
     const long long img_max = it_img > gt_img ? it_img : gt_img;
-    const long long imgs_cap = ((1LL << 31) - 1) / (img_max > 0 ? img_max : 1);
+    const long long imgs_cap = 0x7fffff00LL / (img_max > 0 ? img_max : 1);
     if (imgs_cap < 4) return 0;
     return (s.N + (imgs_cap - 3) - 1) / (imgs_cap - 3);
+}
+
+// MFMA tiles of 32 that `extent` rows or columns take in the kernel's tiles of at most three, and
+// how many whole tiles of that size: the fewest padded rows, then the fewest tiles
+void tile_extent(int extent, int unit, int& t, int& step, int& tiles)
+{
+    long long best = -1;
+    for (int k = 3; k >= 1; --k) {
+        int st = 32 * k;
+        if (extent > st) st = st / unit * unit;  // several tiles: each begins at a whole capsule
+        if (st == 0) continue;
+        const int n = ceil_div_i(extent, st);
+        const long long padded = (long long)n * 32 * k;
+        if (best < 0 || padded < best) {
+            best = padded;
+            t = k;
+            step = st;
+            tiles = n;
+        }
+    }
 }
 
 // Tiles and the split of the K loop (host side, pure arithmetic).
@@ -447,10 +585,10 @@ Wgrad32Plan make_plan(const ConvShape& s)
     P.D1C = pl.cw ? s.D1 / pl.cw : 1;
     P.rows = s.C * s.D2;
     P.cols = s.M * s.D3;
-    pl.tn = P.cols <= 32 ? 1 : P.cols <= 64 ? 2 : P.cols <= 96 ? 3 : 4;
-    pl.nw = P.rows <= 128 ? 2 : 4;
-    P.row_tiles = ceil_div_i(P.rows, 64 * pl.nw);
-    P.col_tiles = ceil_div_i(P.cols, 32 * pl.tn);
+    // square capsules need no transposed copies; their tiles begin at whole channels
+    P.natural = s.D1 == s.D2 && s.D1 == s.D3;
+    tile_extent(P.rows, P.natural ? s.D2 : 1, pl.tm, P.row_step, P.row_tiles);
+    tile_extent(P.cols, P.natural ? s.D3 : 1, pl.tn, P.col_step, P.col_tiles);
     P.ntaps = s.kh * s.kw;
     P.tiles = P.ntaps * s.D0 * P.row_tiles * P.col_tiles;
     P.out_elems = (long long)s.kernel_elems();
@@ -459,29 +597,29 @@ Wgrad32Plan make_plan(const ConvShape& s)
                      : 0u;  // 0: divide
     P.it_img_bytes = (long long)s.H * s.W * s.C * s.D0 * s.D1 * s.D2 * 4;
     P.gt_img_bytes = (long long)s.Ho * s.Wo * s.M * s.D0 * s.D1 * s.D3 * 4;
-    // square capsules whose tiles begin at whole channels need no transposed copies
-    P.natural = s.D1 == s.D2 && s.D1 == s.D3 &&
-                (P.row_tiles == 1 || (64 * pl.nw) % s.D2 == 0) &&
-                (P.col_tiles == 1 || (32 * pl.tn) % s.D3 == 0);
     pl.it_bytes = P.natural ? 0 : (size_t)s.N * P.it_img_bytes;
     pl.gt_bytes = P.natural ? 0 : (size_t)s.N * P.gt_img_bytes;
 
     // Split of the K loop (a tap's valid output pixels, at most N*Ho*Wo) over workgroups.  The
-    // workgroups resident at a time are bounded by LDS and registers; the split aims at one
-    // full round of them and keeps at least 16 stages per workgroup.  A range of N*rect/nsplit
-    // pixels touches at most N/nsplit + 3 images: their bytes must stay below 2^31 (a lower
-    // bound on nsplit), and the partial sums below 1 GiB (an upper bound).
-    const int kch = stage_chunks(P.D1C, pl.nw);
-    const size_t lds = (size_t)ring_depth(kch, pl.tn) * kch * (64 * pl.nw + (32 * pl.tn + 63) / 64 * 64) * 16;
-    long long per_cu = (long long)(160 * 1024 / lds);
-    const int wps = waves_per_simd(pl.tn, kch);  // by registers
-    if (per_cu > 4 * wps / pl.nw) per_cu = 4 * wps / pl.nw;
-    if (per_cu < 1) per_cu = 1;
+    // one-wave workgroups resident at a time are bounded by LDS and by registers (eight per CU where
+    // 256 of them hold a tile, else four); the split aims at one full round of them and keeps at
+    // least 8 stages per workgroup.  A range of N*rect/nsplit pixels touches at most N/nsplit + 3
+    // images: their bytes must stay below 2^31 (a lower bound on nsplit), and the partial sums
+    // below 1 GiB (an upper bound).
+    long long per_cu = (long long)(160 * 1024 / lds_bytes_of(pl.tm, pl.tn));
+    const int by_registers = pl.tm + pl.tn <= 4 ? 8 : 4;
+    if (per_cu > by_registers) per_cu = by_registers;
     const long long slots = 256 * per_cu;
     const long long full = (long long)s.N * s.Ho * s.Wo;
     long long want = slots / P.tiles;
     if (want < 1) want = 1;
-    const long long min_pix = 16LL * (kch / P.D1C);
+    // more rounds where a range would be longer than 3072 K values (the rounding of a sum grows with
+    // its length: 3x3x3 capsules, 32 channels, 64 images of 32x32: ranges of 5300 values 1.10e-6,
+    // of 2660 7.8e-7; the fp32 instructions 1.05e-6)
+    long long rounds = 1;
+    while (rounds < 4 && full * s.D1 / (rounds * slots / P.tiles > 0 ? rounds * slots / P.tiles : 1) > 3072) ++rounds;
+    if (rounds * slots / P.tiles > want) want = rounds * slots / P.tiles;
+    const long long min_pix = 8LL * SLOTS / P.D1C;
     if (want > (full + min_pix - 1) / min_pix) want = (full + min_pix - 1) / min_pix;
     if (want > 3072) want = 3072;
     while (want > 1 && (double)want * P.out_elems * 4 > (double)(1 << 30)) --want;
@@ -493,6 +631,45 @@ Wgrad32Plan make_plan(const ConvShape& s)
     return pl;
 }
 
+template <int CW, int TM, int TN, int NAT>
+hipError_t launch_one(const Wgrad32Params& P, hipStream_t stream)
+{
+    auto kern = wgrad32_kernel<CW, TM, TN, NAT>;
+    constexpr int lds_bytes = lds_bytes_of(TM, TN);
+    static std::atomic<unsigned long long> lds_set{0};
+    hipError_t err = set_dynamic_lds_once(reinterpret_cast<const void*>(kern), lds_bytes, lds_set);
+    if (err != hipSuccess) return err;
+    kern<<<dim3((unsigned)P.items), dim3(64), lds_bytes, stream>>>(P);
+    return hipGetLastError();
+}
+
+template <int CW, int TM, int TN>
+hipError_t launch_nat(const Wgrad32Params& P, hipStream_t stream)
+{
+    if (!P.natural) return launch_one<CW, TM, TN, 0>(P, stream);
+    return P.D1C == 1 ? launch_one<CW, TM, TN, 1>(P, stream) : launch_one<CW, TM, TN, 2>(P, stream);
+}
+
+template <int CW, int TM>
+hipError_t launch_tn(const Wgrad32Plan& pl, hipStream_t stream)
+{
+    switch (pl.tn) {
+        case 1: return launch_nat<CW, TM, 1>(pl.P, stream);
+        case 2: return launch_nat<CW, TM, 2>(pl.P, stream);
+        default: return launch_nat<CW, TM, 3>(pl.P, stream);
+    }
+}
+
+template <int CW>
+hipError_t launch_tm(const Wgrad32Plan& pl, hipStream_t stream)
+{
+    switch (pl.tm) {
+        case 1: return launch_tn<CW, 1>(pl, stream);
+        case 2: return launch_tn<CW, 2>(pl, stream);
+        default: return launch_tn<CW, 3>(pl, stream);
+    }
+}
+
 hipError_t launch_transpose32(const void* src, void* dst, size_t nmat, int A, int B,
                               hipStream_t stream)
 {
@@ -502,47 +679,6 @@ hipError_t launch_transpose32(const void* src, void* dst, size_t nmat, int A, in
     transpose_caps32_kernel<<<(unsigned)blocks, 256, 0, stream>>>(
         static_cast<const float*>(src), static_cast<float*>(dst), A, B, total);
     return hipGetLastError();
-}
-
-template <int CW, int TN, int NW, int KCH, bool NAT>
-hipError_t launch_nat(const Wgrad32Params& P, hipStream_t stream)
-{
-    constexpr int BM = 64 * NW, BNL = (32 * TN + 63) / 64 * 64;
-    auto kern = wgrad32_kernel<CW, TN, NW, KCH, NAT>;
-    const size_t lds_bytes = (size_t)ring_depth(KCH, TN) * KCH * (BM + BNL) * 16;
-    static std::atomic<unsigned long long> lds_set{0};
-    hipError_t err = set_dynamic_lds_once(reinterpret_cast<const void*>(kern), (int)lds_bytes, lds_set);
-    if (err != hipSuccess) return err;
-    kern<<<dim3((unsigned)P.items), dim3(64 * NW), lds_bytes, stream>>>(P);
-    return hipGetLastError();
-}
-
-template <int CW, int TN, int NW, int KCH>
-hipError_t launch_kch(const Wgrad32Params& P, hipStream_t stream)
-{
-    return P.natural ? launch_nat<CW, TN, NW, KCH, true>(P, stream)
-                     : launch_nat<CW, TN, NW, KCH, false>(P, stream);
-}
-
-template <int CW, int TN, int NW>
-hipError_t launch_one(const Wgrad32Params& P, hipStream_t stream)
-{
-    if constexpr (NW == 4)
-        return launch_kch<CW, TN, NW, 4>(P, stream);
-    else
-        return P.D1C == 4 ? launch_kch<CW, TN, NW, 4>(P, stream)
-                          : launch_kch<CW, TN, NW, 2>(P, stream);
-}
-
-template <int CW, int NW>
-hipError_t launch_tn(const Wgrad32Params& P, int tn, hipStream_t stream)
-{
-    switch (tn) {
-        case 1: return launch_one<CW, 1, NW>(P, stream);
-        case 2: return launch_one<CW, 2, NW>(P, stream);
-        case 3: return launch_one<CW, 3, NW>(P, stream);
-        default: return launch_one<CW, 4, NW>(P, stream);
-    }
 }
 
 }  // namespace
@@ -557,7 +693,7 @@ bool wgrad32_eligible(const ConvShape& s)
     if (it_img >= (1LL << 31) || gt_img >= (1LL << 31)) return false;
     if ((long long)s.stride * s.W * s.C * s.D0 * s.D1 * s.D2 * 4 >= (1LL << 30)) return false;
     if ((long long)s.C * s.D2 >= (1 << 24) || (long long)s.M * s.D3 >= (1 << 24)) return false;
-    const long long tiles = (long long)s.kh * s.kw * s.D0 * (((long long)s.C * s.D2 + 127) / 128) *
+    const long long tiles = (long long)s.kh * s.kw * s.D0 * (((long long)s.C * s.D2 + 31) / 32) *
                             (((long long)s.M * s.D3 + 31) / 32);
     const long long lo = split_lower_bound(s);
     if (lo == 0 || lo > 3072) return false;
@@ -594,10 +730,7 @@ hipError_t launch_wgrad32(const ConvShape& s, const void* input, const void* dou
         pl.P.gt = gt;
     }
     pl.P.out = pl.P.nsplit > 1 ? partial : dkernel;
-    if (pl.cw == 3)
-        err = pl.nw == 4 ? launch_tn<3, 4>(pl.P, pl.tn, stream) : launch_tn<3, 2>(pl.P, pl.tn, stream);
-    else
-        err = pl.nw == 4 ? launch_tn<4, 4>(pl.P, pl.tn, stream) : launch_tn<4, 2>(pl.P, pl.tn, stream);
+    err = pl.cw == 3 ? launch_tm<3>(pl, stream) : launch_tm<4>(pl, stream);
     if (err != hipSuccess) return err;
     if (pl.P.nsplit > 1)
         err = launch_splitk_reduce(partial, dkernel, pl.P.out_elems, pl.P.nsplit, stream);

@@ -87,3 +87,62 @@ def test_results_of_any_magnitude(shape, scale):
     # products below 2^-126 are rounded to multiples of 2^-149
     floor = 180 * 2.0 ** -149
     assert np.abs(got - ref).max() <= 1e-5 * np.abs(ref).max() + floor
+
+
+# ---- kernel gradient on the same decomposition: tiles of 1 .. 3 by 1 .. 3 MFMA tiles (several of
+# them beginning at whole capsules), both chunk widths, one, two and four chunks per capsule column,
+# square capsules (read in place) and others (transposed copies), ranges long enough to change sign
+WGRAD_SHAPES = [
+    (3, 7, 9, 5, 3, 3, 3, 1, 1, 3, 3, 3, 3),       # 15 x 9
+    (2, 8, 7, 22, 33, 2, 2, 1, 0, 1, 3, 3, 3),     # 66 x 99: several tiles of whole 3-row capsules
+    (2, 6, 6, 11, 17, 3, 3, 2, 1, 1, 6, 6, 6),     # 66 x 102, two 3-float chunks
+    (1, 5, 6, 3, 9, 2, 2, 1, 1, 1, 12, 12, 12),    # 36 x 108, four 3-float chunks
+    (2, 9, 9, 7, 25, 3, 3, 1, 1, 1, 4, 4, 4),      # 28 x 100
+    (2, 7, 7, 13, 9, 3, 3, 1, 2, 1, 8, 8, 8),      # 104 x 72
+    (2, 6, 5, 5, 4, 2, 2, 1, 0, 2, 16, 16, 16),    # 80 x 64, four 4-float chunks
+    (3, 9, 7, 20, 14, 3, 3, 1, 1, 1, 6, 5, 4),     # 100 x 56, transposed
+    (2, 9, 7, 9, 13, 3, 3, 3, 1, 1, 4, 5, 7),      # 45 x 91, transposed, stride 3
+    (40, 20, 20, 4, 5, 1, 1, 1, 0, 1, 4, 4, 4),    # ranges of many stages
+]
+
+
+def wgrad(w, x, g):
+    return cc.conv_bwd_kernel(to_device(x, wl.FP32), to_device(g, wl.FP32), (w.kh, w.kw), w.stride,
+                              w.pad).cpu().numpy()
+
+
+@pytest.mark.parametrize("shape", WGRAD_SHAPES, ids=["x".join(map(str, s)) for s in WGRAD_SHAPES])
+def test_split_kernel_gradient_matches_oracle(shape):
+    from oracle import capsconv
+    w = small("splitw_" + "x".join(map(str, shape)), wl.FP32, *shape, seed=614)
+    for v in (w, wl.integer_variant(w)):
+        x = wl.generate(v)[0]
+        g = wl.generate_dout(v)[0]
+        ref = capsconv.conv_bwd_kernel(x, g, (v.kh, v.kw), v.stride, v.pad)
+        got = wgrad(v, x, g)
+        if v is w:
+            # random sums of n terms: 2^-24 sqrt(n) of their size, n <= 16000
+            assert np.abs(got - ref).max() <= 1e-5 * np.abs(ref).max()
+        else:
+            assert np.array_equal(got, ref)
+
+
+@pytest.mark.parametrize("value", [np.inf, np.nan, -3.4028235e38])
+@pytest.mark.parametrize("shape", [(2, 9, 9, 4, 9, 3, 3, 1, 0, 1, 4, 4, 4), (2, 9, 9, 5, 9, 3, 3, 1, 0, 3, 3, 3, 3)],
+                         ids=["4x4", "3x3x3"])
+def test_kernel_gradient_of_values_bf16_cannot_hold(shape, value):
+    from oracle import capsconv
+    w = small("specialw", wl.FP32, *shape, seed=615)
+    x = np.clip(wl.generate(w)[0], -1, 1)
+    g = np.clip(wl.generate_dout(w)[0], -1, 1) * np.float32(0.125)
+    x.flat[53] = value
+    with np.errstate(invalid="ignore", over="ignore"):
+        ref = capsconv.conv_bwd_kernel(x, g, (w.kh, w.kw), w.stride, w.pad)
+    got = wgrad(w, x, g)
+    assert np.array_equal(np.isnan(got), np.isnan(ref))
+    inf = np.isinf(ref)
+    assert np.array_equal(got[inf], ref[inf].astype(np.float32))
+    ok = np.isfinite(ref) & (np.abs(ref) < 1e30)
+    assert ok.any() and np.abs(got[ok] - ref[ok]).max() <= 1e-5 * np.abs(ref[ok]).max()
+    big = np.isfinite(ref) & (np.abs(ref) >= 1e30) & (np.abs(ref) < 3e38)
+    assert (np.abs(got[big] - ref[big]) <= 1e-5 * np.abs(ref[big])).all()
