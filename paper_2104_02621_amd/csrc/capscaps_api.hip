@@ -63,7 +63,13 @@ int choose_path(const ConvShape& s)
     const long long cols = (long long)s.M * s.D3;
     if (kdim <= 24) return CAPSCAPS_PATH_DIRECT;
     const double flops = 2.0 * (double)s.out_elems() * (double)kdim;
-    if (cols <= 8 && (s.D2 % 4 != 0 || s.D3 % 4 != 0) && flops >= 5e7 && capscaps::wave_conv_eligible(s))
+    // (fp32 layers from 5e8 FLOPs on: the lane-per-row kernel, which contracts on the bf16 matrix
+    // instructions -- 6x5 . 5x4 capsules, 8 columns, 9.9 GFLOP 399 against 1473 us; 3x3x3 capsules, 6
+    // columns, 0.5 GFLOP 32 against 153 us)
+    const bool split32 = s.dtype == CAPSCAPS_FP32 && flops >= 5e8 &&
+                         (capscaps::mfma_rechunk_preferred(s) || capscaps::mfma_dma32_supported(s));
+    if (!split32 && cols <= 8 && (s.D2 % 4 != 0 || s.D3 % 4 != 0) && flops >= 5e7 &&
+        capscaps::wave_conv_eligible(s))
         return CAPSCAPS_PATH_DIRECT;
     switch (capscaps::mfma_auto_kernel(s)) {
         case capscaps::MfmaKernel::Tuned16: return CAPSCAPS_PATH_MFMA_TUNED16;

@@ -83,6 +83,8 @@ MfmaKernel mfma_auto_kernel(const ConvShape& s);  // what Auto resolves to (neve
 bool mfma_tuned16_supported(const ConvShape& s);
 bool mfma_dma32_supported(const ConvShape& s);
 bool mfma_small_supported(const ConvShape& s);
+// fp32 layers whose rows are written out in runs of four K values first (igemm_conv.hip)
+bool mfma_rechunk_preferred(const ConvShape& s);
 size_t mfma_workspace_bytes(const ConvShape& s);  // enough for every MfmaKernel choice (with
                                                   // s.out16: for Auto, the only choice then)
 size_t mfma_kernel_workspace_bytes(const ConvShape& s, MfmaKernel which);  // for that kernel only

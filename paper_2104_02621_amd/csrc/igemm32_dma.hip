@@ -508,14 +508,16 @@ Dma32Plan igemm32_dma_plan(const ConvShape& s)
 bool igemm32_dma_preferred(const ConvShape& s)
 {
     if (!igemm32_dma_eligible(s)) return false;
-    // fp32: from 3e9 nominal FLOPs on this kernel beats the any-shape and the small-problem one,
-    // split K loop or not (16 .. 64 channels of 4x4 and 8x8 capsules, 25 to 98 tiles of 256 rows: 3.7
-    // GFLOP 48 against 57 us, 4.8 GFLOP 56 against 59, 7.4 GFLOP 72 against 104; 1.9 GFLOP 44 against
-    // 30 us); capsule rows of 3k floats, which the others load element by element, from 1.2e9
-    // (32 channels of 3x3x3 capsules, 1.5 GFLOP: 36 against 72 us)
+    // fp32: where its four-wave tiles fill the chip, and from 3e9 nominal FLOPs on with a split K
+    // loop or one-wave tiles too (16 .. 64 channels of 4x4 and 8x8 capsules, 25 to 98 tiles of 256
+    // rows: 3.7 GFLOP 48 against 57 us on the small-problem kernel, 4.8 GFLOP 56 against 59, 7.4 GFLOP 72
+    // against 104; 1.9 GFLOP 44 against 30 us); capsule rows of 3k floats, which the others load
+    // element by element, from 5e8 (3x3x3 capsules: 0.5 GFLOP 32 against 65 us, 1.5 GFLOP 36 against 72)
     if (s.dtype == 0) {
+        const Dma32Plan pl = igemm32_dma_plan(s);
+        if (pl.nw == 4 && (long long)pl.P.row_tiles * pl.P.col_tiles * s.D0 >= 256) return true;
         const double flops = 2.0 * (double)s.out_elems() * s.kh * s.kw * s.C * s.D2;
-        return flops >= (igemm32_dma_chunk_width(s) == 3 ? 1.2e9 : 3e9);
+        return flops >= (igemm32_dma_chunk_width(s) == 3 ? 5e8 : 3e9);
     }
     // 16-bit: square capsules of 8 or 16 rows belong to the 256x256-tile kernel, which is 1.12 ..
     // 1.17x faster on whole column tiles (configs 3 and 5: 0.92 against 1.03 ms, 14.2 against

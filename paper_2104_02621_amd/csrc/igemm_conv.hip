@@ -560,9 +560,114 @@ bool shape_supported(const ConvShape& s)
     return true;
 }
 
+// ---- fp32 layers whose capsule rows no 12- or 16-byte copy fits (D2 = 1, 2, 5, 7, 9 ..).  This
+// kernel would load their input element by element (a 20 -> 14 channel 5x5 layer of 6x5 . 5x4
+// capsules, 20 images of 31x27: 643 us, 40 TFLOP/s).  Large ones are written out with the K values of
+// a row in runs of four, [pixel][k / 4][d0][d1][k % 4], k = (c, d2), padded with zeros: a layer of
+// 4-float capsule rows for the lane-per-row kernel.  The copy is made for a few images at a time,
+// so that the scratch stays small (48 MiB) and in the memory-side cache.
+constexpr size_t RECHUNK_BYTES = (size_t)48 << 20;
+constexpr size_t RECHUNK_TOTAL = (size_t)80 << 20;  // all scratch of the route (capscaps_conv_fwd_static has as much)
+
+__global__ __launch_bounds__(256) void rechunk_kernel(const float* __restrict__ src,
+                                                      float4v* __restrict__ dst, int C, int D2,
+                                                      int rows, int KQ, long long pixsz, unsigned total)
+{
+    const unsigned id = blockIdx.x * 256u + threadIdx.x;
+    if (id >= total) return;
+    unsigned r = id;
+    const int row = (int)(r % (unsigned)rows); r /= (unsigned)rows;
+    const int kq = (int)(r % (unsigned)KQ);
+    const float* p = src + (long long)(r / (unsigned)KQ) * pixsz + (long long)row * D2;
+    int c = 4 * kq / D2, d2 = 4 * kq - c * D2;
+    float4v v;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        v[e] = c < C ? p[(long long)c * rows * D2 + d2] : 0.f;
+        if (++d2 == D2) {
+            d2 = 0;
+            ++c;
+        }
+    }
+    dst[id] = v;
+}
+
+struct RechunkPlan {
+    bool ok;
+    ConvShape layer;  // the re-chunked layer, N = images of one part
+    int images;       // ... of all but the last part
+    size_t in_bytes, repack_bytes, partial_bytes;
+    size_t bytes() const { return in_bytes + ((repack_bytes + 255) & ~(size_t)255) + partial_bytes; }
+};
+
+// From 1.2e9 FLOPs on (5 GFLOP: 70 us against 109 on the small-problem kernel and 161 on this one).
+RechunkPlan rechunk_plan(const ConvShape& s)
+{
+    RechunkPlan rp{};
+    if (s.dtype != 0 || s.pad_w_set || s.out_view || igemm32_dma_chunk_width(s) != 0) return rp;
+    if (2.0 * (double)s.out_elems() * s.kh * s.kw * s.C * s.D2 < 1.2e9) return rp;
+    ConvShape f = s;
+    f.kernel_view = false;
+    f.C = ceil_div((long long)s.C * s.D2, 4);
+    f.D2 = 4;
+    f.N = 1;
+    const size_t img = f.in_elems() * 4;
+    if (img > RECHUNK_BYTES) return rp;
+    const int most = (int)(RECHUNK_BYTES / img), parts = ceil_div(s.N, most < s.N ? most : s.N);
+    rp.images = ceil_div(s.N, parts);
+    for (int n : {rp.images, s.N % rp.images}) {  // a whole part and the last one
+        if (n == 0) continue;
+        f.N = n;
+        if (!igemm32_dma_eligible(f)) return rp;
+        const Dma32Plan pl = igemm32_dma_plan(f);
+        if (pl.repack_bytes > rp.repack_bytes) rp.repack_bytes = pl.repack_bytes;
+        const size_t partial = (pl.partial_bytes + 255) & ~(size_t)255;
+        if (partial > rp.partial_bytes) rp.partial_bytes = partial;
+    }
+    f.N = rp.images;
+    rp.layer = f;
+    rp.in_bytes = (img * rp.images + 255) & ~(size_t)255;
+    rp.ok = rp.bytes() <= RECHUNK_TOTAL;
+    return rp;
+}
+
+hipError_t launch_rechunked(const ConvShape& s, const RechunkPlan& rp, const void* in,
+                            const void* kernel, float* out, void* workspace, hipStream_t stream)
+{
+    char* ws = static_cast<char*>(workspace);
+    float* partial = reinterpret_cast<float*>(ws + rp.in_bytes + ((rp.repack_bytes + 255) & ~(size_t)255));
+    ConvShape f = rp.layer;
+    const size_t img_in = s.in_elems() / s.N, img_out = s.out_elems() / s.N;
+    for (int n0 = 0; n0 < s.N; n0 += rp.images) {
+        f.N = s.N - n0 < rp.images ? s.N - n0 : rp.images;
+        Dma32Plan pl = igemm32_dma_plan(f);
+        pl.P.in = ws;
+        pl.P.kp = ws + rp.in_bytes;
+        float* dst = out + n0 * img_out;
+        pl.P.out = pl.P.nsplit > 1 ? partial : dst;
+        hipError_t err = hipSuccess;
+        if (n0 == 0) {  // (the packed kernel is the same for every number of images)
+            err = launch_repack_split(s, pl, kernel, ws + rp.in_bytes, stream);
+            if (err != hipSuccess) return err;
+        }
+        const unsigned total = (unsigned)(f.in_elems() / 4);
+        rechunk_kernel<<<(total + 255) / 256, 256, 0, stream>>>(
+            static_cast<const float*>(in) + n0 * img_in, reinterpret_cast<float4v*>(ws), s.C, s.D2,
+            s.D0 * s.D1, f.C, (long long)s.C * s.D0 * s.D1 * s.D2, total);
+        err = hipGetLastError();
+        if (err == hipSuccess) err = launch_igemm32_split(pl, stream);
+        if (err == hipSuccess && pl.P.nsplit > 1)
+            err = launch_splitk_reduce(partial, dst, pl.P.out_elems, pl.P.nsplit, stream, 0);
+        if (err != hipSuccess) return err;
+    }
+    return hipSuccess;
+}
+
 hipError_t launch_igemm(const ConvShape& s, const void* in, const void* kernel, float* out,
                         void* workspace, hipStream_t stream, MfmaKernel which)
 {
+    const RechunkPlan rp = rechunk_plan(s);
+    if (rp.ok) return launch_rechunked(s, rp, in, kernel, out, workspace, stream);
     Plan pl = make_plan(s, which);
     if (pl.blocks <= 0 || pl.blocks > 0x7fffffffLL) return hipErrorInvalidValue;
     char* ws = static_cast<char*>(workspace);
@@ -692,8 +797,7 @@ size_t mfma_workspace_bytes(const ConvShape& s)
     size_t need = 0;
     for (MfmaKernel which : {MfmaKernel::Generic, MfmaKernel::Tuned16}) {
         if (which == MfmaKernel::Tuned16 && !igemm16_fast_eligible(s)) continue;
-        const Plan pl = make_plan(s, which);
-        const size_t bytes = ((pl.repack_bytes + 255) & ~(size_t)255) + pl.partial_bytes;
+        const size_t bytes = mfma_kernel_workspace_bytes(s, which);
         if (bytes > need) need = bytes;
     }
     if (igemm32_dma_eligible(s)) {
@@ -710,6 +814,8 @@ size_t mfma_kernel_workspace_bytes(const ConvShape& s, MfmaKernel which)
     if (which == MfmaKernel::Auto) which = mfma_auto_kernel(s);
     if (which == MfmaKernel::Small) return igemm_small_workspace_bytes(s);
     if (which == MfmaKernel::Dma32) return dma32_workspace_bytes(igemm32_dma_plan(s));
+    const RechunkPlan rp = rechunk_plan(s);
+    if (rp.ok) return rp.bytes();
     const Plan pl = make_plan(s, which);
     return ((pl.repack_bytes + 255) & ~(size_t)255) + pl.partial_bytes;
 }
@@ -718,9 +824,12 @@ MfmaKernel mfma_auto_kernel(const ConvShape& s)
 {
     if (igemm32_dma_preferred(s)) return MfmaKernel::Dma32;
     if (igemm16_fast_preferred(s)) return MfmaKernel::Tuned16;
+    if (rechunk_plan(s).ok) return MfmaKernel::Generic;
     if (igemm_small_preferred(s)) return MfmaKernel::Small;
     return MfmaKernel::Generic;
 }
+
+bool mfma_rechunk_preferred(const ConvShape& s) { return shape_supported(s) && rechunk_plan(s).ok; }
 
 bool mfma_dma32_supported(const ConvShape& s)
 {

@@ -146,3 +146,43 @@ def test_kernel_gradient_of_values_bf16_cannot_hold(shape, value):
     assert ok.any() and np.abs(got[ok] - ref[ok]).max() <= 1e-5 * np.abs(ref[ok]).max()
     big = np.isfinite(ref) & (np.abs(ref) >= 1e30) & (np.abs(ref) < 3e38)
     assert (np.abs(got[big] - ref[big]) <= 1e-5 * np.abs(ref[big])).all()
+
+
+# ---- fp32 capsule rows no 12- or 16-byte copy fits: layers large enough to be written out in runs
+# of four K values first (D2 = 1, 2, 5, 7, 9), one part and several, forward and through the
+# transposed kernel view of the input gradient
+RECHUNK_SHAPES = [
+    (12, 20, 17, 11, 14, 5, 5, 1, 2, 1, 6, 5, 4),
+    (40, 24, 24, 9, 17, 3, 3, 2, 1, 2, 4, 7, 3),
+    (60, 28, 28, 33, 12, 3, 3, 1, 0, 1, 2, 1, 5),
+    (30, 32, 32, 13, 18, 3, 3, 1, 1, 1, 5, 2, 9),
+]
+
+
+@pytest.mark.parametrize("shape", RECHUNK_SHAPES, ids=["x".join(map(str, s)) for s in RECHUNK_SHAPES])
+def test_rows_of_any_length_match_oracle(shape):
+    w = small("rechunk_" + "x".join(map(str, shape)), wl.FP32, *shape, seed=616)
+    assert w.flops_nominal() >= 1.2e9
+    full_compare(w, cc.PATH_AUTO)
+
+
+def test_input_written_out_in_several_parts():
+    """150 MB of input: parts of 48 MiB, the last one shorter; small integers, so every kernel gives
+    the same bits."""
+    w = wl.integer_variant(small("parts", wl.FP32, 230, 40, 41, 10, 6, 3, 3, 1, 1, 1, 2, 5, 4, seed=617))
+    x, k = (to_device(t, wl.FP32) for t in wl.generate(w)[:2])
+    assert np.prod(w.input_shape) * 4 > 2 * (48 << 20)
+    a = run_gpu(w, x, k, cc.PATH_AUTO)
+    b = run_gpu(w, x, k, cc.PATH_DIRECT)
+    assert bool((a == b).all())
+
+
+@pytest.mark.parametrize("shape", [(24, 16, 18, 12, 10, 3, 3, 1, 1, 1, 6, 4, 5), (30, 15, 15, 8, 12, 5, 5, 2, 2, 1, 4, 8, 7)])
+def test_input_gradient_with_rows_of_any_length(shape):
+    from oracle import capsconv
+    w = small("rechunk_dx", wl.FP32, *shape, seed=618)
+    k = wl.generate(w)[1]
+    g = wl.generate_dout(w)[0]
+    ref = capsconv.conv_bwd_input(g, k, (w.H, w.W), w.stride, w.pad)
+    got = cc.conv_bwd_input(to_device(g, wl.FP32), to_device(k, wl.FP32), (w.H, w.W), w.stride, w.pad)
+    assert np.abs(got.cpu().numpy() - ref).max() <= 1e-5 * np.abs(ref).max()
