@@ -129,14 +129,15 @@ struct IgemmParams {
     float* tail_partial;
 };
 
-// Shared launch helpers (igemm_conv.hip).  Repack: 16-byte chunks of `cw` valid K elements
-// (zero-filled up to the slot's 4 floats / 8 halves); kgroup as documented at repack_kernel.
-hipError_t launch_repack(const ConvShape& s, const void* kernel, void* kp, int cw, int KQP,
+// Shared launch helpers (igemm_conv.hip).  Repack: 16-byte chunks of 4 floats or 8 halves;
+// kgroup as documented at repack_kernel.
+hipError_t launch_repack(const ConvShape& s, const void* kernel, void* kp, int KQP,
                          int colsp, int kgroup, size_t chunks, hipStream_t stream);
 hipError_t launch_splitk_reduce(const float* partial, float* out, long long elems, int nsplit,
                                 hipStream_t stream, int out16 = 0);
 
-// fp32 kernel with direct-to-LDS copies (igemm32_dma.hip): capsule rows of 3k or 4k floats.
+// Lane-per-row kernels with direct-to-LDS copies: 16-bit (igemm32_dma.hip), and fp32 capsule rows of
+// 3k or 4k floats (igemm32_split.hip).  Lengths and offsets in units of 4 bytes.
 struct Dma32Params {
     const void* in;
     const void* kp;
@@ -211,7 +212,8 @@ bool wgrad16_eligible(const ConvShape& s);
 size_t wgrad16_workspace_bytes(const ConvShape& s);
 hipError_t launch_wgrad16(const ConvShape& s, const void* input, const void* dout, float* dkernel,
                           void* workspace, hipStream_t stream);
-// ... and for fp32, capsule heights D1 of 3, 4, 6, 8, 12 or 16 floats (wgrad32.hip).
+// ... and for fp32 on the bf16 instructions, capsule heights D1 of 3, 4, 6, 8, 12 or 16 floats
+// (wgrad32.hip).
 bool wgrad32_eligible(const ConvShape& s);
 size_t wgrad32_workspace_bytes(const ConvShape& s);
 hipError_t launch_wgrad32(const ConvShape& s, const void* input, const void* dout, float* dkernel,
