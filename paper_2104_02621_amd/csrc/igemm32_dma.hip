@@ -528,13 +528,16 @@ bool igemm32_dma_preferred(const ConvShape& s)
         const long long pad256 = (cols + 255) / 256 * 256, pad128 = (cols + 127) / 128 * 128;
         if (pad256 * 100 < pad128 * 115) return false;
     }
-    // Fewer tiles than CUs, and too few for the 256x256-tile kernel: with one-wave tiles or a split K loop, from 9e9 nominal FLOPs on (14x14
+    // Fewer tiles than CUs (128 .. 255 of 256 rows), and too few for the 256x256-tile kernel: with one-wave
+    // tiles or a split K loop, from 9e9 nominal FLOPs on (14x14
     // images: 14.8 GFLOP of 4x4 capsules 51 against 60 us on the any-shape kernel, of 1x8 . 8x16 capsules
     // 42 against 54, 16.7 GFLOP of 4x8 . 8x16 47 against 55, 59 GFLOP of 16x16 105 against 155; 7.4 GFLOP of
     // 4x4 39 against 37)
     const Dma32Plan pl = igemm32_dma_plan(s);
     if (pl.nw == 4 && pl.P.nsplit == 1) return true;
-    return !igemm16_fast_preferred(s) && 2.0 * (double)s.out_elems() * s.kh * s.kw * s.C * s.D2 >= 9e9;
+    const long long tiles = (long long)ceil_div_ll(pl.P.rows, 256) * pl.P.col_tiles * s.D0;
+    return tiles >= 128 && !igemm16_fast_preferred(s) &&
+           2.0 * (double)s.out_elems() * s.kh * s.kw * s.C * s.D2 >= 9e9;
 }
 
 hipError_t launch_igemm32_dma(const Dma32Plan& pl, hipStream_t stream)
