@@ -1,6 +1,11 @@
-// Internal: fp32 values as the sum of three bf16 values, x = x1 + x2 + x3, each the rounding of
-// what the ones before leave over (exact: 3 x 8 significant bits and the signs of the remainders
-// hold fp32's 24), for the kernels that contract fp32 operands on the bf16 matrix instructions.
+// Internal: fp32 values as the sum of three bf16 values, 2^23 x = x1 + x2 + x3, each the rounding
+// of what the ones before leave over, for the kernels that contract fp32 operands on the bf16 matrix
+// instructions.  3 x 8 significant bits and the signs of the remainders hold fp32's 24; the factor
+// makes that hold for every magnitude: fp32's smallest step, 2^-149, becomes 2^-126, bf16's smallest
+// normal value, so no term of any value, subnormal ones included, is cut off at the bottom of
+// bf16's range.  (Unscaled, x3 of a value below 2^-110 would be, an absolute loss that the other
+// operand multiplies: 1e-38 times 1e20 came out 3e-3 off.)  At the top, values of 2^104 and more
+// and sums of 2^82 and more leave the range: they make the sum infinite or NaN (see SplitCheck).
 #pragma once
 #include <hip/hip_runtime.h>
 
@@ -32,24 +37,49 @@ __device__ __forceinline__ float minus_bf16(float x, unsigned pair, unsigned min
                                            __builtin_bit_cast(bf16x2v, minus_one), x, false);
 }
 
+constexpr float SPLIT_SCALE = 0x1p23f;     // of each operand
+constexpr float SPLIT_UNSCALE = 0x1p-46f;  // ... and of the sums of their products, back
+
 // Sums over split values that have to be taken again on the fp32 instructions: those that are not
-// finite (an infinity, a NaN, a value that rounds to infinity in bf16), and those that are not
-// zero but below 2^-80, where operands below 2^-110, whose x3 is cut off by bf16's exponent range,
-// may matter.
+// finite (an infinity, a NaN, a value or a sum that the scale factors take out of range).
 struct SplitCheck {
     float poison = 0.f;
-    unsigned small = 0xffffffffu;
     __device__ __forceinline__ void take(const float16v& acc)
     {
 #pragma unroll
-        for (int r = 0; r < 16; ++r) {
-            poison = fmaf(acc[r], 0.f, poison);  // NaN from an infinity or a NaN
-            const unsigned m = 2 * __builtin_bit_cast(unsigned, acc[r]) - 1;  // zero: the largest
-            small = m < small ? m : small;
-        }
+        for (int r = 0; r < 16; ++r) poison = fmaf(acc[r], 0.f, poison);  // NaN from an infinity or a NaN
     }
-    __device__ __forceinline__ bool failed() const { return poison != 0.f || small < ((127u - 80u) << 24); }
+    __device__ __forceinline__ bool failed() const { return poison != 0.f; }
 };
+
+// The steps of splitting a pair of values: both scaled, then three times rounded, with the
+// remainders taken in between.
+constexpr int SPLIT_STEPS = 9;
+
+// A kernel value the scale factor takes out of bf16's range (2^104 and more, an infinity, a NaN) is
+// packed as a NaN, which spoils every sum it enters, and its 32 bits in the other two terms'
+// places, for the sums taken again.
+constexpr unsigned short SPLIT_MARK = 0x7fffu;
+__device__ __forceinline__ void split_kernel_value(float x, unsigned short (&t)[3])
+{
+    const float xs = x * SPLIT_SCALE;
+    t[0] = round_to_16(xs, 1);
+    if ((t[0] & 0x7f80u) == 0x7f80u) {
+        const unsigned bits = __builtin_bit_cast(unsigned, x);
+        t[0] = SPLIT_MARK;
+        t[1] = (unsigned short)(bits >> 16);
+        t[2] = (unsigned short)bits;
+        return;
+    }
+    const float r1 = xs - low_half(t[0]);
+    t[1] = round_to_16(r1, 1);
+    t[2] = round_to_16(r1 - low_half(t[1]), 1);
+}
+__device__ __forceinline__ float joined_kernel_value(unsigned t0, unsigned t1, unsigned t2)
+{
+    const float sum = (low_half(t0) + low_half(t1)) + low_half(t2);
+    return t0 == SPLIT_MARK ? __builtin_bit_cast(float, t1 << 16 | t2) : sum * (1.f / SPLIT_SCALE);
+}
 
 // Side operations dealt out over the gaps after matrix instructions: operation t of `count` goes into
 // gap first + t * (gaps - first) / count; those of gap i are [dealt_before(i), dealt_before(i + 1)).

@@ -3,10 +3,8 @@
 // K = (tap, c, d2); paper Algorithm 2), for capsule rows of 3k or 4k floats.
 //
 // Bound: the matrix rate.  The fp32 matrix instructions of this chip run at a sixteenth of the
-// bf16 ones (157 against 2517 TFLOP/s), so every fp32 value is written as the sum of three bf16
-// values, x = x1 + x2 + x3, each the rounding of what the ones before leave over: 3 x 8
-// significant bits (and the signs of the remainders) hold the 24 bits of an fp32 value exactly.
-// A product is then nine bf16 products, each exact in the fp32 accumulator; the six with
+// bf16 ones (157 against 2517 TFLOP/s), so every fp32 value is written, times 2^23, as the exact sum
+// of three bf16 values (bf16_split.h).  A product is then nine bf16 products, each exact in the fp32 accumulator; the six with
 // i + j <= 4 are added up, smallest first, and the three left out (x2 y3, x3 y2, x3 y3) are below
 // 2^-25 of the product, less than the rounding of one fp32 addition.  Six instructions for 16 K
 // values take 192 cycles per 32 x 32 tile where the fp32 ones take 512.  The sums themselves
@@ -18,19 +16,17 @@
 // power limit leaves (1.5 .. 1.6 GHz); 3-float chunks also at the rate of the L1 lookups (57 per
 // copy, 16 where 4-float rows lie side by side).
 //
-// What the decomposition cannot represent is recomputed: infinities and NaNs (and values that
-// round to infinity in bf16) leave NaN in the sums they belong to, and operands below 2^-110 lose
-// bits of x3 to bf16's exponent range, which matters only to results that are as small.  A
-// workgroup that finds a result that is not finite, or not zero and below 2^-80, runs its K loop
-// again on the fp32 matrix instructions from the same LDS data (the input side lies there
-// unsplit; the kernel side's three values add up to the fp32 value exactly).
+// What the decomposition cannot represent is recomputed: infinities, NaNs, values of 2^104 and more
+// and sums of 2^82 and more make their sums infinite or NaN.  A workgroup that finds a sum that is
+// not finite runs its K loop again on the fp32 matrix instructions from the same LDS data (the
+// input side lies there unsplit; the kernel side's three terms give the fp32 value exactly).
 //
 // Unit of data movement on the input side: a 16-byte LDS slot holding CW = 3 or 4 consecutive d2
 // of one capsule row ("chunk"); a 3-float chunk is copied by a 12-byte buffer load, which lands at
 // a 16-byte lane stride.  A stage of the K loop is 4 slots of every row.  The lower half wave
 // takes slots 0 and 1 of its row, the upper half slots 2 and 3: 8 values (CW = 4), the K extent of
 // one bf16 instruction, or 6 (CW = 3), so that four stages make three instructions' worth.  The
-// values are split in registers (5.5 vector instructions each, under the matrix instructions of the
+// values are split in registers (4.5 vector instructions each, under the matrix instructions of the
 // SIMD's other wave); the kernel tensor is split once per call, by the repack pass.
 //
 // Tile: 64*NW rows x 32*TN columns; wave w copies and contracts rows 64w..64w+63 (two MFMA row
@@ -246,16 +242,20 @@ void igemm32_split_kernel(const Dma32Params P)
         // K values of one period, split: pairs per row tile and term
         unsigned iv[TM][3][WORDS];
         float lo[NPAIR], hi[NPAIR];  // the pairs being split: what the terms so far leave over
-        // step `k` (0 .. 6) of splitting pair `p` of a stage at place `pos` of the period
+        // step `k` (0 .. SPLIT_STEPS - 1) of splitting pair `p` of a stage at place `pos` of the period
         auto split_step = [&](int p, int k, int pos) {
             unsigned(&w)[3][WORDS] = iv[p / CW];
-            const int at = pos * CW + p % CW;
-            if (k % 3 == 0)
-                w[k / 3][at] = round_pair(lo[p], hi[p]);
-            else if (k % 3 == 1)
-                lo[p] = minus_bf16(lo[p], w[k / 3][at], one.lo);
+            const int at = pos * CW + p % CW, t = (k - 2) / 3;
+            if (k == 0)
+                lo[p] *= SPLIT_SCALE;
+            else if (k == 1)
+                hi[p] *= SPLIT_SCALE;
+            else if (k % 3 == 2)
+                w[t][at] = round_pair(lo[p], hi[p]);
+            else if (k % 3 == 0)
+                lo[p] = minus_bf16(lo[p], w[t][at], one.lo);
             else
-                hi[p] = minus_bf16(hi[p], w[k / 3][at], one.hi);
+                hi[p] = minus_bf16(hi[p], w[t][at], one.hi);
         };
         auto take_input = [&](const char* slot) {
             float4v raw[TM][2];
@@ -292,7 +292,7 @@ void igemm32_split_kernel(const Dma32Params P)
         __syncthreads();
         take_input(smem);
 #pragma unroll
-        for (int k = 0; k < 7; ++k)
+        for (int k = 0; k < SPLIT_STEPS; ++k)
 #pragma unroll
             for (int p = 0; p < NPAIR; ++p) split_step(p, k, 0);
         chunk_t kb[2][3];  // kernel operands of a column tile, double-buffered
@@ -325,7 +325,7 @@ void igemm32_split_kernel(const Dma32Params P)
                 take_input(smem + a_next);
                 // side operations, dealt out over the gaps after the matrix instructions: the
                 // copies, the operands of the next column tile, the next stage's splitting
-                constexpr int NSTEP = 7 * NPAIR, GAPS = NMMA > 0 ? NMMA : 1;
+                constexpr int NSTEP = SPLIT_STEPS * NPAIR, GAPS = NMMA > 0 ? NMMA : 1;
                 constexpr int FIRST = NMMA > 0 ? 6 : 0;  // the input values need time to arrive
                 static_for<GAPS>([&](auto I) {
                     constexpr int i = decltype(I)::value;
@@ -376,6 +376,10 @@ void igemm32_split_kernel(const Dma32Params P)
         }
         // the copies of the surplus stages still write into this workgroup's LDS
         __builtin_amdgcn_s_waitcnt(0x0F70);
+#pragma unroll
+        for (int a = 0; a < TN; ++a)
+#pragma unroll
+            for (int b = 0; b < TM; ++b) acc[a][b] *= SPLIT_UNSCALE;
     }
 
     // ---- the same sums on the fp32 matrix instructions, one stage at a time
@@ -410,11 +414,11 @@ void igemm32_split_kernel(const Dma32Params P)
                         for (int t = 0; t < 3; ++t) k[t] = read_kernel(smem + B_LDS, a, t);
 #pragma unroll
                         for (int e = 0; e < 8; ++e) {
-                            float v[3];
+                            unsigned v[3];
 #pragma unroll
                             for (int t = 0; t < 3; ++t)
-                                v[t] = e & 1 ? high_half(k[t][e / 2]) : low_half(k[t][e / 2]);
-                            const float kv = (v[0] + v[1]) + v[2];
+                                v[t] = e & 1 ? k[t][e / 2] >> 16 : k[t][e / 2] & 0xffffu;
+                            const float kv = joined_kernel_value(v[0], v[1], v[2]);
 #pragma unroll
                             for (int b = 0; b < TM; ++b)
                                 acc[a][b] = __builtin_amdgcn_mfma_f32_32x32x2f32(kv, ix[b][V0 + e], acc[a][b], 0, 0, 0);
@@ -571,18 +575,10 @@ __global__ __launch_bounds__(256) void repack_split_kernel(const SplitRepackPara
             x = P.kernel[P.k_base + p * P.k_sp + q * P.k_sq + c * P.k_sc + m * P.k_sm + d0 * P.k_sd0 +
                          d2 * P.k_sd2 + d3 * P.k_sd3];
         }
-        // x = t1 + t2 + t3 exactly, also where the rounding to bf16 would overflow (then t1 is
-        // truncated) and for infinities and NaNs (t2 = t3 = 0)
-        const unsigned bits = __builtin_bit_cast(unsigned, x);
-        const bool finite = (bits & 0x7f800000u) != 0x7f800000u;
-        unsigned short t1 = round_to_16(x, 1);
-        if (finite && (t1 & 0x7f80u) == 0x7f80u) t1 = (unsigned short)(bits >> 16);
-        const float r1 = finite ? x - low_half(t1) : 0.f;
-        const unsigned short t2 = round_to_16(r1, 1);
-        const unsigned short t3 = round_to_16(r1 - low_half(t2), 1);
-        w[0][e] = t1;
-        w[1][e] = t2;
-        w[2][e] = t3;
+        unsigned short t[3];
+        split_kernel_value(x, t);
+#pragma unroll
+        for (int i = 0; i < 3; ++i) w[i][e] = t[i];
     }
     const size_t step = ((size_t)d0 * P.col_tiles + col_tile) * P.ksteps + ks;
 #pragma unroll

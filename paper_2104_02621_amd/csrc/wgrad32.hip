@@ -3,12 +3,12 @@
 // inside the image; the K_diff result of the paper's Algorithm 4 read as the derivative of
 // Algorithm 2's sum), for capsule heights D1 of 3, 4, 6, 8, 12 or 16 floats.
 //
-// Bound: the matrix rate.  As in igemm32_split.hip every fp32 value is the exact sum of three bf16
-// values (bf16_split.h) and six bf16 products take the place of one fp32 product: 192 instead of
-// 512 cycles per 32 x 32 tile and 16 K values; a workgroup whose sums are not finite, or not zero
-// and below 2^-80, takes them again on the fp32 instructions.  Both operands are split in
+// Bound: the matrix rate.  As in igemm32_split.hip every fp32 value, times 2^23, is the exact sum of
+// three bf16 values (bf16_split.h) and six bf16 products take the place of one fp32 product: 192
+// instead of 512 cycles per 32 x 32 tile and 16 K values; a workgroup with a sum that is not finite
+// takes its sums again on the fp32 instructions.  Both operands are split in
 // registers, so the tile is what decides: a workgroup is ONE wave with up to 96 x 96 of the result
-// (3 x 3 MFMA tiles: 54 matrix instructions beside 168 vector instructions of splitting per 16 K
+// (3 x 3 MFMA tiles: 54 matrix instructions beside 216 vector instructions of splitting per 16 K
 // values), with LDS of its own and no barrier.  Measured (N = 64, 32x32, 3x3, 32 -> 32 channels of
 // 3x3x3 capsules): 0.92 ms on the fp32 instructions with 128 x 96 tiles of two waves, 0.66 ms here
 // (error against 64-bit sums 1.05e-6 and 7.8e-7); 35 % of the cycles issue no matrix instruction
@@ -310,23 +310,26 @@ void wgrad32_kernel(const Wgrad32Params P)
         // taken with alternating sign: every FLIP stages the accumulators and the row operand
         // change sign, every other range begins with the other sign, and the dropped parts cancel.
         constexpr int FLIP = 48;  // a multiple of both periods
-        unsigned sign = split & 1 ? 0x80000000u : 0u;  // of the row values being split
-        // step `k` (0 .. 6) of splitting pair `p` of a stage at place `pos` of the period
+        unsigned row_scale = __builtin_bit_cast(unsigned, SPLIT_SCALE) | (unsigned)split << 31;  // of the row values being split
+        // step `k` (0 .. SPLIT_STEPS - 1) of splitting pair `p` of a stage at place `pos` of the period
         auto split_step = [&](int p, int k, int pos) {
             unsigned(&w)[3][WORDS] = iv[p / CW];
-            const int at = pos * CW + p % CW;
-            if (k == 0 && p / CW < TM) {
-                lo[p] = __builtin_bit_cast(float, __builtin_bit_cast(unsigned, lo[p]) ^ sign);
-                hi[p] = __builtin_bit_cast(float, __builtin_bit_cast(unsigned, hi[p]) ^ sign);
-            }
-            if (k % 3 == 0) {
-                w[k / 3][at] = round_pair(lo[p], hi[p]);
-                asm volatile("" : "+v"(w[k / 3][at]));  // (stays in the gap it is dealt to)
-            } else if (k % 3 == 1) {
-                lo[p] = minus_bf16(lo[p], w[k / 3][at], one.lo);
+            const int at = pos * CW + p % CW, t = (k - 2) / 3;
+            const float scale = p / CW < TM ? __builtin_bit_cast(float, row_scale) : SPLIT_SCALE;
+            if (k == 0) {
+                lo[p] *= scale;
+                asm volatile("" : "+v"(lo[p]));  // (stays in the gap it is dealt to)
+            } else if (k == 1) {
+                hi[p] *= scale;
+                asm volatile("" : "+v"(hi[p]));
+            } else if (k % 3 == 2) {
+                w[t][at] = round_pair(lo[p], hi[p]);
+                asm volatile("" : "+v"(w[t][at]));
+            } else if (k % 3 == 0) {
+                lo[p] = minus_bf16(lo[p], w[t][at], one.lo);
                 asm volatile("" : "+v"(lo[p]));
             } else {
-                hi[p] = minus_bf16(hi[p], w[k / 3][at], one.hi);
+                hi[p] = minus_bf16(hi[p], w[t][at], one.hi);
                 asm volatile("" : "+v"(hi[p]));
             }
         };
@@ -367,7 +370,7 @@ void wgrad32_kernel(const Wgrad32Params P)
 #pragma unroll
         for (int t = 0; t < TT; ++t) take_tile(smem, t, lo + t * CW, hi + t * CW);
 #pragma unroll
-        for (int k = 0; k < 7; ++k)
+        for (int k = 0; k < SPLIT_STEPS; ++k)
 #pragma unroll
             for (int p = 0; p < NPAIR; ++p) split_step(p, k, 0);
         __builtin_amdgcn_s_waitcnt(VMCNT_KEEP & 0xF0FF);  // stage 1 has landed, the reads are done
@@ -377,7 +380,7 @@ void wgrad32_kernel(const Wgrad32Params P)
         for (int st = 0; st < nstages; st += PER) {
             if (to_flip == 0) {
                 to_flip = FLIP;
-                sign ^= 0x80000000u;
+                row_scale ^= 0x80000000u;
 #pragma unroll
                 for (int a = 0; a < TN; ++a)
 #pragma unroll
@@ -407,7 +410,7 @@ void wgrad32_kernel(const Wgrad32Params P)
                 for (int t = 0; t < TT; ++t) take_tile(smem + nxt, t, lo + t * CW, hi + t * CW);
                 // side operations, dealt out over the gaps after the matrix instructions: the
                 // pixel walk and the copies of the stage NB ahead, the next stage's splitting
-                constexpr int NSTEP = 7 * NPAIR, GAPS = NMMA;
+                constexpr int NSTEP = SPLIT_STEPS * NPAIR, GAPS = NMMA;
                 constexpr int FIRST = NMMA / 6;  // the values need time to arrive
                 constexpr int NWALK = SLOTS * PIECES, NSIDE = NWALK + NCOPY;
                 static_for<GAPS>([&](auto I) {
@@ -439,12 +442,11 @@ void wgrad32_kernel(const Wgrad32Params P)
             constexpr int NM3 = 3 * TN * TM * SPLIT_PRODUCTS, begin = 3 * NM3 / 4;
             static_for<NM3 - begin>([&](auto I) { multiply(std::integral_constant<int, begin + decltype(I)::value>{}); });
         }
-        if (sign != 0) {
+        const float unscale = row_scale >> 31 ? -SPLIT_UNSCALE : SPLIT_UNSCALE;
 #pragma unroll
-            for (int a = 0; a < TN; ++a)
+        for (int a = 0; a < TN; ++a)
 #pragma unroll
-                for (int b = 0; b < TM; ++b) acc[a][b] = -acc[a][b];
-        }
+            for (int b = 0; b < TM; ++b) acc[a][b] *= unscale;
     }
 
     // ---- the same sums on the fp32 matrix instructions, one stage at a time

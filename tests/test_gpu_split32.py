@@ -186,3 +186,54 @@ def test_input_gradient_with_rows_of_any_length(shape):
     ref = capsconv.conv_bwd_input(g, k, (w.H, w.W), w.stride, w.pad)
     got = cc.conv_bwd_input(to_device(g, wl.FP32), to_device(k, wl.FP32), (w.H, w.W), w.stride, w.pad)
     assert np.abs(got.cpu().numpy() - ref).max() <= 1e-5 * np.abs(ref).max()
+
+
+# ---- operands of opposite magnitudes: what a split drops of a tiny operand is multiplied by the other
+# one, so a result of ordinary size may rest on it, and a kernel tensor may be as small as an input
+MAGNITUDES = [(1, 1e-36), (1, 1e-39), (1, 1e-41), (1e-36, 1e30), (1e30, 1e-36), (1e-38, 1e20), (1e20, 1e-38),
+              (1e-40, 1e35), (1e35, 1e-40), (1e-41, 1), (1e15, 1e15), (1e-44, 1e30)]
+
+
+def scaled(a, scale):
+    return (a.astype(np.float64) * scale).astype(np.float32)
+
+
+def check_magnitude(got, ref):
+    # sums of fp32 products: 1e-5 of the largest result, and below 2^-126 multiples of 2^-149 (one
+    # rounding per addition at most, fewer than 4000 of them)
+    assert np.isfinite(got).all()
+    assert np.abs(got - ref).max() <= 1e-5 * np.abs(ref).max() + 4000 * 2.0 ** -149
+
+
+@pytest.mark.parametrize("scales", MAGNITUDES, ids=lambda s: f"{s[0]:g}x{s[1]:g}")
+@pytest.mark.parametrize("shape", SPECIAL + [(12, 20, 17, 11, 14, 5, 5, 1, 2, 1, 6, 5, 4)],
+                         ids=["4x4", "3x3x3", "rows_of_5"])
+def test_forward_with_operands_of_any_magnitude(shape, scales):
+    w = small("magnitudes", wl.FP32, *shape, seed=619)
+    x, k = (scaled(a, s) for a, s in zip(wl.generate(w)[:2], scales))
+    path = cc.PATH_AUTO if shape[12] == 4 and shape[11] == 5 else cc.PATH_MFMA_TUNED32
+    got = run_gpu(w, to_device(x, wl.FP32), to_device(k, wl.FP32), path).cpu().numpy()
+    check_magnitude(got, exact64(w, x, k))
+
+
+@pytest.mark.parametrize("scales", MAGNITUDES, ids=lambda s: f"{s[0]:g}x{s[1]:g}")
+def test_input_gradient_with_operands_of_any_magnitude(scales):
+    from oracle import capsconv
+    w = small("magnitudes_dx", wl.FP32, 24, 18, 18, 16, 16, 3, 3, 1, 1, 1, 3, 3, 3, seed=620)
+    args = (w.N, w.H, w.W, w.M, w.C, w.kh, w.kw, 1, 1, w.D0, w.D1, w.D3, w.D2, w.dtype)
+    assert cc.capscaps_select_path(*args) == cc.PATH_MFMA_TUNED32
+    k = scaled(wl.generate(w)[1], scales[1])
+    g = scaled(wl.generate_dout(w)[0], scales[0])
+    got = cc.conv_bwd_input(to_device(g, wl.FP32), to_device(k, wl.FP32), (w.H, w.W), w.stride, w.pad)
+    check_magnitude(got.cpu().numpy(), capsconv.conv_bwd_input(g, k, (w.H, w.W), w.stride, w.pad))
+
+
+@pytest.mark.parametrize("scales", MAGNITUDES, ids=lambda s: f"{s[0]:g}x{s[1]:g}")
+@pytest.mark.parametrize("shape", [WGRAD_SHAPES[0], WGRAD_SHAPES[4], WGRAD_SHAPES[7]],
+                         ids=["3x3x3", "4x4", "6x5.5x4"])
+def test_kernel_gradient_with_operands_of_any_magnitude(shape, scales):
+    from oracle import capsconv
+    w = small("magnitudes_dk", wl.FP32, *shape, seed=621)
+    x = scaled(wl.generate(w)[0], scales[0])
+    g = scaled(wl.generate_dout(w)[0], scales[1])
+    check_magnitude(wgrad(w, x, g), capsconv.conv_bwd_kernel(x, g, (w.kh, w.kw), w.stride, w.pad))
