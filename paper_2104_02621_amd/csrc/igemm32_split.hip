@@ -8,7 +8,13 @@
 // i + j <= 4 are added up, smallest first, and the three left out (x2 y3, x3 y2, x3 y3) are below
 // 2^-25 of the product, less than the rounding of one fp32 addition.  Six instructions for 16 K
 // values take 192 cycles per 32 x 32 tile where the fp32 ones take 512.  The sums themselves
-// stay in fp32, with fewer roundings than before (6 accumulations per 16 K values, not 8).
+// stay in fp32, with fewer roundings (6 accumulations per 16 K values, not 8).  The bf16 instructions
+// drop what lies far below the accumulator's last bit toward minus infinity, which in a long K loop
+// adds up; the accumulators and the input values change sign every FLIP stages, so that the dropped
+// parts cancel.  Root mean square error against 64-bit sums (results of size 1) at K = 1152, 9600,
+// 55296, 131072: fp32 instructions 6.1e-7, 1.8e-6, 4.2e-6, 6.5e-6, here 5.2e-7, 1.5e-6, 3.2e-6,
+// 4.7e-6, mean errors below 6e-8 (without the sign change 5.2e-7, 1.6e-6, 4.1e-6, 6.9e-6, of that
+// -6e-8, -4.9e-7, -2.3e-6, -4.8e-6 in one direction).
 //
 // Measured (N = 64, 32x32, 3x3, 32 -> 32 channels): 3x3x3 capsules 0.776 ms on the fp32
 // instructions, 0.546 ms here (error against 64-bit sums 5.2e-7 and 4.4e-7), 4x4 capsules 0.664
@@ -239,6 +245,9 @@ void igemm32_split_kernel(const Dma32Params P)
     // ---- the K loop on the split values
     {
         const MinusOne one;
+        constexpr int FLIP = 96;  // stages; a multiple of both periods
+        // of the input values being split; the ranges of a split K loop begin with either sign
+        unsigned in_scale = __builtin_bit_cast(unsigned, SPLIT_SCALE) | (unsigned)split << 31;
         // K values of one period, split: pairs per row tile and term
         unsigned iv[TM][3][WORDS];
         float lo[NPAIR], hi[NPAIR];  // the pairs being split: what the terms so far leave over
@@ -247,9 +256,9 @@ void igemm32_split_kernel(const Dma32Params P)
             unsigned(&w)[3][WORDS] = iv[p / CW];
             const int at = pos * CW + p % CW, t = (k - 2) / 3;
             if (k == 0)
-                lo[p] *= SPLIT_SCALE;
+                lo[p] *= __builtin_bit_cast(float, in_scale);
             else if (k == 1)
-                hi[p] *= SPLIT_SCALE;
+                hi[p] *= __builtin_bit_cast(float, in_scale);
             else if (k % 3 == 2)
                 w[t][at] = round_pair(lo[p], hi[p]);
             else if (k % 3 == 0)
@@ -306,7 +315,24 @@ void igemm32_split_kernel(const Dma32Params P)
         // ring slots (byte offsets): input of the next stage (read) and of the one three ahead
         // (copied into: this stage's own slot), kernel of this stage and of the next
         unsigned a_next = A_BYTES, a_cur = 0, b_cur = B_LDS;
+        int to_flip = FLIP;
         for (int st = 0; st < my_stages; st += PER) {
+            if (to_flip == 0) {
+                to_flip = FLIP;
+                in_scale ^= 0x80000000u;
+#pragma unroll
+                for (int a = 0; a < TN; ++a)
+#pragma unroll
+                    for (int b = 0; b < TM; ++b) acc[a][b] = -acc[a][b];
+                // the input values of the stage at hand, a period's first, are split already
+#pragma unroll
+                for (int b = 0; b < TM; ++b)
+#pragma unroll
+                    for (int t = 0; t < 3; ++t)
+#pragma unroll
+                        for (int i = 0; i < CW; ++i) iv[b][t][i] ^= 0x80008000u;
+            }
+            to_flip -= PER;
             static_for<PER>([&](auto POS) {
                 constexpr int pos = decltype(POS)::value, next = (pos + 1) % PER;
                 constexpr int NMMA = has_step(pos) ? TN * TM * 6 : 0;
@@ -376,10 +402,11 @@ void igemm32_split_kernel(const Dma32Params P)
         }
         // the copies of the surplus stages still write into this workgroup's LDS
         __builtin_amdgcn_s_waitcnt(0x0F70);
+        const float unscale = in_scale >> 31 ? -SPLIT_UNSCALE : SPLIT_UNSCALE;
 #pragma unroll
         for (int a = 0; a < TN; ++a)
 #pragma unroll
-            for (int b = 0; b < TM; ++b) acc[a][b] *= SPLIT_UNSCALE;
+            for (int b = 0; b < TM; ++b) acc[a][b] *= unscale;
     }
 
     // ---- the same sums on the fp32 matrix instructions, one stage at a time
