@@ -84,8 +84,12 @@ bool misaligned(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) !
 // Scratch of the entry point that allocates nothing (capscaps_conv_fwd_static): a fixed array in
 // every GPU's memory, there from the moment the library's code is loaded on that GPU until the
 // process ends.  In host code the array's name stands for the symbol, not for a device address:
-// the address on the current device is looked up once per device and kept.
-static __device__ __align__(256) unsigned char scratch[CAPSCAPS_STATIC_SCRATCH_BYTES];
+// the address on the current device is looked up once per device and kept.  The array is larger
+// than the limit callers are told: an fp32 kernel tensor is packed as three bf16 terms, half as
+// much again as fp32 values (and rounded up to whole tiles), and the limit counts the values.
+constexpr size_t SCRATCH_LIMIT = CAPSCAPS_STATIC_SCRATCH_BYTES;
+constexpr size_t SCRATCH_ARRAY = (size_t)128 << 20;
+static __device__ __align__(256) unsigned char scratch[SCRATCH_ARRAY];
 
 constexpr int kMaxDevices = 64;
 std::mutex g_scratch_mutex;
@@ -107,6 +111,32 @@ int scratch_of_current_device(void** ptr)
     }
     *ptr = g_scratch_ptr[dev];
     return CAPSCAPS_OK;
+}
+
+bool own_choice_fits_scratch(const ConvShape& s)
+{
+    const size_t need = capscaps::forward_workspace_bytes(s);
+    if (need <= SCRATCH_LIMIT) return true;
+    return need <= SCRATCH_ARRAY && s.dtype == CAPSCAPS_FP32 && choose_path(s) == CAPSCAPS_PATH_MFMA_TUNED32 &&
+           need - capscaps::mfma_split_overhead_bytes(s) <= SCRATCH_LIMIT;
+}
+
+// A kernel whose scratch fits where that of the library's own choice does not; Auto: none.  The
+// lane-per-row kernel is the choice that may need too much: for the copy of the input with its
+// channels paired (16-bit capsule rows of 4), for an fp32 kernel tensor in bf16 terms, for the partial
+// sums of its large tiles.  16-bit layers that fill the chip with its tiles are refused instead.
+capscaps::MfmaKernel leaner_kernel(const ConvShape& s)
+{
+    using capscaps::MfmaKernel;
+    if (s.dtype != CAPSCAPS_FP32 &&
+        (choose_path(s) != CAPSCAPS_PATH_MFMA_TUNED32 || capscaps::igemm32_dma_fills_chip(s)))
+        return MfmaKernel::Auto;
+    if (capscaps::mfma_kernel_workspace_bytes(s, MfmaKernel::Generic) <= SCRATCH_LIMIT)
+        return MfmaKernel::Generic;
+    if (s.dtype == CAPSCAPS_FP32 && capscaps::mfma_small_supported(s) &&
+        capscaps::mfma_kernel_workspace_bytes(s, MfmaKernel::Small) <= SCRATCH_LIMIT)
+        return MfmaKernel::Small;
+    return MfmaKernel::Auto;
 }
 
 int run(const void* input, const void* kernel, void* out, const ConvShape& s, int path,
@@ -301,18 +331,10 @@ int capscaps_conv_fwd_static(const void* input, const void* kernel, void* out, i
     ConvShape s;
     const int rc = fill_shape(s, N, H, W, C, M, kh, kw, stride, pad, D0, D1, D2, D3, dtype);
     if (rc != CAPSCAPS_OK) return rc;
-    // the scratch must fit the fixed array: that of the library's own kernel choice, else that of
-    // a kernel that needs less (fp32 layers: the kernel tensor split into bf16 terms takes half as
-    // much again as repacked fp32 values, and larger tiles mean larger partial sums)
-    constexpr size_t room = CAPSCAPS_STATIC_SCRATCH_BYTES;
     capscaps::MfmaKernel lean = capscaps::MfmaKernel::Auto;
-    if (capscaps::forward_workspace_bytes(s) > room) {
-        if (s.dtype != CAPSCAPS_FP32) return CAPSCAPS_ESCRATCH;
-        lean = capscaps::MfmaKernel::Generic;
-        if (capscaps::mfma_kernel_workspace_bytes(s, lean) > room) lean = capscaps::MfmaKernel::Small;
-        if (lean == capscaps::MfmaKernel::Small &&
-            (!capscaps::mfma_small_supported(s) || capscaps::mfma_kernel_workspace_bytes(s, lean) > room))
-            return CAPSCAPS_ESCRATCH;
+    if (!own_choice_fits_scratch(s)) {
+        lean = leaner_kernel(s);
+        if (lean == capscaps::MfmaKernel::Auto) return CAPSCAPS_ESCRATCH;
     }
     void* ws = nullptr;
     const int rs = scratch_of_current_device(&ws);
@@ -320,7 +342,7 @@ int capscaps_conv_fwd_static(const void* input, const void* kernel, void* out, i
     if (lean != capscaps::MfmaKernel::Auto)
         return hip_status(capscaps::launch_mfma(s, input, kernel, static_cast<float*>(out), ws,
                                                 static_cast<hipStream_t>(stream), lean));
-    return run(input, kernel, out, s, CAPSCAPS_PATH_AUTO, ws, (size_t)CAPSCAPS_STATIC_SCRATCH_BYTES,
+    return run(input, kernel, out, s, CAPSCAPS_PATH_AUTO, ws, SCRATCH_ARRAY,
                static_cast<hipStream_t>(stream));
 }
 

@@ -88,6 +88,9 @@ bool mfma_rechunk_preferred(const ConvShape& s);
 size_t mfma_workspace_bytes(const ConvShape& s);  // enough for every MfmaKernel choice (with
                                                   // s.out16: for Auto, the only choice then)
 size_t mfma_kernel_workspace_bytes(const ConvShape& s, MfmaKernel which);  // for that kernel only
+// fp32 layers on the lane-per-row kernel: what their packed kernel takes beyond its fp32 values
+size_t mfma_split_overhead_bytes(const ConvShape& s);
+bool igemm32_dma_fills_chip(const ConvShape& s);  // with four-wave tiles and an unsplit K loop
 hipError_t launch_mfma(const ConvShape& s, const void* in, const void* kernel, float* out,
                        void* workspace, hipStream_t stream, MfmaKernel which = MfmaKernel::Auto);
 

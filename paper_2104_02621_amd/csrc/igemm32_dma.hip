@@ -505,6 +505,12 @@ Dma32Plan igemm32_dma_plan(const ConvShape& s)
     return pl;
 }
 
+bool igemm32_dma_fills_chip(const ConvShape& s)
+{
+    const Dma32Plan pl = igemm32_dma_plan(s);
+    return pl.nw == 4 && pl.P.nsplit == 1;
+}
+
 bool igemm32_dma_preferred(const ConvShape& s)
 {
     if (!igemm32_dma_eligible(s)) return false;

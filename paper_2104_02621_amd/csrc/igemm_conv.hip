@@ -832,6 +832,13 @@ size_t mfma_kernel_workspace_bytes(const ConvShape& s, MfmaKernel which)
     return ((pl.repack_bytes + 255) & ~(size_t)255) + pl.partial_bytes;
 }
 
+size_t mfma_split_overhead_bytes(const ConvShape& s)
+{
+    const Dma32Plan pl = igemm32_dma_plan(s);
+    const size_t values = s.kernel_elems() * sizeof(float);
+    return pl.repack_bytes > values ? pl.repack_bytes - values : 0;
+}
+
 MfmaKernel mfma_auto_kernel(const ConvShape& s)
 {
     if (igemm32_dma_preferred(s)) return MfmaKernel::Dma32;

@@ -8,7 +8,7 @@ import pytest
 from oracle import capsconv
 from paper_2104_02621_amd import capscaps as cc
 from paper_2104_02621_amd import workloads as wl
-from tests.gpu_util import check, shape_args, to_device
+from tests.gpu_util import check, run_gpu, shape_args, to_device
 
 pytestmark = pytest.mark.gpu
 
@@ -79,3 +79,36 @@ def test_static_scratch_rejects_what_does_not_fit():
                                      torch.cuda.current_stream().cuda_stream)
     assert rc == cc.ESCRATCH
     assert "scratch" in cc.capscaps_strerror(rc)
+
+
+def test_static_scratch_holds_a_split_fp32_kernel():
+    """66 MiB of fp32 kernel values are packed as 99 MiB of bf16 terms: the limit counts the values."""
+    w = wl.Workload("static_split", wl.FP32, 1, 3, 3, 128, 200, 5, 5, 1, 2, 3, 3, 3, 3, "normal", "normal", 0.1,
+                    907, 908)
+    args = shape_args(w)
+    assert cc.capscaps_select_path(*args) == cc.PATH_MFMA_TUNED32
+    assert cc.capscaps_conv_fwd_workspace_bytes(*args) > cc.STATIC_SCRATCH_BYTES
+    _both(w)
+
+
+@pytest.mark.parametrize("dtype", [wl.BF16, wl.FP16], ids=["bf16", "fp16"])
+def test_static_scratch_without_the_paired_input(dtype):
+    """A 16-bit layer of 4x4 capsules whose own choice needs a channel-paired copy of the whole input,
+    more than the array holds, runs on the any-shape kernel."""
+    import torch
+    w = wl.Workload("static_pair", dtype, 64, 28, 28, 64, 32, 3, 3, 2, 1, 1, 4, 4, 4, "normal", "normal", 0.1,
+                    909, 910)
+    args = shape_args(w)
+    assert cc.capscaps_select_path(*args) == cc.PATH_MFMA_TUNED32
+    assert w.N * w.H * w.W * w.C * 16 * 2 > cc.STATIC_SCRATCH_BYTES
+    i_st, k_st, i32, k32 = wl.generate(w)
+    I, K = to_device(i_st, dtype), to_device(k_st, dtype)
+    out = torch.full(w.out_shape, float("nan"), dtype=torch.float32, device="cuda")
+    rc = cc.capscaps_conv_fwd_static(I.data_ptr(), K.data_ptr(), out.data_ptr(), *args,
+                                     torch.cuda.current_stream().cuda_stream)
+    assert rc == cc.OK, cc.capscaps_strerror(rc)
+    assert torch.equal(out, run_gpu(w, I, K, cc.PATH_MFMA_GENERIC))
+    which = wl.sample_capsules(w, 1500, seed=911)
+    ref, S = capsconv.conv_fwd_subset(i32, k32, which, w.stride, w.pad, with_abs_sum=True)
+    idx = torch.from_numpy(which.astype(np.int64)).cuda()
+    check(w, out[idx[:, 0], idx[:, 1], idx[:, 2], idx[:, 3]].cpu().numpy(), ref, S, "static scratch, sampled")
