@@ -147,12 +147,15 @@ int capscaps_conv_fwd_out16(const void* input, const void* kernel, void* out, in
 /*
  * capscaps_conv_fwd_ex for callers that cannot allocate device memory or hand over a workspace:
  * code under HIP graph capture, tight serving loops, harnesses that forbid allocation.  Same
- * operator, arguments, layouts, kernels and results as capscaps_conv_fwd_ex, but the scratch
- * (repacked kernel, partial sums of split reductions) is a fixed array of
- * CAPSCAPS_STATIC_SCRATCH_BYTES in each GPU's memory that exists from the moment the library's
- * code is loaded on that GPU until the process ends.  The call allocates and frees nothing and
- * calls no allocating routine; a problem whose scratch does not fit returns CAPSCAPS_ESCRATCH
- * before anything is launched (all five benchmark configurations fit).  The device that holds the
+ * operator, arguments and layouts as capscaps_conv_fwd_ex, but the scratch
+ * (repacked kernel, partial sums of split reductions) is a fixed array in each GPU's memory that
+ * exists from the moment the library's code is loaded on that GPU until the process ends.  The call
+ * allocates and frees nothing and calls no allocating routine.  Where the scratch of the kernel that
+ * capscaps_conv_fwd_ex would choose fits CAPSCAPS_STATIC_SCRATCH_BYTES (of an fp32 kernel tensor
+ * packed as bf16 terms, its fp32 values count), that kernel runs and the results have the same bits;
+ * where it does not, a kernel that needs less may run (the any-shape kernel, for fp32 also the one for
+ * small problems), whose fp32 sums are taken in another order; where neither fits, the call returns
+ * CAPSCAPS_ESCRATCH before anything is launched (all five benchmark configurations fit).  The device that holds the
  * buffers must be the current device.  The first call on a device looks up the array's address
  * there (make that call outside a graph capture).  All calls on one GPU share that GPU's array:
  * calls that may overlap on one GPU (different streams, or graphs replayed concurrently) race on

@@ -1,6 +1,6 @@
 """The entry point that allocates nothing (capscaps_conv_fwd_static, scratch in a fixed device
-array) against capscaps_conv_fwd_ex (scratch from the caller), through the C ABI: same kernels,
-so the same bits; and both against the oracle.  Two calls in a row, the second with a smaller
+array) against capscaps_conv_fwd_ex (scratch from the caller), through the C ABI: same kernels where
+the scratch fits, so the same bits; and both against the oracle.  Two calls in a row, the second with a smaller
 input, so that what the first call left in the shared array cannot leak into the second."""
 import numpy as np
 import pytest
@@ -95,19 +95,31 @@ def test_static_scratch_holds_a_split_fp32_kernel():
 def test_static_scratch_without_the_paired_input(dtype):
     """A 16-bit layer of 4x4 capsules whose own choice needs a channel-paired copy of the whole input,
     more than the array holds, runs on the any-shape kernel."""
-    import torch
     w = wl.Workload("static_pair", dtype, 64, 28, 28, 64, 32, 3, 3, 2, 1, 1, 4, 4, 4, "normal", "normal", 0.1,
                     909, 910)
-    args = shape_args(w)
-    assert cc.capscaps_select_path(*args) == cc.PATH_MFMA_TUNED32
     assert w.N * w.H * w.W * w.C * 16 * 2 > cc.STATIC_SCRATCH_BYTES
+    _runs_on_a_leaner_kernel(w, cc.PATH_MFMA_GENERIC)
+
+
+def test_static_scratch_without_the_split_kernel():
+    """An fp32 layer whose kernel tensor in bf16 terms and partial sums do not fit the array (129 MiB):
+    its repacked fp32 values do not either (84 MiB), so the kernel that reads the tensor in place runs."""
+    w = wl.Workload("static_lean", wl.FP32, 1, 3, 3, 256, 128, 5, 5, 1, 2, 3, 3, 3, 3, "normal", "normal", 0.1,
+                    912, 913)
+    _runs_on_a_leaner_kernel(w, cc.PATH_MFMA_SMALL)
+
+
+def _runs_on_a_leaner_kernel(w, path):
+    import torch
+    args, dtype = shape_args(w), w.dtype
+    assert cc.capscaps_select_path(*args) == cc.PATH_MFMA_TUNED32
     i_st, k_st, i32, k32 = wl.generate(w)
     I, K = to_device(i_st, dtype), to_device(k_st, dtype)
     out = torch.full(w.out_shape, float("nan"), dtype=torch.float32, device="cuda")
     rc = cc.capscaps_conv_fwd_static(I.data_ptr(), K.data_ptr(), out.data_ptr(), *args,
                                      torch.cuda.current_stream().cuda_stream)
     assert rc == cc.OK, cc.capscaps_strerror(rc)
-    assert torch.equal(out, run_gpu(w, I, K, cc.PATH_MFMA_GENERIC))
+    assert torch.equal(out, run_gpu(w, I, K, path))
     which = wl.sample_capsules(w, 1500, seed=911)
     ref, S = capsconv.conv_fwd_subset(i32, k32, which, w.stride, w.pad, with_abs_sum=True)
     idx = torch.from_numpy(which.astype(np.int64)).cuda()
