@@ -177,8 +177,10 @@ size_t capscaps_conv_fwd_workspace_bytes(int N, int H, int W, int C, int M, int 
                                          int dtype);
 
 /*
- * Which path CAPSCAPS_PATH_AUTO resolves to for these arguments (CAPSCAPS_PATH_DIRECT or one of
- * the CAPSCAPS_PATH_MFMA_* kernel variants), or a negative status for invalid arguments.
+ * Which path CAPSCAPS_PATH_AUTO resolves to for these arguments (CAPSCAPS_PATH_DIRECT, one of
+ * the CAPSCAPS_PATH_MFMA_* kernel variants, or CAPSCAPS_PATH_MFMA for large fp32 layers of capsule
+ * rows that CAPSCAPS_PATH_MFMA_TUNED32 does not take: that variant on a copy of the input in
+ * `workspace`, its rows in runs of four K values), or a negative status for invalid arguments.
  * Host-only.
  */
 int capscaps_select_path(int N, int H, int W, int C, int M, int kh, int kw, int stride, int pad,

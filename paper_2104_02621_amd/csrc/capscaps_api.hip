@@ -75,6 +75,8 @@ int choose_path(const ConvShape& s)
         case capscaps::MfmaKernel::Tuned16: return CAPSCAPS_PATH_MFMA_TUNED16;
         case capscaps::MfmaKernel::Dma32: return CAPSCAPS_PATH_MFMA_TUNED32;
         case capscaps::MfmaKernel::Small: return CAPSCAPS_PATH_MFMA_SMALL;
+        // (the lane-per-row kernel again, but on a copy of the input that only the library's choice makes)
+        case capscaps::MfmaKernel::Rechunk: return CAPSCAPS_PATH_MFMA;
         default: return CAPSCAPS_PATH_MFMA_GENERIC;
     }
 }

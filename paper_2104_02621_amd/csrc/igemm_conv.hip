@@ -386,9 +386,7 @@ Plan make_plan(const ConvShape& s, MfmaKernel which)
     // small tiles and, if still short of blocks, split the K loop.
     const int kCUs = 256;
     const TileChoice choices[3] = {{256, 256}, {128, 128}, {64, 64}};
-    pl.fast = which == MfmaKernel::Tuned16
-                  ? igemm16_fast_eligible(s)
-                  : which == MfmaKernel::Auto && igemm16_fast_preferred(s);
+    pl.fast = which == MfmaKernel::Tuned16 && igemm16_fast_eligible(s);
     int pick = 2;
     if (pl.fast) pick = 0;
     for (int i = 0; i < 3 && !pl.fast; ++i) {
@@ -671,8 +669,6 @@ hipError_t launch_rechunked(const ConvShape& s, const RechunkPlan& rp, const voi
 hipError_t launch_igemm(const ConvShape& s, const void* in, const void* kernel, float* out,
                         void* workspace, hipStream_t stream, MfmaKernel which)
 {
-    const RechunkPlan rp = rechunk_plan(s);
-    if (rp.ok) return launch_rechunked(s, rp, in, kernel, out, workspace, stream);
     Plan pl = make_plan(s, which);
     if (pl.blocks <= 0 || pl.blocks > 0x7fffffffLL) return hipErrorInvalidValue;
     char* ws = static_cast<char*>(workspace);
@@ -807,7 +803,7 @@ size_t mfma_workspace_bytes(const ConvShape& s)
     // 16-bit output is offered with the library's own kernel choice only
     if (s.out16 != 0) return mfma_kernel_workspace_bytes(s, MfmaKernel::Auto);
     size_t need = 0;
-    for (MfmaKernel which : {MfmaKernel::Generic, MfmaKernel::Tuned16}) {
+    for (MfmaKernel which : {MfmaKernel::Generic, MfmaKernel::Tuned16, MfmaKernel::Rechunk}) {
         if (which == MfmaKernel::Tuned16 && !igemm16_fast_eligible(s)) continue;
         const size_t bytes = mfma_kernel_workspace_bytes(s, which);
         if (bytes > need) need = bytes;
@@ -826,8 +822,10 @@ size_t mfma_kernel_workspace_bytes(const ConvShape& s, MfmaKernel which)
     if (which == MfmaKernel::Auto) which = mfma_auto_kernel(s);
     if (which == MfmaKernel::Small) return igemm_small_workspace_bytes(s);
     if (which == MfmaKernel::Dma32) return dma32_workspace_bytes(igemm32_dma_plan(s));
-    const RechunkPlan rp = rechunk_plan(s);
-    if (rp.ok) return rp.bytes();
+    if (which == MfmaKernel::Rechunk) {
+        const RechunkPlan rp = rechunk_plan(s);
+        return rp.ok ? rp.bytes() : 0;
+    }
     const Plan pl = make_plan(s, which);
     return ((pl.repack_bytes + 255) & ~(size_t)255) + pl.partial_bytes;
 }
@@ -843,7 +841,7 @@ MfmaKernel mfma_auto_kernel(const ConvShape& s)
 {
     if (igemm32_dma_preferred(s)) return MfmaKernel::Dma32;
     if (igemm16_fast_preferred(s)) return MfmaKernel::Tuned16;
-    if (rechunk_plan(s).ok) return MfmaKernel::Generic;
+    if (rechunk_plan(s).ok) return MfmaKernel::Rechunk;
     if (igemm_small_preferred(s)) return MfmaKernel::Small;
     return MfmaKernel::Generic;
 }
@@ -873,11 +871,13 @@ hipError_t launch_mfma(const ConvShape& s, const void* in, const void* kernel, f
     if ((s.pad_w_set || s.out_view) && !(which == MfmaKernel::Tuned16 && igemm16_fast_eligible(s)) &&
         !(which == MfmaKernel::Dma32 && igemm32_dma_eligible(s)))
         return hipErrorInvalidValue;
-    if (which == MfmaKernel::Dma32 || (which == MfmaKernel::Auto && igemm32_dma_preferred(s)))
-        return launch_dma32(s, in, kernel, out, workspace, stream);
-    if (which == MfmaKernel::Small ||
-        (which == MfmaKernel::Auto && mfma_auto_kernel(s) == MfmaKernel::Small))
-        return launch_igemm_small(s, in, kernel, out, workspace, stream);
+    if (which == MfmaKernel::Auto) which = mfma_auto_kernel(s);
+    if (which == MfmaKernel::Dma32) return launch_dma32(s, in, kernel, out, workspace, stream);
+    if (which == MfmaKernel::Small) return launch_igemm_small(s, in, kernel, out, workspace, stream);
+    if (which == MfmaKernel::Rechunk) {
+        const RechunkPlan rp = rechunk_plan(s);
+        return rp.ok ? launch_rechunked(s, rp, in, kernel, out, workspace, stream) : hipErrorInvalidValue;
+    }
     return launch_igemm(s, in, kernel, out, workspace, stream, which);
 }
 

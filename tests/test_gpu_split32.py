@@ -7,7 +7,7 @@ import pytest
 
 from paper_2104_02621_amd import capscaps as cc
 from paper_2104_02621_amd import workloads as wl
-from tests.gpu_util import run_gpu, to_device
+from tests.gpu_util import run_gpu, shape_args, to_device
 from tests.test_gpu_parity import full_compare, small
 
 pytestmark = pytest.mark.gpu
@@ -267,3 +267,19 @@ def test_errors_of_long_sums_have_no_direction(shape):
     # 96 stages of 16 (12) K values at most: 576 instructions; the mean of independent errors, over
     # 500000 results, is far below that
     assert abs(mean) <= 576 * 2 ** -9 * 2 ** -23 + 5 * rms / err.numel() ** 0.5
+
+
+def test_forced_any_shape_kernel_runs_on_rows_of_any_length():
+    """The any-shape kernel, forced, gives an image the same bits in a batch of 20 and in one of 640: it
+    adds up the K values in one order.  The library's own choice for the large batch, which contracts
+    bf16 terms, does not."""
+    import torch
+    big = small("generic_rows", wl.FP32, 640, 32, 32, 2, 2, 3, 3, 1, 1, 2, 1, 5, 5, seed=623)
+    few = small("generic_rows", wl.FP32, 20, 32, 32, 2, 2, 3, 3, 1, 1, 2, 1, 5, 5, seed=623)
+    assert big.flops_nominal() >= 1.2e9
+    assert cc.capscaps_select_path(*shape_args(big)) == cc.PATH_MFMA
+    x, k = (to_device(t, wl.FP32) for t in wl.generate(big)[:2])
+    ref = run_gpu(few, x[:20].contiguous(), k, cc.PATH_MFMA_GENERIC)
+    assert torch.equal(run_gpu(big, x, k, cc.PATH_MFMA_GENERIC)[:20], ref)
+    own = run_gpu(big, x, k, cc.PATH_MFMA)
+    assert torch.equal(run_gpu(big, x, k, cc.PATH_AUTO), own) and not torch.equal(own[:20], ref)
