@@ -56,29 +56,42 @@ int fill_shape(ConvShape& s, int N, int H, int W, int C, int M, int kh, int kw, 
 //     the layer is large enough for throughput to count (a tiny one is latency-bound, and the
 //     single-stage matrix-core kernel has the shorter latency);
 // it also serves what the matrix-core path cannot address.
-int choose_path(const ConvShape& s)
+//
+// The path and, on the matrix cores, the kernel.  A call asks once: the kernels' plans take a
+// microsecond of host time together, which a launch-bound layer would wait for.
+struct Choice {
+    int path;
+    capscaps::MfmaKernel kernel;
+};
+Choice choose(const ConvShape& s)
 {
-    if (!capscaps::mfma_supported(s)) return CAPSCAPS_PATH_DIRECT;
+    const Choice direct = {CAPSCAPS_PATH_DIRECT, capscaps::MfmaKernel::Auto};
+    if (!capscaps::mfma_supported(s)) return direct;
     const long long kdim = (long long)s.kh * s.kw * s.C * s.D2;
     const long long cols = (long long)s.M * s.D3;
-    if (kdim <= 24) return CAPSCAPS_PATH_DIRECT;
+    if (kdim <= 24) return direct;
     const double flops = 2.0 * (double)s.out_elems() * (double)kdim;
     // (fp32 layers from 5e8 FLOPs on: the lane-per-row kernel, which contracts on the bf16 matrix
     // instructions -- 6x5 . 5x4 capsules, 8 columns, 9.9 GFLOP 399 against 1473 us; 3x3x3 capsules, 6
     // columns, 0.5 GFLOP 32 against 153 us)
-    const bool split32 = s.dtype == CAPSCAPS_FP32 && flops >= 5e8 &&
-                         (capscaps::mfma_rechunk_preferred(s) || capscaps::mfma_dma32_supported(s));
-    if (!split32 && cols <= 8 && (s.D2 % 4 != 0 || s.D3 % 4 != 0) && flops >= 5e7 &&
-        capscaps::wave_conv_eligible(s))
-        return CAPSCAPS_PATH_DIRECT;
-    switch (capscaps::mfma_auto_kernel(s)) {
-        case capscaps::MfmaKernel::Tuned16: return CAPSCAPS_PATH_MFMA_TUNED16;
-        case capscaps::MfmaKernel::Dma32: return CAPSCAPS_PATH_MFMA_TUNED32;
-        case capscaps::MfmaKernel::Small: return CAPSCAPS_PATH_MFMA_SMALL;
-        // (the lane-per-row kernel again, but on a copy of the input that only the library's choice makes)
-        case capscaps::MfmaKernel::Rechunk: return CAPSCAPS_PATH_MFMA;
-        default: return CAPSCAPS_PATH_MFMA_GENERIC;
+    if (cols <= 8 && (s.D2 % 4 != 0 || s.D3 % 4 != 0) && flops >= 5e7 && capscaps::wave_conv_eligible(s)) {
+        const bool split32 = s.dtype == CAPSCAPS_FP32 && flops >= 5e8 &&
+                             (capscaps::mfma_rechunk_preferred(s) || capscaps::mfma_dma32_supported(s));
+        if (!split32) return direct;
     }
+    const capscaps::MfmaKernel kernel = capscaps::mfma_auto_kernel(s);
+    switch (kernel) {
+        case capscaps::MfmaKernel::Tuned16: return {CAPSCAPS_PATH_MFMA_TUNED16, kernel};
+        case capscaps::MfmaKernel::Dma32: return {CAPSCAPS_PATH_MFMA_TUNED32, kernel};
+        case capscaps::MfmaKernel::Small: return {CAPSCAPS_PATH_MFMA_SMALL, kernel};
+        // (the lane-per-row kernel again, but on a copy of the input that only the library's choice makes)
+        case capscaps::MfmaKernel::Rechunk: return {CAPSCAPS_PATH_MFMA, kernel};
+        default: return {CAPSCAPS_PATH_MFMA_GENERIC, kernel};
+    }
+}
+size_t scratch_bytes(const ConvShape& s, const Choice& c)
+{
+    return c.path == CAPSCAPS_PATH_DIRECT ? 0 : capscaps::mfma_kernel_workspace_bytes(s, c.kernel);
 }
 
 bool misaligned(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) != 0; }
@@ -115,11 +128,11 @@ int scratch_of_current_device(void** ptr)
     return CAPSCAPS_OK;
 }
 
-bool own_choice_fits_scratch(const ConvShape& s)
+bool fits_scratch(const ConvShape& s, const Choice& own)
 {
-    const size_t need = capscaps::forward_workspace_bytes(s);
+    const size_t need = scratch_bytes(s, own);
     if (need <= SCRATCH_LIMIT) return true;
-    return need <= SCRATCH_ARRAY && s.dtype == CAPSCAPS_FP32 && choose_path(s) == CAPSCAPS_PATH_MFMA_TUNED32 &&
+    return need <= SCRATCH_ARRAY && s.dtype == CAPSCAPS_FP32 && own.path == CAPSCAPS_PATH_MFMA_TUNED32 &&
            need - capscaps::mfma_split_overhead_bytes(s) <= SCRATCH_LIMIT;
 }
 
@@ -127,11 +140,11 @@ bool own_choice_fits_scratch(const ConvShape& s)
 // lane-per-row kernel is the choice that may need too much: for the copy of the input with its
 // channels paired (16-bit capsule rows of 4), for an fp32 kernel tensor in bf16 terms, for the partial
 // sums of its large tiles.  16-bit layers that fill the chip with its tiles are refused instead.
-capscaps::MfmaKernel leaner_kernel(const ConvShape& s)
+capscaps::MfmaKernel leaner_kernel(const ConvShape& s, const Choice& own)
 {
     using capscaps::MfmaKernel;
     if (s.dtype != CAPSCAPS_FP32 &&
-        (choose_path(s) != CAPSCAPS_PATH_MFMA_TUNED32 || capscaps::igemm32_dma_fills_chip(s)))
+        (own.path != CAPSCAPS_PATH_MFMA_TUNED32 || capscaps::igemm32_dma_fills_chip(s)))
         return MfmaKernel::Auto;
     if (capscaps::mfma_kernel_workspace_bytes(s, MfmaKernel::Generic) <= SCRATCH_LIMIT)
         return MfmaKernel::Generic;
@@ -141,20 +154,34 @@ capscaps::MfmaKernel leaner_kernel(const ConvShape& s)
     return MfmaKernel::Auto;
 }
 
+// The library's own choice; it needs scratch for the kernel it picks only.
+int run_choice(const void* input, const void* kernel, void* out, const ConvShape& s, const Choice& c,
+               void* workspace, size_t workspace_bytes, hipStream_t stream)
+{
+    float* dst = static_cast<float*>(out);
+    if (c.path == CAPSCAPS_PATH_DIRECT)
+        return hip_status(capscaps::launch_direct(s, input, kernel, dst, stream));
+    const size_t need = scratch_bytes(s, c);
+    if (need > 0 && (workspace == nullptr || workspace_bytes < need)) return CAPSCAPS_EWORKSPACE;
+    if (need > 0 && misaligned(workspace)) return CAPSCAPS_EINVAL;
+    return hip_status(capscaps::launch_mfma(s, input, kernel, dst, workspace, stream, c.kernel));
+}
+
 int run(const void* input, const void* kernel, void* out, const ConvShape& s, int path,
         void* workspace, size_t workspace_bytes, hipStream_t stream)
 {
-    // the library's own choice needs scratch for the kernel it picks only; a forced path is
-    // held to the size that covers every kernel (what the size query reports)
-    const bool own_choice = path == CAPSCAPS_PATH_AUTO || path == CAPSCAPS_PATH_MFMA;
-    if (path == CAPSCAPS_PATH_AUTO) path = choose_path(s);
     hipError_t err;
-    if (path == CAPSCAPS_PATH_DIRECT) {
+    if (path == CAPSCAPS_PATH_AUTO) {
+        return run_choice(input, kernel, out, s, choose(s), workspace, workspace_bytes, stream);
+    } else if (path == CAPSCAPS_PATH_DIRECT) {
         err = capscaps::launch_direct(s, input, kernel, static_cast<float*>(out), stream);
     } else if (path == CAPSCAPS_PATH_MFMA || path == CAPSCAPS_PATH_MFMA_GENERIC ||
                path == CAPSCAPS_PATH_MFMA_TUNED16 || path == CAPSCAPS_PATH_MFMA_TUNED32 ||
                path == CAPSCAPS_PATH_MFMA_SMALL) {
         if (!capscaps::mfma_supported(s)) return CAPSCAPS_EUNSUPPORTED;
+        if (path == CAPSCAPS_PATH_MFMA)
+            return run_choice(input, kernel, out, s, {path, capscaps::mfma_auto_kernel(s)}, workspace,
+                              workspace_bytes, stream);
         if (path == CAPSCAPS_PATH_MFMA_TUNED16 && !capscaps::mfma_tuned16_supported(s))
             return CAPSCAPS_EUNSUPPORTED;
         if (path == CAPSCAPS_PATH_MFMA_TUNED32 && !capscaps::mfma_dma32_supported(s))
@@ -162,13 +189,12 @@ int run(const void* input, const void* kernel, void* out, const ConvShape& s, in
         if (path == CAPSCAPS_PATH_MFMA_SMALL && !capscaps::mfma_small_supported(s))
             return CAPSCAPS_EUNSUPPORTED;
         const capscaps::MfmaKernel which =
-            path == CAPSCAPS_PATH_MFMA           ? capscaps::MfmaKernel::Auto
-            : path == CAPSCAPS_PATH_MFMA_GENERIC ? capscaps::MfmaKernel::Generic
+            path == CAPSCAPS_PATH_MFMA_GENERIC   ? capscaps::MfmaKernel::Generic
             : path == CAPSCAPS_PATH_MFMA_TUNED16 ? capscaps::MfmaKernel::Tuned16
             : path == CAPSCAPS_PATH_MFMA_SMALL   ? capscaps::MfmaKernel::Small
                                                  : capscaps::MfmaKernel::Dma32;
-        const size_t need = own_choice ? capscaps::mfma_kernel_workspace_bytes(s, capscaps::MfmaKernel::Auto)
-                                       : capscaps::mfma_workspace_bytes(s);
+        // a forced kernel is held to the size that covers every one (what the size query reports)
+        const size_t need = capscaps::mfma_workspace_bytes(s);
         if (need > 0 && (workspace == nullptr || workspace_bytes < need))
             return CAPSCAPS_EWORKSPACE;
         if (need > 0 && misaligned(workspace)) return CAPSCAPS_EINVAL;
@@ -186,12 +212,9 @@ namespace capscaps {
 
 int status_from_hip(hipError_t err) { return hip_status(err); }
 
-size_t forward_workspace_bytes(const ConvShape& s)
-{
-    return choose_path(s) == CAPSCAPS_PATH_DIRECT ? 0 : mfma_kernel_workspace_bytes(s, MfmaKernel::Auto);
-}
+size_t forward_workspace_bytes(const ConvShape& s) { return scratch_bytes(s, choose(s)); }
 
-bool forward_auto_repacks_kernel(const ConvShape& s) { return choose_path(s) != CAPSCAPS_PATH_DIRECT; }
+bool forward_auto_repacks_kernel(const ConvShape& s) { return choose(s).path != CAPSCAPS_PATH_DIRECT; }
 
 int forward_auto(const ConvShape& s, const void* in, const void* kernel, float* out,
                  void* workspace, size_t workspace_bytes, hipStream_t stream)
@@ -244,7 +267,7 @@ int capscaps_select_path(int N, int H, int W, int C, int M, int kh, int kw, int 
     ConvShape s;
     const int rc = fill_shape(s, N, H, W, C, M, kh, kw, stride, pad, D0, D1, D2, D3, dtype);
     if (rc != CAPSCAPS_OK) return rc;
-    return choose_path(s);
+    return choose(s).path;
 }
 
 int capscaps_conv_fwd_path(const void* input, const void* kernel, void* out, int N, int H, int W,
@@ -309,14 +332,14 @@ int capscaps_conv_fwd(const void* input, const void* kernel, void* out, int N, i
     const int rc = fill_shape(s, N, H, W, C, M, kh, kw, stride, 0, D0, D1, D2, D3, dtype);
     if (rc != CAPSCAPS_OK) return rc;
     hipStream_t st = static_cast<hipStream_t>(stream);
-    const int path = choose_path(s);
-    const size_t need = path != CAPSCAPS_PATH_DIRECT ? capscaps::mfma_workspace_bytes(s) : 0;
+    const Choice own = choose(s);
+    const size_t need = scratch_bytes(s, own);
     void* ws = nullptr;
     if (need > 0) {
         const hipError_t err = hipMallocAsync(&ws, need, st);
         if (err != hipSuccess) return hip_status(err);
     }
-    const int status = run(input, kernel, out, s, path, ws, need, st);
+    const int status = run_choice(input, kernel, out, s, own, ws, need, st);
     if (ws != nullptr) {
         const hipError_t err = hipFreeAsync(ws, st);
         if (err != hipSuccess && status == CAPSCAPS_OK) return hip_status(err);
@@ -333,9 +356,10 @@ int capscaps_conv_fwd_static(const void* input, const void* kernel, void* out, i
     ConvShape s;
     const int rc = fill_shape(s, N, H, W, C, M, kh, kw, stride, pad, D0, D1, D2, D3, dtype);
     if (rc != CAPSCAPS_OK) return rc;
+    const Choice own = choose(s);
     capscaps::MfmaKernel lean = capscaps::MfmaKernel::Auto;
-    if (!own_choice_fits_scratch(s)) {
-        lean = leaner_kernel(s);
+    if (!fits_scratch(s, own)) {
+        lean = leaner_kernel(s, own);
         if (lean == capscaps::MfmaKernel::Auto) return CAPSCAPS_ESCRATCH;
     }
     void* ws = nullptr;
@@ -344,8 +368,7 @@ int capscaps_conv_fwd_static(const void* input, const void* kernel, void* out, i
     if (lean != capscaps::MfmaKernel::Auto)
         return hip_status(capscaps::launch_mfma(s, input, kernel, static_cast<float*>(out), ws,
                                                 static_cast<hipStream_t>(stream), lean));
-    return run(input, kernel, out, s, CAPSCAPS_PATH_AUTO, ws, SCRATCH_ARRAY,
-               static_cast<hipStream_t>(stream));
+    return run_choice(input, kernel, out, s, own, ws, SCRATCH_ARRAY, static_cast<hipStream_t>(stream));
 }
 
 size_t capscaps_conv_bwd_input_workspace_bytes(int N, int H, int W, int C, int M, int kh, int kw,

@@ -513,6 +513,12 @@ bool igemm32_dma_fills_chip(const ConvShape& s)
 
 bool igemm32_dma_preferred(const ConvShape& s)
 {
+    // (most small layers leave here, before any plan is made: every rule below asks for 128 tiles of
+    // 256 rows, or in fp32 for that many FLOPs, and a tile has at least 30 columns)
+    const double flops = 2.0 * (double)s.out_elems() * s.kh * s.kw * s.C * s.D2;
+    const double most_tiles = (double)((s.pixels() * s.D1 + 255) / 256) *
+                              (double)(((long long)s.M * s.D3 + 29) / 30) * s.D0;
+    if (most_tiles < 128 && !(s.dtype == 0 && flops >= 5e8)) return false;
     if (!igemm32_dma_eligible(s)) return false;
     // fp32: where its four-wave tiles fill the chip, and from 3e9 nominal FLOPs on with a split K
     // loop or one-wave tiles too (16 .. 64 channels of 4x4 and 8x8 capsules, 25 to 98 tiles of 256
@@ -522,7 +528,6 @@ bool igemm32_dma_preferred(const ConvShape& s)
     if (s.dtype == 0) {
         const Dma32Plan pl = igemm32_dma_plan(s);
         if (pl.nw == 4 && (long long)pl.P.row_tiles * pl.P.col_tiles * s.D0 >= 256) return true;
-        const double flops = 2.0 * (double)s.out_elems() * s.kh * s.kw * s.C * s.D2;
         return flops >= (igemm32_dma_chunk_width(s) == 3 ? 5e8 : 3e9);
     }
     // 16-bit: square capsules of 8 or 16 rows belong to the 256x256-tile kernel, which is 1.12 ..
@@ -543,7 +548,7 @@ bool igemm32_dma_preferred(const ConvShape& s)
     if (pl.nw == 4 && pl.P.nsplit == 1) return true;
     const long long tiles = (long long)ceil_div_ll(pl.P.rows, 256) * pl.P.col_tiles * s.D0;
     return tiles >= 128 && !igemm16_fast_preferred(s) &&
-           2.0 * (double)s.out_elems() * s.kh * s.kw * s.C * s.D2 >= 9e9;
+           flops >= 9e9;
 }
 
 hipError_t launch_igemm32_dma(const Dma32Plan& pl, hipStream_t stream)
