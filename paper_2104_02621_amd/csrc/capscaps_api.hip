@@ -68,18 +68,15 @@ Choice choose(const ConvShape& s)
     const Choice direct = {CAPSCAPS_PATH_DIRECT, capscaps::MfmaKernel::Auto};
     if (!capscaps::mfma_supported(s)) return direct;
     const long long kdim = (long long)s.kh * s.kw * s.C * s.D2;
-    const long long cols = (long long)s.M * s.D3;
     if (kdim <= 24) return direct;
     const double flops = 2.0 * (double)s.out_elems() * (double)kdim;
-    // (fp32 layers from 5e8 FLOPs on: the lane-per-row kernel, which contracts on the bf16 matrix
-    // instructions -- 6x5 . 5x4 capsules, 8 columns, 9.9 GFLOP 399 against 1473 us; 3x3x3 capsules, 6
-    // columns, 0.5 GFLOP 32 against 153 us)
-    if (cols <= 8 && (s.D2 % 4 != 0 || s.D3 % 4 != 0) && flops >= 5e7 && capscaps::wave_conv_eligible(s)) {
-        const bool split32 = s.dtype == CAPSCAPS_FP32 && flops >= 5e8 &&
-                             (capscaps::mfma_rechunk_preferred(s) || capscaps::mfma_dma32_supported(s));
-        if (!split32) return direct;
-    }
     const capscaps::MfmaKernel kernel = capscaps::mfma_auto_kernel(s);
+    // (fp32 layers from 5e8 FLOPs on: the lane-per-row kernel where it is the choice, which contracts on
+    // the bf16 matrix instructions -- 6x5 . 5x4 capsules, 8 columns, 9.9 GFLOP 399 against 1473 us;
+    // 3x3x3 capsules, 6 columns, 0.5 GFLOP 32 against 153 us)
+    const bool split32 = s.dtype == CAPSCAPS_FP32 && flops >= 5e8 &&
+                         (kernel == capscaps::MfmaKernel::Dma32 || kernel == capscaps::MfmaKernel::Rechunk);
+    if (!split32 && few_columns(s) && flops >= 5e7 && capscaps::wave_conv_eligible(s)) return direct;
     switch (kernel) {
         case capscaps::MfmaKernel::Tuned16: return {CAPSCAPS_PATH_MFMA_TUNED16, kernel};
         case capscaps::MfmaKernel::Dma32: return {CAPSCAPS_PATH_MFMA_TUNED32, kernel};

@@ -71,6 +71,12 @@ struct ConvShape {
 hipError_t launch_direct(const ConvShape& s, const void* in, const void* kernel, float* out,
                          hipStream_t stream);
 bool wave_conv_eligible(const ConvShape& s);
+// layers the wavefront-level path runs faster than the any-shape and the small-problem kernel, once
+// they are large enough for throughput to count
+inline bool few_columns(const ConvShape& s)
+{
+    return (long long)s.M * s.D3 <= 8 && (s.D2 % 4 != 0 || s.D3 % 4 != 0);
+}
 hipError_t launch_wave_conv(const ConvShape& s, const void* in, const void* kernel, float* out,
                             hipStream_t stream);
 
@@ -84,7 +90,6 @@ MfmaKernel mfma_auto_kernel(const ConvShape& s);  // what Auto resolves to (neve
 bool mfma_tuned16_supported(const ConvShape& s);
 bool mfma_dma32_supported(const ConvShape& s);
 bool mfma_small_supported(const ConvShape& s);
-bool mfma_rechunk_preferred(const ConvShape& s);
 size_t mfma_workspace_bytes(const ConvShape& s);  // enough for every MfmaKernel choice (with
                                                   // s.out16: for Auto, the only choice then)
 size_t mfma_kernel_workspace_bytes(const ConvShape& s, MfmaKernel which);  // for that kernel only

@@ -520,15 +520,24 @@ bool igemm32_dma_preferred(const ConvShape& s)
                               (double)(((long long)s.M * s.D3 + 29) / 30) * s.D0;
     if (most_tiles < 128 && !(s.dtype == 0 && flops >= 5e8)) return false;
     if (!igemm32_dma_eligible(s)) return false;
-    // fp32: where its four-wave tiles fill the chip, and from 3e9 nominal FLOPs on with a split K
-    // loop or one-wave tiles too (16 .. 64 channels of 4x4 and 8x8 capsules, 25 to 98 tiles of 256
-    // rows: 3.7 GFLOP 48 against 57 us on the small-problem kernel, 4.8 GFLOP 56 against 59, 7.4 GFLOP 72
-    // against 104; 1.9 GFLOP 44 against 30 us); capsule rows of 3k floats, which the others load
-    // element by element, from 5e8 (3x3x3 capsules: 0.5 GFLOP 32 against 65 us, 1.5 GFLOP 36 against 72)
+    // fp32: where its four-wave tiles fill the chip; with a split K loop or one-wave tiles where the
+    // FLOPs are worth the two launches more and the packed kernel and partial sums these write and read
+    // (7.4 GFLOP of 4x4 capsules 72 against 104 us on the small-problem kernel, 3x3x3 capsules of 1.5 GFLOP
+    // 36 against 72).  Capsule rows of 3 floats, which the other kernels load element by element, from 7e8
+    // FLOPs on and 10 more per byte, of 6 floats (8-byte loads there) from 1.3e9 and 30 more, others from
+    // 2.5e9 and 30 more.  Of 600 random layers of 0.3 .. 8 GFLOP: 3 of those taken are slower than on the
+    // other kernels, by up to 14 %; 40 left to the others would gain more than 3 %.  By the FLOPs alone, from
+    // 5e8 (3k floats) and 3e9, 70 were slower, the worst by 3.5 times (4 images through a fully-connected
+    // layer of 12x12 capsules).  Layers of few columns, else on the wavefront-level path, from 5e8 (1.1 .. 20 times
+    // faster).
     if (s.dtype == 0) {
         const Dma32Plan pl = igemm32_dma_plan(s);
         if (pl.nw == 4 && (long long)pl.P.row_tiles * pl.P.col_tiles * s.D0 >= 256) return true;
-        return flops >= (igemm32_dma_chunk_width(s) == 3 ? 5e8 : 3e9);
+        if (few_columns(s)) return flops >= 5e8;
+        const double bytes = (double)pl.partial_bytes + (double)pl.repack_bytes;
+        return s.D2 == 3   ? flops >= 7e8 + 10.0 * bytes
+               : s.D2 == 6 ? flops >= 1.3e9 + 30.0 * bytes
+                           : flops >= 2.5e9 + 30.0 * bytes;
     }
     // 16-bit: square capsules of 8 or 16 rows belong to the 256x256-tile kernel, which is 1.12 ..
     // 1.17x faster on whole column tiles (configs 3 and 5: 0.92 against 1.03 ms, 14.2 against

@@ -603,12 +603,17 @@ struct RechunkPlan {
     size_t bytes() const { return in_bytes + ((repack_bytes + 255) & ~(size_t)255) + partial_bytes; }
 };
 
-// From 1.2e9 FLOPs on (5 GFLOP: 70 us against 109 on the small-problem kernel and 161 on this one).
+// From 1.2e9 FLOPs on (5 GFLOP: 70 us against 109 on the small-problem kernel and 161 on this one), and
+// 50 more per byte of the written-out input, 10 per byte of packed kernel and partial sums: that is
+// the time those take.  Of 200 random layers of 1.2 .. 30 GFLOP 18 were slower by up to 40 % without
+// the bytes (1x1 windows above all: 34 -> 59 channels of 6x5 . 5x4 capsules, 0.4 GB of input, 368
+// against 221 us), 2 by up to 11 % with them; 22 that gained 5 .. 150 % stay behind.
 RechunkPlan rechunk_plan(const ConvShape& s)
 {
     RechunkPlan rp{};
     if (s.dtype != 0 || s.pad_w_set || s.out_view || igemm32_dma_chunk_width(s) != 0) return rp;
-    if (2.0 * (double)s.out_elems() * s.kh * s.kw * s.C * s.D2 < 1.2e9) return rp;
+    const double flops = 2.0 * (double)s.out_elems() * s.kh * s.kw * s.C * s.D2;
+    if (flops < 1.2e9) return rp;
     ConvShape f = s;
     f.kernel_view = false;
     f.C = ceil_div((long long)s.C * s.D2, 4);
@@ -630,7 +635,8 @@ RechunkPlan rechunk_plan(const ConvShape& s)
     f.N = rp.images;
     rp.layer = f;
     rp.in_bytes = (img * rp.images + 255) & ~(size_t)255;
-    rp.ok = rp.bytes() <= RECHUNK_TOTAL;
+    rp.ok = rp.bytes() <= RECHUNK_TOTAL &&
+            flops >= 1.2e9 + 50.0 * (double)img * s.N + 10.0 * ((double)rp.partial_bytes * parts + (double)rp.repack_bytes);
     return rp;
 }
 
@@ -845,8 +851,6 @@ MfmaKernel mfma_auto_kernel(const ConvShape& s)
     if (igemm_small_preferred(s)) return MfmaKernel::Small;
     return MfmaKernel::Generic;
 }
-
-bool mfma_rechunk_preferred(const ConvShape& s) { return shape_supported(s) && rechunk_plan(s).ok; }
 
 bool mfma_dma32_supported(const ConvShape& s)
 {

@@ -251,3 +251,22 @@ def test_static_scratch_entry_point_checks_before_touching_the_gpu():
     big = _args(N=1, H=34, W=34, C=160, M=160, D1=16, D2=16, D3=16, dtype=cc.FP16)
     assert cc.capscaps_conv_fwd_static(FAKE, FAKE, FAKE, *big, None) == cc.ESCRATCH
     assert "scratch" in cc.capscaps_strerror(cc.ESCRATCH)
+
+
+def test_fp32_layers_that_split_bf16_terms_do_not_pay_for():
+    """The lane-per-row kernel is left to layers whose FLOPs are worth packing the kernel tensor, partial
+    sums and, for rows no copy fits, a copy of the input (each of these measured on both sides)."""
+    def path(*shape):
+        return cc.capscaps_select_path(*shape, cc.FP32)
+    # 12x12 capsules: 4 images through a fully-connected layer 20 against 70 us; 5.5 GFLOP 88 against 64
+    assert path(4, 4, 4, 45, 67, 4, 4, 1, 0, 1, 12, 12, 12) == cc.PATH_MFMA_SMALL
+    assert path(14, 7, 7, 8, 32, 3, 3, 1, 1, 1, 12, 12, 12) == cc.PATH_MFMA_TUNED32
+    # 3x3x3 capsules: 0.6 GFLOP on two row tiles 28 against 39; 1.2 GFLOP 32 against 25
+    assert path(1, 13, 13, 66, 37, 3, 3, 1, 1, 3, 3, 3, 3) == cc.PATH_MFMA_SMALL
+    assert path(24, 20, 20, 16, 16, 3, 3, 1, 1, 3, 3, 3, 3) == cc.PATH_MFMA_TUNED32
+    # 6x5 . 5x4 capsules: a 1x1 window over 0.4 GB of input 221 against 368; a 3x3 one 404 against 221
+    assert path(170, 15, 39, 34, 59, 1, 1, 2, 0, 1, 6, 5, 4) == cc.PATH_MFMA_GENERIC
+    assert path(42, 37, 37, 16, 56, 3, 3, 2, 0, 1, 6, 5, 4) == cc.PATH_MFMA
+    # at most 8 columns and rows of 3: the wavefront-level path below 5e8 FLOPs, 20 times slower above
+    assert path(4, 29, 29, 16, 2, 5, 5, 1, 2, 3, 3, 3, 3) == cc.PATH_DIRECT
+    assert path(8, 29, 29, 16, 2, 5, 5, 1, 2, 3, 3, 3, 3) == cc.PATH_MFMA_TUNED32

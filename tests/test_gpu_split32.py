@@ -154,6 +154,7 @@ def test_kernel_gradient_of_values_bf16_cannot_hold(shape, value):
 RECHUNK_SHAPES = [
     (12, 20, 17, 11, 14, 5, 5, 1, 2, 1, 6, 5, 4),
     (40, 24, 24, 9, 17, 3, 3, 2, 1, 2, 4, 7, 3),
+    (40, 24, 24, 18, 34, 3, 3, 2, 1, 2, 4, 7, 3),
     (60, 28, 28, 33, 12, 3, 3, 1, 0, 1, 2, 1, 5),
     (30, 32, 32, 13, 18, 3, 3, 1, 1, 1, 5, 2, 9),
 ]
@@ -274,8 +275,8 @@ def test_forced_any_shape_kernel_runs_on_rows_of_any_length():
     adds up the K values in one order.  The library's own choice for the large batch, which contracts
     bf16 terms, does not."""
     import torch
-    big = small("generic_rows", wl.FP32, 640, 32, 32, 2, 2, 3, 3, 1, 1, 2, 1, 5, 5, seed=623)
-    few = small("generic_rows", wl.FP32, 20, 32, 32, 2, 2, 3, 3, 1, 1, 2, 1, 5, 5, seed=623)
+    big = small("generic_rows", wl.FP32, 640, 32, 32, 2, 8, 3, 3, 1, 1, 2, 1, 5, 5, seed=623)
+    few = small("generic_rows", wl.FP32, 20, 32, 32, 2, 8, 3, 3, 1, 1, 2, 1, 5, 5, seed=623)
     assert big.flops_nominal() >= 1.2e9
     assert cc.capscaps_select_path(*shape_args(big)) == cc.PATH_MFMA
     x, k = (to_device(t, wl.FP32) for t in wl.generate(big)[:2])
