@@ -30,6 +30,8 @@
 // ahead of their use, between the matrix instructions of the stage before.
 #include <hip/hip_runtime.h>
 
+#include <cmath>
+
 #include "bf16_split.h"
 #include "igemm_common.h"
 #include "lds_dma.h"
@@ -60,6 +62,57 @@ struct Wgrad32Params {
     long long items;      // tiles * nsplit = workgroups
     long long out_elems;  // elements of dK
     long long it_img_bytes, gt_img_bytes;
+};
+
+// What a workgroup contracts: a tile of a tap's products over a range of the tap's pixels.
+struct Item {
+    int split, row_tile, col_tile, tap, d0, tp, tq;
+    // Per image the output pixels whose tap (tp, tq) reads a real input pixel form a rectangle of nx x ny
+    // from (x_lo, y_lo) on; the rectangles of all images, image after image, row after row, are one
+    // sequence, cut into nsplit equal ranges.  This one's has npix pixels, from (xs, ys) of the
+    // rectangle of image n0 to image n_last.
+    int nx, ny, x_lo, y_lo, npix, n0, n_last, xs, ys;
+    __device__ __forceinline__ explicit Item(const Wgrad32Params& P)
+    {
+        // each XCD (workgroups are dealt to the 8 XCDs in turn) gets a contiguous range of items,
+        // pixel range slowest, so its resident workgroups read the same pixels
+        long long item = blockIdx.x;
+        const long long per = P.items / 8;
+        if (item < per * 8) item = (item % 8) * per + item / 8;
+        split = (int)(item / P.tiles);
+        int rest = (int)(item % P.tiles);
+        col_tile = rest % P.col_tiles;
+        rest /= P.col_tiles;
+        row_tile = rest % P.row_tiles;
+        rest /= P.row_tiles;
+        tap = rest % P.ntaps;
+        d0 = rest / P.ntaps;
+        tp = tap / P.kw;
+        tq = tap - tp * P.kw;
+        const int s = P.stride;
+        const int tx = P.pad - tp, ty = P.pad - tq;
+        x_lo = tx > 0 ? (tx + s - 1) / s : 0;
+        y_lo = ty > 0 ? (ty + s - 1) / s : 0;
+        const int hx = P.H - 1 + tx, hy = P.W - 1 + ty;
+        int x_hi = hx >= 0 ? hx / s : -1, y_hi = hy >= 0 ? hy / s : -1;
+        if (x_hi > P.Ho - 1) x_hi = P.Ho - 1;
+        if (y_hi > P.Wo - 1) y_hi = P.Wo - 1;
+        nx = x_hi - x_lo + 1;
+        ny = y_hi - y_lo + 1;
+        if (nx <= 0 || ny <= 0) nx = ny = 0;
+        const long long rect = (long long)nx * ny, total = rect * P.N;
+        const long long tps = (total + P.nsplit - 1) / P.nsplit;
+        long long t0 = (long long)split * tps;
+        if (t0 > total) t0 = total;
+        long long t1 = t0 + tps;
+        if (t1 > total) t1 = total;
+        npix = (int)(t1 - t0);
+        n0 = npix > 0 ? (int)(t0 / rect) : 0;
+        n_last = npix > 0 ? (int)((t1 - 1) / rect) : n0;
+        const int r0 = npix > 0 ? (int)(t0 - (long long)n0 * rect) : 0;  // position in image n0
+        xs = ny > 0 ? r0 / ny : 0;
+        ys = ny > 0 ? r0 - xs * ny : 0;
+    }
 };
 
 // dst[x][b][a] = src[x][a][b] for matrices of A x B floats.  One thread per element.
@@ -100,55 +153,14 @@ void wgrad32_kernel(const Wgrad32Params P)
 
     extern __shared__ char smem[];
 
-    // ---- which item: each XCD (workgroups are dealt to the 8 XCDs in turn) gets a contiguous
-    // range of items, pixel range slowest, so its resident workgroups read the same pixels
-    long long item = blockIdx.x;
-    {
-        const long long per = P.items / 8;
-        if (item < per * 8) item = (item % 8) * per + item / 8;
-    }
-    const int split = (int)(item / P.tiles);
-    int rest = (int)(item % P.tiles);
-    const int col_tile = rest % P.col_tiles;
-    rest /= P.col_tiles;
-    const int row_tile = rest % P.row_tiles;
-    rest /= P.row_tiles;
-    const int tap = rest % P.ntaps;
-    const int d0 = rest / P.ntaps;
-    const int tp = tap / P.kw, tq = tap - tp * P.kw;
+    // ---- the item, and its pixels
+    const Item it(P);
+    const int split = it.split, row_tile = it.row_tile, col_tile = it.col_tile, tap = it.tap, d0 = it.d0;
+    const int tp = it.tp, tq = it.tq, nx = it.nx, ny = it.ny, x_lo = it.x_lo, y_lo = it.y_lo;
+    const int npix = it.npix, n0 = it.n0, n_last = it.n_last, xs = it.xs, ys = it.ys, s = P.stride;
 
     const int lane = threadIdx.x & 63;
     const int h = lane >> 5, lr = lane & 31;
-
-    // ---- the pixels of this item.  Per image the output pixels whose tap (tp, tq) reads a
-    // real input pixel form a rectangle; the rectangles of all images, image after image, row
-    // after row, are one sequence, of which this item contracts the range [t0, t1).
-    const int s = P.stride;
-    int nx, ny, x_lo, y_lo;
-    {
-        const int tx = P.pad - tp, ty = P.pad - tq;
-        x_lo = tx > 0 ? (tx + s - 1) / s : 0;
-        y_lo = ty > 0 ? (ty + s - 1) / s : 0;
-        const int hx = P.H - 1 + tx, hy = P.W - 1 + ty;
-        int x_hi = hx >= 0 ? hx / s : -1, y_hi = hy >= 0 ? hy / s : -1;
-        if (x_hi > P.Ho - 1) x_hi = P.Ho - 1;
-        if (y_hi > P.Wo - 1) y_hi = P.Wo - 1;
-        nx = x_hi - x_lo + 1;
-        ny = y_hi - y_lo + 1;
-        if (nx <= 0 || ny <= 0) nx = ny = 0;
-    }
-    // every tap's sequence is cut into nsplit equal ranges
-    const long long rect = (long long)nx * ny, total = rect * P.N;
-    const long long tps = (total + P.nsplit - 1) / P.nsplit;
-    long long t0 = (long long)split * tps;
-    if (t0 > total) t0 = total;
-    long long t1 = t0 + tps;
-    if (t1 > total) t1 = total;
-    const int npix = (int)(t1 - t0);
-    const int n0 = npix > 0 ? (int)(t0 / rect) : 0;
-    const int n_last = npix > 0 ? (int)((t1 - 1) / rect) : n0;
-    const int r0 = npix > 0 ? (int)(t0 - (long long)n0 * rect) : 0;  // position in image n0
-    const int xs = ny > 0 ? r0 / ny : 0, ys = ny > 0 ? r0 - xs * ny : 0;
     const int ipix = P.C * P.D0 * P.D2 * P.D1 * 4;  // bytes per pixel of It / Gt
     const int gpix = P.M * P.D0 * P.D3 * P.D1 * 4;
     const int i_step = s * ipix, g_step = gpix;
@@ -524,9 +536,186 @@ void wgrad32_kernel(const Wgrad32Params P)
     }
 }
 
+// The same contraction on the fp32 matrix instructions, for layers with at most 32 columns whose operands
+// are transposed copies.  There the splitting does not pay: a wave of the kernel above takes two row tiles
+// and one column tile, 1.5 splits per six products, and copies 3 KB to LDS per 32 x 32 results and 16 K
+// values; here NW = 2 or 4 waves share a column tile, 64 rows each, and 2.25 KB.  Measured: 16 -> 8
+// channels of 4x16 . 16x4 capsules, 25 images of 28x28, 6x6 window, stride 2: 147 us above, 131 here;
+// 40 -> 8 channels of 6x5 . 5x4, 7 images of 36x20, 6x6: 164 and 133.  KCH chunks per row and stage, ring
+// of three stages, one barrier per stage.
+constexpr int NARROW_RING = 3;
+constexpr int narrow_chunks(int d1c, int nw) { return d1c == 4 || nw == 4 ? 4 : 2; }
+constexpr int narrow_lds_bytes(int nw, int kch) { return NARROW_RING * kch * (64 * nw + 64) * 16; }
+template <int CW, int NW, int KCH>
+__global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(KCH == 2 ? 3 : 2)))
+void wgrad32_narrow_kernel(const Wgrad32Params P)
+{
+    constexpr int NB = NARROW_RING, TM = 2;
+    constexpr int BM = 64 * NW, BN = 64;  // (32 columns, copied by whole waves)
+    constexpr int A_BYTES = KCH * BM * 16, B_BYTES = KCH * BN * 16, STAGE_BYTES = A_BYTES + B_BYTES;
+    constexpr int BPW = KCH / NW;  // column-side copies per wave and stage
+    static_assert(KCH % NW == 0, "column copies divide evenly over the waves");
+    constexpr int KEEP = (NB - 2) * (KCH + BPW);  // copies that may be in flight at a barrier
+    static_assert(KEEP < 16, "vmcnt's low bits");
+    constexpr int OOB = (int)0x80000000u, NO_PIXEL = 0x7fffff00;  // (marks as in the kernel above)
+
+    extern __shared__ char smem[];
+    const Item it(P);
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int h = lane >> 5, lr = lane & 31;
+
+    const int s = P.stride, ny = it.ny, nx = it.nx;
+    const int ipix = P.C * P.D0 * P.D2 * P.D1 * 4, gpix = P.M * P.D0 * P.D3 * P.D1 * 4;
+    const int i_step = s * ipix, g_step = gpix;
+    const int i_rowjump = (s * P.W - (ny - 1) * s) * ipix, g_rowjump = (P.Wo - (ny - 1)) * gpix;
+    const int i_imgjump = (P.H * P.W - nx * s * P.W) * ipix, g_imgjump = (P.Ho * P.Wo - nx * P.Wo) * gpix;
+    int i_cur = (((it.x_lo + it.xs) * s - (P.pad - it.tp)) * P.W + ((it.y_lo + it.ys) * s - (P.pad - it.tq))) * ipix;
+    int g_cur = ((it.x_lo + it.xs) * P.Wo + it.y_lo + it.ys) * gpix;
+    int left = it.npix, yl = ny - it.ys, xl = nx - it.xs;
+    const int images = it.n_last + 1 - it.n0;
+    const rsrc_t rs_it = make_rsrc(static_cast<const char*>(P.it) + (long long)it.n0 * P.it_img_bytes,
+                                   (unsigned)(images * P.it_img_bytes));
+    const rsrc_t rs_gt = make_rsrc(static_cast<const char*>(P.gt) + (long long)it.n0 * P.gt_img_bytes,
+                                   (unsigned)(images * P.gt_img_bytes));
+    const unsigned lds0 = (unsigned)(size_t)(__attribute__((address_space(3))) char*)smem;
+
+    unsigned a_voff, b_voff;
+    {
+        const int R = it.row_tile * BM + wave * 64 + lane, c = R / P.D2, d2 = R - c * P.D2;
+        a_voff = R < P.rows ? (unsigned)((((c * P.D0 + it.d0) * P.D2 + d2) * P.D1) * 4) : (unsigned)OOB;
+        const int m = lane / P.D3, d3 = lane - m * P.D3;
+        b_voff = lane < P.cols ? (unsigned)((((m * P.D0 + it.d0) * P.D3 + d3) * P.D1) * 4) : (unsigned)OOB;
+    }
+    const int pps = KCH / P.D1C;  // pixels per stage
+    const int d1c_shift = P.D1C == 1 ? 0 : P.D1C == 2 ? 1 : 2;
+    const int nstages = (it.npix + pps - 1) / pps;
+
+    // copies of the next stage, its pixels each the next valid output pixel of the tap's rectangle
+    auto issue_stage = [&](int slot) {
+        const unsigned stage = lds0 + slot * STAGE_BYTES;
+        int i_soff[KCH], g_soff[KCH];
+#pragma unroll
+        for (int j = 0; j < KCH; ++j) {
+            i_soff[j] = g_soff[j] = NO_PIXEL;
+            if (j < pps) {
+                if (left > 0) {
+                    i_soff[j] = i_cur;
+                    g_soff[j] = g_cur;
+                }
+                --left;
+                --yl;
+                if (yl != 0) {
+                    i_cur += i_step;
+                    g_cur += g_step;
+                } else {
+                    yl = ny;
+                    --xl;
+                    i_cur += i_rowjump;
+                    g_cur += g_rowjump;
+                    if (xl == 0) {
+                        xl = nx;
+                        i_cur += i_imgjump;
+                        g_cur += g_imgjump;
+                    }
+                }
+            }
+        }
+        // chunk q of the stage: part q % D1C of pixel q / D1C
+#pragma unroll
+        for (int q = 0; q < KCH; ++q) {
+            const int slot_px = q >> d1c_shift, part = q - (slot_px << d1c_shift);
+            int px = i_soff[0];
+#pragma unroll
+            for (int k = 1; k < KCH; ++k) px = slot_px == k ? i_soff[k] : px;
+            copy_to_lds_dwords<CW>(rs_it, stage + (q * BM + 64 * wave) * 16, a_voff, px + part * CW * 4);
+        }
+#pragma unroll
+        for (int j = 0; j < BPW; ++j) {
+            const int q = wave * BPW + j;
+            const int slot_px = q >> d1c_shift, part = q - (slot_px << d1c_shift);
+            int px = g_soff[0];
+#pragma unroll
+            for (int k = 1; k < KCH; ++k) px = slot_px == k ? g_soff[k] : px;
+            copy_to_lds_dwords<CW>(rs_gt, stage + A_BYTES + q * 1024, b_voff, px + part * CW * 4);
+        }
+    };
+
+    float16v acc[TM];
+    bool live[TM];  // row tiles of this wave that hold at least one real row
+#pragma unroll
+    for (int b = 0; b < TM; ++b) {
+        live[b] = it.row_tile * BM + 64 * wave + b * 32 < P.rows;
+#pragma unroll
+        for (int r = 0; r < 16; ++r) acc[b][r] = 0.f;
+    }
+    float4v k4[KCH / 2], i4[KCH / 2][TM];
+
+    static_for<NB - 1>([&](auto S0) { issue_stage(decltype(S0)::value); });
+    __builtin_amdgcn_s_waitcnt(0x0F70 | KEEP);
+    __syncthreads();
+    for (int st = 0; st < nstages; st += NB) {  // surplus stages contract zeros
+        static_for<NB>([&](auto SLOT) {
+            constexpr int slot = decltype(SLOT)::value;
+            const char* stage = smem + slot * STAGE_BYTES;
+#pragma unroll
+            for (int t = 0; t < KCH / 2; ++t) {  // lanes 0..31 take chunk 2t, lanes 32..63 chunk 2t+1
+                k4[t] = *reinterpret_cast<const float4v*>(stage + A_BYTES + ((2 * t + h) * BN + lr) * 16);
+#pragma unroll
+                for (int b = 0; b < TM; ++b)
+                    i4[t][b] = *reinterpret_cast<const float4v*>(stage + ((2 * t + h) * BM + 64 * wave + b * 32 + lr) * 16);
+            }
+            issue_stage((slot + NB - 1) % NB);
+#pragma unroll
+            for (int t = 0; t < KCH / 2; ++t)
+#pragma unroll
+                for (int b = 0; b < TM; ++b) {
+                    if (!live[b]) continue;  // wave-uniform
+#pragma unroll
+                    for (int u = 0; u < CW; ++u)
+                        acc[b] = __builtin_amdgcn_mfma_f32_32x32x2f32(k4[t][u], i4[t][b][u], acc[b], 0, 0, 0);
+                }
+            // this wave's copies of the next stage have landed, its reads of this stage are done;
+            // after the barrier both hold for every wave
+            __builtin_amdgcn_s_waitcnt((0x0F70 | KEEP) & 0xF0FF);
+            __syncthreads();
+        });
+    }
+    // the copies of the surplus stages still write (zeros) into this workgroup's LDS
+    __builtin_amdgcn_s_waitcnt(0x0F70);
+
+    float* __restrict__ out = P.out + (long long)it.split * P.out_elems;
+    const long long caps = (long long)P.D0 * P.D2 * P.D3;
+#pragma unroll
+    for (int b = 0; b < TM; ++b) {
+        const int R = it.row_tile * BM + 64 * wave + b * 32 + lr;
+        if (R >= P.rows) continue;
+        const int c = R / P.D2, d2 = R - c * P.D2;
+        float* orow = out + ((long long)it.tap * P.C + c) * P.M * caps + ((long long)it.d0 * P.D2 + d2) * P.D3;
+#pragma unroll
+        for (int g = 0; g < 4; ++g) {
+            const int j0 = 8 * g + 4 * h;  // registers 4g .. 4g+3 hold columns j0 .. j0+3
+            if ((P.D3 & 3) == 0) {
+                if (j0 < P.cols) {
+                    const int m = j0 / P.D3, d3 = j0 - m * P.D3;
+                    const float4v v = {acc[b][4 * g], acc[b][4 * g + 1], acc[b][4 * g + 2], acc[b][4 * g + 3]};
+                    *reinterpret_cast<float4v*>(orow + (long long)m * caps + d3) = v;
+                }
+            } else {
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    const int j = j0 + u, m = j / P.D3, d3 = j - m * P.D3;
+                    if (j < P.cols) orow[(long long)m * caps + d3] = acc[b][4 * g + u];
+                }
+            }
+        }
+    }
+}
+
 struct Wgrad32Plan {
     Wgrad32Params P;
     int cw, tn, tm;
+    int narrow_waves;  // wgrad32_narrow_kernel with that many waves; 0: wgrad32_kernel
     size_t it_bytes, gt_bytes, partial_bytes;
 };
 
@@ -556,24 +745,36 @@ long long split_lower_bound(const ConvShape& s)
     return (s.N + (imgs_cap - 3) - 1) / (imgs_cap - 3);
 }
 
-// MFMA tiles of 32 that `extent` rows or columns take in the kernel's tiles of at most three, and
-// how many whole tiles of that size: the fewest padded rows, then the fewest tiles
-void tile_extent(int extent, int unit, int& t, int& step, int& tiles)
+// Rows (columns) of `extent` that a tile of k MFMA tiles of 32 takes; 0: less than a capsule
+int tile_step(int extent, int unit, int k)
 {
-    long long best = -1;
-    for (int k = 3; k >= 1; --k) {
-        int st = 32 * k;
-        if (extent > st) st = st / unit * unit;  // several tiles: each begins at a whole capsule
-        if (st == 0) continue;
-        const int n = ceil_div_i(extent, st);
-        const long long padded = (long long)n * 32 * k;
-        if (best < 0 || padded < best) {
-            best = padded;
-            t = k;
-            step = st;
-            tiles = n;
+    return extent > 32 * k ? 32 * k / unit * unit : 32 * k;  // several tiles: each begins at a whole capsule
+}
+
+// Tile: the least estimated time, of `steps` steps of 16 K values in every tile of all taps.  A wave splits
+// TM + TN operands for TM x TN products: cost, in ns per 32 x 32 results and step with all SIMDs busy, is
+// the mean of six capsule shapes with 576 rows and columns.  The code of a large tile takes time to arrive
+// and to get under way: start, in us, is what tiny layers take more than with 1 x 1 tiles.  (By the fewest
+// padded rows alone 150 x 220 took 1 x 1 tiles, 262 us at 12 GFLOP, now 161, and 96 x 384 with two dozen K
+// values 3 x 3 ones, 22 us, now 13.)
+void choose_tile(Wgrad32Params& P, double steps, int& tm, int& tn)
+{
+    static const double cost[3][3] = {{650, 470, 540}, {470, 360, 385}, {540, 385, 330}};
+    static const double start[3][3] = {{0, 1.3, 4.5}, {1.5, 4, 8}, {5, 9, 15}};
+    const int row_unit = P.natural ? P.D2 : 1, col_unit = P.natural ? P.D3 : 1;
+    double best = -1;
+    for (int a = 3; a >= 1; --a)
+        for (int b = 3; b >= 1; --b) {
+            const int rs = tile_step(P.rows, row_unit, a), cs = tile_step(P.cols, col_unit, b);
+            if (rs == 0 || cs == 0) continue;
+            const int rt = ceil_div_i(P.rows, rs), ct = ceil_div_i(P.cols, cs);
+            const double busy = steps * P.ntaps * P.D0 * rt * ct * a * b * cost[a - 1][b - 1];
+            const double time = start[a - 1][b - 1] + busy / (1024 * 1e3);  // 1024 SIMDs
+            if (best >= 0 && time >= best) continue;
+            best = time;
+            tm = a; P.row_step = rs; P.row_tiles = rt;
+            tn = b; P.col_step = cs; P.col_tiles = ct;
         }
-    }
 }
 
 // Tiles and the split of the K loop (host side, pure arithmetic).
@@ -589,9 +790,18 @@ Wgrad32Plan make_plan(const ConvShape& s)
     P.cols = s.M * s.D3;
     // square capsules need no transposed copies; their tiles begin at whole channels
     P.natural = s.D1 == s.D2 && s.D1 == s.D3;
-    tile_extent(P.rows, P.natural ? s.D2 : 1, pl.tm, P.row_step, P.row_tiles);
-    tile_extent(P.cols, P.natural ? s.D3 : 1, pl.tn, P.col_step, P.col_tiles);
     P.ntaps = s.kh * s.kw;
+    const long long full = (long long)s.N * s.Ho * s.Wo;
+    const double steps = (double)full * s.D1 / 16;  // of 16 K values, per tap
+    if (!P.natural && P.cols <= 32) {
+        pl.narrow_waves = P.rows <= 128 ? 2 : 4;
+        P.row_step = 64 * pl.narrow_waves;
+        P.row_tiles = ceil_div_i(P.rows, P.row_step);
+        P.col_step = 32;
+        P.col_tiles = 1;
+    } else {
+        choose_tile(P, steps, pl.tm, pl.tn);
+    }
     P.tiles = P.ntaps * s.D0 * P.row_tiles * P.col_tiles;
     P.out_elems = (long long)s.kernel_elems();
     P.d3_magic = s.D3 > 1 && (long long)s.M * s.D3 * s.D3 < (1LL << 32)
@@ -608,11 +818,19 @@ Wgrad32Plan make_plan(const ConvShape& s)
     // least 8 stages per workgroup.  A range of N*rect/nsplit pixels touches at most N/nsplit + 3
     // images: their bytes must stay below 2^31 (a lower bound on nsplit), and the partial sums
     // below 1 GiB (an upper bound).
-    long long per_cu = (long long)(160 * 1024 / lds_bytes_of(pl.tm, pl.tn));
-    const int by_registers = pl.tm + pl.tn <= 4 ? 8 : 4;
-    if (per_cu > by_registers) per_cu = by_registers;
+    long long per_cu, min_stages = 8;
+    if (pl.narrow_waves) {
+        const int kch = narrow_chunks(P.D1C, pl.narrow_waves);
+        per_cu = 160 * 1024 / narrow_lds_bytes(pl.narrow_waves, kch);
+        const int by_registers = (kch == 2 ? 12 : 8) / pl.narrow_waves;
+        if (per_cu > by_registers) per_cu = by_registers;
+        min_stages = kch == 2 ? 8 : 16;  // (of 4 chunks)
+    } else {
+        per_cu = 160 * 1024 / lds_bytes_of(pl.tm, pl.tn);
+        const int by_registers = pl.tm + pl.tn <= 4 ? 8 : 4;
+        if (per_cu > by_registers) per_cu = by_registers;
+    }
     const long long slots = 256 * per_cu;
-    const long long full = (long long)s.N * s.Ho * s.Wo;
     long long want = slots / P.tiles;
     if (want < 1) want = 1;
     // more rounds where a range would be longer than 3072 K values (the rounding of a sum grows with
@@ -621,7 +839,16 @@ Wgrad32Plan make_plan(const ConvShape& s)
     long long rounds = 1;
     while (rounds < 4 && full * s.D1 / (rounds * slots / P.tiles > 0 ? rounds * slots / P.tiles : 1) > 3072) ++rounds;
     if (rounds * slots / P.tiles > want) want = rounds * slots / P.tiles;
-    const long long min_pix = 8LL * SLOTS / P.D1C;
+    // fewer where the reduction would take longer than the ranges gain: a wave takes about 1 us per 16 K
+    // values, the reduction 0.04 us per range and 0.65 us per MB of partial sums (16x16 capsules, 3 -> 3
+    // channels, 1x1 window, 440 thousand K values: 2048 ranges 138 us, 819 91)
+    const double per_range = 0.04 + 0.65e-6 * 4.0 * (double)P.out_elems;
+    long long enough = (long long)std::sqrt(steps / per_range);
+    const long long precise = (full * s.D1 + 3071) / 3072;
+    if (enough < precise) enough = precise;
+    if (want > enough) want = enough;
+    if (want < 1) want = 1;
+    const long long min_pix = min_stages * SLOTS / P.D1C;
     if (want > (full + min_pix - 1) / min_pix) want = (full + min_pix - 1) / min_pix;
     if (want > 3072) want = 3072;
     while (want > 1 && (double)want * P.out_elems * 4 > (double)(1 << 30)) --want;
@@ -652,6 +879,25 @@ hipError_t launch_nat(const Wgrad32Params& P, hipStream_t stream)
     return P.D1C == 1 ? launch_one<CW, TM, TN, 1>(P, stream) : launch_one<CW, TM, TN, 2>(P, stream);
 }
 
+template <int CW, int NW, int KCH>
+hipError_t launch_narrow(const Wgrad32Params& P, hipStream_t stream)
+{
+    auto kern = wgrad32_narrow_kernel<CW, NW, KCH>;
+    constexpr int lds_bytes = narrow_lds_bytes(NW, KCH);
+    static std::atomic<unsigned long long> lds_set{0};
+    hipError_t err = set_dynamic_lds_once(reinterpret_cast<const void*>(kern), lds_bytes, lds_set);
+    if (err != hipSuccess) return err;
+    kern<<<dim3((unsigned)P.items), dim3(64 * NW), lds_bytes, stream>>>(P);
+    return hipGetLastError();
+}
+
+template <int CW>
+hipError_t launch_narrow(const Wgrad32Plan& pl, hipStream_t stream)
+{
+    if (pl.narrow_waves == 4) return launch_narrow<CW, 4, 4>(pl.P, stream);
+    return pl.P.D1C == 4 ? launch_narrow<CW, 2, 4>(pl.P, stream) : launch_narrow<CW, 2, 2>(pl.P, stream);
+}
+
 template <int CW, int TM>
 hipError_t launch_tn(const Wgrad32Plan& pl, hipStream_t stream)
 {
@@ -665,6 +911,7 @@ hipError_t launch_tn(const Wgrad32Plan& pl, hipStream_t stream)
 template <int CW>
 hipError_t launch_tm(const Wgrad32Plan& pl, hipStream_t stream)
 {
+    if (pl.narrow_waves) return launch_narrow<CW>(pl, stream);
     switch (pl.tm) {
         case 1: return launch_tn<CW, 1>(pl, stream);
         case 2: return launch_tn<CW, 2>(pl, stream);

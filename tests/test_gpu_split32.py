@@ -105,6 +105,18 @@ WGRAD_SHAPES = [
     (40, 20, 20, 4, 5, 1, 1, 1, 0, 1, 4, 4, 4),    # ranges of many stages
 ]
 
+# transposed copies and at most 32 columns: two and four waves per workgroup on the fp32 instructions, one,
+# two and four chunks of 3 and 4 floats per capsule column, 32 columns and fewer, stored by fours and one by one
+WGRAD_SHAPES += [
+    (3, 9, 7, 20, 8, 3, 3, 1, 1, 1, 6, 5, 4),       # 100 x 32
+    (2, 8, 9, 43, 5, 3, 3, 2, 1, 2, 3, 4, 6),       # 172 x 30, four waves
+    (2, 7, 7, 3, 2, 3, 2, 1, 1, 1, 12, 5, 7),       # 15 x 14, four chunks, two waves
+    (5, 6, 5, 70, 4, 2, 2, 1, 0, 1, 4, 4, 8),       # 280 x 32, two row tiles
+    (2, 6, 5, 9, 2, 3, 3, 1, 1, 1, 16, 16, 3),      # 144 x 6, four chunks, four waves
+    (2, 9, 9, 33, 1, 1, 1, 3, 0, 1, 8, 2, 1),       # 66 x 1
+    (40, 16, 16, 4, 3, 1, 1, 1, 0, 1, 4, 5, 4),     # ranges of many stages
+]
+
 
 def wgrad(w, x, g):
     return cc.conv_bwd_kernel(to_device(x, wl.FP32), to_device(g, wl.FP32), (w.kh, w.kw), w.stride,
