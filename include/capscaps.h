@@ -110,7 +110,9 @@ int capscaps_conv_fwd(const void* input, const void* kernel, void* out, int N, i
 /*
  * Same operator with symmetric zero padding `pad` and caller-provided scratch.
  * `workspace` must hold at least capscaps_conv_fwd_workspace_bytes(...) bytes for the same
- * arguments (it may be NULL when that is 0); too small -> CAPSCAPS_EWORKSPACE.
+ * arguments (it may be NULL when that is 0); too small -> CAPSCAPS_EWORKSPACE.  The size belongs to
+ * the library it was asked of: a program that keeps sizes asks again when the library changes (fp32
+ * layers of rows that are no multiple of 3 or 4 floats came to need up to 80 MiB where 1 was enough).
  */
 int capscaps_conv_fwd_ex(const void* input, const void* kernel, void* out, int N, int H, int W,
                          int C, int M, int kh, int kw, int stride, int pad, int D0, int D1, int D2,

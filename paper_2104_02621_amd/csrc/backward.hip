@@ -16,7 +16,7 @@
 // A stride s > 1 splits dI into s*s phases, the pixels with equal ((h+pad) mod s, (w+pad) mod s):
 // phase (a,b) is a stride-1 convolution of G with the window taps p = a, a+s, ..., q = b, b+s, ...
 // (flipped), whose output pixels lie s apart in dI.  Where every phase fits a tuned forward
-// kernel (16-bit, or fp32 with enough rows for its four-wave tiles) that kernel runs each phase
+// kernel (for the lane-per-row one: where it is the library's choice) that kernel runs each phase
 // with its own row and column padding and writes through an output stride: no multiplication
 // by zeros.  Otherwise the output gradient is spread out: G is copied into a zero
 // buffer of the stride-1 output extent (H+2*pad-kh+1 rows), pixel (x,y) at (x*s, y*s).  The
@@ -225,7 +225,7 @@ int phase_kernel(const ConvShape& f)
     if (f.dtype != 0 && mfma_tuned16_supported(f) &&
         (long long)f.N * f.Ho * f.Wo * f.D1 >= 256LL * 128)
         return 16;
-    // the lane-per-row kernel with its four-wave tiles and an unsplit K loop
+    // the lane-per-row kernel with an unsplit K loop (an output view takes no partial sums)
     if (mfma_dma32_supported(f) && igemm32_dma_preferred(f)) return 32;
     return 0;
 }

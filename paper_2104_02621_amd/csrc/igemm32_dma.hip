@@ -463,7 +463,7 @@ Dma32Plan igemm32_dma_plan(const ConvShape& s)
     // rows (4 .. 5 % faster than 4; 8-chunk stages, one workgroup per CU, 22 % slower), else 4
     // (vector capsules, whose consecutive rows are different pixels: a lane's 4 chunks are one
     // 64-byte run of memory; 11 .. 26 % faster than 2-chunk stages).  fp32: 4
-    const int KCH = (s.dtype != 0 && pl.nw == 4 && pl.tn >= 3 && P.D2C <= 2 && !(s.dtype != 0 && s.D1 <= 2)) ? 2 : 4;
+    const int KCH = (s.dtype != 0 && pl.nw == 4 && pl.tn >= 3 && P.D2C <= 2 && s.D1 > 2) ? 2 : 4;
     P.kch = KCH;
     const int groups = (KK + KCH - 1) / KCH;
     pl.kqp = groups * KCH;
@@ -543,16 +543,18 @@ bool igemm32_dma_preferred(const ConvShape& s)
     // 1.17x faster on whole column tiles (configs 3 and 5: 0.92 against 1.03 ms, 14.2 against
     // 16.6 ms) -- unless its 256-column tiles pad the columns much further than this kernel's
     // 128-column ones (320 or 384 columns: this kernel 14 % and 7 % faster)
-    if (s.dtype != 0 && igemm16_fast_preferred(s)) {
+    if (igemm16_fast_preferred(s)) {
         const long long cols = (long long)s.M * s.D3;
         const long long pad256 = (cols + 255) / 256 * 256, pad128 = (cols + 127) / 128 * 128;
         if (pad256 * 100 < pad128 * 115) return false;
     }
-    // Fewer tiles than CUs (128 .. 255 of 256 rows), and too few for the 256x256-tile kernel: with one-wave
-    // tiles or a split K loop, from 9e9 nominal FLOPs on (14x14
-    // images: 14.8 GFLOP of 4x4 capsules 51 against 60 us on the any-shape kernel, of 1x8 . 8x16 capsules
-    // 42 against 54, 16.7 GFLOP of 4x8 . 8x16 47 against 55, 59 GFLOP of 16x16 105 against 155; 7.4 GFLOP of
-    // 4x4 39 against 37)
+    // Fewer tiles than CUs (128 .. 255 of 256 rows), and too few for the 256x256-tile kernel's rule: with
+    // one-wave tiles (a split K loop where few row tiles meet many columns), from 9e9 nominal FLOPs on.  59
+    // random layers of 9 .. 240 GFLOP against the any-shape kernel: 0.98 .. 2.5 times as fast, median 1.4 (14x14
+    // images: 14.8 GFLOP of 4x4 capsules 51 against 60 us, of 1x8 . 8x16 capsules 42 against 54; 7.4 GFLOP of
+    // 4x4 39 against 37).  The line at 128 tiles is not where the gain ends: a layer of 32 (8x8 capsules, 9.7
+    // GFLOP) takes 65 us on the any-shape kernel, 50 on this one.  Square capsules of 8 and 16 rows run up to
+    // 1.5 times faster still where the 256x256-tile kernel is forced (237 GFLOP of 16x16: 403 us here, 271).
     const Dma32Plan pl = igemm32_dma_plan(s);
     if (pl.nw == 4 && pl.P.nsplit == 1) return true;
     const long long tiles = (long long)ceil_div_ll(pl.P.rows, 256) * pl.P.col_tiles * s.D0;

@@ -342,11 +342,9 @@ void igemm32_split_kernel(const Dma32Params P)
                 const unsigned b_after = b_next + B_BYTES == B_LDS + NBB * B_BYTES ? B_LDS : b_next + B_BYTES;
                 const unsigned b_fill = NBB == 3 ? b_after : b_next;
                 constexpr bool fill = has_step(pos + NBB - 1);
-                // parity of the operand buffer the stage's first column tile is in
-                constexpr int par = 0;
                 if constexpr (!AHEAD && NMMA > 0) {
 #pragma unroll
-                    for (int t = 0; t < 3; ++t) kb[par][t] = read_kernel(smem + b_cur, 0, t);
+                    for (int t = 0; t < 3; ++t) kb[0][t] = read_kernel(smem + b_cur, 0, t);
                 }
                 take_input(smem + a_next);
                 // side operations, dealt out over the gaps after the matrix instructions: the
