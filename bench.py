@@ -39,7 +39,7 @@ PEAK_ALU_TFLOPS = 78.6   # fp32 FMAs on the vector ALUs without the packed forms
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "hbm_traffic.json")
 KERNEL_SOURCES = {  # what the dominant kernel of each benchmark configuration is built from
     1: ["igemm_small.hip", "igemm_common.h", "conv_shape.h"],
-    2: ["igemm32_split.hip", "igemm32_dma.hip", "igemm_conv.hip", "igemm_common.h", "lds_dma.h", "conv_shape.h"],
+    2: ["igemm32_split.hip", "bf16_split.h", "igemm32_dma.hip", "igemm_conv.hip", "igemm_common.h", "lds_dma.h", "conv_shape.h"],
     3: ["igemm16_fast.hip", "igemm_conv.hip", "igemm_common.h", "lds_dma.h", "conv_shape.h"],
     4: ["igemm_small.hip", "igemm_common.h", "conv_shape.h"],
     5: ["igemm16_fast.hip", "igemm_conv.hip", "igemm_common.h", "lds_dma.h", "conv_shape.h"],
@@ -372,6 +372,37 @@ def bench_net5(args):
     print(json.dumps(result), flush=True)
 
 
+def on_bf16_instructions(w, op, path):
+    """Does this fp32 call take six bf16 matrix products for one fp32 product?  Forward: the lane-per-row
+    kernel, also on the written-out copy of the input (reported as PATH_MFMA).  Input gradient: the route of
+    the convolution it is (of the output gradient spread out to stride 1, or of the fully-connected
+    layer's 1x1 window).  Kernel gradient: capsule heights of 3 or 4 times 1, 2 or 4, but for
+    layers of at most 32 columns that are not square."""
+    from paper_2104_02621_amd import capscaps as cc
+    from paper_2104_02621_amd import workloads as wl
+    if w.dtype != wl.FP32:
+        return False
+    split = (cc.PATH_MFMA_TUNED32, cc.PATH_MFMA)
+    if op == "fwd":
+        if path not in (cc.PATH_AUTO, cc.PATH_MFMA):
+            return path == cc.PATH_MFMA_TUNED32
+        return cc.capscaps_select_path(w.N, w.H, w.W, w.C, w.M, w.kh, w.kw, w.stride, w.pad, w.D0, w.D1,
+                                       w.D2, w.D3, w.dtype) in split
+    if op == "bwd_input":
+        if w.pad == 0 and (w.kh, w.kw) == (w.H, w.W):
+            conv = (w.N, 1, 1, w.M, w.kh * w.kw * w.C, 1, 1, 1, 0)
+        elif w.kh == w.kw and w.pad <= w.kh - 1:
+            conv = (w.N, w.H + 2 * w.pad - w.kh + 1, w.W + 2 * w.pad - w.kw + 1, w.M, w.C, w.kh, w.kw, 1,
+                    w.kh - 1 - w.pad)
+        else:
+            return False
+        return cc.capscaps_select_path(*conv, w.D0, w.D1, w.D3, w.D2, w.dtype) in split
+    if op == "bwd_kernel":
+        square = w.D1 == w.D2 == w.D3
+        return w.D1 in (3, 4, 6, 8, 12, 16) and (square or w.M * w.D3 > 32)
+    return False
+
+
 def main():
     ap = argparse.ArgumentParser()
     ap.add_argument("--gpus", type=int, default=1)
@@ -557,9 +588,7 @@ def main():
     dname = wl.DTYPE_NAMES[w.dtype]
     achieved_tflops = flops_exact / (kernel_ms * 1e-3) / 1e12
     chosen = cc.capscaps_select_path(*shape) if path in (cc.PATH_AUTO, cc.PATH_MFMA) else path
-    # fp32 layers on the lane-per-row kernel (and their gradients) take six bf16 matrix products for
-    # one fp32 product
-    split32 = w.dtype == wl.FP32 and cc.capscaps_select_path(*shape) == 5 and path != cc.PATH_DIRECT
+    split32 = on_bf16_instructions(w, args.op, path)
     peak = PEAK_TFLOPS["bf16"] / 6 if split32 else PEAK_TFLOPS[dname]
     result = {
         "metric": ("capsule-conv useful GFLOP/s at 1 GPU + % of MFMA roofline" if args.op == "fwd"
