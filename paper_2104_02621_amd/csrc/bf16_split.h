@@ -1,6 +1,7 @@
 // Internal: fp32 values as the sum of three bf16 values, 2^23 x = x1 + x2 + x3, each the rounding
 // of what the ones before leave over, for the kernels that contract fp32 operands on the bf16 matrix
-// instructions.  3 x 8 significant bits and the signs of the remainders hold fp32's 24; the factor
+// instructions (Henry, Tang and Heinecke, "Leveraging the bfloat16 Artificial Intelligence Datatype For
+// Higher-Precision Computations", 2019).  3 x 8 significant bits and the signs of the remainders hold fp32's 24; the factor
 // makes that hold for every magnitude: fp32's smallest step, 2^-149, becomes 2^-126, bf16's smallest
 // normal value, so no term of any value, subnormal ones included, is cut off at the bottom of
 // bf16's range.  (Unscaled, x3 of a value below 2^-110 would be, an absolute loss that the other
@@ -41,7 +42,12 @@ constexpr float SPLIT_SCALE = 0x1p23f;     // of each operand
 constexpr float SPLIT_UNSCALE = 0x1p-46f;  // ... and of the sums of their products, back
 
 // Sums over split values that have to be taken again on the fp32 instructions: those that are not
-// finite (an infinity, a NaN, a value or a sum that the scale factors take out of range).
+// finite (an infinity, a NaN, a value or a sum that the scale factors take out of range).  A workgroup
+// takes all of its sums again, one stage at a time, which is the one case where the time of a call
+// depends on its data: 32 -> 32 channels of 3x3x3 capsules, N = 64, 32x32, with a NaN in every tile 1.5
+// instead of 0.57 ms forward, 1.6 instead of 0.67 ms kernel gradient; one infinity in the input reaches a
+// few tiles (forward 0.57 ms) but a whole range of every tap's pixels (kernel gradient 0.86 ms).
+// Values of 1e-37: no difference.
 struct SplitCheck {
     float poison = 0.f;
     __device__ __forceinline__ void take(const float16v& acc)
