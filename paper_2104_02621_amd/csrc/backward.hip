@@ -206,6 +206,7 @@ ConvShape bwd_input_phase_shape(const ConvShape& s, const PhaseDim& ph, const Ph
     ConvShape f{s.N, s.Ho, s.Wo, s.M, s.C, ph.taps, pw.taps, 1, ph.taps - 1 - ph.lo,
                 s.D0, s.D1, s.D3, s.D2, ph.count, pw.count, s.dtype};
     f.out16 = s.out16;
+    f.in_gradient = true;
     f.pad_w_set = true;
     f.pad_w = pw.taps - 1 - pw.lo;
     f.out_view = true;
@@ -277,6 +278,7 @@ ConvShape bwd_input_fc_shape(const ConvShape& s)
     ConvShape f{s.N, 1, 1, s.M, s.kh * s.kw * s.C, 1, 1, 1, 0, s.D0, s.D1, s.D3, s.D2, 1, 1,
                 s.dtype};
     f.out16 = s.out16;
+    f.in_gradient = true;
     return f;
 }
 // dI as a forward convolution of the (spread-out) G with the flipped, transposed kernel
@@ -287,6 +289,7 @@ ConvShape bwd_input_conv_shape(const ConvShape& s)
     ConvShape f{s.N, spread_h(s), spread_w(s), s.M, s.C, s.kh, s.kw, 1, s.kh - 1 - s.pad,
                 s.D0, s.D1, s.D3, s.D2, s.H, s.W, s.dtype};
     f.out16 = s.out16;
+    f.in_gradient = true;
     return f;
 }
 // dK as a forward convolution of the re-laid-out input with the (spread-out) output gradient

@@ -51,6 +51,10 @@ struct ConvShape {
     // m*k_sm + d0*k_sd0 + d2*k_sd2 + d3*k_sd3 of `kernel` instead of densely (strides may be
     // negative: a flipped window).
     bool kernel_view = false;
+    // in_gradient: an input gradient run as this convolution, whose kernel tensor lies transposed in
+    // memory (for the choice of the kernel; set also where kernel_view is not, so that the scratch
+    // asked for is that of the kernel that runs)
+    bool in_gradient = false;
     // in_paired (lane-per-row kernel, 16-bit capsule rows of 4 elements): `input` already is the
     // channel-paired copy [pixel][c/2][d0][d1][c%2][d2] (a caller that runs several convolutions
     // on one input pairs it once)

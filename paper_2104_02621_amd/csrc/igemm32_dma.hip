@@ -24,6 +24,8 @@
 // every offset and copy of this kernel stays as it is.
 #include <hip/hip_runtime.h>
 
+#include <cmath>
+
 #include "igemm_common.h"
 #include "lds_dma.h"
 
@@ -505,6 +507,32 @@ Dma32Plan igemm32_dma_plan(const ConvShape& s)
     return pl;
 }
 
+namespace {
+
+// Estimated times of an fp32 layer, us, least-squares fits over 730 random layers of 0.3 .. 8 GFLOP (most
+// within 15 % of the measured time): three launches, the stages of the rounds of tiles, partial sums and the
+// packed kernel written and read ...
+double split_us(const Dma32Plan& pl)
+{
+    const double rounds = ceil((double)pl.blocks / (pl.nw == 4 ? 512 : 1024));
+    const int stages = pl.P.nsplit > 1 ? pl.P.stages_per_split : pl.P.nstages;
+    return 12 + (pl.P.nsplit > 1 ? 4.6 : 0) + (0.27 * pl.tn + 0.20) * stages * rounds +
+           0.48e-6 * (double)pl.partial_bytes + 0.45e-6 * (double)pl.repack_bytes;
+}
+// ... and the kernel it would run on otherwise: the FLOPs of its tiles at the rate its input loads allow
+// (16 bytes; 8 for rows of 6 floats; element by element for rows of 3)
+double other_fp32_us(const ConvShape& s)
+{
+    const bool small = igemm_small_preferred(s);
+    const long long rows = (s.pixels() * s.D1 + 63) / 64 * 64, unit = small ? 16 : 64;
+    const long long cols = ((long long)s.M * s.D3 + unit - 1) / unit * unit;
+    const double gflop = 2e-9 * (double)rows * (double)cols * s.D0 * s.kh * s.kw * s.C * s.D2;
+    if (small) return 7.5 + gflop * (s.D2 == 3 ? 33 : s.D2 == 6 ? 28 : 14.4);
+    return 12 + gflop * (s.D2 == 3 ? 21 : s.D2 == 6 ? 18 : 13.6);
+}
+
+}  // namespace
+
 bool igemm32_dma_fills_chip(const ConvShape& s)
 {
     const Dma32Plan pl = igemm32_dma_plan(s);
@@ -520,24 +548,22 @@ bool igemm32_dma_preferred(const ConvShape& s)
                               (double)(((long long)s.M * s.D3 + 29) / 30) * s.D0;
     if (most_tiles < 128 && !(s.dtype == 0 && flops >= 5e8)) return false;
     if (!igemm32_dma_eligible(s)) return false;
-    // fp32: where its four-wave tiles fill the chip; with a split K loop or one-wave tiles where the
-    // FLOPs are worth the two launches more and the packed kernel and partial sums these write and read
-    // (7.4 GFLOP of 4x4 capsules 72 against 104 us on the small-problem kernel, 3x3x3 capsules of 1.5 GFLOP
-    // 36 against 72).  Capsule rows of 3 floats, which the other kernels load element by element, from 7e8
-    // FLOPs on and 10 more per byte, of 6 floats (8-byte loads there) from 1.3e9 and 30 more, others from
-    // 2.5e9 and 30 more.  Of 600 random layers of 0.3 .. 8 GFLOP: 3 of those taken are slower than on the
-    // other kernels, by up to 14 %; 40 left to the others would gain more than 3 %.  By the FLOPs alone, from
-    // 5e8 (3k floats) and 3e9, 70 were slower, the worst by 3.5 times (4 images through a fully-connected
-    // layer of 12x12 capsules).  Layers of few columns, else on the wavefront-level path, from 5e8 (1.1 .. 20 times
-    // faster).
+    // fp32: where its four-wave tiles fill the chip, and from 5e8 FLOPs on where it is estimated to be the
+    // faster one (7.4 GFLOP of 4x4 capsules 72 against 104 us on the small-problem kernel; 3x3x3 capsules of 1.5
+    // GFLOP 36 against 72; 4 images through a fully-connected layer of 12x12 capsules 70 against 20).  Of 730
+    // random layers of 0.3 .. 8 GFLOP, of those taken 17 are slower than on the other kernels, by up to
+    // 28 % (3 .. 10 us), 37 left to the others would gain more than 3 %; with FLOPs alone, from 5e8 (3k
+    // floats) and 3e9, 82 and 56.  Layers of few columns, else on the wavefront-level path, are 1.1 .. 20 times
+    // faster from 5e8 on.  Input gradients read the kernel tensor transposed, which the small-problem kernel
+    // does with strides: from 5e8 and 3e9 FLOPs (5x9x6 pixels, 48 -> 8 channels of 12x12 capsules spread out
+    // from stride 2: 53 against 166 us), but for those of few rows (a fully-connected layer's).
     if (s.dtype == 0) {
         const Dma32Plan pl = igemm32_dma_plan(s);
         if (pl.nw == 4 && (long long)pl.P.row_tiles * pl.P.col_tiles * s.D0 >= 256) return true;
-        if (few_columns(s)) return flops >= 5e8;
-        const double bytes = (double)pl.partial_bytes + (double)pl.repack_bytes;
-        return s.D2 == 3   ? flops >= 7e8 + 10.0 * bytes
-               : s.D2 == 6 ? flops >= 1.3e9 + 30.0 * bytes
-                           : flops >= 2.5e9 + 30.0 * bytes;
+        if (flops < 5e8) return false;
+        if (few_columns(s)) return true;
+        if (s.in_gradient && pl.P.rows >= 256 && flops >= (pl.cw == 3 ? 5e8 : 3e9)) return true;
+        return split_us(pl) < 0.95 * other_fp32_us(s);
     }
     // 16-bit: square capsules of 8 or 16 rows belong to the 256x256-tile kernel, which is 1.12 ..
     // 1.17x faster on whole column tiles (configs 3 and 5: 0.92 against 1.03 ms, 14.2 against

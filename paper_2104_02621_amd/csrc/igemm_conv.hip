@@ -603,11 +603,12 @@ struct RechunkPlan {
     size_t bytes() const { return in_bytes + ((repack_bytes + 255) & ~(size_t)255) + partial_bytes; }
 };
 
-// From 1.2e9 FLOPs on (5 GFLOP: 70 us against 109 on the small-problem kernel and 161 on this one), and
-// 50 more per byte of the written-out input, 10 per byte of packed kernel and partial sums: that is
-// the time those take.  Of 200 random layers of 1.2 .. 30 GFLOP 18 were slower by up to 40 % without
-// the bytes (1x1 windows above all: 34 -> 59 channels of 6x5 . 5x4 capsules, 0.4 GB of input, 368
-// against 221 us), 2 by up to 11 % with them; 22 that gained 5 .. 150 % stay behind.
+// From 1.2e9 FLOPs on (5 GFLOP: 70 us against 109 on the small-problem kernel and 161 on this one), and 36
+// per byte of the written-out input, below which writing and reading it takes the time (1x1 windows above
+// all: 34 -> 59 channels of 6x5 . 5x4 capsules, 0.4 GB of input, 368 against 221 us).  Of 200 random layers
+// of 1.2 .. 30 GFLOP, of those taken 8 are slower than otherwise, by up to 15 %, 5 left would gain more than
+// 3 %; by the FLOPs alone 18 were slower, by up to 40 %.  Input gradients (kernel tensor read transposed): by the
+// FLOPs alone.
 RechunkPlan rechunk_plan(const ConvShape& s)
 {
     RechunkPlan rp{};
@@ -620,7 +621,7 @@ RechunkPlan rechunk_plan(const ConvShape& s)
     f.D2 = 4;
     f.N = 1;
     const size_t img = f.in_elems() * 4;
-    if (img > RECHUNK_BYTES) return rp;
+    if (img > RECHUNK_BYTES || (!s.in_gradient && flops < 36.0 * (double)img * s.N)) return rp;
     const int most = (int)(RECHUNK_BYTES / img), parts = ceil_div(s.N, most < s.N ? most : s.N);
     rp.images = ceil_div(s.N, parts);
     for (int n : {rp.images, s.N % rp.images}) {  // a whole part and the last one
@@ -635,8 +636,7 @@ RechunkPlan rechunk_plan(const ConvShape& s)
     f.N = rp.images;
     rp.layer = f;
     rp.in_bytes = (img * rp.images + 255) & ~(size_t)255;
-    rp.ok = rp.bytes() <= RECHUNK_TOTAL &&
-            flops >= 1.2e9 + 50.0 * (double)img * s.N + 10.0 * ((double)rp.partial_bytes * parts + (double)rp.repack_bytes);
+    rp.ok = rp.bytes() <= RECHUNK_TOTAL;
     return rp;
 }
 

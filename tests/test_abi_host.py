@@ -254,8 +254,9 @@ def test_static_scratch_entry_point_checks_before_touching_the_gpu():
 
 
 def test_fp32_layers_that_split_bf16_terms_do_not_pay_for():
-    """The lane-per-row kernel is left to layers whose FLOPs are worth packing the kernel tensor, partial
-    sums and, for rows no copy fits, a copy of the input (each of these measured on both sides)."""
+    """The lane-per-row kernel is left to layers it is estimated to be faster on, what packing the kernel
+    tensor, partial sums and, for rows no copy fits, a copy of the input take counted in (each of these
+    measured on both sides)."""
     def path(*shape):
         return cc.capscaps_select_path(*shape, cc.FP32)
     # 12x12 capsules: 4 images through a fully-connected layer 20 against 70 us; 5.5 GFLOP 88 against 64
@@ -267,6 +268,8 @@ def test_fp32_layers_that_split_bf16_terms_do_not_pay_for():
     # 6x5 . 5x4 capsules: a 1x1 window over 0.4 GB of input 221 against 368; a 3x3 one 404 against 221
     assert path(170, 15, 39, 34, 59, 1, 1, 2, 0, 1, 6, 5, 4) == cc.PATH_MFMA_GENERIC
     assert path(42, 37, 37, 16, 56, 3, 3, 2, 0, 1, 6, 5, 4) == cc.PATH_MFMA
+    # 2-float rows and 9 columns at stride 2, 38 MB of input: 138 against 59
+    assert path(20, 27, 14, 58, 2, 6, 6, 2, 3, 1, 5, 2, 9) == cc.PATH_MFMA
     # at most 8 columns and rows of 3: the wavefront-level path below 5e8 FLOPs, 20 times slower above
     assert path(4, 29, 29, 16, 2, 5, 5, 1, 2, 3, 3, 3, 3) == cc.PATH_DIRECT
     assert path(8, 29, 29, 16, 2, 5, 5, 1, 2, 3, 3, 3, 3) == cc.PATH_MFMA_TUNED32

@@ -82,8 +82,9 @@ def test_static_scratch_rejects_what_does_not_fit():
 
 
 def test_static_scratch_holds_a_split_fp32_kernel():
-    """61 MiB of fp32 kernel values are packed as 91 MiB of bf16 terms: the limit counts the values."""
-    w = wl.Workload("static_split", wl.FP32, 2, 3, 3, 256, 256, 3, 3, 1, 1, 3, 3, 3, 3, "normal", "normal", 0.1,
+    """56 MiB of fp32 kernel values are packed as bf16 terms, 91 MiB with the partial sums: the limit counts
+    the values."""
+    w = wl.Workload("static_split", wl.FP32, 8, 3, 3, 256, 128, 5, 5, 1, 2, 1, 1, 3, 6, "normal", "normal", 0.1,
                     907, 908)
     args = shape_args(w)
     assert cc.capscaps_select_path(*args) == cc.PATH_MFMA_TUNED32
@@ -102,9 +103,9 @@ def test_static_scratch_without_the_paired_input(dtype):
 
 
 def test_static_scratch_without_the_split_kernel():
-    """An fp32 layer whose kernel tensor in bf16 terms and partial sums do not fit the array (131 MiB):
-    its repacked fp32 values do not either (84 MiB), so the kernel that reads the tensor in place runs."""
-    w = wl.Workload("static_lean", wl.FP32, 1, 4, 4, 256, 128, 5, 5, 1, 2, 3, 3, 3, 3, "normal", "normal", 0.1,
+    """An fp32 layer whose kernel tensor in bf16 terms and partial sums do not fit the array (144 MiB):
+    its repacked fp32 values do not either (88 MiB), so the kernel that reads the tensor in place runs."""
+    w = wl.Workload("static_lean", wl.FP32, 8, 3, 3, 256, 200, 5, 5, 1, 2, 1, 1, 3, 6, "normal", "normal", 0.1,
                     912, 913)
     _runs_on_a_leaner_kernel(w, cc.PATH_MFMA_SMALL)
 
