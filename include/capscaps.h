@@ -183,7 +183,9 @@ size_t capscaps_conv_fwd_workspace_bytes(int N, int H, int W, int C, int M, int 
  * the CAPSCAPS_PATH_MFMA_* kernel variants, or CAPSCAPS_PATH_MFMA for large fp32 layers of capsule
  * rows that CAPSCAPS_PATH_MFMA_TUNED32 does not take: that variant on a copy of the input in
  * `workspace`, its rows in runs of four K values), or a negative status for invalid arguments.
- * Host-only.
+ * 16-bit layers below the tuned variants' sizes run on a kernel of 64 .. 128-row tiles that reads the
+ * kernel tensor in place; it has no code of its own: the variant that the layer falls to otherwise
+ * (and that takes it when forced) is reported, and its workspace asked for.  Host-only.
  */
 int capscaps_select_path(int N, int H, int W, int C, int M, int kh, int kw, int stride, int pad,
                          int D0, int D1, int D2, int D3, int dtype);
@@ -204,7 +206,8 @@ int capscaps_select_path(int N, int H, int W, int C, int M, int kh, int kw, int 
  * The shape arguments are those of the forward call whose gradients are wanted.  The input
  * gradient is itself a capsule convolution of `dout` with the flipped, transposed kernel and runs
  * on the forward kernels (a stride s > 1 as s*s interleaved stride-1 convolutions where every one
- * of them fits a tuned kernel (see CAPSCAPS_PATH_MFMA_TUNED16 / _TUNED32) and has enough pixels,
+ * of them fits a tuned kernel (see CAPSCAPS_PATH_MFMA_TUNED16 / _TUNED32) and has enough pixels, or, for
+ * 16-bit types, in one launch of the small-tile kernel,
  * else on `dout` spread out to stride 1 in `workspace`); the kernel gradient runs on dedicated
  * matrix-core kernels for 16-bit capsules of 8 or 16 rows (4-row ones that are 4x4 with even
  * channel counts, and ones of 1, 2 or 4 rows whose widths are multiples of 8) and fp32

@@ -235,6 +235,36 @@ int phase_kernel(const ConvShape& f)
 // kernel read the output gradient with its channels paired; it is paired once for all of them
 bool phases_pair_dout(const ConvShape& s) { return s.dtype != 0 && s.D3 == 4 && s.M % 2 == 0; }
 
+// The input gradient as phases in one launch of the small-tile 16-bit kernel (any window, padding and
+// stride up to 4; a stride of 1 is one phase).  Returns their number, 0 if there are too many.
+constexpr int kMaxPhases = 16;
+int bwd_input_phases(const ConvShape& s, ConvShape (&f)[kMaxPhases])
+{
+    if (s.dtype == 0 || s.stride > 4) return 0;
+    const long long sD2 = s.D3, sD0 = (long long)s.D2 * s.D3, sM = sD0 * s.D0, sC = sM * s.M,
+                    sQ = sC * s.C, sP = sQ * s.kw;
+    int n = 0;
+    for (int a = 0; a < s.stride; ++a)
+        for (int b = 0; b < s.stride; ++b) {
+            const PhaseDim ph = phase_dim(s.H, s.kh, s.stride, s.pad, a);
+            const PhaseDim pw = phase_dim(s.W, s.kw, s.stride, s.pad, b);
+            if (ph.count == 0 || pw.count == 0) continue;
+            ConvShape& g = f[n++];
+            g = bwd_input_phase_shape(s, ph, pw, a, b);
+            g.kernel_view = true;
+            g.k_base = (long long)(a + s.stride * (ph.taps - 1)) * sP +
+                       (long long)(b + s.stride * (pw.taps - 1)) * sQ;
+            g.k_sp = -s.stride * sP;
+            g.k_sq = -s.stride * sQ;
+            g.k_sc = sM;
+            g.k_sm = sC;
+            g.k_sd0 = sD0;
+            g.k_sd2 = 1;
+            g.k_sd3 = sD2;
+        }
+    return n;
+}
+
 // every phase that has both pixels and taps must fit a tuned kernel and fill the chip
 bool bwd_input_as_phases(const ConvShape& s)
 {
@@ -283,6 +313,24 @@ ConvShape bwd_input_fc_shape(const ConvShape& s)
 }
 // dI as a forward convolution of the (spread-out) G with the flipped, transposed kernel
 bool bwd_input_as_conv(const ConvShape& s) { return s.kh == s.kw && s.pad <= s.kh - 1; }
+// Strided layers, and the windows and paddings that the convolution form does not cover, on the small-tile
+// kernel: always where `dout` would be spread out (s^2 times the work) or gathered element by element
+// (40 random layers: 0.2 .. 0.95 times the time), else
+// where one launch is estimated 30 % faster than the phases' launches on the tuned kernels.
+// Stride 1 otherwise is a convolution whose kernel the forward pass's rules pick.
+bool bwd_input_on_mid(const ConvShape& s, const ConvShape* f, int n, size_t room)
+{
+    if (!igemm_mid_eligible(f, n, s.kernel_elems())) return false;
+    if (s.stride == 1 && bwd_input_as_conv(s)) return false;
+    if (!bwd_input_as_phases(s)) return true;
+    double other = 0;
+    for (int i = 0; i < n; ++i) {
+        if (f[i].kh * f[i].kw == 0) continue;
+        other += igemm16_tuned_us(f[i], phase_kernel(f[i]) == 16 ? MfmaKernel::Tuned16 : MfmaKernel::Dma32);
+    }
+    return igemm_mid_us(f, n, s.kernel_elems(), room) < 0.7 * other;
+}
+
 ConvShape bwd_input_conv_shape(const ConvShape& s)
 {
     // input Gs [N][Hs][Ws][M][D0][D1][D3], kernel K' [kh][kw][M][C][D0][D3][D2] -> dI [N][H][W][C][D0][D1][D2]
@@ -364,6 +412,14 @@ int launch_bwd_input(const ConvShape& s, const void* dout, const void* kernel, f
         hipError_t err = launch_permute(kernel, ws, pm, eb, stream);
         if (err != hipSuccess) return status_from_hip(err);
         return forward_auto(f, dout, ws, din, ws + used, workspace_bytes - used, stream);
+    }
+    {
+        ConvShape f[kMaxPhases];
+        const int n = bwd_input_phases(s, f);
+        const size_t room = bwd_input_workspace_bytes(s);
+        if (n > 0 && bwd_input_on_mid(s, f, n, room))
+            return status_from_hip(launch_igemm_mid(f, n, s.kernel_elems(), dout, kernel, din, workspace,
+                                                      room, stream));
     }
     if (bwd_input_as_phases(s)) {
         char* ws = static_cast<char*>(workspace);

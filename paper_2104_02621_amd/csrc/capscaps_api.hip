@@ -5,7 +5,7 @@
 #include <mutex>
 
 #include "../../include/capscaps.h"
-#include "conv_shape.h"
+#include "igemm_common.h"
 
 using capscaps::ConvShape;
 
@@ -62,7 +62,15 @@ int fill_shape(ConvShape& s, int N, int H, int W, int C, int M, int kh, int kw, 
 struct Choice {
     int path;
     capscaps::MfmaKernel kernel;
+    // 16-bit: the layer runs on the small-tile kernel (igemm_mid.hip) instead.  Path, scratch and
+    // what is refused for lack of it stay those of `kernel`; the partial sums fit in that scratch.
+    bool mid = false;
 };
+bool runs_mid(const ConvShape& s, capscaps::MfmaKernel kernel)
+{
+    return s.dtype != CAPSCAPS_FP32 &&
+           capscaps::igemm_mid_preferred(s, kernel, capscaps::mfma_kernel_workspace_bytes(s, kernel));
+}
 Choice choose(const ConvShape& s)
 {
     const Choice direct = {CAPSCAPS_PATH_DIRECT, capscaps::MfmaKernel::Auto};
@@ -71,6 +79,7 @@ Choice choose(const ConvShape& s)
     if (kdim <= 24) return direct;
     const double flops = 2.0 * (double)s.out_elems() * (double)kdim;
     const capscaps::MfmaKernel kernel = capscaps::mfma_auto_kernel(s);
+    const bool mid = runs_mid(s, kernel);
     // (fp32 layers from 5e8 FLOPs on: the lane-per-row kernel where it is the choice, which contracts on
     // the bf16 matrix instructions -- 6x5 . 5x4 capsules, 8 columns, 9.9 GFLOP 399 against 1473 us;
     // 3x3x3 capsules, 6 columns, 0.5 GFLOP 32 against 153 us)
@@ -78,12 +87,12 @@ Choice choose(const ConvShape& s)
                          (kernel == capscaps::MfmaKernel::Dma32 || kernel == capscaps::MfmaKernel::Rechunk);
     if (!split32 && few_columns(s) && flops >= 5e7 && capscaps::wave_conv_eligible(s)) return direct;
     switch (kernel) {
-        case capscaps::MfmaKernel::Tuned16: return {CAPSCAPS_PATH_MFMA_TUNED16, kernel};
-        case capscaps::MfmaKernel::Dma32: return {CAPSCAPS_PATH_MFMA_TUNED32, kernel};
-        case capscaps::MfmaKernel::Small: return {CAPSCAPS_PATH_MFMA_SMALL, kernel};
+        case capscaps::MfmaKernel::Tuned16: return {CAPSCAPS_PATH_MFMA_TUNED16, kernel, mid};
+        case capscaps::MfmaKernel::Dma32: return {CAPSCAPS_PATH_MFMA_TUNED32, kernel, mid};
+        case capscaps::MfmaKernel::Small: return {CAPSCAPS_PATH_MFMA_SMALL, kernel, mid};
         // (the lane-per-row kernel again, but on a copy of the input that only the library's choice makes)
         case capscaps::MfmaKernel::Rechunk: return {CAPSCAPS_PATH_MFMA, kernel};
-        default: return {CAPSCAPS_PATH_MFMA_GENERIC, kernel};
+        default: return {CAPSCAPS_PATH_MFMA_GENERIC, kernel, mid};
     }
 }
 size_t scratch_bytes(const ConvShape& s, const Choice& c)
@@ -161,6 +170,9 @@ int run_choice(const void* input, const void* kernel, void* out, const ConvShape
     const size_t need = scratch_bytes(s, c);
     if (need > 0 && (workspace == nullptr || workspace_bytes < need)) return CAPSCAPS_EWORKSPACE;
     if (need > 0 && misaligned(workspace)) return CAPSCAPS_EINVAL;
+    if (c.mid)
+        return hip_status(capscaps::launch_igemm_mid(&s, 1, s.kernel_elems(), input, kernel, dst,
+                                                       workspace, need, stream));
     return hip_status(capscaps::launch_mfma(s, input, kernel, dst, workspace, stream, c.kernel));
 }
 
@@ -176,9 +188,11 @@ int run(const void* input, const void* kernel, void* out, const ConvShape& s, in
                path == CAPSCAPS_PATH_MFMA_TUNED16 || path == CAPSCAPS_PATH_MFMA_TUNED32 ||
                path == CAPSCAPS_PATH_MFMA_SMALL) {
         if (!capscaps::mfma_supported(s)) return CAPSCAPS_EUNSUPPORTED;
-        if (path == CAPSCAPS_PATH_MFMA)
-            return run_choice(input, kernel, out, s, {path, capscaps::mfma_auto_kernel(s)}, workspace,
-                              workspace_bytes, stream);
+        if (path == CAPSCAPS_PATH_MFMA) {
+            const capscaps::MfmaKernel own = capscaps::mfma_auto_kernel(s);
+            return run_choice(input, kernel, out, s,
+                              {path, own, runs_mid(s, own)}, workspace, workspace_bytes, stream);
+        }
         if (path == CAPSCAPS_PATH_MFMA_TUNED16 && !capscaps::mfma_tuned16_supported(s))
             return CAPSCAPS_EUNSUPPORTED;
         if (path == CAPSCAPS_PATH_MFMA_TUNED32 && !capscaps::mfma_dma32_supported(s))
