@@ -549,6 +549,11 @@ int launch_bwd_input(const ConvShape& s, const void* dout, const void* kernel, f
 int launch_bwd_kernel(const ConvShape& s, const void* input, const void* dout, float* dkernel,
                       void* workspace, size_t workspace_bytes, hipStream_t stream)
 {
+    if (s.dtype != 0) {
+        const size_t room = bwd_kernel_workspace_bytes(s);
+        if (wgrad_mid_preferred(s, room))
+            return status_from_hip(launch_wgrad_mid(s, input, dout, dkernel, workspace, room, stream));
+    }
     if (wgrad16_eligible(s))
         return status_from_hip(launch_wgrad16(s, input, dout, dkernel, workspace, stream));
     if (wgrad32_eligible(s))

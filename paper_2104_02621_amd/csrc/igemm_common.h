@@ -227,6 +227,11 @@ bool wgrad16_eligible(const ConvShape& s);
 size_t wgrad16_workspace_bytes(const ConvShape& s);
 hipError_t launch_wgrad16(const ConvShape& s, const void* input, const void* dout, float* dkernel,
                           void* workspace, hipStream_t stream);
+// ... and for layers below its tiles' sizes (wgrad_mid.hip); partial sums take at most `room` bytes
+bool wgrad_mid_eligible(const ConvShape& s);
+bool wgrad_mid_preferred(const ConvShape& s, size_t room);  // ... and is the library's choice
+hipError_t launch_wgrad_mid(const ConvShape& s, const void* input, const void* dout, float* dkernel,
+                              void* workspace, size_t room, hipStream_t stream);
 // ... and for fp32 on the bf16 instructions, capsule heights D1 of 3, 4, 6, 8, 12 or 16 floats
 // (wgrad32.hip).
 bool wgrad32_eligible(const ConvShape& s);

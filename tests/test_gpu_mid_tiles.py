@@ -67,3 +67,21 @@ def test_small_tiles_on_integers(shape, dtype):
             # sums of integers are exact in fp32 (|sum| < 2^24); the 16-bit results are those, rounded once
             want = torch.from_numpy(refs[name].astype(np.float32)).to(t.dtype)
             assert torch.equal(t.cpu(), want.reshape(t.shape)), (w.name, name, out16)
+
+
+@pytest.mark.parametrize("caps", [(1, 4, 4, 4), (1, 8, 8, 8), (1, 1, 8, 16)], ids=str)
+def test_infinities_stay_with_the_taps_that_meet_them(caps):
+    """An infinite output gradient at a corner pixel reaches only the kernel gradient's taps that lie inside the
+    image there: it never meets the zeros of the padding."""
+    import torch
+    w = _layer((2, 6, 6, 3, 4, 3, 3, 1, 1, caps), wl.BF16)
+    i32, k32, g32 = _data(w)
+    i32 = np.abs(i32) + 1
+    g32[0, 0, 0] = np.inf
+    got = cc.conv_bwd_kernel(_gpu(i32, wl.BF16), _gpu(g32, wl.BF16), (3, 3), 1, 1)
+    torch.cuda.synchronize()
+    got = got.cpu().numpy()
+    inside = np.zeros((3, 3), bool)
+    inside[1:, 1:] = True
+    assert np.isposinf(got[inside]).all()
+    assert np.isfinite(got[~inside]).all()
