@@ -29,6 +29,7 @@
 #include <hip/hip_fp16.h>
 
 #include "igemm_common.h"
+#include "mid_tiles.h"
 
 namespace capscaps {
 namespace {
@@ -240,7 +241,7 @@ bool phases_pair_dout(const ConvShape& s) { return s.dtype != 0 && s.D3 == 4 && 
 constexpr int kMaxPhases = 16;
 int bwd_input_phases(const ConvShape& s, ConvShape (&f)[kMaxPhases])
 {
-    if (s.dtype == 0 || s.stride > 4) return 0;
+    if (s.stride > 4) return 0;
     const long long sD2 = s.D3, sD0 = (long long)s.D2 * s.D3, sM = sD0 * s.D0, sC = sM * s.M,
                     sQ = sC * s.C, sP = sQ * s.kw;
     int n = 0;
@@ -313,24 +314,6 @@ ConvShape bwd_input_fc_shape(const ConvShape& s)
 }
 // dI as a forward convolution of the (spread-out) G with the flipped, transposed kernel
 bool bwd_input_as_conv(const ConvShape& s) { return s.kh == s.kw && s.pad <= s.kh - 1; }
-// Strided layers, and the windows and paddings that the convolution form does not cover, on the small-tile
-// kernel: always where `dout` would be spread out (s^2 times the work) or gathered element by element
-// (40 random layers: 0.2 .. 0.95 times the time), else
-// where one launch is estimated 30 % faster than the phases' launches on the tuned kernels.
-// Stride 1 otherwise is a convolution whose kernel the forward pass's rules pick.
-bool bwd_input_on_mid(const ConvShape& s, const ConvShape* f, int n, size_t room)
-{
-    if (!igemm_mid_eligible(f, n, s.kernel_elems())) return false;
-    if (s.stride == 1 && bwd_input_as_conv(s)) return false;
-    if (!bwd_input_as_phases(s)) return true;
-    double other = 0;
-    for (int i = 0; i < n; ++i) {
-        if (f[i].kh * f[i].kw == 0) continue;
-        other += igemm16_tuned_us(f[i], phase_kernel(f[i]) == 16 ? MfmaKernel::Tuned16 : MfmaKernel::Dma32);
-    }
-    return igemm_mid_us(f, n, s.kernel_elems(), room) < 0.7 * other;
-}
-
 ConvShape bwd_input_conv_shape(const ConvShape& s)
 {
     // input Gs [N][Hs][Ws][M][D0][D1][D3], kernel K' [kh][kw][M][C][D0][D3][D2] -> dI [N][H][W][C][D0][D1][D2]
@@ -340,6 +323,42 @@ ConvShape bwd_input_conv_shape(const ConvShape& s)
     f.in_gradient = true;
     return f;
 }
+// fp32: against the estimates of what would run, the spread-out gradient's zeros counted in (20 random strided
+// layers: 19 of them 0.15 .. 0.85 times the time, one whose phases fill the bf16 kernel's tiles stays there)
+bool bwd_input_on_mid32(const ConvShape& s, const ConvShape* f, int n, size_t room)
+{
+    double other = 0;
+    if (bwd_input_as_phases(s)) {
+        for (int i = 0; i < n; ++i)  // (the phases' launches overlap: 9 us less than their calls' times)
+            if (f[i].kh * f[i].kw > 0) other += igemm32_us(f[i], MfmaKernel::Dma32) - 9.0;
+    } else if (bwd_input_as_conv(s)) {
+        const ConvShape c = bwd_input_conv_shape(s);
+        other = 8.0 + igemm32_us(c, mfma_auto_kernel(c));
+    } else {
+        return true;
+    }
+    return igemm_mid_us(f, n, s.kernel_elems(), room) < 0.75 * other;
+}
+
+// Strided layers, and the windows and paddings that the convolution form does not cover, on the small-tile
+// kernel: always where `dout` would be spread out (s^2 times the work) or gathered element by element
+// (40 random layers: 0.2 .. 0.95 times the time), else
+// where one launch is estimated 30 % faster than the phases' launches on the tuned kernels.
+// Stride 1 otherwise is a convolution whose kernel the forward pass's rules pick.
+bool bwd_input_on_mid(const ConvShape& s, const ConvShape* f, int n, size_t room)
+{
+    if (!igemm_mid_eligible(f, n, s.kernel_elems())) return false;
+    if (s.stride == 1 && bwd_input_as_conv(s)) return false;
+    if (s.dtype == 0) return bwd_input_on_mid32(s, f, n, room);
+    if (!bwd_input_as_phases(s)) return true;
+    double other = 0;
+    for (int i = 0; i < n; ++i) {
+        if (f[i].kh * f[i].kw == 0) continue;
+        other += igemm16_tuned_us(f[i], phase_kernel(f[i]) == 16 ? MfmaKernel::Tuned16 : MfmaKernel::Dma32);
+    }
+    return igemm_mid_us(f, n, s.kernel_elems(), room) < 0.7 * other;
+}
+
 // dK as a forward convolution of the re-laid-out input with the (spread-out) output gradient
 // as the window
 ConvShape bwd_kernel_conv_shape(const ConvShape& s)
@@ -549,7 +568,7 @@ int launch_bwd_input(const ConvShape& s, const void* dout, const void* kernel, f
 int launch_bwd_kernel(const ConvShape& s, const void* input, const void* dout, float* dkernel,
                       void* workspace, size_t workspace_bytes, hipStream_t stream)
 {
-    if (s.dtype != 0) {
+    {
         const size_t room = bwd_kernel_workspace_bytes(s);
         if (wgrad_mid_preferred(s, room))
             return status_from_hip(launch_wgrad_mid(s, input, dout, dkernel, workspace, room, stream));

@@ -6,6 +6,7 @@
 
 #include "../../include/capscaps.h"
 #include "igemm_common.h"
+#include "mid_tiles.h"
 
 using capscaps::ConvShape;
 
@@ -68,8 +69,9 @@ struct Choice {
 };
 bool runs_mid(const ConvShape& s, capscaps::MfmaKernel kernel)
 {
-    return s.dtype != CAPSCAPS_FP32 &&
-           capscaps::igemm_mid_preferred(s, kernel, capscaps::mfma_kernel_workspace_bytes(s, kernel));
+    if (s.dtype == CAPSCAPS_FP32 && !s.in_gradient) return false;
+    if (!capscaps::igemm_mid_eligible(&s, 1, s.kernel_elems())) return false;
+    return capscaps::igemm_mid_preferred(s, kernel, capscaps::mfma_kernel_workspace_bytes(s, kernel));
 }
 Choice choose(const ConvShape& s)
 {

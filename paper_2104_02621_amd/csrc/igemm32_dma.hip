@@ -533,6 +533,11 @@ double other_fp32_us(const ConvShape& s)
 
 }  // namespace
 
+double igemm32_us(const ConvShape& s, MfmaKernel which)
+{
+    return which == MfmaKernel::Dma32 ? split_us(igemm32_dma_plan(s)) : other_fp32_us(s);
+}
+
 bool igemm32_dma_fills_chip(const ConvShape& s)
 {
     const Dma32Plan pl = igemm32_dma_plan(s);

@@ -207,31 +207,11 @@ size_t igemm_small_workspace_bytes(const ConvShape& s);
 hipError_t launch_igemm_small(const ConvShape& s, const void* in, const void* kernel, float* out,
                               void* workspace, hipStream_t stream);
 
-// 16-bit layers below the tuned kernels' sizes (igemm_mid.hip): one launch, kernel tensor read in
-// place, tiles of 64 or 128 rows and columns.  `f`: one forward pass, or an input gradient as
-// one convolution or as the n phases of a strided layer (all written by the one launch; geometry
-// overrides allowed).  `kernel_elems`: of the whole kernel tensor.  Partial sums of a split K loop take
-// at most `room` bytes of the workspace.
-bool igemm_mid_eligible(const ConvShape* f, int n, size_t kernel_elems);
-// ... and is the library's choice for a convolution that `otherwise` would run
-bool igemm_mid_preferred(const ConvShape& s, MfmaKernel otherwise, size_t room);
-// estimated times, us: of this kernel, and of Tuned16 or Dma32
-double igemm_mid_us(const ConvShape* f, int n, size_t kernel_elems, size_t room);
-double igemm16_tuned_us(const ConvShape& s, MfmaKernel which);
-hipError_t launch_igemm_mid(const ConvShape* f, int n, size_t kernel_elems, const void* in,
-                              const void* kernel, float* out, void* workspace, size_t room,
-                              hipStream_t stream);
-
 // Kernel gradient on the matrix cores for 16-bit types, D1 in {8, 16} (wgrad16.hip).
 bool wgrad16_eligible(const ConvShape& s);
 size_t wgrad16_workspace_bytes(const ConvShape& s);
 hipError_t launch_wgrad16(const ConvShape& s, const void* input, const void* dout, float* dkernel,
                           void* workspace, hipStream_t stream);
-// ... and for layers below its tiles' sizes (wgrad_mid.hip); partial sums take at most `room` bytes
-bool wgrad_mid_eligible(const ConvShape& s);
-bool wgrad_mid_preferred(const ConvShape& s, size_t room);  // ... and is the library's choice
-hipError_t launch_wgrad_mid(const ConvShape& s, const void* input, const void* dout, float* dkernel,
-                              void* workspace, size_t room, hipStream_t stream);
 // ... and for fp32 on the bf16 instructions, capsule heights D1 of 3, 4, 6, 8, 12 or 16 floats
 // (wgrad32.hip).
 bool wgrad32_eligible(const ConvShape& s);

@@ -1,5 +1,5 @@
-// 16-bit capsule convolution for layers too small for the 256-row tiles (forward pass and input
-// gradient): one launch, kernel tensor read in place, small tiles, direct-to-LDS copies.
+// Capsule convolution for layers too small for the 256-row tiles (16-bit forward pass and input gradient;
+// fp32 input gradient on the fp32 matrix instructions): one launch, kernel tensor read in place, small tiles, direct-to-LDS copies.
 //
 // What bounds such a layer is not the matrix cores but everything around them: the launch of a
 // repack pass, operands staged through registers, a reduction launch, and a K loop whose every
@@ -15,6 +15,9 @@
 //       of 8 columns x 1 line, [K block][column chunk][line], the line of every other pair of
 //       chunks XORed with 4 so that a half-wave's reads touch every bank once; for 4-element
 //       columns a slot is 2 lines x 4 columns and the order of memory is conflict-free as it is.
+// fp32 (input gradients only: its forward pass is not faster here than on igemm_small.hip's narrower tiles):
+// a K block is 4 values, so rows of 4k floats are the rows of 8k halves above, byte for byte, and one
+// 16-byte read feeds four matrix instructions (as in Mma<f32_tag>).
 // The K blocks of a stage are a flat sequence (tap, channel block): short channel extents pad
 // nothing.  A wave copies the K blocks w, w + 4 .. of a stage: one (tap, channel) walk per block in
 // scalar registers, one address and range test per row in the lanes.  Out-of-range offsets read as
@@ -100,6 +103,7 @@ __global__ __launch_bounds__(256, 2) void igemm_mid_kernel(const MidParams P)
     constexpr int A_BYTES = KBS * RA * 1024, STAGE = KBS * (RA + RB) * 1024;
     constexpr int NKB = KBS / 4, NCOPY = NKB * (RA + RB);
     constexpr int TM = RA * WC / 2, TN = WC == 1 ? 1 : RB;  // 32 x 32 tiles of a wave
+    constexpr bool F32 = std::is_same_v<Tag, f32_tag>;
     constexpr int BN = 32 * TN * WC;
     constexpr int KEEP = (NST - 2) * NCOPY;  // copies that may be in flight at a stage's barrier
     static_assert(KEEP < 64 && KBS % 4 == 0, "vmcnt is a 6-bit counter");
@@ -247,7 +251,9 @@ __global__ __launch_bounds__(256, 2) void igemm_mid_kernel(const MidParams P)
     // layers were up to 2.2 times as far from exact sums as the small-problem kernel's, whose waves share
     // the K loop), and matrix instructions that do not wait for each other
     constexpr int NACC = KBS / 2;
-    float16v acc[NACC][TM][TN] = {};
+    // fp32 adds them, in pairs, to another set every FLUSH stages (an instruction takes only two K values there)
+    constexpr int FLUSH = 4;
+    float16v acc[NACC][TM][TN] = {}, sum[F32 ? TM : 1][TN] = {};
     int wr_slot = 0, rd_slot = 0;
     const unsigned lds0 = (unsigned)(size_t)(__attribute__((address_space(3))) char*)smem;
 #pragma unroll
@@ -282,6 +288,19 @@ __global__ __launch_bounds__(256, 2) void igemm_mid_kernel(const MidParams P)
 #pragma unroll
                 for (int j = 0; j < TN; ++j) Mma<Tag>::run(fb[j], fa[i], acc[k][i][j]);
         }
+        if constexpr (F32)
+            if (j % FLUSH == FLUSH - 1) {
+#pragma unroll
+                for (int i = 0; i < TM; ++i)
+#pragma unroll
+                    for (int b = 0; b < TN; ++b) {
+                        sum[i][b] += NACC == 4 ? (acc[0][i][b] + acc[1][i][b]) +
+                                                     (acc[NACC - 2][i][b] + acc[NACC - 1][i][b])
+                                               : acc[0][i][b] + acc[NACC - 1][i][b];
+#pragma unroll
+                        for (int a = 0; a < NACC; ++a) acc[a][i][b] = float16v{};
+                    }
+            }
         rd_slot = rd_slot == (NST - 1) * STAGE ? 0 : rd_slot + STAGE;
     }
     // no copy may still be on its way into this workgroup's LDS when it ends
@@ -295,6 +314,13 @@ __global__ __launch_bounds__(256, 2) void igemm_mid_kernel(const MidParams P)
             for (int i = 0; i < TM; ++i)
 #pragma unroll
                 for (int j = 0; j < TN; ++j) acc[a][i][j] += acc[a + w][i][j];
+
+    if constexpr (F32) {
+#pragma unroll
+        for (int i = 0; i < TM; ++i)
+#pragma unroll
+            for (int j = 0; j < TN; ++j) acc[0][i][j] += sum[i][j];
+    }
 
     // ---- store: a lane holds 4 consecutive columns of a row, four times per 32 columns
     float* out = P.out + (P.nsplit > 1 ? (long long)split * P.out_elems : 0);
@@ -347,12 +373,15 @@ struct MidPlan {
     size_t partial_bytes;
 };
 
-// K blocks per copy: rows of 16 elements and more: both halves of 32 bytes; capsules of one or two rows: 64
+int elem_size(const ConvShape& s) { return s.dtype == 0 ? 4 : 2; }
+
+// K blocks per copy: rows of 32 bytes and more: both halves of 32; capsules of one or two rows: 64
 // bytes of a pixel
 int mid_group(const ConvShape& s)
 {
-    if (s.D2 % 8 != 0) return 2;
-    return s.D1 <= 2 ? 4 : s.D2 >= 16 ? 2 : 1;
+    const int row = s.D2 * elem_size(s) / 2;
+    if (row % 8 != 0) return 2;
+    return s.D1 <= 2 ? 4 : row >= 16 ? 2 : 1;
 }
 
 // Tiles, and what they take: us per stage with one, two, three workgroups on a CU, stages' worth of
@@ -369,6 +398,12 @@ constexpr Tile TILES[] = {{1, 1, 64, 8, 3, {0.327, 0.382, 0.517}, 5.2, 3.2},
                           {2, 1, 64, 4, 3, {0.283, 0.359, 0.448}, 8.6, 2.8},
                           {2, 2, 128, 4, 2, {0.374, 0.486, 0.486}, 9.0, 2.5},
                           {2, 1, 32, 4, 3, {0.248, 0.269, 0.333}, 8.5, 2.9}};
+// fp32: the matrix instructions are the limit (70 layers, 20 %)
+constexpr Tile TILES32[] = {{1, 1, 64, 8, 3, {0.757, 1.133, 1.622}, 2.4, 2.3},
+                            {1, 2, 128, 4, 3, {0.705, 1.116, 1.553}, 3.2, 2.8},
+                            {2, 1, 64, 4, 3, {0.687, 1.198, 1.548}, 3.5, 3.0},
+                            {2, 2, 128, 4, 2, {1.174, 2.081, 2.081}, 3.0, 3.6},
+                            {2, 1, 32, 4, 3, {0.470, 0.713, 0.932}, 3.8, 2.8}};
 struct Choice {
     int tile, nsplit;
     double us;
@@ -379,7 +414,7 @@ Choice choose(const ConvShape* f, int n, int kpt, int cols, size_t room)
     const double out_bytes = 4.0 * (s.out_view ? (double)s.out_alloc : (double)s.out_elems());
     Choice best{0, 1, 1e30};
     for (int t = 0; t < 5; ++t) {
-        const Tile& tl = TILES[t];
+        const Tile& tl = s.dtype == 0 ? TILES32[t] : TILES[t];
         if ((tl.bn == 32 && cols > 96) || (tl.bn == 128 && cols <= 64)) continue;
         for (int nsplit = 1; nsplit <= 32; nsplit += nsplit < 4 ? 1 : nsplit / 2) {
             long long tiles = 0, most = 0, sum = 0;
@@ -412,27 +447,28 @@ MidPlan mid_plan(const ConvShape* f, int n, size_t kernel_elems, size_t room)
     MidParams& P = pl.P;
     const ConvShape& s = f[0];
     const Strides k = kernel_strides(s);
-    pl.wide = s.D2 % 8 == 0;
+    const int es = elem_size(s), row = s.D2 * es / 2;  // capsule rows in units of 2 bytes
+    pl.wide = row % 8 == 0;
     pl.kt = !s.in_gradient;
-    P.in_bytes = (unsigned)(s.in_elems() * 2);
-    P.k_bytes = (unsigned)(kernel_elems * 2);
+    P.in_bytes = (unsigned)(s.in_elems() * es);
+    P.k_bytes = (unsigned)(kernel_elems * es);
     P.H = s.H; P.W = s.W; P.stride = s.stride; P.D1 = s.D1; P.C = s.C; P.D0 = s.D0;
-    P.in_sd0 = s.D1 * s.D2 * 2;
+    P.in_sd0 = s.D1 * s.D2 * es;
     P.pix_bytes = s.C * s.D0 * P.in_sd0;
-    P.d1_bytes = s.D2 * 2;
+    P.d1_bytes = s.D2 * es;
     P.in_blk = 16;
-    P.kb_shift = pl.wide ? log2_of(s.D2 / 8) : 0;
+    P.kb_shift = pl.wide ? log2_of(row / 8) : 0;
     P.kb_mask = (1 << P.kb_shift) - 1;
     P.in_kb = s.D0 * P.in_sd0 * (pl.wide ? 1 : 2);
     P.kq = pl.wide ? s.C << P.kb_shift : (s.C + 1) / 2;
     pl.g = mid_group(s);
     P.kpt = (P.kq + pl.g - 1) / pl.g * pl.g;
     P.kpt_magic = P.kpt == 1 ? 0u : (unsigned)(((1ull << 32) + P.kpt - 1) / P.kpt);
-    P.k_sp = (int)(k.sp * 2); P.k_sq = (int)(k.sq * 2); P.k_sd0 = (int)(k.sd0 * 2);
-    P.k_sm = (int)(k.sm * 2); P.k_c2 = (int)(k.sc * 2);
-    P.k_kb = (int)(k.sc * 2) * (pl.wide ? 1 : 2);
-    P.k_blk = (int)(k.sd2 * 8 * 2);
-    P.k_col = (int)((pl.kt ? k.sd2 : k.sd3) * 2);
+    P.k_sp = (int)(k.sp * es); P.k_sq = (int)(k.sq * es); P.k_sd0 = (int)(k.sd0 * es);
+    P.k_sm = (int)(k.sm * es); P.k_c2 = (int)(k.sc * es);
+    P.k_kb = (int)(k.sc * es) * (pl.wide ? 1 : 2);
+    P.k_blk = (int)(k.sd2 * 16);  // the values of a 16-byte K block times es
+    P.k_col = (int)((pl.kt ? k.sd2 : k.sd3) * es);
     P.dc_shift = log2_of(s.D3);
     P.cols = s.M * s.D3;
     P.nphase = n;
@@ -446,7 +482,7 @@ MidPlan mid_plan(const ConvShape* f, int n, size_t kernel_elems, size_t room)
     P.out_elems = s.out_view ? s.out_alloc : (long long)s.out_elems();
     // tile and split of the K loop: the least estimated time
     const Choice ch = choose(f, n, P.kpt, P.cols, room);
-    const Tile& tl = TILES[ch.tile];
+    const Tile& tl = TILES[ch.tile];  // (the same shapes for both)
     pl.ra = tl.ra;
     pl.rb = tl.rb;
     pl.wc = tl.bn == 32 ? 1 : 2;
@@ -465,7 +501,7 @@ MidPlan mid_plan(const ConvShape* f, int n, size_t kernel_elems, size_t room)
         F.kw_magic = g.kw <= 1 ? 0 : (int)(unsigned)(((1ull << 32) + g.kw - 1) / g.kw);
         F.by_wo = fast_div(g.Wo);
         F.by_ho = fast_div(g.Ho);
-        F.k_base = (int)(g.kernel_view ? g.k_base * 2 : 0);
+        F.k_base = (int)(g.kernel_view ? g.k_base * es : 0);
         F.out_base = g.out_view ? g.out_base : 0;
     }
     const long long tiles = (long long)row_tiles * P.col_tiles * s.D0;
@@ -521,6 +557,18 @@ hipError_t launch_tag(const MidPlan& pl, hipStream_t stream)
                        : launch_out<Tag, true, 1>(pl, stream);
 }
 
+template <int G>
+hipError_t launch_f32_group(const MidPlan& pl, hipStream_t stream)
+{
+    return launch_mode<f32_tag, true, G, false, false>(pl, stream);
+}
+hipError_t launch_f32(const MidPlan& pl, hipStream_t stream)
+{
+    return pl.g == 4   ? launch_f32_group<4>(pl, stream)
+           : pl.g == 2 ? launch_f32_group<2>(pl, stream)
+                       : launch_f32_group<1>(pl, stream);
+}
+
 }  // namespace
 
 // Shapes the kernel can run.  `f`: n phases of one input gradient, or one forward pass or input
@@ -528,17 +576,20 @@ hipError_t launch_tag(const MidPlan& pl, hipStream_t stream)
 bool igemm_mid_eligible(const ConvShape* f, int n, size_t kernel_elems)
 {
     const ConvShape& s = f[0];
-    if (s.dtype == 0 || n < 1 || n > MAX_PHASES || s.in_paired) return false;
+    if (n < 1 || n > MAX_PHASES || s.in_paired) return false;
     if (s.H > MAX_EXTENT || s.W > MAX_EXTENT || s.stride > MAX_EXTENT) return false;
     if (!pow2(s.D3) || s.D3 < 4) return false;  // 4 consecutive columns per lane, shifts
-    if (s.D2 % 8 == 0) {
+    if (s.dtype == 0) {
+        if (!s.in_gradient || !pow2(s.D2) || s.D2 < 4) return false;
+    } else if (s.D2 % 8 == 0) {
         if (!pow2(s.D2) || (!s.in_gradient && s.D3 % 8 != 0)) return false;
     } else if (s.D2 != 4 || s.D1 % 2 != 0 || (!s.in_gradient && s.D3 != 4)) {
         return false;
     }
-    if (s.in_elems() * 2 >= MAX_TENSOR_BYTES || kernel_elems * 2 >= MAX_TENSOR_BYTES) return false;
+    const size_t es = elem_size(s);
+    if (s.in_elems() * es >= MAX_TENSOR_BYTES || kernel_elems * es >= MAX_TENSOR_BYTES) return false;
     const bool cols_ok = (long long)s.M * s.D3 < (1LL << 24);
-    const long long kpt = (s.D2 % 8 == 0 ? (long long)s.C * (s.D2 / 8) : (s.C + 1) / 2) + 3;
+    const long long kpt = (long long)s.C * (s.D2 * es < 16 ? 1 : s.D2 * es / 16) + 3;
     for (int i = 0; i < n; ++i) {
         const long long rows = f[i].pixels() * s.D1, kbs = (long long)f[i].kh * f[i].kw * kpt;
         if (rows >= (1LL << 30) || f[i].out_sn < 0 || f[i].out_sx < 0 || f[i].out_sy < 0) return false;
@@ -575,9 +626,20 @@ double igemm16_tuned_us(const ConvShape& s, MfmaKernel which)
 // loop and next to no work, where that kernel's many short pieces win (2 images, a 5x5 window over 77 channels of
 // 4x4: 11.0 against 9.3 us).  Against the kernels of 256-row tiles where the estimates differ by 30 %
 // (by a tenth: 12 of 200 random layers were 4 .. 21 % slower, by a fifth 7 of 150).
+// fp32 input gradients: against the small-problem and the any-shape kernel, which read the kernel tensor
+// through strides or after a repack pass, from 24 columns on, but for a few tiles of a long K loop (28 random layers 0.41 .. 0.85 times the time, one
+// of 5.6 us 0.3 us slower; 8 and 16 columns 1.13 and 1.2 times); against the kernel on bf16 instructions where
+// the estimates differ by a quarter.
 bool igemm_mid_preferred(const ConvShape& s, MfmaKernel otherwise, size_t room)
 {
-    if (!igemm_mid_eligible(&s, 1, s.kernel_elems())) return false;
+    if (s.dtype == 0) {
+        if (otherwise == MfmaKernel::Generic || otherwise == MfmaKernel::Small)
+            return (long long)s.M * s.D3 >= 24 &&
+                   (2.0 * (double)s.out_elems() * s.kh * s.kw * s.C * s.D2 >= 1e8 ||
+                    mid_plan(&s, 1, s.kernel_elems(), room).us < 12);
+        return otherwise == MfmaKernel::Dma32 &&
+               mid_plan(&s, 1, s.kernel_elems(), room).us < 0.75 * igemm32_us(s, otherwise);
+    }
     if (otherwise == MfmaKernel::Generic) return true;
     const double us = mid_plan(&s, 1, s.kernel_elems(), room).us;
     if (otherwise == MfmaKernel::Small)
@@ -599,8 +661,9 @@ hipError_t launch_igemm_mid(const ConvShape* f, int n, size_t kernel_elems, cons
     pl.P.kernel = kernel;
     float* partial = static_cast<float*>(workspace);
     pl.P.out = pl.P.nsplit > 1 ? partial : out;
-    const hipError_t err = f[0].dtype == 1 ? launch_tag<bf16_tag>(pl, stream)
-                                           : launch_tag<f16_tag>(pl, stream);
+    const hipError_t err = f[0].dtype == 0   ? launch_f32(pl, stream)
+                           : f[0].dtype == 1 ? launch_tag<bf16_tag>(pl, stream)
+                                             : launch_tag<f16_tag>(pl, stream);
     if (err != hipSuccess || pl.P.nsplit == 1) return err;
     return launch_splitk_reduce(partial, out, pl.P.out_elems, pl.P.nsplit, stream, f[0].out16);
 }

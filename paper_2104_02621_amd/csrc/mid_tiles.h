@@ -1,10 +1,35 @@
-// Internal: what the small-tile 16-bit kernels (igemm_mid.hip, wgrad_mid.hip) share.
+// Internal: the small-tile kernels (igemm_mid.hip, wgrad_mid.hip), and what they share.
 #pragma once
 #include <hip/hip_runtime.h>
 
 #include "igemm_common.h"
 
 namespace capscaps {
+
+// Forward pass (16-bit) and input gradient of layers below the tuned kernels' sizes (igemm_mid.hip): one launch,
+// kernel tensor read in place, tiles of 64 or 128 rows and columns.  `f`: one forward pass, or an input gradient as
+// one convolution or as the n phases of a strided layer (all written by the one launch; geometry
+// overrides allowed).  `kernel_elems`: of the whole kernel tensor.  Partial sums of a split K loop take
+// at most `room` bytes of the workspace.
+bool igemm_mid_eligible(const ConvShape* f, int n, size_t kernel_elems);
+// ... and is the library's choice for a convolution it can run and that `otherwise` would
+bool igemm_mid_preferred(const ConvShape& s, MfmaKernel otherwise, size_t room);
+// estimated times, us: of this kernel, and of Tuned16 or Dma32
+double igemm_mid_us(const ConvShape* f, int n, size_t kernel_elems, size_t room);
+double igemm16_tuned_us(const ConvShape& s, MfmaKernel which);
+// ... of the fp32 kernels (igemm32_dma.hip)
+double igemm32_us(const ConvShape& s, MfmaKernel which);
+hipError_t launch_igemm_mid(const ConvShape* f, int n, size_t kernel_elems, const void* in,
+                            const void* kernel, float* out, void* workspace, size_t room,
+                            hipStream_t stream);
+
+// Kernel gradient of such layers (wgrad_mid.hip); partial sums take at most `room` bytes
+bool wgrad_mid_eligible(const ConvShape& s);
+bool wgrad_mid_preferred(const ConvShape& s, size_t room);  // ... and is the library's choice
+hipError_t launch_wgrad_mid(const ConvShape& s, const void* input, const void* dout, float* dkernel,
+                            void* workspace, size_t room, hipStream_t stream);
+double wgrad32_us(const ConvShape& s);  // estimated time of launch_wgrad32, us
+
 namespace {
 
 constexpr unsigned OOB = 0x80000000u;           // an offset no tensor reaches: reads as zero

@@ -757,7 +757,7 @@ int tile_step(int extent, int unit, int k)
 // and to get under way: start, in us, is what tiny layers take more than with 1 x 1 tiles.  (By the fewest
 // padded rows alone 150 x 220 took 1 x 1 tiles, 262 us at 12 GFLOP, now 161, and 96 x 384 with two dozen K
 // values 3 x 3 ones, 22 us, now 13.)
-void choose_tile(Wgrad32Params& P, double steps, int& tm, int& tn)
+double choose_tile(Wgrad32Params& P, double steps, int& tm, int& tn)
 {
     static const double cost[3][3] = {{650, 470, 540}, {470, 360, 385}, {540, 385, 330}};
     static const double start[3][3] = {{0, 1.3, 4.5}, {1.5, 4, 8}, {5, 9, 15}};
@@ -775,6 +775,7 @@ void choose_tile(Wgrad32Params& P, double steps, int& tm, int& tn)
             tm = a; P.row_step = rs; P.row_tiles = rt;
             tn = b; P.col_step = cs; P.col_tiles = ct;
         }
+    return best;
 }
 
 // Tiles and the split of the K loop (host side, pure arithmetic).
@@ -950,6 +951,23 @@ bool wgrad32_eligible(const ConvShape& s)
     if (tiles * 3072 >= (1LL << 31)) return false;  // the split never exceeds 3072 ranges
     if ((long long)s.N * s.Ho * s.Wo >= (1LL << 31)) return false;  // pixel counts are 32-bit
     return true;
+}
+
+// A fit over 47 random layers of square capsules, 0.001 .. 38 GFLOP, 16 % root mean square: launches, the tiles'
+// estimate (its scale is that of six layers of 576 rows and columns), and the partial sums of as many ranges as
+// the reduction is worth.
+double wgrad32_us(const ConvShape& s)
+{
+    Wgrad32Params P{};
+    int tm, tn;
+    P.natural = s.D1 == s.D2 && s.D1 == s.D3;
+    P.D2 = s.D2; P.D3 = s.D3; P.D0 = s.D0;
+    P.rows = s.C * s.D2;
+    P.cols = s.M * s.D3;
+    P.ntaps = s.kh * s.kw;
+    const double steps = (double)s.pixels() * s.D1 / 16;
+    const double busy = choose_tile(P, steps, tm, tn);
+    return 8.8 + 0.52 * busy + 0.99 * std::sqrt(steps * 4e-6 * (double)s.kernel_elems());
 }
 
 size_t wgrad32_workspace_bytes(const ConvShape& s)

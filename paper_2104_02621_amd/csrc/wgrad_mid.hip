@@ -1,4 +1,5 @@
-// Kernel gradient for 16-bit element types, layers too small for the 256x256 tiles of wgrad16.hip: per
+// Kernel gradient of layers too small for the tiles of wgrad16.hip and wgrad32.hip (16-bit types; fp32 on the
+// fp32 matrix instructions): per
 // window tap one GEMM with rows (c, d2), columns (m, d3) and K (n, x, y, d1), both tensors read
 // in place, whatever the channel counts.
 //
@@ -40,7 +41,8 @@ struct WmidParams {
     long long out_elems;
 };
 
-// WIDE: D2 and D3 are multiples of 8, else both 4 (and D1 = 4).
+// WIDE: rows and columns come in 16-byte chunks (D2 and D3 multiples of 8, in fp32 of 4), else both are 4 (and
+// D1 = 4).  fp32: a K block is 4 lines, a slot 4 columns of one, and a lane reads its column's 4 values one by one.
 template <typename Tag, int D1, bool WIDE, int RA, int RB, int KBS, int NST>
 __global__ __launch_bounds__(256, 2) void wgrad_mid_kernel(const WmidParams P)
 {
@@ -48,13 +50,15 @@ __global__ __launch_bounds__(256, 2) void wgrad_mid_kernel(const WmidParams P)
     constexpr int NKB = KBS / 4, NCOPY = NKB * (RA + RB);
     constexpr int KEEP = (NST - 2) * NCOPY;
     static_assert(KEEP < 64, "vmcnt is a 6-bit counter");
-    constexpr int PPB = D1 < 8 ? 8 / D1 : 1;  // pixels per K block of 8 lines
-    constexpr int HALVES = D1 > 8 ? D1 / 8 : 1;  // K blocks per pixel
+    constexpr bool F32 = std::is_same_v<Tag, f32_tag>;
+    constexpr int ES = F32 ? 4 : 2, LINES = F32 ? 4 : 8;  // K lines per K block
+    constexpr int PPB = D1 < LINES ? LINES / D1 : 1;    // pixels per K block
+    constexpr int HALVES = D1 > LINES ? D1 / LINES : 1;  // K blocks per pixel
     static_assert(HALVES <= 4, "a wave's K blocks are every fourth: always the same part of a pixel");
     // accumulators: one per K step of a stage (128x128 tiles: one), the larger tiles' added to a second set
     // every FLUSH stages, so that chains of roundings stay short: K loops are long here
-    constexpr int NACC = RA * RB == 4 ? 1 : KBS / 2, FLUSH = 16;
-    constexpr bool SUM = RA * RB > 1;
+    constexpr int NACC = RA * RB == 4 ? 1 : KBS / 2, FLUSH = F32 ? 4 : 16;
+    constexpr bool SUM = RA * RB > 1 || std::is_same_v<Tag, f32_tag>;
     extern __shared__ char smem[];
 
     int L = blockIdx.x;
@@ -71,11 +75,11 @@ __global__ __launch_bounds__(256, 2) void wgrad_mid_kernel(const WmidParams P)
 
     // ---- copy side: what lane i copies of a unit.  WIDE: line (i & 7) XOR 4 in every other pair of chunks,
     // columns 8 (i >> 3) ..; else pixel i >> 5, capsule (i >> 1) & 15, lines 2 (i & 1) and the next
-    const int j8 = lane >> 3;
-    const int line = WIDE ? (lane & 7) ^ (((j8 >> 1) & 1) << 2) : (lane & 1) * 2;
-    const int psub = WIDE ? (D1 < 8 ? line / D1 : 0) : lane >> 5;
-    const int d1 = WIDE ? line % (D1 < 8 ? D1 : 8) + wave % HALVES * 8 : line;
-    const int first_col = WIDE ? 8 * j8 : 4 * ((lane >> 1) & 15);
+    const int j8 = F32 ? lane >> 2 : lane >> 3;
+    const int line = F32 ? (lane & 3) ^ (j8 >> 2 & 3) : WIDE ? (lane & 7) ^ (((j8 >> 1) & 1) << 2) : (lane & 1) * 2;
+    const int psub = WIDE ? (D1 < LINES ? line / D1 : 0) : lane >> 5;
+    const int d1 = WIDE ? line % (D1 < LINES ? D1 : LINES) + wave % HALVES * LINES : line;
+    const int first_col = F32 ? 4 * j8 : WIDE ? 8 * j8 : 4 * ((lane >> 1) & 15);
     int tap_p[RA], tap_q[RA];
     unsigned a_off[RA], b_off[RB];
 #pragma unroll
@@ -88,14 +92,14 @@ __global__ __launch_bounds__(256, 2) void wgrad_mid_kernel(const WmidParams P)
         r = r < P.rows ? r : 0;
         tap_p[i] = tap / P.kw;
         tap_q[i] = tap - tap_p[i] * P.kw;
-        a_off[i] = (unsigned)((r >> P.d2_shift) * P.in_sc + (r & ((1 << P.d2_shift) - 1)) * 2 + d1 * P.line_in +
+        a_off[i] = (unsigned)((r >> P.d2_shift) * P.in_sc + (r & ((1 << P.d2_shift) - 1)) * ES + d1 * P.line_in +
                               d0 * P.in_sd0);
     }
 #pragma unroll
     for (int i = 0; i < RB; ++i) {
         int c = col0 + 64 * i + first_col;
         c = c < P.cols ? c : 0;
-        b_off[i] = (unsigned)((c >> P.d3_shift) * P.g_sm + (c & ((1 << P.d3_shift) - 1)) * 2 + d1 * P.line_g +
+        b_off[i] = (unsigned)((c >> P.d3_shift) * P.g_sm + (c & ((1 << P.d3_shift) - 1)) * ES + d1 * P.line_g +
                               d0 * P.g_sd0);
     }
 
@@ -144,17 +148,32 @@ __global__ __launch_bounds__(256, 2) void wgrad_mid_kernel(const WmidParams P)
 
     // ---- read side
     const int wr = wave >> 1, wc = wave & 1, half = lane >> 5, l31 = lane & 31;
+    auto lane_at = [&](int c) {
+        if (!F32) return transposed_at<WIDE>(lane, c);
+        const int j = c / 4 + (l31 >> 2);
+        return j * 64 + ((j >> 2 & 3) << 4) + (l31 & 3) * 4;
+    };
     int a_rd[RA], b_rd[RB];
 #pragma unroll
     for (int i = 0; i < RA; ++i) {
         const int r = wr * 32 * RA + 32 * i;
-        a_rd[i] = (half * RA + (r >> 6)) * 1024 + transposed_at<WIDE>(lane, r & 63);
+        a_rd[i] = (half * RA + (r >> 6)) * 1024 + lane_at(r & 63);
     }
 #pragma unroll
     for (int i = 0; i < RB; ++i) {
         const int c = wc * 32 * RB + 32 * i;
-        b_rd[i] = A_BYTES + (half * RB + (c >> 6)) * 1024 + transposed_at<WIDE>(lane, c & 63);
+        b_rd[i] = A_BYTES + (half * RB + (c >> 6)) * 1024 + lane_at(c & 63);
     }
+    auto read_frag = [&](int at, int rd) -> chunk_t {
+        if constexpr (F32) {  // line u: address bits 4 and 5
+            chunk_t v;
+#pragma unroll
+            for (int u = 0; u < 4; ++u) v[u] = *reinterpret_cast<const unsigned*>(smem + at + (rd ^ (u << 4)));
+            return v;
+        } else {
+            return read_transposed(smem, at + rd, at + (WIDE ? rd ^ 64 : rd + 512));
+        }
+    };
 
     float16v acc[NACC][RA][RB] = {}, sum[SUM ? RA : 1][RB] = {};
     int wr_slot = 0, rd_slot = 0;
@@ -173,15 +192,9 @@ __global__ __launch_bounds__(256, 2) void wgrad_mid_kernel(const WmidParams P)
         for (int k = 0; k < KBS / 2; ++k) {
             chunk_t fa[RA], fb[RB];
 #pragma unroll
-            for (int i = 0; i < RB; ++i) {
-                const int at = rd_slot + k * 2 * RB * 1024;
-                fb[i] = read_transposed(smem, at + b_rd[i], at + (WIDE ? b_rd[i] ^ 64 : b_rd[i] + 512));
-            }
+            for (int i = 0; i < RB; ++i) fb[i] = read_frag(rd_slot + k * 2 * RB * 1024, b_rd[i]);
 #pragma unroll
-            for (int i = 0; i < RA; ++i) {
-                const int at = rd_slot + k * 2 * RA * 1024;
-                fa[i] = read_transposed(smem, at + a_rd[i], at + (WIDE ? a_rd[i] ^ 64 : a_rd[i] + 512));
-            }
+            for (int i = 0; i < RA; ++i) fa[i] = read_frag(rd_slot + k * 2 * RA * 1024, a_rd[i]);
 #pragma unroll
             for (int i = 0; i < RA; ++i)
 #pragma unroll
@@ -193,8 +206,12 @@ __global__ __launch_bounds__(256, 2) void wgrad_mid_kernel(const WmidParams P)
                 for (int i = 0; i < RA; ++i)
 #pragma unroll
                     for (int j2 = 0; j2 < RB; ++j2) {
-                        sum[i][j2] += NACC == 2 ? acc[0][i][j2] + acc[NACC - 1][i][j2] : acc[0][i][j2];
-                        acc[0][i][j2] = acc[NACC - 1][i][j2] = float16v{};
+                        sum[i][j2] += NACC == 4 ? (acc[0][i][j2] + acc[NACC / 4][i][j2]) +
+                                                      (acc[NACC / 2][i][j2] + acc[NACC - 1][i][j2])
+                                      : NACC == 2 ? acc[0][i][j2] + acc[NACC - 1][i][j2]
+                                                  : acc[0][i][j2];
+#pragma unroll
+                        for (int a = 0; a < NACC; ++a) acc[a][i][j2] = float16v{};
                     }
             }
         rd_slot = rd_slot == (NST - 1) * STAGE ? 0 : rd_slot + STAGE;
@@ -253,6 +270,12 @@ constexpr Tile TILES[] = {{1, 1, 8, 3, {0.247, 0.424, 0.652}, 3.7, 3.3},
                           {2, 1, 4, 3, {0.212, 0.347, 0.503}, 7.6, 3.0},
                           {2, 2, 4, 2, {0.303, 0.517, 0.517}, 5.7, 3.2}};
 
+// fp32: the matrix instructions are the limit (60 layers, 6 %)
+constexpr Tile TILES32[] = {{1, 1, 8, 3, {0.700, 1.196, 1.572}, 2.5, 1.5},
+                            {1, 2, 4, 3, {0.668, 1.152, 1.570}, 2.5, 2.2},
+                            {2, 1, 4, 3, {0.679, 1.172, 1.585}, 3.0, 1.7},
+                            {2, 2, 4, 2, {1.136, 2.064, 2.064}, 1.0, 3.5}};
+
 struct WmidPlan {
     WmidParams P;
     int ra, rb;
@@ -264,11 +287,12 @@ WmidPlan wmid_plan(const ConvShape& s, size_t room)
 {
     WmidPlan pl{};
     WmidParams& P = pl.P;
-    P.in_bytes = (unsigned)(s.in_elems() * 2);
-    P.g_bytes = (unsigned)(s.out_elems() * 2);
+    const int es = s.dtype == 0 ? 4 : 2;
+    P.in_bytes = (unsigned)(s.in_elems() * es);
+    P.g_bytes = (unsigned)(s.out_elems() * es);
     P.H = s.H; P.W = s.W; P.stride = s.stride; P.pad = s.pad; P.kw = s.kw; P.C = s.C; P.D0 = s.D0;
-    P.line_in = s.D2 * 2;
-    P.line_g = s.D3 * 2;
+    P.line_in = s.D2 * es;
+    P.line_g = s.D3 * es;
     P.in_sd0 = s.D1 * P.line_in;
     P.g_sd0 = s.D1 * P.line_g;
     P.in_sc = s.D0 * P.in_sd0;
@@ -281,7 +305,7 @@ WmidPlan wmid_plan(const ConvShape& s, size_t room)
     P.d3_shift = log2_of(s.D3);
     const int blocks = ceil_div(P.rows, 64);
     P.pixels = (int)s.pixels();
-    P.kbs = ceil_div((long long)P.pixels * s.D1, 8);
+    P.kbs = ceil_div((long long)P.pixels * s.D1, 16 / es);
     P.Wo = s.Wo; P.Ho = s.Ho;
     P.by_wo = fast_div(s.Wo);
     P.by_ho = fast_div(s.Ho);
@@ -292,7 +316,7 @@ WmidPlan wmid_plan(const ConvShape& s, size_t room)
     pl.us = 1e30;
     int kbs = 8;
     P.nsplit = 1;
-    for (const Tile& tl : TILES) {
+    for (const Tile& tl : s.dtype == 0 ? TILES32 : TILES) {
         const int per_tap = s.pad > 0 ? ceil_div(blocks, tl.ra) * tl.ra : blocks;
         const long long tiles = (long long)ceil_div((long long)s.kh * s.kw * per_tap, tl.ra) * ceil_div(P.cols, 64 * tl.rb) * s.D0;
         const int all = ceil_div(P.kbs, tl.kbs);
@@ -301,7 +325,7 @@ WmidPlan wmid_plan(const ConvShape& s, size_t room)
             if (nsplit > 1 && (stages < 2 || (double)nsplit * out_bytes > (double)room)) break;
             const long long wgs = tiles * nsplit, round = 256LL * tl.wgs, full = wgs / round,
                             rest = wgs % round;
-            const double slow = s.D1 <= 2 ? 1.3 : 1.0;
+            const double slow = s.D1 <= 2 && s.dtype != 0 ? 1.3 : 1.0;
             double us = tl.call + (double)full * (stages + tl.extra) * tl.us[tl.wgs - 1] * slow;
             if (rest > 0) us += (stages + tl.extra) * tl.us[(rest + 255) / 256 - 1] * slow;
             if (nsplit > 1) us += 3.0 + nsplit * out_bytes / 4e6;
@@ -350,7 +374,8 @@ hipError_t launch_mode(const WmidPlan& pl, hipStream_t stream)
 template <typename Tag>
 hipError_t launch_tag(const WmidPlan& pl, const ConvShape& s, hipStream_t stream)
 {
-    if (s.D2 == 4) return launch_mode<Tag, 4, false>(pl, stream);
+    if constexpr (!std::is_same_v<Tag, f32_tag>)
+        if (s.D2 == 4) return launch_mode<Tag, 4, false>(pl, stream);
     switch (s.D1) {
         case 1: return launch_mode<Tag, 1, true>(pl, stream);
         case 2: return launch_mode<Tag, 2, true>(pl, stream);
@@ -364,16 +389,19 @@ hipError_t launch_tag(const WmidPlan& pl, const ConvShape& s, hipStream_t stream
 
 bool wgrad_mid_eligible(const ConvShape& s)
 {
-    if (s.dtype == 0 || !s.plain() || s.out16 != 0) return false;
-    if (s.D2 == 4 || s.D3 == 4) {
+    if (!s.plain() || s.out16 != 0) return false;
+    const size_t es = s.dtype == 0 ? 4 : 2;
+    if (s.dtype == 0) {
+        if (s.D2 < 4 || s.D3 < 4 || !pow2(s.D2) || !pow2(s.D3) || !pow2(s.D1) || s.D1 > 16) return false;
+    } else if (s.D2 == 4 || s.D3 == 4) {
         if (s.D1 != 4 || s.D2 != 4 || s.D3 != 4) return false;
     } else if (s.D2 % 8 != 0 || s.D3 % 8 != 0 || !pow2(s.D2) || !pow2(s.D3) ||
                !(s.D1 == 1 || s.D1 == 2 || s.D1 == 4 || s.D1 == 8 || s.D1 == 16)) {
         return false;
     }
     // 32-bit offsets below the out-of-range mark, also those of the pixels a K loop's end runs past
-    const size_t gpix = (size_t)s.M * s.D0 * s.D1 * s.D3 * 2;
-    if (s.in_elems() * 2 >= MAX_TENSOR_BYTES || s.out_elems() * 2 + 512 * gpix >= MAX_TENSOR_BYTES)
+    const size_t gpix = (size_t)s.M * s.D0 * s.D1 * s.D3 * es;
+    if (s.in_elems() * es >= MAX_TENSOR_BYTES || s.out_elems() * es + 512 * gpix >= MAX_TENSOR_BYTES)
         return false;
     if (s.H > (1 << 14) || s.W > (1 << 14) || s.kh > (1 << 12) || s.kw > (1 << 12) || s.pad > (1 << 14) ||
         s.stride > (1 << 14))
@@ -391,6 +419,12 @@ bool wgrad_mid_eligible(const ConvShape& s)
 bool wgrad_mid_preferred(const ConvShape& s, size_t room)
 {
     if (!wgrad_mid_eligible(s)) return false;
+    // fp32: where estimated 15 % faster than wgrad32_kernel (47 random layers: the 22 that leave it take 0.37 .. 0.97
+    // of its time)
+    // and at least 64 K values (shorter sums have fewer roundings there: 3e-8 against 5e-8)
+    if (s.dtype == 0)
+        return !wgrad32_eligible(s) ||
+               (s.pixels() * s.D1 >= 64 && wmid_plan(s, room).us < 0.85 * wgrad32_us(s));
     if (!wgrad16_eligible(s)) return true;
     const int rows = s.C * s.D2, cols = s.M * s.D3, nt = rows > 128 ? 1 : rows > 64 ? 2 : 4;
     const double gflop = 2e-9 * (double)(s.pixels() * s.D1) * ceil_div(s.kh * s.kw, nt) * s.D0 *
@@ -406,8 +440,9 @@ hipError_t launch_wgrad_mid(const ConvShape& s, const void* input, const void* d
     pl.P.g = dout;
     float* partial = static_cast<float*>(workspace);
     pl.P.out = pl.P.nsplit > 1 ? partial : dkernel;
-    const hipError_t err = s.dtype == 1 ? launch_tag<bf16_tag>(pl, s, stream)
-                                        : launch_tag<f16_tag>(pl, s, stream);
+    const hipError_t err = s.dtype == 0   ? launch_tag<f32_tag>(pl, s, stream)
+                           : s.dtype == 1 ? launch_tag<bf16_tag>(pl, s, stream)
+                                          : launch_tag<f16_tag>(pl, s, stream);
     if (err != hipSuccess || pl.P.nsplit == 1) return err;
     return launch_splitk_reduce(partial, dkernel, pl.P.out_elems, pl.P.nsplit, stream);
 }
