@@ -416,25 +416,34 @@ Choice choose(const ConvShape* f, int n, int kpt, int cols, size_t room)
     for (int t = 0; t < 5; ++t) {
         const Tile& tl = s.dtype == 0 ? TILES32[t] : TILES[t];
         if ((tl.bn == 32 && cols > 96) || (tl.bn == 128 && cols <= 64)) continue;
+        // (a launch-bound call waits for this: rows and stages of the phases once per tile, and no more
+        // pieces once they have made it slower)
+        int row_tiles[MAX_PHASES], stages_of[MAX_PHASES];
+        double tiles = 0, tile_best = 1e30;
+        for (int i = 0; i < n; ++i) {
+            row_tiles[i] = (int)((unsigned)(f[i].pixels() * s.D1 + 64 * tl.ra - 1) / (64u * tl.ra));
+            stages_of[i] = (int)((unsigned)(f[i].kh * f[i].kw * kpt + tl.kbs - 1) / (unsigned)tl.kbs);
+            tiles += row_tiles[i];
+        }
+        const double per_split = tiles * ((cols + tl.bn - 1) / tl.bn) * s.D0, round = 256.0 * tl.wgs;
         for (int nsplit = 1; nsplit <= 32; nsplit += nsplit < 4 ? 1 : nsplit / 2) {
-            long long tiles = 0, most = 0, sum = 0;
+            int most = 0;
+            double sum = 0;
             for (int i = 0; i < n; ++i) {
-                const long long rt = ceil_div(f[i].pixels() * s.D1, 64 * tl.ra);
-                const long long st = ceil_div(ceil_div((long long)f[i].kh * f[i].kw * kpt, tl.kbs), nsplit);
-                tiles += rt;
-                sum += rt * st;
+                const int st = (stages_of[i] + nsplit - 1) / nsplit;
+                sum += (double)row_tiles[i] * st;
                 if (st > most) most = st;
             }
-            if (nsplit > 1 && (most < 2 || (double)nsplit * out_bytes > (double)room)) break;
-            const double stages = (double)sum / (double)tiles;
-            const long long blocks = tiles * ceil_div(cols, tl.bn) * s.D0 * nsplit;
-            const long long round = 256LL * tl.wgs, full = blocks / round, rest = blocks % round;
-            double us = tl.call + (double)full * (stages + tl.extra) * tl.us[tl.wgs - 1];
+            if (nsplit > 1 && (most < 2 || nsplit * out_bytes > (double)room)) break;
+            const double stages = sum / tiles, blocks = per_split * nsplit;
+            const double full = (double)(long long)(blocks / round), rest = blocks - full * round;
+            double us = tl.call + full * (stages + tl.extra) * tl.us[tl.wgs - 1];
             if (rest > 0)
-                us += ((full ? stages : (double)most) + tl.extra) * tl.us[(rest + 255) / 256 - 1];
+                us += ((full > 0 ? stages : (double)most) + tl.extra) * tl.us[(int)((rest + 255) / 256) - 1];
             if (nsplit > 1) us += 3.0 + nsplit * out_bytes / 4e6;
             if (us < best.us) best = {t, nsplit, us};
-            if (blocks >= 1024) break;
+            if (us < tile_best) tile_best = us;
+            if (blocks >= 1024 || (nsplit > 2 && us > 1.1 * tile_best)) break;
         }
     }
     return best;

@@ -320,15 +320,17 @@ WmidPlan wmid_plan(const ConvShape& s, size_t room)
         const int per_tap = s.pad > 0 ? ceil_div(blocks, tl.ra) * tl.ra : blocks;
         const long long tiles = (long long)ceil_div((long long)s.kh * s.kw * per_tap, tl.ra) * ceil_div(P.cols, 64 * tl.rb) * s.D0;
         const int all = ceil_div(P.kbs, tl.kbs);
+        double tile_best = 1e30;
         for (int nsplit = 1; nsplit <= 512; nsplit += nsplit < 4 ? 1 : nsplit / 4) {
-            const int stages = ceil_div(all, nsplit);
+            const int stages = (all + nsplit - 1) / nsplit;
             if (nsplit > 1 && (stages < 2 || (double)nsplit * out_bytes > (double)room)) break;
-            const long long wgs = tiles * nsplit, round = 256LL * tl.wgs, full = wgs / round,
-                            rest = wgs % round;
+            const double wgs = (double)tiles * nsplit, round = 256.0 * tl.wgs;
+            const double full = (double)(long long)(wgs / round), rest = wgs - full * round;
             const double slow = s.D1 <= 2 && s.dtype != 0 ? 1.3 : 1.0;
-            double us = tl.call + (double)full * (stages + tl.extra) * tl.us[tl.wgs - 1] * slow;
-            if (rest > 0) us += (stages + tl.extra) * tl.us[(rest + 255) / 256 - 1] * slow;
+            double us = tl.call + full * (stages + tl.extra) * tl.us[tl.wgs - 1] * slow;
+            if (rest > 0) us += (stages + tl.extra) * tl.us[(int)((rest + 255) / 256) - 1] * slow;
             if (nsplit > 1) us += 3.0 + nsplit * out_bytes / 4e6;
+            if (us < tile_best) tile_best = us;
             if (us < pl.us) {
                 pl.us = us;
                 pl.ra = tl.ra;
@@ -336,7 +338,8 @@ WmidPlan wmid_plan(const ConvShape& s, size_t room)
                 P.nsplit = nsplit;
                 kbs = tl.kbs;
             }
-            if (wgs >= 1536) break;
+            // (no more ranges once they have made it slower)
+            if (wgs >= 1536 || (nsplit > 2 && us > 1.1 * tile_best)) break;
         }
     }
     P.blocks_per_tap = s.pad > 0 ? ceil_div(blocks, pl.ra) * pl.ra : blocks;
