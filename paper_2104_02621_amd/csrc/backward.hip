@@ -24,7 +24,8 @@
 // The fully-connected layer's dI (one output pixel, window = image) is a 1x1 convolution whose
 // output channels are the (h,w,c) of the input.  The layout changes are done by one strided
 // copy kernel.  What these forms do not cover (dI with a non-square window or pad > kh-1)
-// takes a plain gather kernel, one thread per element of dI.
+// takes the small-tile kernel (igemm_mid.hip), or, for capsules it cannot run, a plain gather
+// kernel, one thread per element of dI.
 #include <hip/hip_bf16.h>
 #include <hip/hip_fp16.h>
 
@@ -436,9 +437,10 @@ int launch_bwd_input(const ConvShape& s, const void* dout, const void* kernel, f
         ConvShape f[kMaxPhases];
         const int n = bwd_input_phases(s, f);
         const size_t room = bwd_input_workspace_bytes(s);
+        // (in the place of the gather kernel: like it, no tap outside the image)
         if (n > 0 && bwd_input_on_mid(s, f, n, room))
-            return status_from_hip(launch_igemm_mid(f, n, s.kernel_elems(), dout, kernel, din, workspace,
-                                                      room, stream));
+            return status_from_hip(launch_igemm_mid(f, n, s.kernel_elems(), dout, kernel, din, workspace, room,
+                                                    stream, !bwd_input_as_phases(s) && !bwd_input_as_conv(s)));
     }
     if (bwd_input_as_phases(s)) {
         char* ws = static_cast<char*>(workspace);

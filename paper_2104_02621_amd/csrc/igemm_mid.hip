@@ -61,6 +61,7 @@ struct MidParams {
     int k_sp, k_sq, k_kb, k_blk, k_sd0, k_sm, k_col, k_c2;  // kernel tensor, bytes
     int dc_shift;                     // log2 of the columns per output capsule row
     int cols, col_tiles, D0, tiles, nsplit, nphase, xcd_per;
+    int skip_taps;                    // see sum_inside
     FastDiv by_d1;
     long long out_sn, out_sx, out_sy, out_elems;  // elements
     int out_sm, out_sd0;
@@ -92,6 +93,42 @@ __device__ __forceinline__ int region_at(int r, int kb)
     const int g = kb % G, group = kb / G * (R * G * 1024);
     if (WIDE) return group + r * (G * 16) + ((g ^ row_swizzle<WIDE, G>(r)) << 4);
     return group + (r >> 2) * 128 + (((2 * g) ^ row_swizzle<WIDE, G>(r)) << 5) + (r & 3) * 8;
+}
+
+template <typename Tag>
+__device__ __forceinline__ float value_at(const void* base, long long byte)
+{
+    const char* at = static_cast<const char*>(base) + byte;
+    if constexpr (std::is_same_v<Tag, f32_tag>) return *reinterpret_cast<const float*>(at);
+    else if constexpr (std::is_same_v<Tag, f16_tag>) return (float)*reinterpret_cast<const _Float16*>(at);
+    else return __builtin_bit_cast(float, (unsigned)*reinterpret_cast<const unsigned short*>(at) << 16);
+}
+// One element of an input gradient (image n, window corner h, w, capsule row d1, column m, dc) as a plain sum
+// over the taps inside the image.  The matrix instructions multiply the zeros outside it by the kernel tensor's values, which
+// an infinite or NaN one there turns into a NaN.
+template <typename Tag>
+__device__ __forceinline__ float sum_inside(const MidParams& P, const MidPhase& F, int n, int h, int w, int d0, int d1, int m, int dc)
+{
+    constexpr int ES = sizeof(typename Tag::elem);
+    const int kh = F.kw > 0 ? F.kbs / (P.kpt * F.kw) : 0, row = P.d1_bytes / ES;
+    float acc = 0.f;
+    for (int p = 0; p < kh; ++p) {
+        if ((unsigned)(h + p) >= (unsigned)P.H) continue;
+        for (int q = 0; q < F.kw; ++q) {
+            if ((unsigned)(w + q) >= (unsigned)P.W) continue;
+            long long a = (((long long)n * P.H + h + p) * P.W + w + q) * P.pix_bytes + (long long)d0 * P.in_sd0 +
+                          (long long)d1 * P.d1_bytes;
+            long long b = F.k_base + (long long)p * P.k_sp + (long long)q * P.k_sq + (long long)d0 * P.k_sd0 +
+                          (long long)m * P.k_sm + (long long)dc * P.k_col;
+            for (int c = 0; c < P.C; ++c) {
+                for (int e = 0; e < row; ++e)
+                    acc = fmaf(value_at<Tag>(P.in, a + e * ES), value_at<Tag>(P.kernel, b + e * ES), acc);
+                a += (long long)P.D0 * P.in_sd0;
+                b += P.k_c2;
+            }
+        }
+    }
+    return acc;
 }
 
 // KT: the kernel tensor has its columns contiguous (transposing read), else its K values.  Tile:
@@ -324,6 +361,8 @@ __global__ __launch_bounds__(256, 2) void igemm_mid_kernel(const MidParams P)
 
     // ---- store: a lane holds 4 consecutive columns of a row, four times per 32 columns
     float* out = P.out + (P.nsplit > 1 ? (long long)split * P.out_elems : 0);
+    constexpr int KIND = OUT16 ? (std::is_same_v<Tag, f16_tag> ? 2 : 1) : 0;
+    float nan = 0.f;
 #pragma unroll
     for (int i = 0; i < TM; ++i) {
         const int r = row0 + arow + 32 * i;
@@ -342,9 +381,35 @@ __global__ __launch_bounds__(256, 2) void igemm_mid_kernel(const MidParams P)
                 const int m = col >> P.dc_shift, dc = col & ((1 << P.dc_shift) - 1);
                 const float16v& d = acc[0][i][j];
                 const float4v v = {d[4 * u], d[4 * u + 1], d[4 * u + 2], d[4 * u + 3]};
-                store4(out, at + (long long)m * P.out_sm + dc, v, OUT16 ? (std::is_same_v<Tag, f16_tag> ? 2 : 1) : 0);
+                store4(out, at + (long long)m * P.out_sm + dc, v, KIND);
+                if constexpr (!KT)
+#pragma unroll
+                    for (int k = 0; k < 4; ++k) nan = fmaf(v[k], 0.f, nan);  // NaN from an infinity or a NaN
             }
     }
+    // NaNs of a layer whose out-of-image taps must not count (unsplit K loops only): this lane's once more, one by one
+    if constexpr (!KT)
+        if (P.skip_taps && nan != 0.f)
+#pragma unroll 1
+            for (int t = 0; t < TM * TN * 4; ++t) {
+                const int r = row0 + arow + 32 * (t / (TN * 4));
+                const int col = col0 + wc * 32 * TN + 8 * (t % (TN * 4)) + 4 * half;
+                if (r >= rows || col >= P.cols) continue;
+                const unsigned pix = div_by((unsigned)r, P.by_d1), d1 = r - pix * P.D1;
+                const unsigned xr = div_by(pix, by_wo), y = pix - xr * Wo;
+                const unsigned n = div_by(xr, by_ho), x = xr - n * Ho;
+                const int m = col >> P.dc_shift, dc = col & ((1 << P.dc_shift) - 1);
+                const long long at = F.out_base + n * P.out_sn + x * P.out_sx + y * P.out_sy +
+                                     (long long)(d0 * P.out_sd0) + ((long long)d1 << P.dc_shift) +
+                                     (long long)m * P.out_sm + dc;
+#pragma unroll 1
+                for (int k = 0; k < 4; ++k) {
+                    const float got = OUT16 ? value_at<Tag>(out, (at + k) * 2) : out[at + k];
+                    if (got == got) continue;
+                    store1(out, at + k, sum_inside<Tag>(P, F, (int)n, (int)x * P.stride - F.pad_h,
+                                                        (int)y * P.stride - F.pad_w, d0, (int)d1, m, dc + k), KIND);
+                }
+            }
 }
 
 struct Strides {
@@ -663,9 +728,10 @@ double igemm_mid_us(const ConvShape* f, int n, size_t kernel_elems, size_t room)
 
 hipError_t launch_igemm_mid(const ConvShape* f, int n, size_t kernel_elems, const void* in,
                               const void* kernel, float* out, void* workspace, size_t room,
-                              hipStream_t stream)
+                              hipStream_t stream, bool skip_taps)
 {
-    MidPlan pl = mid_plan(f, n, kernel_elems, room);
+    MidPlan pl = mid_plan(f, n, kernel_elems, skip_taps ? 0 : room);
+    pl.P.skip_taps = skip_taps;
     pl.P.in = in;
     pl.P.kernel = kernel;
     float* partial = static_cast<float*>(workspace);

@@ -10,7 +10,8 @@ namespace capscaps {
 // kernel tensor read in place, tiles of 64 or 128 rows and columns.  `f`: one forward pass, or an input gradient as
 // one convolution or as the n phases of a strided layer (all written by the one launch; geometry
 // overrides allowed).  `kernel_elems`: of the whole kernel tensor.  Partial sums of a split K loop take
-// at most `room` bytes of the workspace.
+// at most `room` bytes of the workspace.  `skip_taps` (input gradients): an infinite or NaN kernel value reaches
+// only the pixels that its tap reaches (otherwise also, as a NaN, those whose tap lies outside the image).
 bool igemm_mid_eligible(const ConvShape* f, int n, size_t kernel_elems);
 // ... and is the library's choice for a convolution it can run and that `otherwise` would
 bool igemm_mid_preferred(const ConvShape& s, MfmaKernel otherwise, size_t room);
@@ -21,7 +22,7 @@ double igemm16_tuned_us(const ConvShape& s, MfmaKernel which);
 double igemm32_us(const ConvShape& s, MfmaKernel which);
 hipError_t launch_igemm_mid(const ConvShape* f, int n, size_t kernel_elems, const void* in,
                             const void* kernel, float* out, void* workspace, size_t room,
-                            hipStream_t stream);
+                            hipStream_t stream, bool skip_taps = false);
 
 // Kernel gradient of such layers (wgrad_mid.hip); partial sums take at most `room` bytes
 bool wgrad_mid_eligible(const ConvShape& s);

@@ -86,3 +86,31 @@ def test_infinities_stay_with_the_taps_that_meet_them(caps, dtype):
     inside[1:, 1:] = True
     assert np.isposinf(got[inside]).all()
     assert np.isfinite(got[~inside]).all()
+
+
+#                                N  H   W  C  M  kh kw s  p  caps
+@pytest.mark.parametrize("shape", [(2, 6, 5, 3, 4, 1, 3, 1, 1, (1, 8, 8, 8)), (2, 5, 5, 3, 4, 3, 3, 1, 4, (1, 4, 4, 4)),
+                                   (1, 9, 8, 5, 12, 3, 2, 1, 1, (2, 4, 8, 8)), (2, 9, 7, 3, 4, 3, 4, 2, 2, (1, 4, 4, 4)),
+                                   (20, 24, 23, 18, 16, 1, 5, 1, 2, (1, 8, 8, 8))], ids=_id)
+@pytest.mark.parametrize("dtype", [wl.FP32, wl.BF16, wl.FP16], ids=["fp32", "bf16", "fp16"])
+def test_infinite_weights_reach_only_their_pixels(shape, dtype):
+    """Input gradients of non-square windows and of paddings beyond k - 1 are sums over the taps inside the image: an
+    infinite and a NaN kernel value reach the pixels that these taps reach and no others."""
+    import torch
+    w = _layer(shape, dtype)
+    rng = np.random.default_rng(78)
+    k32 = rng.integers(1, 4, size=w.kernel_shape).astype(np.float32)
+    g32 = rng.integers(1, 3, size=w.out_shape).astype(np.float32)
+    k32[0, 0, 0, 0, 0, 0, 0] = np.inf
+    k32[-1, -1, 1, 1, 0, 1, 1] = np.nan
+    finite = np.where(np.isfinite(k32), k32, 0).astype(np.float32)
+    want = capsconv.conv_bwd_input(g32, finite, (w.H, w.W), w.stride, w.pad)
+    reach = lambda bad: capsconv.conv_bwd_input(g32, bad.astype(np.float32), (w.H, w.W), w.stride, w.pad) > 0
+    want[reach(np.isinf(k32))] = np.inf
+    want[reach(np.isnan(k32))] = np.nan
+    assert np.isfinite(want).any() and np.isinf(want).any() and np.isnan(want).any()
+    for out16 in (False,) if dtype == wl.FP32 else (False, True):
+        got = cc.conv_bwd_input(_gpu(g32, dtype), _gpu(k32, dtype), (w.H, w.W), w.stride, w.pad, out16=out16)
+        torch.cuda.synchronize()
+        ref = torch.from_numpy(want.astype(np.float32)).to(got.dtype).reshape(got.shape)
+        assert torch.equal(got.cpu().nan_to_num(nan=-1.0, posinf=-2.0), ref.nan_to_num(nan=-1.0, posinf=-2.0)), out16
