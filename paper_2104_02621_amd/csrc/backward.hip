@@ -237,7 +237,7 @@ int phase_kernel(const ConvShape& f)
 // kernel read the output gradient with its channels paired; it is paired once for all of them
 bool phases_pair_dout(const ConvShape& s) { return s.dtype != 0 && s.D3 == 4 && s.M % 2 == 0; }
 
-// The input gradient as phases in one launch of the small-tile 16-bit kernel (any window, padding and
+// The input gradient as phases in one launch of the small-tile kernel (any window, padding and
 // stride up to 4; a stride of 1 is one phase).  Returns their number, 0 if there are too many.
 constexpr int kMaxPhases = 16;
 int bwd_input_phases(const ConvShape& s, ConvShape (&f)[kMaxPhases])
@@ -326,38 +326,40 @@ ConvShape bwd_input_conv_shape(const ConvShape& s)
 }
 // fp32: against the estimates of what would run, the spread-out gradient's zeros counted in (20 random strided
 // layers: 19 of them 0.15 .. 0.85 times the time, one whose phases fill the bf16 kernel's tiles stays there)
-bool bwd_input_on_mid32(const ConvShape& s, const ConvShape* f, int n, size_t room)
+bool mid_preferred32(const ConvShape& s, const BwdInputPlan& plan, const ConvShape* f, int n, double us)
 {
     double other = 0;
-    if (bwd_input_as_phases(s)) {
+    if (plan.form == BwdInputPlan::Phases) {
         for (int i = 0; i < n; ++i)  // (the phases' launches overlap: 9 us less than their calls' times)
             if (f[i].kh * f[i].kw > 0) other += igemm32_us(f[i], MfmaKernel::Dma32) - 9.0;
-    } else if (bwd_input_as_conv(s)) {
-        const ConvShape c = bwd_input_conv_shape(s);
-        other = 8.0 + igemm32_us(c, mfma_auto_kernel(c));
     } else {
-        return true;
+        const ConvShape c = bwd_input_conv_shape(s);
+        other = 8.0 + igemm32_us(c, plan.fwd.kernel == MfmaKernel::Auto ? mfma_auto_kernel(c) : plan.fwd.kernel);
     }
-    return igemm_mid_us(f, n, s.kernel_elems(), room) < 0.75 * other;
+    return us < 0.75 * other;
 }
 
 // Strided layers, and the windows and paddings that the convolution form does not cover, on the small-tile
-// kernel: always where `dout` would be spread out (s^2 times the work) or gathered element by element
+// kernel: always where `dout` would be spread out (16-bit; s^2 times the work) or gathered element by element
 // (40 random layers: 0.2 .. 0.95 times the time), else
 // where one launch is estimated 30 % faster than the phases' launches on the tuned kernels.
 // Stride 1 otherwise is a convolution whose kernel the forward pass's rules pick.
-bool bwd_input_on_mid(const ConvShape& s, const ConvShape* f, int n, size_t room)
+MidPick bwd_input_on_mid(const ConvShape& s, const BwdInputPlan& plan, const ConvShape* f, int n)
 {
-    if (!igemm_mid_eligible(f, n, s.kernel_elems())) return false;
-    if (s.stride == 1 && bwd_input_as_conv(s)) return false;
-    if (s.dtype == 0) return bwd_input_on_mid32(s, f, n, room);
-    if (!bwd_input_as_phases(s)) return true;
-    double other = 0;
-    for (int i = 0; i < n; ++i) {
-        if (f[i].kh * f[i].kw == 0) continue;
-        other += igemm16_tuned_us(f[i], phase_kernel(f[i]) == 16 ? MfmaKernel::Tuned16 : MfmaKernel::Dma32);
+    if (!igemm_mid_eligible(f, n, s.kernel_elems())) return {};
+    const MidEstimate e = igemm_mid_best(f, n, plan.bytes);
+    bool take = true;
+    if (s.dtype == 0 && plan.form != BwdInputPlan::Gather) {
+        take = mid_preferred32(s, plan, f, n, e.us);
+    } else if (plan.form == BwdInputPlan::Phases) {
+        double other = 0;
+        for (int i = 0; i < n; ++i) {
+            if (f[i].kh * f[i].kw == 0) continue;
+            other += igemm16_tuned_us(f[i], phase_kernel(f[i]) == 16 ? MfmaKernel::Tuned16 : MfmaKernel::Dma32);
+        }
+        take = e.us < 0.7 * other;
     }
-    return igemm_mid_us(f, n, s.kernel_elems(), room) < 0.7 * other;
+    return take ? e.pick : MidPick{};
 }
 
 // dK as a forward convolution of the re-laid-out input with the (spread-out) output gradient
@@ -371,11 +373,17 @@ ConvShape bwd_kernel_conv_shape(const ConvShape& s)
 
 }  // namespace
 
-size_t bwd_input_workspace_bytes(const ConvShape& s)
+BwdInputPlan bwd_input_plan(const ConvShape& s)
 {
+    BwdInputPlan plan{BwdInputPlan::Gather, {}, 0};
     const size_t kbytes = align256(s.kernel_elems() * elem_bytes(s));
-    if (bwd_input_as_fc(s)) return kbytes + forward_workspace_bytes(bwd_input_fc_shape(s));
-    if (bwd_input_as_phases(s)) {
+    if (bwd_input_as_fc(s)) {
+        const ConvShape f = bwd_input_fc_shape(s);
+        plan.form = BwdInputPlan::FullyConnected;
+        plan.fwd = forward_choice(f);
+        plan.bytes = kbytes + forward_choice_bytes(f, plan.fwd);
+    } else if (bwd_input_as_phases(s)) {
+        plan.form = BwdInputPlan::Phases;
         size_t fwd = 0;
         for (int a = 0; a < s.stride; ++a)
             for (int b = 0; b < s.stride; ++b) {
@@ -388,61 +396,65 @@ size_t bwd_input_workspace_bytes(const ConvShape& s)
                 if (need > fwd) fwd = need;
             }
         // the phases' sub-kernels together are one kernel tensor
-        return kbytes + fwd + (phases_pair_dout(s) ? align256(s.out_elems() * elem_bytes(s)) : 0);
+        plan.bytes = kbytes + fwd + (phases_pair_dout(s) ? align256(s.out_elems() * elem_bytes(s)) : 0);
+    } else if (bwd_input_as_conv(s)) {
+        const ConvShape f = bwd_input_conv_shape(s);
+        plan.form = BwdInputPlan::Convolution;
+        plan.fwd = forward_choice(f);
+        plan.bytes = kbytes + (s.stride > 1 ? align256(spread_elems(s) * elem_bytes(s)) : 0) +
+                     forward_choice_bytes(f, plan.fwd);
     }
-    if (!bwd_input_as_conv(s)) return 0;
-    const size_t gbytes = s.stride > 1 ? align256(spread_elems(s) * elem_bytes(s)) : 0;
-    return kbytes + gbytes + forward_workspace_bytes(bwd_input_conv_shape(s));
+    return plan;
 }
 
 size_t bwd_kernel_workspace_bytes(const ConvShape& s)
 {
     if (wgrad16_eligible(s)) return wgrad16_workspace_bytes(s);
     if (wgrad32_eligible(s)) return wgrad32_workspace_bytes(s);
+    const ConvShape f = bwd_kernel_conv_shape(s);
     return align256(s.in_elems() * elem_bytes(s)) + align256(spread_elems(s) * elem_bytes(s)) +
-           align256(s.kernel_elems() * sizeof(float)) +
-           forward_workspace_bytes(bwd_kernel_conv_shape(s));
+           align256(s.kernel_elems() * sizeof(float)) + forward_choice_bytes(f, forward_choice(f));
 }
 
 // `din` holds fp32 elements, or with s.out16 set 16-bit elements of that kind (every route's
 // convolution shape carries s.out16 on, so its kernels round once at their stores).
-int launch_bwd_input(const ConvShape& s, const void* dout, const void* kernel, float* din,
-                     void* workspace, size_t workspace_bytes, hipStream_t stream)
+int launch_bwd_input(const ConvShape& s, const BwdInputPlan& plan, const void* dout, const void* kernel,
+                     float* din, void* workspace, size_t workspace_bytes, hipStream_t stream)
 {
     const int eb = elem_bytes(s);
     const long long sD3 = 1, sD2 = s.D3, sD0 = (long long)s.D2 * s.D3, sM = sD0 * s.D0,
                     sC = sM * s.M, sQ = sC * s.C, sP = sQ * s.kw;
-    if (bwd_input_as_fc(s)) {
+    if (plan.form == BwdInputPlan::FullyConnected) {
         char* ws = static_cast<char*>(workspace);
         const size_t used = align256(s.kernel_elems() * eb);
         // K2[m][(h,w,c)][d0][d3][d2] = K[h][w][c][m][d0][d2][d3]; (h,w,c) is one index of stride sC
         ConvShape f = bwd_input_fc_shape(s);
-        if (forward_auto_repacks_kernel(f)) {  // read in place, through the repack pass
+        if (plan.fwd.takes_kernel_view) {  // read in place
             f.kernel_view = true;
             f.k_sc = sM;
             f.k_sm = sC;
             f.k_sd0 = sD0;
             f.k_sd2 = sD3;
             f.k_sd3 = sD2;
-            return forward_auto(f, dout, kernel, din, ws + used, workspace_bytes - used, stream);
+            return forward_run(f, plan.fwd, dout, kernel, din, ws + used, workspace_bytes - used, stream);
         }
         const Permute7 pm = gather_into_dense(
             {1, 1, s.M, (long long)s.kh * s.kw * s.C, s.D0, s.D3, s.D2},
             {0, 0, sM, sC, sD0, sD3, sD2}, 0);
         hipError_t err = launch_permute(kernel, ws, pm, eb, stream);
         if (err != hipSuccess) return status_from_hip(err);
-        return forward_auto(f, dout, ws, din, ws + used, workspace_bytes - used, stream);
+        return forward_run(f, plan.fwd, dout, ws, din, ws + used, workspace_bytes - used, stream);
     }
-    {
+    if (s.stride > 1 || plan.form == BwdInputPlan::Gather) {
         ConvShape f[kMaxPhases];
         const int n = bwd_input_phases(s, f);
-        const size_t room = bwd_input_workspace_bytes(s);
         // (in the place of the gather kernel: like it, no tap outside the image)
-        if (n > 0 && bwd_input_on_mid(s, f, n, room))
-            return status_from_hip(launch_igemm_mid(f, n, s.kernel_elems(), dout, kernel, din, workspace, room,
-                                                    stream, !bwd_input_as_phases(s) && !bwd_input_as_conv(s)));
+        if (n > 0)
+            if (const MidPick pick = bwd_input_on_mid(s, plan, f, n))
+                return status_from_hip(launch_igemm_mid(f, n, s.kernel_elems(), pick, dout, kernel, din, workspace,
+                                                        stream, plan.form == BwdInputPlan::Gather));
     }
-    if (bwd_input_as_phases(s)) {
+    if (plan.form == BwdInputPlan::Phases) {
         char* ws = static_cast<char*>(workspace);
         const size_t kbytes = align256(s.kernel_elems() * eb);
         const long long pix = (long long)s.C * s.D0 * s.D1 * s.D2;
@@ -503,14 +515,14 @@ int launch_bwd_input(const ConvShape& s, const void* dout, const void* kernel, f
             }
         return 0;
     }
-    if (bwd_input_as_conv(s)) {
+    if (plan.form == BwdInputPlan::Convolution) {
         char* ws = static_cast<char*>(workspace);
         const void* kflip = ws;
         size_t used = align256(s.kernel_elems() * eb);
         // K'[p'][q'][m][c][d0][d3][d2] = K[kh-1-p'][kw-1-q'][c][m][d0][d2][d3]
         ConvShape f = bwd_input_conv_shape(s);
         hipError_t err = hipSuccess;
-        if (forward_auto_repacks_kernel(f)) {  // read in place, through the repack pass
+        if (plan.fwd.takes_kernel_view) {  // read in place
             f.kernel_view = true;
             f.k_base = (long long)(s.kh - 1) * sP + (long long)(s.kw - 1) * sQ;
             f.k_sp = -sP;
@@ -551,7 +563,7 @@ int launch_bwd_input(const ConvShape& s, const void* dout, const void* kernel, f
             if (err != hipSuccess) return status_from_hip(err);
             g = gs;
         }
-        return forward_auto(f, g, kflip, din, ws + used, workspace_bytes - used, stream);
+        return forward_run(f, plan.fwd, g, kflip, din, ws + used, workspace_bytes - used, stream);
     }
     const size_t total = s.in_elems();
     hipError_t err;
@@ -567,14 +579,11 @@ int launch_bwd_input(const ConvShape& s, const void* dout, const void* kernel, f
     return status_from_hip(err);
 }
 
-int launch_bwd_kernel(const ConvShape& s, const void* input, const void* dout, float* dkernel,
+int launch_bwd_kernel(const ConvShape& s, size_t need, const void* input, const void* dout, float* dkernel,
                       void* workspace, size_t workspace_bytes, hipStream_t stream)
 {
-    {
-        const size_t room = bwd_kernel_workspace_bytes(s);
-        if (wgrad_mid_preferred(s, room))
-            return status_from_hip(launch_wgrad_mid(s, input, dout, dkernel, workspace, room, stream));
-    }
+    if (const MidPick pick = wgrad_mid_choice(s, need))
+        return status_from_hip(launch_wgrad_mid(s, pick, input, dout, dkernel, workspace, stream));
     if (wgrad16_eligible(s))
         return status_from_hip(launch_wgrad16(s, input, dout, dkernel, workspace, stream));
     if (wgrad32_eligible(s))
@@ -613,8 +622,8 @@ int launch_bwd_kernel(const ConvShape& s, const void* input, const void* dout, f
         hipError_t err = launch_permute(dout, g_t, pm, eb, stream);
         if (err != hipSuccess) return status_from_hip(err);
     }
-    const int rc = forward_auto(bwd_kernel_conv_shape(s), in_t, g_t, dk_t, ws + used,
-                                workspace_bytes - used, stream);
+    const ConvShape f = bwd_kernel_conv_shape(s);
+    const int rc = forward_run(f, forward_choice(f), in_t, g_t, dk_t, ws + used, workspace_bytes - used, stream);
     if (rc != 0) return rc;
     // dK[p][q][c][m][d0][d2][d3] = dK'[c][p][q][m][d0][d2][d3]
     const long long caps = (long long)s.D0 * s.D2 * s.D3, sM = caps, sQ = sM * s.M,

@@ -9,6 +9,7 @@
 #include "mid_tiles.h"
 
 using capscaps::ConvShape;
+using Choice = capscaps::ForwardChoice;
 
 namespace {
 
@@ -58,30 +59,17 @@ int fill_shape(ConvShape& s, int N, int H, int W, int C, int M, int kh, int kw, 
 //     single-stage matrix-core kernel has the shorter latency);
 // it also serves what the matrix-core path cannot address.
 //
-// The path and, on the matrix cores, the kernel.  A call asks once: the kernels' plans take a
-// microsecond of host time together, which a launch-bound layer would wait for.
-struct Choice {
-    int path;
-    capscaps::MfmaKernel kernel;
-    // 16-bit: the layer runs on the small-tile kernel (igemm_mid.hip) instead.  Path, scratch and
-    // what is refused for lack of it stay those of `kernel`; the partial sums fit in that scratch.
-    bool mid = false;
-};
-bool runs_mid(const ConvShape& s, capscaps::MfmaKernel kernel)
-{
-    if (s.dtype == CAPSCAPS_FP32 && !s.in_gradient) return false;
-    if (!capscaps::igemm_mid_eligible(&s, 1, s.kernel_elems())) return false;
-    return capscaps::igemm_mid_preferred(s, kernel, capscaps::mfma_kernel_workspace_bytes(s, kernel));
-}
+// The path and, on the matrix cores, the kernel.  16-bit layers below the tuned kernels' sizes and fp32 input
+// gradients may run on the small-tile kernel instead (run_choice): path, scratch and what is refused for lack of
+// it stay those of `kernel`, and the partial sums fit in that scratch.
 Choice choose(const ConvShape& s)
 {
-    const Choice direct = {CAPSCAPS_PATH_DIRECT, capscaps::MfmaKernel::Auto};
+    const Choice direct = {CAPSCAPS_PATH_DIRECT, capscaps::MfmaKernel::Auto, false};
     if (!capscaps::mfma_supported(s)) return direct;
     const long long kdim = (long long)s.kh * s.kw * s.C * s.D2;
     if (kdim <= 24) return direct;
     const double flops = 2.0 * (double)s.out_elems() * (double)kdim;
     const capscaps::MfmaKernel kernel = capscaps::mfma_auto_kernel(s);
-    const bool mid = runs_mid(s, kernel);
     // (fp32 layers from 5e8 FLOPs on: the lane-per-row kernel where it is the choice, which contracts on
     // the bf16 matrix instructions -- 6x5 . 5x4 capsules, 8 columns, 9.9 GFLOP 399 against 1473 us;
     // 3x3x3 capsules, 6 columns, 0.5 GFLOP 32 against 153 us)
@@ -89,12 +77,12 @@ Choice choose(const ConvShape& s)
                          (kernel == capscaps::MfmaKernel::Dma32 || kernel == capscaps::MfmaKernel::Rechunk);
     if (!split32 && few_columns(s) && flops >= 5e7 && capscaps::wave_conv_eligible(s)) return direct;
     switch (kernel) {
-        case capscaps::MfmaKernel::Tuned16: return {CAPSCAPS_PATH_MFMA_TUNED16, kernel, mid};
-        case capscaps::MfmaKernel::Dma32: return {CAPSCAPS_PATH_MFMA_TUNED32, kernel, mid};
-        case capscaps::MfmaKernel::Small: return {CAPSCAPS_PATH_MFMA_SMALL, kernel, mid};
+        case capscaps::MfmaKernel::Tuned16: return {CAPSCAPS_PATH_MFMA_TUNED16, kernel, true};
+        case capscaps::MfmaKernel::Dma32: return {CAPSCAPS_PATH_MFMA_TUNED32, kernel, true};
+        case capscaps::MfmaKernel::Small: return {CAPSCAPS_PATH_MFMA_SMALL, kernel, true};
         // (the lane-per-row kernel again, but on a copy of the input that only the library's choice makes)
-        case capscaps::MfmaKernel::Rechunk: return {CAPSCAPS_PATH_MFMA, kernel};
-        default: return {CAPSCAPS_PATH_MFMA_GENERIC, kernel, mid};
+        case capscaps::MfmaKernel::Rechunk: return {CAPSCAPS_PATH_MFMA, kernel, true};
+        default: return {CAPSCAPS_PATH_MFMA_GENERIC, kernel, true};
     }
 }
 size_t scratch_bytes(const ConvShape& s, const Choice& c)
@@ -172,9 +160,9 @@ int run_choice(const void* input, const void* kernel, void* out, const ConvShape
     const size_t need = scratch_bytes(s, c);
     if (need > 0 && (workspace == nullptr || workspace_bytes < need)) return CAPSCAPS_EWORKSPACE;
     if (need > 0 && misaligned(workspace)) return CAPSCAPS_EINVAL;
-    if (c.mid)
-        return hip_status(capscaps::launch_igemm_mid(&s, 1, s.kernel_elems(), input, kernel, dst,
-                                                       workspace, need, stream));
+    if (const capscaps::MidPick pick = capscaps::igemm_mid_choice(s, c.kernel, need))
+        return hip_status(
+            capscaps::launch_igemm_mid(&s, 1, s.kernel_elems(), pick, input, kernel, dst, workspace, stream));
     return hip_status(capscaps::launch_mfma(s, input, kernel, dst, workspace, stream, c.kernel));
 }
 
@@ -190,11 +178,9 @@ int run(const void* input, const void* kernel, void* out, const ConvShape& s, in
                path == CAPSCAPS_PATH_MFMA_TUNED16 || path == CAPSCAPS_PATH_MFMA_TUNED32 ||
                path == CAPSCAPS_PATH_MFMA_SMALL) {
         if (!capscaps::mfma_supported(s)) return CAPSCAPS_EUNSUPPORTED;
-        if (path == CAPSCAPS_PATH_MFMA) {
-            const capscaps::MfmaKernel own = capscaps::mfma_auto_kernel(s);
-            return run_choice(input, kernel, out, s,
-                              {path, own, runs_mid(s, own)}, workspace, workspace_bytes, stream);
-        }
+        if (path == CAPSCAPS_PATH_MFMA)
+            return run_choice(input, kernel, out, s, {path, capscaps::mfma_auto_kernel(s), true}, workspace,
+                              workspace_bytes, stream);
         if (path == CAPSCAPS_PATH_MFMA_TUNED16 && !capscaps::mfma_tuned16_supported(s))
             return CAPSCAPS_EUNSUPPORTED;
         if (path == CAPSCAPS_PATH_MFMA_TUNED32 && !capscaps::mfma_dma32_supported(s))
@@ -225,16 +211,16 @@ namespace capscaps {
 
 int status_from_hip(hipError_t err) { return hip_status(err); }
 
-size_t forward_workspace_bytes(const ConvShape& s) { return scratch_bytes(s, choose(s)); }
+ForwardChoice forward_choice(const ConvShape& s) { return choose(s); }
 
-bool forward_auto_repacks_kernel(const ConvShape& s) { return choose(s).path != CAPSCAPS_PATH_DIRECT; }
+size_t forward_choice_bytes(const ConvShape& s, const ForwardChoice& c) { return scratch_bytes(s, c); }
 
-int forward_auto(const ConvShape& s, const void* in, const void* kernel, float* out,
-                 void* workspace, size_t workspace_bytes, hipStream_t stream)
+int forward_run(const ConvShape& s, const ForwardChoice& c, const void* in, const void* kernel, float* out,
+                void* workspace, size_t workspace_bytes, hipStream_t stream)
 {
     if (s.pad_w_set || s.out_view) return CAPSCAPS_EINVAL;
-    if (s.kernel_view && !forward_auto_repacks_kernel(s)) return CAPSCAPS_EINVAL;
-    return run(in, kernel, out, s, CAPSCAPS_PATH_AUTO, workspace, workspace_bytes, stream);
+    if (s.kernel_view && !c.takes_kernel_view) return CAPSCAPS_EINVAL;
+    return run_choice(in, kernel, out, s, c, workspace, workspace_bytes, stream);
 }
 
 int forward_tuned16(const ConvShape& s, const void* in, const void* kernel, float* out,
@@ -316,7 +302,7 @@ size_t capscaps_conv_fwd_out16_workspace_bytes(int N, int H, int W, int C, int M
     if (fill_shape(s, N, H, W, C, M, kh, kw, stride, pad, D0, D1, D2, D3, dtype) != CAPSCAPS_OK)
         return 0;
     s.out16 = dtype;
-    return capscaps::forward_workspace_bytes(s);
+    return scratch_bytes(s, choose(s));
 }
 
 int capscaps_conv_fwd_out16(const void* input, const void* kernel, void* out, int N, int H, int W,
@@ -391,7 +377,7 @@ size_t capscaps_conv_bwd_input_workspace_bytes(int N, int H, int W, int C, int M
     ConvShape s;
     if (fill_shape(s, N, H, W, C, M, kh, kw, stride, pad, D0, D1, D2, D3, dtype) != CAPSCAPS_OK)
         return 0;
-    return capscaps::bwd_input_workspace_bytes(s);
+    return capscaps::bwd_input_plan(s).bytes;
 }
 
 size_t capscaps_conv_bwd_kernel_workspace_bytes(int N, int H, int W, int C, int M, int kh, int kw,
@@ -414,10 +400,10 @@ int capscaps_conv_bwd_input(const void* dout, const void* kernel, void* dinput, 
     ConvShape s;
     const int rc = fill_shape(s, N, H, W, C, M, kh, kw, stride, pad, D0, D1, D2, D3, dtype);
     if (rc != CAPSCAPS_OK) return rc;
-    const size_t need = capscaps::bwd_input_workspace_bytes(s);
-    if (need > 0 && (workspace == nullptr || workspace_bytes < need)) return CAPSCAPS_EWORKSPACE;
-    if (need > 0 && misaligned(workspace)) return CAPSCAPS_EINVAL;
-    return capscaps::launch_bwd_input(s, dout, kernel, static_cast<float*>(dinput), workspace,
+    const capscaps::BwdInputPlan plan = capscaps::bwd_input_plan(s);
+    if (plan.bytes > 0 && (workspace == nullptr || workspace_bytes < plan.bytes)) return CAPSCAPS_EWORKSPACE;
+    if (plan.bytes > 0 && misaligned(workspace)) return CAPSCAPS_EINVAL;
+    return capscaps::launch_bwd_input(s, plan, dout, kernel, static_cast<float*>(dinput), workspace,
                                       workspace_bytes, static_cast<hipStream_t>(stream));
 }
 
@@ -430,7 +416,7 @@ size_t capscaps_conv_bwd_input_out16_workspace_bytes(int N, int H, int W, int C,
     if (fill_shape(s, N, H, W, C, M, kh, kw, stride, pad, D0, D1, D2, D3, dtype) != CAPSCAPS_OK)
         return 0;
     s.out16 = dtype;
-    return capscaps::bwd_input_workspace_bytes(s);
+    return capscaps::bwd_input_plan(s).bytes;
 }
 
 int capscaps_conv_bwd_input_out16(const void* dout, const void* kernel, void* dinput, int N, int H,
@@ -445,10 +431,10 @@ int capscaps_conv_bwd_input_out16(const void* dout, const void* kernel, void* di
     const int rc = fill_shape(s, N, H, W, C, M, kh, kw, stride, pad, D0, D1, D2, D3, dtype);
     if (rc != CAPSCAPS_OK) return rc;
     s.out16 = dtype;
-    const size_t need = capscaps::bwd_input_workspace_bytes(s);
-    if (need > 0 && (workspace == nullptr || workspace_bytes < need)) return CAPSCAPS_EWORKSPACE;
-    if (need > 0 && misaligned(workspace)) return CAPSCAPS_EINVAL;
-    return capscaps::launch_bwd_input(s, dout, kernel, static_cast<float*>(dinput), workspace,
+    const capscaps::BwdInputPlan plan = capscaps::bwd_input_plan(s);
+    if (plan.bytes > 0 && (workspace == nullptr || workspace_bytes < plan.bytes)) return CAPSCAPS_EWORKSPACE;
+    if (plan.bytes > 0 && misaligned(workspace)) return CAPSCAPS_EINVAL;
+    return capscaps::launch_bwd_input(s, plan, dout, kernel, static_cast<float*>(dinput), workspace,
                                       workspace_bytes, static_cast<hipStream_t>(stream));
 }
 
@@ -465,7 +451,7 @@ int capscaps_conv_bwd_kernel(const void* input, const void* dout, void* dkernel,
     const size_t need = capscaps::bwd_kernel_workspace_bytes(s);
     if (need > 0 && (workspace == nullptr || workspace_bytes < need)) return CAPSCAPS_EWORKSPACE;
     if (need > 0 && misaligned(workspace)) return CAPSCAPS_EINVAL;
-    return capscaps::launch_bwd_kernel(s, input, dout, static_cast<float*>(dkernel), workspace,
+    return capscaps::launch_bwd_kernel(s, need, input, dout, static_cast<float*>(dkernel), workspace,
                                        workspace_bytes, static_cast<hipStream_t>(stream));
 }
 

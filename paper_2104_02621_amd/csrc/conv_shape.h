@@ -104,15 +104,21 @@ hipError_t launch_mfma(const ConvShape& s, const void* in, const void* kernel, f
                        void* workspace, hipStream_t stream, MfmaKernel which = MfmaKernel::Auto);
 
 // The forward pass with the library's own path choice, and the scratch it needs (defined next
-// to the C ABI); used by the backward pass, which for stride 1 is two forward convolutions.
-// Both return a status code of the C ABI; `status_from_hip` maps a HIP error to one and
+// to the C ABI); used by the backward pass, which for stride 1 is two forward convolutions.  A call
+// chooses once (the kernels' plans take host time that a launch-bound layer waits for).
+// forward_run returns a status code of the C ABI; `status_from_hip` maps a HIP error to one and
 // records it for the ABI's diagnostic call.
-size_t forward_workspace_bytes(const ConvShape& s);
-int forward_auto(const ConvShape& s, const void* in, const void* kernel, float* out,
-                 void* workspace, size_t workspace_bytes, hipStream_t stream);
-// whether that choice is a matrix-core kernel, which takes the kernel tensor through a repack
-// pass and therefore accepts s.kernel_view (the wavefront-level path reads it densely)
-bool forward_auto_repacks_kernel(const ConvShape& s);
+struct ForwardChoice {
+    int path;           // CAPSCAPS_PATH_*
+    MfmaKernel kernel;  // on the matrix cores
+    // whether that is a matrix-core kernel, which takes the kernel tensor in place or through a repack
+    // pass and therefore accepts s.kernel_view (the wavefront-level path reads it densely)
+    bool takes_kernel_view;
+};
+ForwardChoice forward_choice(const ConvShape& s);
+size_t forward_choice_bytes(const ConvShape& s, const ForwardChoice& c);
+int forward_run(const ConvShape& s, const ForwardChoice& c, const void* in, const void* kernel, float* out,
+                void* workspace, size_t workspace_bytes, hipStream_t stream);
 // the tuned 16-bit kernel, geometry overrides allowed (EUNSUPPORTED if it cannot run the shape)
 int forward_tuned16(const ConvShape& s, const void* in, const void* kernel, float* out,
                     void* workspace, size_t workspace_bytes, hipStream_t stream);
@@ -121,13 +127,19 @@ int forward_tuned32(const ConvShape& s, const void* in, const void* kernel, floa
                     void* workspace, size_t workspace_bytes, hipStream_t stream);
 int status_from_hip(hipError_t err);
 
-// Backward pass (backward.hip): gradients with respect to input and kernel, fp32 results.
-size_t bwd_input_workspace_bytes(const ConvShape& s);
+// Backward pass (backward.hip): gradients with respect to input and kernel, fp32 results.  A plan is made
+// once per call; `bytes` is the scratch.
+struct BwdInputPlan {
+    enum Form { FullyConnected, Phases, Convolution, Gather } form;  // see backward.hip
+    ForwardChoice fwd;                                               // of the first and the third
+    size_t bytes;
+};
+BwdInputPlan bwd_input_plan(const ConvShape& s);
 size_t bwd_kernel_workspace_bytes(const ConvShape& s);
-// Return a status code of the C ABI.
-int launch_bwd_input(const ConvShape& s, const void* dout, const void* kernel, float* din,
-                     void* workspace, size_t workspace_bytes, hipStream_t stream);
-int launch_bwd_kernel(const ConvShape& s, const void* input, const void* dout, float* dkernel,
+// Return a status code of the C ABI; the caller has checked the scratch (`need`: of the kernel gradient).
+int launch_bwd_input(const ConvShape& s, const BwdInputPlan& plan, const void* dout, const void* kernel,
+                     float* din, void* workspace, size_t workspace_bytes, hipStream_t stream);
+int launch_bwd_kernel(const ConvShape& s, size_t need, const void* input, const void* dout, float* dkernel,
                       void* workspace, size_t workspace_bytes, hipStream_t stream);
 
 // The paper's second scheme (Algorithm 5) as a comparison implementation (scheme2.hip).

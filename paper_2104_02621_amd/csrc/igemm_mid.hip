@@ -24,6 +24,7 @@
 // zeros (padding taps, missing rows and columns, the K tail).
 // The input gradient of a strided layer is stride^2 convolutions on interleaved pixels ("phases");
 // all of them run in the one launch.
+#include <algorithm>
 #include <atomic>
 
 #include "igemm_common.h"
@@ -433,9 +434,7 @@ struct MidPlan {
     MidParams P;
     bool wide, kt, out16;
     int ra, rb, wc, g;
-    double us;  // estimated
     long long blocks;
-    size_t partial_bytes;
 };
 
 int elem_size(const ConvShape& s) { return s.dtype == 0 ? 4 : 2; }
@@ -447,6 +446,17 @@ int mid_group(const ConvShape& s)
     const int row = s.D2 * elem_size(s) / 2;
     if (row % 8 != 0) return 2;
     return s.D1 <= 2 ? 4 : row >= 16 ? 2 : 1;
+}
+// K blocks of a tap, as they are and padded to whole copies
+int k_blocks(const ConvShape& s)
+{
+    const int row = s.D2 * elem_size(s) / 2;
+    return row % 8 == 0 ? s.C << log2_of(row / 8) : (s.C + 1) / 2;
+}
+int padded_k_blocks(const ConvShape& s)
+{
+    const int g = mid_group(s);
+    return (k_blocks(s) + g - 1) / g * g;
 }
 
 // Tiles, and what they take: us per stage with one, two, three workgroups on a CU, stages' worth of
@@ -469,29 +479,35 @@ constexpr Tile TILES32[] = {{1, 1, 64, 8, 3, {0.757, 1.133, 1.622}, 2.4, 2.3},
                             {2, 1, 64, 4, 3, {0.687, 1.198, 1.548}, 3.5, 3.0},
                             {2, 2, 128, 4, 2, {1.174, 2.081, 2.081}, 3.0, 3.6},
                             {2, 1, 32, 4, 3, {0.470, 0.713, 0.932}, 3.8, 2.8}};
-struct Choice {
-    int tile, nsplit;
-    double us;
-};
-Choice choose(const ConvShape* f, int n, int kpt, int cols, size_t room)
+
+}  // namespace
+
+MidEstimate igemm_mid_best(const ConvShape* f, int n, size_t room)
 {
     const ConvShape& s = f[0];
+    const int kpt = padded_k_blocks(s), cols = s.M * s.D3;
     const double out_bytes = 4.0 * (s.out_view ? (double)s.out_alloc : (double)s.out_elems());
-    Choice best{0, 1, 1e30};
+    MidEstimate best{{0, 1}, 1e30};
     for (int t = 0; t < 5; ++t) {
         const Tile& tl = s.dtype == 0 ? TILES32[t] : TILES[t];
         if ((tl.bn == 32 && cols > 96) || (tl.bn == 128 && cols <= 64)) continue;
         // (a launch-bound call waits for this: rows and stages of the phases once per tile, and no more
         // pieces once they have made it slower)
         int row_tiles[MAX_PHASES], stages_of[MAX_PHASES];
-        double tiles = 0, tile_best = 1e30;
+        double tiles = 0, work = 0, tile_best = 1e30;
         for (int i = 0; i < n; ++i) {
             row_tiles[i] = (int)((unsigned)(f[i].pixels() * s.D1 + 64 * tl.ra - 1) / (64u * tl.ra));
             stages_of[i] = (int)((unsigned)(f[i].kh * f[i].kw * kpt + tl.kbs - 1) / (unsigned)tl.kbs);
             tiles += row_tiles[i];
+            work += (double)row_tiles[i] * stages_of[i];
         }
-        const double per_split = tiles * ((cols + tl.bn - 1) / tl.bn) * s.D0, round = 256.0 * tl.wgs;
+        const double across = (double)((cols + tl.bn - 1) / tl.bn) * s.D0, per_split = tiles * across;
+        const double round = 256.0 * tl.wgs, rate = 0.95 * tl.us[tl.wgs - 1] / round;
         for (int nsplit = 1; nsplit <= 32; nsplit += nsplit < 4 ? 1 : nsplit / 2) {
+            // (this and more pieces take so long at least: a workgroup's set-up, or all of them at the full chip's rate)
+            const double least = std::max(tl.extra * tl.us[0], (work * across + per_split * nsplit * tl.extra) * rate) +
+                                 tl.call + (nsplit > 1 ? 3.0 + nsplit * out_bytes * 2.5e-7 : 0.0);
+            if (least >= best.us || (nsplit > 1 && nsplit * out_bytes > (double)room)) break;
             int most = 0;
             double sum = 0;
             for (int i = 0; i < n; ++i) {
@@ -499,14 +515,14 @@ Choice choose(const ConvShape* f, int n, int kpt, int cols, size_t room)
                 sum += (double)row_tiles[i] * st;
                 if (st > most) most = st;
             }
-            if (nsplit > 1 && (most < 2 || nsplit * out_bytes > (double)room)) break;
+            if (nsplit > 1 && most < 2) break;
             const double stages = sum / tiles, blocks = per_split * nsplit;
             const double full = (double)(long long)(blocks / round), rest = blocks - full * round;
             double us = tl.call + full * (stages + tl.extra) * tl.us[tl.wgs - 1];
             if (rest > 0)
                 us += ((full > 0 ? stages : (double)most) + tl.extra) * tl.us[(int)((rest + 255) / 256) - 1];
-            if (nsplit > 1) us += 3.0 + nsplit * out_bytes / 4e6;
-            if (us < best.us) best = {t, nsplit, us};
+            if (nsplit > 1) us += 3.0 + nsplit * out_bytes * 2.5e-7;
+            if (us < best.us) best = {{t, nsplit}, us};
             if (us < tile_best) tile_best = us;
             if (blocks >= 1024 || (nsplit > 2 && us > 1.1 * tile_best)) break;
         }
@@ -514,8 +530,9 @@ Choice choose(const ConvShape* f, int n, int kpt, int cols, size_t room)
     return best;
 }
 
-// `room`: bytes of workspace partial sums may take
-MidPlan mid_plan(const ConvShape* f, int n, size_t kernel_elems, size_t room)
+namespace {
+
+MidPlan mid_plan(const ConvShape* f, int n, size_t kernel_elems, MidPick pick)
 {
     MidPlan pl{};
     MidParams& P = pl.P;
@@ -534,9 +551,9 @@ MidPlan mid_plan(const ConvShape* f, int n, size_t kernel_elems, size_t room)
     P.kb_shift = pl.wide ? log2_of(row / 8) : 0;
     P.kb_mask = (1 << P.kb_shift) - 1;
     P.in_kb = s.D0 * P.in_sd0 * (pl.wide ? 1 : 2);
-    P.kq = pl.wide ? s.C << P.kb_shift : (s.C + 1) / 2;
+    P.kq = k_blocks(s);
     pl.g = mid_group(s);
-    P.kpt = (P.kq + pl.g - 1) / pl.g * pl.g;
+    P.kpt = padded_k_blocks(s);
     P.kpt_magic = P.kpt == 1 ? 0u : (unsigned)(((1ull << 32) + P.kpt - 1) / P.kpt);
     P.k_sp = (int)(k.sp * es); P.k_sq = (int)(k.sq * es); P.k_sd0 = (int)(k.sd0 * es);
     P.k_sm = (int)(k.sm * es); P.k_c2 = (int)(k.sc * es);
@@ -554,13 +571,10 @@ MidPlan mid_plan(const ConvShape* f, int n, size_t kernel_elems, size_t room)
     P.out_sx = s.out_view ? s.out_sx : pix * s.Wo;
     P.out_sn = s.out_view ? s.out_sn : pix * s.Wo * s.Ho;
     P.out_elems = s.out_view ? s.out_alloc : (long long)s.out_elems();
-    // tile and split of the K loop: the least estimated time
-    const Choice ch = choose(f, n, P.kpt, P.cols, room);
-    const Tile& tl = TILES[ch.tile];  // (the same shapes for both)
+    const Tile& tl = TILES[pick.tile];  // (the same shapes for both)
     pl.ra = tl.ra;
     pl.rb = tl.rb;
     pl.wc = tl.bn == 32 ? 1 : 2;
-    pl.us = ch.us;
     P.col_tiles = ceil_div(P.cols, tl.bn);
     const int kbs = tl.kbs;
     int row_tiles = 0;
@@ -580,12 +594,11 @@ MidPlan mid_plan(const ConvShape* f, int n, size_t kernel_elems, size_t room)
     }
     const long long tiles = (long long)row_tiles * P.col_tiles * s.D0;
     P.tiles = (int)tiles;
-    const int nsplit = ch.nsplit;
+    const int nsplit = pick.nsplit;
     P.nsplit = nsplit;
     for (int i = 0; i < n; ++i) P.ph[i].stages_per_split = ceil_div(ceil_div(P.ph[i].kbs, kbs), nsplit);
     pl.blocks = tiles * nsplit;
     P.xcd_per = (int)(pl.blocks / 8);
-    pl.partial_bytes = nsplit > 1 ? (size_t)nsplit * P.out_elems * 4 : 0;
     pl.out16 = s.out16 != 0 && nsplit == 1;  // (with a split the reduction rounds)
     return pl;
 }
@@ -704,33 +717,28 @@ double igemm16_tuned_us(const ConvShape& s, MfmaKernel which)
 // through strides or after a repack pass, from 24 columns on, but for a few tiles of a long K loop (28 random layers 0.41 .. 0.85 times the time, one
 // of 5.6 us 0.3 us slower; 8 and 16 columns 1.13 and 1.2 times); against the kernel on bf16 instructions where
 // the estimates differ by a quarter.
-bool igemm_mid_preferred(const ConvShape& s, MfmaKernel otherwise, size_t room)
+MidPick igemm_mid_choice(const ConvShape& s, MfmaKernel otherwise, size_t room)
 {
-    if (s.dtype == 0) {
-        if (otherwise == MfmaKernel::Generic || otherwise == MfmaKernel::Small)
-            return (long long)s.M * s.D3 >= 24 &&
-                   (2.0 * (double)s.out_elems() * s.kh * s.kw * s.C * s.D2 >= 1e8 ||
-                    mid_plan(&s, 1, s.kernel_elems(), room).us < 12);
-        return otherwise == MfmaKernel::Dma32 &&
-               mid_plan(&s, 1, s.kernel_elems(), room).us < 0.75 * igemm32_us(s, otherwise);
-    }
-    if (otherwise == MfmaKernel::Generic) return true;
-    const double us = mid_plan(&s, 1, s.kernel_elems(), room).us;
-    if (otherwise == MfmaKernel::Small)
-        return us <= 9.5 || 2.0 * (double)s.out_elems() * s.kh * s.kw * s.C * s.D2 >= 3e7;
-    return us < 0.7 * igemm16_tuned_us(s, otherwise);
+    if ((s.dtype == 0 && !s.in_gradient) || !igemm_mid_eligible(&s, 1, s.kernel_elems())) return {};
+    const double flops = 2.0 * (double)s.out_elems() * s.kh * s.kw * s.C * s.D2;
+    const bool tuned = otherwise != MfmaKernel::Generic && otherwise != MfmaKernel::Small;
+    if (s.dtype == 0 && (tuned ? otherwise != MfmaKernel::Dma32 : (long long)s.M * s.D3 < 24)) return {};
+    const MidEstimate e = igemm_mid_best(&s, 1, room);
+    bool take;
+    if (s.dtype == 0)
+        take = tuned ? e.us < 0.75 * igemm32_us(s, otherwise) : flops >= 1e8 || e.us < 12;
+    else if (tuned)
+        take = e.us < 0.7 * igemm16_tuned_us(s, otherwise);
+    else
+        take = otherwise == MfmaKernel::Generic || e.us <= 9.5 || flops >= 3e7;
+    return take ? e.pick : MidPick{};
 }
 
-double igemm_mid_us(const ConvShape* f, int n, size_t kernel_elems, size_t room)
+hipError_t launch_igemm_mid(const ConvShape* f, int n, size_t kernel_elems, MidPick pick, const void* in,
+                            const void* kernel, float* out, void* workspace, hipStream_t stream, bool skip_taps)
 {
-    return mid_plan(f, n, kernel_elems, room).us;
-}
-
-hipError_t launch_igemm_mid(const ConvShape* f, int n, size_t kernel_elems, const void* in,
-                              const void* kernel, float* out, void* workspace, size_t room,
-                              hipStream_t stream, bool skip_taps)
-{
-    MidPlan pl = mid_plan(f, n, kernel_elems, skip_taps ? 0 : room);
+    if (skip_taps) pick.nsplit = 1;  // (partial sums cannot tell)
+    MidPlan pl = mid_plan(f, n, kernel_elems, pick);
     pl.P.skip_taps = skip_taps;
     pl.P.in = in;
     pl.P.kernel = kernel;

@@ -6,6 +6,16 @@
 
 namespace capscaps {
 
+// Tile (an index into the kernel's table; negative: the layer stays on another kernel) and pieces of the K loop.
+struct MidPick {
+    int tile = -1, nsplit = 1;
+    explicit operator bool() const { return tile >= 0; }
+};
+struct MidEstimate {
+    MidPick pick;
+    double us;
+};
+
 // Forward pass (16-bit) and input gradient of layers below the tuned kernels' sizes (igemm_mid.hip): one launch,
 // kernel tensor read in place, tiles of 64 or 128 rows and columns.  `f`: one forward pass, or an input gradient as
 // one convolution or as the n phases of a strided layer (all written by the one launch; geometry
@@ -13,22 +23,22 @@ namespace capscaps {
 // at most `room` bytes of the workspace.  `skip_taps` (input gradients): an infinite or NaN kernel value reaches
 // only the pixels that its tap reaches (otherwise also, as a NaN, those whose tap lies outside the image).
 bool igemm_mid_eligible(const ConvShape* f, int n, size_t kernel_elems);
-// ... and is the library's choice for a convolution it can run and that `otherwise` would
-bool igemm_mid_preferred(const ConvShape& s, MfmaKernel otherwise, size_t room);
-// estimated times, us: of this kernel, and of Tuned16 or Dma32
-double igemm_mid_us(const ConvShape* f, int n, size_t kernel_elems, size_t room);
+MidEstimate igemm_mid_best(const ConvShape* f, int n, size_t room);  // the least estimated time
+// the library's choice for a convolution that `otherwise` would run
+MidPick igemm_mid_choice(const ConvShape& s, MfmaKernel otherwise, size_t room);
+// estimated time of Tuned16 or Dma32, us
 double igemm16_tuned_us(const ConvShape& s, MfmaKernel which);
 // ... of the fp32 kernels (igemm32_dma.hip)
 double igemm32_us(const ConvShape& s, MfmaKernel which);
-hipError_t launch_igemm_mid(const ConvShape* f, int n, size_t kernel_elems, const void* in,
-                            const void* kernel, float* out, void* workspace, size_t room,
-                            hipStream_t stream, bool skip_taps = false);
+hipError_t launch_igemm_mid(const ConvShape* f, int n, size_t kernel_elems, MidPick pick, const void* in,
+                            const void* kernel, float* out, void* workspace, hipStream_t stream,
+                            bool skip_taps = false);
 
 // Kernel gradient of such layers (wgrad_mid.hip); partial sums take at most `room` bytes
 bool wgrad_mid_eligible(const ConvShape& s);
-bool wgrad_mid_preferred(const ConvShape& s, size_t room);  // ... and is the library's choice
-hipError_t launch_wgrad_mid(const ConvShape& s, const void* input, const void* dout, float* dkernel,
-                            void* workspace, size_t room, hipStream_t stream);
+MidPick wgrad_mid_choice(const ConvShape& s, size_t room);  // the library's
+hipError_t launch_wgrad_mid(const ConvShape& s, MidPick pick, const void* input, const void* dout, float* dkernel,
+                            void* workspace, hipStream_t stream);
 double wgrad32_us(const ConvShape& s);  // estimated time of launch_wgrad32, us
 
 namespace {

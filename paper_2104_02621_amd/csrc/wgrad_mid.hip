@@ -16,6 +16,7 @@
 //     (capsules of 8 and 16 rows: one pixel per copy, a lane read; of 1, 2, 4: 8, 4, 2 pixels per copy,
 //     each lane fetches its own).
 //   * The K loop is cut into equal ranges over workgroups; splitk_reduce adds the pieces in a fixed order.
+#include <algorithm>
 #include <atomic>
 
 #include "igemm_common.h"
@@ -276,18 +277,64 @@ constexpr Tile TILES32[] = {{1, 1, 8, 3, {0.700, 1.196, 1.572}, 2.5, 1.5},
                             {2, 1, 4, 3, {0.679, 1.172, 1.585}, 3.0, 1.7},
                             {2, 2, 4, 2, {1.136, 2.064, 2.064}, 1.0, 3.5}};
 
+const Tile& tile_of(const ConvShape& s, int tile) { return s.dtype == 0 ? TILES32[tile] : TILES[tile]; }
+// blocks of 64 rows per tap (see WmidParams)
+int row_blocks_per_tap(const ConvShape& s, int ra)
+{
+    const int blocks = ceil_div((long long)s.C * s.D2, 64);
+    return s.pad > 0 ? ceil_div(blocks, ra) * ra : blocks;
+}
+int k_blocks(const ConvShape& s) { return ceil_div(s.pixels() * s.D1, s.dtype == 0 ? 4 : 8); }
+
+// tile and ranges: the least estimated time
+MidEstimate wgrad_mid_best(const ConvShape& s, size_t room)
+{
+    const double out_bytes = 4.0 * (double)s.kernel_elems();
+    const int kbs = k_blocks(s);
+    const double slow = s.D1 <= 2 && s.dtype != 0 ? 1.3 : 1.0;
+    MidEstimate best{{0, 1}, 1e30};
+    for (int t = 0; t < 4; ++t) {
+        const Tile& tl = tile_of(s, t);
+        const long long tiles = (long long)ceil_div((long long)s.kh * s.kw * row_blocks_per_tap(s, tl.ra), tl.ra) *
+                                ceil_div((long long)s.M * s.D3, 64 * tl.rb) * s.D0;
+        const int all = ceil_div(kbs, tl.kbs);
+        const double round = 256.0 * tl.wgs, rate = 0.95 * tl.us[tl.wgs - 1] * slow / round;
+        double tile_best = 1e30;
+        for (int nsplit = 1; nsplit <= 512; nsplit += nsplit < 4 ? 1 : nsplit / 4) {
+            // (this and more ranges take so long at least: a workgroup's set-up, or all of them at the full chip's rate)
+            const double least = std::max(tl.extra * tl.us[0], (double)tiles * (all + nsplit * tl.extra) * rate) +
+                                 tl.call + (nsplit > 1 ? 3.0 + nsplit * out_bytes * 2.5e-7 : 0.0);
+            if (least >= best.us) break;
+            const int stages = (all + nsplit - 1) / nsplit;
+            if (nsplit > 1 && (stages < 2 || (double)nsplit * out_bytes > (double)room)) break;
+            const double wgs = (double)tiles * nsplit;
+            const double full = (double)(long long)(wgs / round), rest = wgs - full * round;
+            double us = tl.call + full * (stages + tl.extra) * tl.us[tl.wgs - 1] * slow;
+            if (rest > 0) us += (stages + tl.extra) * tl.us[(int)((rest + 255) / 256) - 1] * slow;
+            if (nsplit > 1) us += 3.0 + nsplit * out_bytes * 2.5e-7;
+            if (us < tile_best) tile_best = us;
+            if (us < best.us) best = {{t, nsplit}, us};
+            // (no more ranges once they have made it slower)
+            if (wgs >= 1536 || (nsplit > 2 && us > 1.1 * tile_best)) break;
+        }
+    }
+    return best;
+}
+
 struct WmidPlan {
     WmidParams P;
     int ra, rb;
-    double us;
     long long blocks;
 };
 
-WmidPlan wmid_plan(const ConvShape& s, size_t room)
+WmidPlan wmid_plan(const ConvShape& s, MidPick pick)
 {
     WmidPlan pl{};
     WmidParams& P = pl.P;
     const int es = s.dtype == 0 ? 4 : 2;
+    const Tile& tl = tile_of(s, pick.tile);
+    pl.ra = tl.ra;
+    pl.rb = tl.rb;
     P.in_bytes = (unsigned)(s.in_elems() * es);
     P.g_bytes = (unsigned)(s.out_elems() * es);
     P.H = s.H; P.W = s.W; P.stride = s.stride; P.pad = s.pad; P.kw = s.kw; P.C = s.C; P.D0 = s.D0;
@@ -303,52 +350,21 @@ WmidPlan wmid_plan(const ConvShape& s, size_t room)
     P.cols = s.M * s.D3;
     P.d2_shift = log2_of(s.D2);
     P.d3_shift = log2_of(s.D3);
-    const int blocks = ceil_div(P.rows, 64);
     P.pixels = (int)s.pixels();
-    P.kbs = ceil_div((long long)P.pixels * s.D1, 16 / es);
+    P.kbs = k_blocks(s);
     P.Wo = s.Wo; P.Ho = s.Ho;
     P.by_wo = fast_div(s.Wo);
     P.by_ho = fast_div(s.Ho);
     P.out_sm = s.D0 * s.D2 * s.D3;
     P.out_sd0 = s.D2 * s.D3;
     P.out_elems = (long long)s.kernel_elems();
-    const double out_bytes = 4.0 * (double)P.out_elems;
-    pl.us = 1e30;
-    int kbs = 8;
-    P.nsplit = 1;
-    for (const Tile& tl : s.dtype == 0 ? TILES32 : TILES) {
-        const int per_tap = s.pad > 0 ? ceil_div(blocks, tl.ra) * tl.ra : blocks;
-        const long long tiles = (long long)ceil_div((long long)s.kh * s.kw * per_tap, tl.ra) * ceil_div(P.cols, 64 * tl.rb) * s.D0;
-        const int all = ceil_div(P.kbs, tl.kbs);
-        double tile_best = 1e30;
-        for (int nsplit = 1; nsplit <= 512; nsplit += nsplit < 4 ? 1 : nsplit / 4) {
-            const int stages = (all + nsplit - 1) / nsplit;
-            if (nsplit > 1 && (stages < 2 || (double)nsplit * out_bytes > (double)room)) break;
-            const double wgs = (double)tiles * nsplit, round = 256.0 * tl.wgs;
-            const double full = (double)(long long)(wgs / round), rest = wgs - full * round;
-            const double slow = s.D1 <= 2 && s.dtype != 0 ? 1.3 : 1.0;
-            double us = tl.call + full * (stages + tl.extra) * tl.us[tl.wgs - 1] * slow;
-            if (rest > 0) us += (stages + tl.extra) * tl.us[(int)((rest + 255) / 256) - 1] * slow;
-            if (nsplit > 1) us += 3.0 + nsplit * out_bytes / 4e6;
-            if (us < tile_best) tile_best = us;
-            if (us < pl.us) {
-                pl.us = us;
-                pl.ra = tl.ra;
-                pl.rb = tl.rb;
-                P.nsplit = nsplit;
-                kbs = tl.kbs;
-            }
-            // (no more ranges once they have made it slower)
-            if (wgs >= 1536 || (nsplit > 2 && us > 1.1 * tile_best)) break;
-        }
-    }
-    P.blocks_per_tap = s.pad > 0 ? ceil_div(blocks, pl.ra) * pl.ra : blocks;
+    P.blocks_per_tap = row_blocks_per_tap(s, pl.ra);
     P.row_blocks = s.kh * s.kw * P.blocks_per_tap;
     P.row_tiles = ceil_div(P.row_blocks, pl.ra);
     P.col_tiles = ceil_div(P.cols, 64 * pl.rb);
     P.tiles = P.row_tiles * P.col_tiles * s.D0;
-    P.stages_per_split = ceil_div(ceil_div(P.kbs, kbs), P.nsplit);
-    P.nsplit = ceil_div(ceil_div(P.kbs, kbs), P.stages_per_split);
+    P.stages_per_split = ceil_div(ceil_div(P.kbs, tl.kbs), pick.nsplit);
+    P.nsplit = ceil_div(ceil_div(P.kbs, tl.kbs), P.stages_per_split);
     pl.blocks = (long long)P.tiles * P.nsplit;
     P.xcd_per = (int)(pl.blocks / 8);
     return pl;
@@ -419,26 +435,27 @@ bool wgrad_mid_eligible(const ConvShape& s)
 // Against wgrad16_kernel where it is estimated a fifth faster (that kernel: 21 us and its 256 x 256 tiles' FLOPs
 // at 1.23 PFLOP/s, fitted over the same layers, 26 % root mean square; 57 of the 70 layers leave it, for 0.15 ..
 // 0.9 of its time).  Against the kernel gradient as a convolution always.
-bool wgrad_mid_preferred(const ConvShape& s, size_t room)
+MidPick wgrad_mid_choice(const ConvShape& s, size_t room)
 {
-    if (!wgrad_mid_eligible(s)) return false;
+    if (!wgrad_mid_eligible(s)) return {};
+    const bool other = s.dtype == 0 ? wgrad32_eligible(s) : wgrad16_eligible(s);
     // fp32: where estimated 15 % faster than wgrad32_kernel (47 random layers: the 22 that leave it take 0.37 .. 0.97
     // of its time)
     // and at least 64 K values (shorter sums have fewer roundings there: 3e-8 against 5e-8)
-    if (s.dtype == 0)
-        return !wgrad32_eligible(s) ||
-               (s.pixels() * s.D1 >= 64 && wmid_plan(s, room).us < 0.85 * wgrad32_us(s));
-    if (!wgrad16_eligible(s)) return true;
+    if (other && s.dtype == 0 && s.pixels() * s.D1 < 64) return {};
+    const MidEstimate e = wgrad_mid_best(s, room);
+    if (!other) return e.pick;
+    if (s.dtype == 0) return e.us < 0.85 * wgrad32_us(s) ? e.pick : MidPick{};
     const int rows = s.C * s.D2, cols = s.M * s.D3, nt = rows > 128 ? 1 : rows > 64 ? 2 : 4;
     const double gflop = 2e-9 * (double)(s.pixels() * s.D1) * ceil_div(s.kh * s.kw, nt) * s.D0 *
                          (256.0 * ceil_div(rows, 256)) * (256.0 * ceil_div(cols, 256));
-    return wmid_plan(s, room).us < 0.8 * (21.0 + gflop / 1.23);
+    return e.us < 0.8 * (21.0 + gflop / 1.23) ? e.pick : MidPick{};
 }
 
-hipError_t launch_wgrad_mid(const ConvShape& s, const void* input, const void* dout, float* dkernel,
-                              void* workspace, size_t room, hipStream_t stream)
+hipError_t launch_wgrad_mid(const ConvShape& s, MidPick pick, const void* input, const void* dout, float* dkernel,
+                            void* workspace, hipStream_t stream)
 {
-    WmidPlan pl = wmid_plan(s, room);
+    WmidPlan pl = wmid_plan(s, pick);
     pl.P.in = input;
     pl.P.g = dout;
     float* partial = static_cast<float*>(workspace);
