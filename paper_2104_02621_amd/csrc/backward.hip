@@ -177,6 +177,13 @@ hipError_t launch_1d(Kern kern, size_t total, hipStream_t stream, Args... args)
 size_t align256(size_t b) { return (b + 255) & ~(size_t)255; }
 int elem_bytes(const ConvShape& s) { return s.dtype == 0 ? 4 : 2; }
 
+void same_small_tiles(ConvShape& f, const ConvShape& s)
+{
+    f.mid_use = s.mid_use;
+    f.mid_tile = s.mid_tile;
+    f.mid_split = s.mid_split;
+}
+
 // extents of the output gradient spread out to stride 1
 int spread_h(const ConvShape& s) { return s.H + 2 * s.pad - s.kh + 1; }
 int spread_w(const ConvShape& s) { return s.W + 2 * s.pad - s.kw + 1; }
@@ -208,6 +215,7 @@ ConvShape bwd_input_phase_shape(const ConvShape& s, const PhaseDim& ph, const Ph
     ConvShape f{s.N, s.Ho, s.Wo, s.M, s.C, ph.taps, pw.taps, 1, ph.taps - 1 - ph.lo,
                 s.D0, s.D1, s.D3, s.D2, ph.count, pw.count, s.dtype};
     f.out16 = s.out16;
+    same_small_tiles(f, s);
     f.in_gradient = true;
     f.pad_w_set = true;
     f.pad_w = pw.taps - 1 - pw.lo;
@@ -310,6 +318,7 @@ ConvShape bwd_input_fc_shape(const ConvShape& s)
     ConvShape f{s.N, 1, 1, s.M, s.kh * s.kw * s.C, 1, 1, 1, 0, s.D0, s.D1, s.D3, s.D2, 1, 1,
                 s.dtype};
     f.out16 = s.out16;
+    same_small_tiles(f, s);
     f.in_gradient = true;
     return f;
 }
@@ -321,9 +330,29 @@ ConvShape bwd_input_conv_shape(const ConvShape& s)
     ConvShape f{s.N, spread_h(s), spread_w(s), s.M, s.C, s.kh, s.kw, 1, s.kh - 1 - s.pad,
                 s.D0, s.D1, s.D3, s.D2, s.H, s.W, s.dtype};
     f.out16 = s.out16;
+    same_small_tiles(f, s);
     f.in_gradient = true;
     return f;
 }
+// ... with the kernel tensor read in place
+void view_kernel(const ConvShape& s, ConvShape& f)
+{
+    f.kernel_view = true;
+    f.k_sc = (long long)s.D2 * s.D3 * s.D0;
+    f.k_sm = f.k_sc * s.M;
+    f.k_sd0 = (long long)s.D2 * s.D3;
+    f.k_sd2 = 1;
+    f.k_sd3 = s.D3;
+}
+void view_flipped_kernel(const ConvShape& s, ConvShape& f)
+{
+    view_kernel(s, f);
+    const long long sQ = f.k_sm * s.C, sP = sQ * s.kw;
+    f.k_base = (long long)(s.kh - 1) * sP + (long long)(s.kw - 1) * sQ;
+    f.k_sp = -sP;
+    f.k_sq = -sQ;
+}
+
 // fp32: against the estimates of what would run, the spread-out gradient's zeros counted in (20 random strided
 // layers: 19 of them 0.15 .. 0.85 times the time, one whose phases fill the bf16 kernel's tiles stays there)
 bool mid_preferred32(const ConvShape& s, const BwdInputPlan& plan, const ConvShape* f, int n, double us)
@@ -344,12 +373,13 @@ bool mid_preferred32(const ConvShape& s, const BwdInputPlan& plan, const ConvSha
 // (40 random layers: 0.2 .. 0.95 times the time), else
 // where one launch is estimated 30 % faster than the phases' launches on the tuned kernels.
 // Stride 1 otherwise is a convolution whose kernel the forward pass's rules pick.
-MidPick bwd_input_on_mid(const ConvShape& s, const BwdInputPlan& plan, const ConvShape* f, int n)
+MidPick bwd_input_on_mid(const ConvShape& s, const BwdInputPlan& plan, const ConvShape* f, int n, size_t room)
 {
-    if (!igemm_mid_eligible(f, n, s.kernel_elems())) return {};
-    const MidEstimate e = igemm_mid_best(f, n, plan.bytes);
+    if (n == 0 || !igemm_mid_eligible(f, n, s.kernel_elems())) return {};
+    const MidEstimate e = igemm_mid_best(f, n, room);
     bool take = true;
-    if (s.dtype == 0 && plan.form != BwdInputPlan::Gather) {
+    if (s.mid_use == 2) {
+    } else if (s.dtype == 0 && plan.form != BwdInputPlan::Gather) {
         take = mid_preferred32(s, plan, f, n, e.us);
     } else if (plan.form == BwdInputPlan::Phases) {
         double other = 0;
@@ -362,13 +392,24 @@ MidPick bwd_input_on_mid(const ConvShape& s, const BwdInputPlan& plan, const Con
     return take ? e.pick : MidPick{};
 }
 
+bool phases_may_run_on_mid(const ConvShape& s, const BwdInputPlan& plan)
+{
+    return plan.form != BwdInputPlan::FullyConnected && (s.stride > 1 || plan.form == BwdInputPlan::Gather);
+}
+size_t small_tile_room(const ConvShape& s, size_t need, size_t workspace_bytes)
+{
+    return s.mid_use == 2 ? workspace_bytes : need;
+}
+
 // dK as a forward convolution of the re-laid-out input with the (spread-out) output gradient
 // as the window
 ConvShape bwd_kernel_conv_shape(const ConvShape& s)
 {
     // input I' [C][H][W][N][D0][D2][D1], kernel G' [Hs][Ws][N][M][D0][D1][D3] -> [C][kh][kw][M][D0][D2][D3]
-    return ConvShape{s.C, s.H, s.W, s.N, s.M, spread_h(s), spread_w(s), 1, s.pad,
-                     s.D0, s.D2, s.D1, s.D3, s.kh, s.kw, s.dtype};
+    ConvShape f{s.C, s.H, s.W, s.N, s.M, spread_h(s), spread_w(s), 1, s.pad,
+                s.D0, s.D2, s.D1, s.D3, s.kh, s.kw, s.dtype};
+    same_small_tiles(f, s);
+    return f;
 }
 
 }  // namespace
@@ -416,6 +457,32 @@ size_t bwd_kernel_workspace_bytes(const ConvShape& s)
            align256(s.kernel_elems() * sizeof(float)) + forward_choice_bytes(f, forward_choice(f));
 }
 
+RouteInfo bwd_input_route(const ConvShape& s, const BwdInputPlan& plan, size_t workspace_bytes)
+{
+    MidPick pick;
+    if (phases_may_run_on_mid(s, plan)) {
+        ConvShape f[kMaxPhases];
+        const int n = bwd_input_phases(s, f);
+        pick = bwd_input_on_mid(s, plan, f, n, small_tile_room(s, plan.bytes, workspace_bytes));
+        if (plan.form == BwdInputPlan::Gather) pick.nsplit = 1;
+    }
+    if (!pick && (plan.form == BwdInputPlan::FullyConnected || plan.form == BwdInputPlan::Convolution)) {
+        const bool fc = plan.form == BwdInputPlan::FullyConnected;
+        ConvShape f = fc ? bwd_input_fc_shape(s) : bwd_input_conv_shape(s);
+        if (plan.fwd.takes_kernel_view && fc) view_kernel(s, f);
+        if (plan.fwd.takes_kernel_view && !fc) view_flipped_kernel(s, f);
+        const size_t used = plan.bytes - forward_choice_bytes(f, plan.fwd);
+        pick = forward_small_tiles(f, plan.fwd, workspace_bytes > used ? workspace_bytes - used : 0);
+    }
+    return {pick.tile, pick.nsplit, plan.form};
+}
+
+RouteInfo bwd_kernel_route(const ConvShape& s, size_t need, size_t workspace_bytes)
+{
+    const MidPick pick = wgrad_mid_choice(s, small_tile_room(s, need, workspace_bytes));
+    return {pick.tile, pick.nsplit, wgrad16_eligible(s) ? 16 : wgrad32_eligible(s) ? 32 : 1};
+}
+
 // `din` holds fp32 elements, or with s.out16 set 16-bit elements of that kind (every route's
 // convolution shape carries s.out16 on, so its kernels round once at their stores).
 int launch_bwd_input(const ConvShape& s, const BwdInputPlan& plan, const void* dout, const void* kernel,
@@ -429,13 +496,8 @@ int launch_bwd_input(const ConvShape& s, const BwdInputPlan& plan, const void* d
         const size_t used = align256(s.kernel_elems() * eb);
         // K2[m][(h,w,c)][d0][d3][d2] = K[h][w][c][m][d0][d2][d3]; (h,w,c) is one index of stride sC
         ConvShape f = bwd_input_fc_shape(s);
-        if (plan.fwd.takes_kernel_view) {  // read in place
-            f.kernel_view = true;
-            f.k_sc = sM;
-            f.k_sm = sC;
-            f.k_sd0 = sD0;
-            f.k_sd2 = sD3;
-            f.k_sd3 = sD2;
+        if (plan.fwd.takes_kernel_view) {
+            view_kernel(s, f);  // ((h,w,c) is one index of stride k_sm)
             return forward_run(f, plan.fwd, dout, kernel, din, ws + used, workspace_bytes - used, stream);
         }
         const Permute7 pm = gather_into_dense(
@@ -445,14 +507,13 @@ int launch_bwd_input(const ConvShape& s, const BwdInputPlan& plan, const void* d
         if (err != hipSuccess) return status_from_hip(err);
         return forward_run(f, plan.fwd, dout, ws, din, ws + used, workspace_bytes - used, stream);
     }
-    if (s.stride > 1 || plan.form == BwdInputPlan::Gather) {
+    if (phases_may_run_on_mid(s, plan)) {
         ConvShape f[kMaxPhases];
         const int n = bwd_input_phases(s, f);
         // (in the place of the gather kernel: like it, no tap outside the image)
-        if (n > 0)
-            if (const MidPick pick = bwd_input_on_mid(s, plan, f, n))
-                return status_from_hip(launch_igemm_mid(f, n, s.kernel_elems(), pick, dout, kernel, din, workspace,
-                                                        stream, plan.form == BwdInputPlan::Gather));
+        if (const MidPick pick = bwd_input_on_mid(s, plan, f, n, small_tile_room(s, plan.bytes, workspace_bytes)))
+            return status_from_hip(launch_igemm_mid(f, n, s.kernel_elems(), pick, dout, kernel, din, workspace,
+                                                    stream, plan.form == BwdInputPlan::Gather));
     }
     if (plan.form == BwdInputPlan::Phases) {
         char* ws = static_cast<char*>(workspace);
@@ -523,15 +584,7 @@ int launch_bwd_input(const ConvShape& s, const BwdInputPlan& plan, const void* d
         ConvShape f = bwd_input_conv_shape(s);
         hipError_t err = hipSuccess;
         if (plan.fwd.takes_kernel_view) {  // read in place
-            f.kernel_view = true;
-            f.k_base = (long long)(s.kh - 1) * sP + (long long)(s.kw - 1) * sQ;
-            f.k_sp = -sP;
-            f.k_sq = -sQ;
-            f.k_sc = sM;
-            f.k_sm = sC;
-            f.k_sd0 = sD0;
-            f.k_sd2 = sD3;
-            f.k_sd3 = sD2;
+            view_flipped_kernel(s, f);
             kflip = kernel;
         } else {
             const Permute7 pm = gather_into_dense({s.kh, s.kw, s.M, s.C, s.D0, s.D3, s.D2},
@@ -582,7 +635,7 @@ int launch_bwd_input(const ConvShape& s, const BwdInputPlan& plan, const void* d
 int launch_bwd_kernel(const ConvShape& s, size_t need, const void* input, const void* dout, float* dkernel,
                       void* workspace, size_t workspace_bytes, hipStream_t stream)
 {
-    if (const MidPick pick = wgrad_mid_choice(s, need))
+    if (const MidPick pick = wgrad_mid_choice(s, small_tile_room(s, need, workspace_bytes)))
         return status_from_hip(launch_wgrad_mid(s, pick, input, dout, dkernel, workspace, stream));
     if (wgrad16_eligible(s))
         return status_from_hip(launch_wgrad16(s, input, dout, dkernel, workspace, stream));

@@ -150,19 +150,25 @@ capscaps::MfmaKernel leaner_kernel(const ConvShape& s, const Choice& own)
     return MfmaKernel::Auto;
 }
 
+capscaps::MidPick small_tiles(const ConvShape& s, const Choice& c, size_t need, size_t workspace_bytes)
+{
+    if (c.path == CAPSCAPS_PATH_DIRECT && s.mid_use != 2) return {};
+    return capscaps::igemm_mid_choice(s, c.kernel, s.mid_use == 2 ? workspace_bytes : need);
+}
+
 // The library's own choice; it needs scratch for the kernel it picks only.
 int run_choice(const void* input, const void* kernel, void* out, const ConvShape& s, const Choice& c,
                void* workspace, size_t workspace_bytes, hipStream_t stream)
 {
     float* dst = static_cast<float*>(out);
-    if (c.path == CAPSCAPS_PATH_DIRECT)
-        return hip_status(capscaps::launch_direct(s, input, kernel, dst, stream));
     const size_t need = scratch_bytes(s, c);
     if (need > 0 && (workspace == nullptr || workspace_bytes < need)) return CAPSCAPS_EWORKSPACE;
     if (need > 0 && misaligned(workspace)) return CAPSCAPS_EINVAL;
-    if (const capscaps::MidPick pick = capscaps::igemm_mid_choice(s, c.kernel, need))
+    if (const capscaps::MidPick pick = small_tiles(s, c, need, workspace_bytes))
         return hip_status(
             capscaps::launch_igemm_mid(&s, 1, s.kernel_elems(), pick, input, kernel, dst, workspace, stream));
+    if (c.path == CAPSCAPS_PATH_DIRECT)
+        return hip_status(capscaps::launch_direct(s, input, kernel, dst, stream));
     return hip_status(capscaps::launch_mfma(s, input, kernel, dst, workspace, stream, c.kernel));
 }
 
@@ -221,6 +227,11 @@ int forward_run(const ConvShape& s, const ForwardChoice& c, const void* in, cons
     if (s.pad_w_set || s.out_view) return CAPSCAPS_EINVAL;
     if (s.kernel_view && !c.takes_kernel_view) return CAPSCAPS_EINVAL;
     return run_choice(in, kernel, out, s, c, workspace, workspace_bytes, stream);
+}
+
+MidPick forward_small_tiles(const ConvShape& s, const ForwardChoice& c, size_t workspace_bytes)
+{
+    return small_tiles(s, c, scratch_bytes(s, c), workspace_bytes);
 }
 
 int forward_tuned16(const ConvShape& s, const void* in, const void* kernel, float* out,
@@ -514,6 +525,60 @@ int capscaps_mfma_yardstick(const void* seed, void* sink, int dtype, int blocks,
         return CAPSCAPS_EINVAL;
     return hip_status(capscaps::launch_yardstick(dtype, seed, static_cast<float*>(sink), blocks,
                                                  iters, static_cast<hipStream_t>(stream)));
+}
+
+// For the tests only (not in the header): a forward pass (op 0), input (1) or kernel gradient (2) with or without the
+// small-tile kernels, and which kernels would run.  `shape`: N, H, W, C, M, kh, kw, stride, pad, D0, D1, D2, D3,
+// dtype; `small_tiles`: ConvShape::mid_use, mid_tile, mid_split; `info`: RouteInfo (forward: form = the path).
+namespace {
+int testing_shape(ConvShape& s, const int* a, int out16, const int* small_tiles)
+{
+    const int rc = fill_shape(s, a[0], a[1], a[2], a[3], a[4], a[5], a[6], a[7], a[8], a[9], a[10], a[11], a[12], a[13]);
+    if (rc != CAPSCAPS_OK) return rc;
+    s.out16 = out16 ? s.dtype : 0;
+    s.mid_use = small_tiles[0];
+    s.mid_tile = small_tiles[1];
+    s.mid_split = small_tiles[2];
+    return CAPSCAPS_OK;
+}
+}  // namespace
+
+int capscaps_testing_conv(int op, const int* shape, int out16, const int* small_tiles, const void* a, const void* b,
+                          void* out, void* workspace, size_t workspace_bytes, void* stream)
+{
+    ConvShape s;
+    const int rc = testing_shape(s, shape, out16, small_tiles);
+    if (rc != CAPSCAPS_OK) return rc;
+    const hipStream_t st = static_cast<hipStream_t>(stream);
+    if (op == 0) return run(a, b, out, s, CAPSCAPS_PATH_AUTO, workspace, workspace_bytes, st);
+    const capscaps::BwdInputPlan plan = op == 1 ? capscaps::bwd_input_plan(s) : capscaps::BwdInputPlan{};
+    const size_t need = op == 1 ? plan.bytes : capscaps::bwd_kernel_workspace_bytes(s);
+    if (need > 0 && (workspace == nullptr || workspace_bytes < need)) return CAPSCAPS_EWORKSPACE;
+    if (op == 1)
+        return capscaps::launch_bwd_input(s, plan, a, b, static_cast<float*>(out), workspace, workspace_bytes, st);
+    return capscaps::launch_bwd_kernel(s, need, a, b, static_cast<float*>(out), workspace, workspace_bytes, st);
+}
+
+int capscaps_testing_route(int op, const int* shape, int out16, const int* small_tiles, size_t workspace_bytes,
+                           int* info)
+{
+    ConvShape s;
+    const int rc = testing_shape(s, shape, out16, small_tiles);
+    if (rc != CAPSCAPS_OK) return rc;
+    capscaps::RouteInfo r{};
+    if (op == 0) {
+        const Choice c = choose(s);
+        const capscaps::MidPick pick = capscaps::forward_small_tiles(s, c, workspace_bytes);
+        r = {pick.tile, pick.nsplit, c.path};
+    } else if (op == 1) {
+        r = capscaps::bwd_input_route(s, capscaps::bwd_input_plan(s), workspace_bytes);
+    } else {
+        r = capscaps::bwd_kernel_route(s, capscaps::bwd_kernel_workspace_bytes(s), workspace_bytes);
+    }
+    info[0] = r.tile;
+    info[1] = r.nsplit;
+    info[2] = r.form;
+    return CAPSCAPS_OK;
 }
 
 const char* capscaps_last_hip_error(void) { return hipGetErrorString(g_last_hip_error); }

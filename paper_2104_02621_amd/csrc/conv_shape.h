@@ -60,6 +60,10 @@ struct ConvShape {
     // on one input pairs it once)
     bool in_paired = false;
     long long k_base = 0, k_sp = 0, k_sq = 0, k_sc = 0, k_sm = 0, k_sd0 = 0, k_sd2 = 0, k_sd3 = 0;
+    // Of this call, the small-tile kernels (mid_tiles.h): 0 = by the library's rules.  For tests: 1 = none; 2 = wherever
+    // they can run, with tile `mid_tile` (negative: the estimate's) and `mid_split` pieces of the K loop (0: the
+    // estimate's) as far as the workspace holds their sums.
+    int mid_use = 0, mid_tile = -1, mid_split = 0;
     int padw() const { return pad_w_set ? pad_w : pad; }
     bool plain() const { return !pad_w_set && !out_view && !kernel_view && !in_paired; }
     long long pixels() const { return (long long)N * Ho * Wo; }
@@ -135,6 +139,13 @@ struct BwdInputPlan {
     size_t bytes;
 };
 BwdInputPlan bwd_input_plan(const ConvShape& s);
+// which kernels run a call (for tests): tile of the small-tile kernel or -1, its pieces of the K loop, and
+// else the plan's form, or for the kernel gradient 16 / 32 for wgrad16.hip / wgrad32.hip, 1 as a convolution
+struct RouteInfo {
+    int tile, nsplit, form;
+};
+RouteInfo bwd_input_route(const ConvShape& s, const BwdInputPlan& plan, size_t workspace_bytes);
+RouteInfo bwd_kernel_route(const ConvShape& s, size_t need, size_t workspace_bytes);
 size_t bwd_kernel_workspace_bytes(const ConvShape& s);
 // Return a status code of the C ABI; the caller has checked the scratch (`need`: of the kernel gradient).
 int launch_bwd_input(const ConvShape& s, const BwdInputPlan& plan, const void* dout, const void* kernel,

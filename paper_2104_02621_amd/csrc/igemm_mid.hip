@@ -527,6 +527,7 @@ MidEstimate igemm_mid_best(const ConvShape* f, int n, size_t room)
             if (blocks >= 1024 || (nsplit > 2 && us > 1.1 * tile_best)) break;
         }
     }
+    if (s.mid_use == 2) best.pick = asked_pick(s, best.pick, 5, out_bytes, room);
     return best;
 }
 
@@ -663,7 +664,8 @@ hipError_t launch_f32(const MidPlan& pl, hipStream_t stream)
 bool igemm_mid_eligible(const ConvShape* f, int n, size_t kernel_elems)
 {
     const ConvShape& s = f[0];
-    if (n < 1 || n > MAX_PHASES || s.in_paired) return false;
+    if (n < 1 || n > MAX_PHASES || s.in_paired || s.mid_use == 1) return false;
+    if (s.in_gradient && (!s.kernel_view || s.k_sd2 != 1)) return false;  // (reads 16 bytes of K values)
     if (s.H > MAX_EXTENT || s.W > MAX_EXTENT || s.stride > MAX_EXTENT) return false;
     if (!pow2(s.D3) || s.D3 < 4) return false;  // 4 consecutive columns per lane, shifts
     if (s.dtype == 0) {
@@ -720,6 +722,7 @@ double igemm16_tuned_us(const ConvShape& s, MfmaKernel which)
 MidPick igemm_mid_choice(const ConvShape& s, MfmaKernel otherwise, size_t room)
 {
     if ((s.dtype == 0 && !s.in_gradient) || !igemm_mid_eligible(&s, 1, s.kernel_elems())) return {};
+    if (s.mid_use == 2) return igemm_mid_best(&s, 1, room).pick;
     const double flops = 2.0 * (double)s.out_elems() * s.kh * s.kw * s.C * s.D2;
     const bool tuned = otherwise != MfmaKernel::Generic && otherwise != MfmaKernel::Small;
     if (s.dtype == 0 && (tuned ? otherwise != MfmaKernel::Dma32 : (long long)s.M * s.D3 < 24)) return {};

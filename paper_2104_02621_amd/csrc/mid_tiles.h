@@ -16,6 +16,15 @@ struct MidEstimate {
     double us;
 };
 
+// what a test asked for (ConvShape::mid_use = 2)
+inline MidPick asked_pick(const ConvShape& s, MidPick pick, int tiles, double out_bytes, size_t room)
+{
+    if (s.mid_tile >= 0) pick.tile = s.mid_tile % tiles;
+    const double fit = (double)room / out_bytes;
+    if (s.mid_split > 0) pick.nsplit = s.mid_split <= fit ? s.mid_split : fit >= 1 ? (int)fit : 1;
+    return pick;
+}
+
 // Forward pass (16-bit) and input gradient of layers below the tuned kernels' sizes (igemm_mid.hip): one launch,
 // kernel tensor read in place, tiles of 64 or 128 rows and columns.  `f`: one forward pass, or an input gradient as
 // one convolution or as the n phases of a strided layer (all written by the one launch; geometry
@@ -26,6 +35,8 @@ bool igemm_mid_eligible(const ConvShape* f, int n, size_t kernel_elems);
 MidEstimate igemm_mid_best(const ConvShape* f, int n, size_t room);  // the least estimated time
 // the library's choice for a convolution that `otherwise` would run
 MidPick igemm_mid_choice(const ConvShape& s, MfmaKernel otherwise, size_t room);
+// ... that a forward pass with the library's choice `c` runs on (capscaps_api.hip)
+MidPick forward_small_tiles(const ConvShape& s, const ForwardChoice& c, size_t workspace_bytes);
 // estimated time of Tuned16 or Dma32, us
 double igemm16_tuned_us(const ConvShape& s, MfmaKernel which);
 // ... of the fp32 kernels (igemm32_dma.hip)

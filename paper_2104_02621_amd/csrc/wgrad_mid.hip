@@ -318,6 +318,7 @@ MidEstimate wgrad_mid_best(const ConvShape& s, size_t room)
             if (wgs >= 1536 || (nsplit > 2 && us > 1.1 * tile_best)) break;
         }
     }
+    if (s.mid_use == 2) best.pick = asked_pick(s, best.pick, 4, out_bytes, room);
     return best;
 }
 
@@ -408,7 +409,7 @@ hipError_t launch_tag(const WmidPlan& pl, const ConvShape& s, hipStream_t stream
 
 bool wgrad_mid_eligible(const ConvShape& s)
 {
-    if (!s.plain() || s.out16 != 0) return false;
+    if (!s.plain() || s.out16 != 0 || s.mid_use == 1) return false;
     const size_t es = s.dtype == 0 ? 4 : 2;
     if (s.dtype == 0) {
         if (s.D2 < 4 || s.D3 < 4 || !pow2(s.D2) || !pow2(s.D3) || !pow2(s.D1) || s.D1 > 16) return false;
@@ -438,6 +439,7 @@ bool wgrad_mid_eligible(const ConvShape& s)
 MidPick wgrad_mid_choice(const ConvShape& s, size_t room)
 {
     if (!wgrad_mid_eligible(s)) return {};
+    if (s.mid_use == 2) return wgrad_mid_best(s, room).pick;
     const bool other = s.dtype == 0 ? wgrad32_eligible(s) : wgrad16_eligible(s);
     // fp32: where estimated 15 % faster than wgrad32_kernel (47 random layers: the 22 that leave it take 0.37 .. 0.97
     // of its time)

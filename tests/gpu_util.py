@@ -1,5 +1,7 @@
 """Helpers shared by the GPU parity tests: upload seeded inputs, call the C ABI through the
 binding, bring results back, and the error measures the tolerances are stated in."""
+import ctypes
+
 import numpy as np
 
 from paper_2104_02621_amd import capscaps as cc
@@ -60,3 +62,47 @@ def check(w: wl.Workload, got, ref, abs_sum, label=""):
     assert primary <= TOL_PRIMARY[w.dtype], msg
     assert secondary <= TOL_VS_ABS_SUM, msg
     return primary, secondary
+
+
+# The small-tile kernels of a call: by the library's rules, none, or wherever they can run with a given tile
+# (an index) and pieces of the K loop.  Test entry points of the library, not in its header.
+BY_RULE, NO_SMALL_TILES = (0, -1, 0), (1, -1, 0)
+FWD, BWD_INPUT, BWD_KERNEL = 0, 1, 2
+
+
+def small_tiles(tile=-1, pieces=0):
+    return (2, tile, pieces)
+
+
+def _ints(values):
+    return (ctypes.c_int * len(values))(*values)
+
+
+def route(w: wl.Workload, op, tiles=BY_RULE, out16=False, workspace_bytes=1 << 40):
+    """(tile of the small-tile kernel or -1, its pieces of the K loop, path / form of the other kernels)."""
+    info = _ints([0, 0, 0])
+    fn = cc._load().capscaps_testing_route
+    fn.argtypes = [ctypes.c_int, ctypes.c_void_p, ctypes.c_int, ctypes.c_void_p, ctypes.c_size_t, ctypes.c_void_p]
+    rc = fn(op, _ints(shape_args(w)), int(out16), _ints(tiles), workspace_bytes, info)
+    assert rc == cc.OK, rc
+    return tuple(info)
+
+
+def run_op(w: wl.Workload, op, a_dev, b_dev, tiles=BY_RULE, out16=False):
+    """A forward pass or gradient with the given use of the small-tile kernels -> device tensor."""
+    import torch
+    args = shape_args(w)
+    shape = (w.out_shape, w.input_shape, w.kernel_shape)[op]
+    need = ((cc.capscaps_conv_fwd_out16_workspace_bytes if out16 else cc.capscaps_conv_fwd_workspace_bytes),
+            (cc.capscaps_conv_bwd_input_out16_workspace_bytes if out16 else cc.capscaps_conv_bwd_input_workspace_bytes),
+            cc.capscaps_conv_bwd_kernel_workspace_bytes)[op](*args)
+    out = torch.full(shape, float("nan"), dtype=a_dev.dtype if out16 else torch.float32, device="cuda")
+    # (partial sums of the pieces a test asks for, behind what the size query covers)
+    ws = torch.empty(need + 16 + 4 * max(tiles[2], 0) * out.numel(), dtype=torch.uint8, device="cuda")
+    fn = cc._load().capscaps_testing_conv
+    p, i = ctypes.c_void_p, ctypes.c_int
+    fn.argtypes = [i, p, i, p, p, p, p, p, ctypes.c_size_t, p]
+    rc = fn(op, _ints(args), int(out16), _ints(tiles), a_dev.data_ptr(), b_dev.data_ptr(), out.data_ptr(),
+            ws.data_ptr(), ws.numel(), torch.cuda.current_stream().cuda_stream)
+    assert rc == cc.OK, f"{w.name}: status {rc} ({cc.capscaps_strerror(rc)}; {cc.capscaps_last_hip_error()})"
+    return out

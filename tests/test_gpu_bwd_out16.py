@@ -11,7 +11,7 @@ import pytest
 from oracle import capsconv
 from paper_2104_02621_amd import capscaps as cc
 from paper_2104_02621_amd import workloads as wl
-from tests.gpu_util import shape_args, to_device
+from tests.gpu_util import BWD_INPUT, NO_SMALL_TILES, route, run_op, shape_args, to_device
 from tests.test_gpu_bwd_parity import BWD_SHAPES, run_bwd_input
 from tests.test_gpu_out16 import ULP16, bits_to_f64, round_on_host, to_bits
 from tests.test_gpu_parity import small
@@ -56,6 +56,13 @@ def test_small_shapes(shape, dtype):
     got = bits_to_f64(got_bits, w.dtype)
     assert (got[SI == 0] == 0).all()  # pixels no window reaches
     within_bound(w, got, dI, SI)
+    if route(w, BWD_INPUT, out16=True)[0] >= 0:  # also on the kernels that larger layers take
+        got_bits = to_bits(run_op(w, BWD_INPUT, g_dev, k_dev, NO_SMALL_TILES, out16=True))
+        din32 = run_op(w, BWD_INPUT, g_dev, k_dev, NO_SMALL_TILES).cpu().numpy()
+        assert np.array_equal(got_bits, round_on_host(din32, w.dtype)), w.name
+        got = bits_to_f64(got_bits, w.dtype)
+        assert (got[SI == 0] == 0).all()
+        within_bound(w, got, dI, SI)
 
 
 @pytest.mark.parametrize("number", [3, 5])

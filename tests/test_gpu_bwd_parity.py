@@ -10,7 +10,8 @@ import pytest
 from oracle import capsconv
 from paper_2104_02621_amd import capscaps as cc
 from paper_2104_02621_amd import workloads as wl
-from tests.gpu_util import check, shape_args, to_device
+from tests.gpu_util import (BWD_INPUT, BWD_KERNEL, NO_SMALL_TILES, check, route, run_op, shape_args,
+                            to_device)
 from tests.test_gpu_parity import SMALL_SHAPES, small
 
 pytestmark = pytest.mark.gpu
@@ -55,6 +56,8 @@ def oracle_bwd(w):
 
 
 def both_gradients(w):
+    """Both gradients against the oracle: as the library runs them and, where that is on the small-tile kernels, also on
+    the kernels that larger layers of the kind take."""
     i_st, k_st, g_st, dI, dK, SI, SK = oracle_bwd(w)
     i_dev, k_dev, g_dev = (to_device(a, w.dtype) for a in (i_st, k_st, g_st))
     got_i = run_bwd_input(w, g_dev, k_dev).cpu().numpy()
@@ -66,9 +69,17 @@ def both_gradients(w):
     dead = SK == 0
     assert (got_k[dead] == 0).all()
     check(w, got_k, dK, np.where(dead, 1.0, SK), "dkernel")
+    for op, a, b, ref, scale, name in ((BWD_INPUT, g_dev, k_dev, dI, SI, "dinput"),
+                                       (BWD_KERNEL, i_dev, g_dev, dK, SK, "dkernel")):
+        if route(w, op)[0] >= 0:
+            got = run_op(w, op, a, b, NO_SMALL_TILES).cpu().numpy()
+            assert (got[scale == 0] == 0).all()
+            check(w, got, ref, np.where(scale == 0, 1.0, scale), name + ", not on small tiles")
     return got_i, got_k, dI, dK
 
 
+# (Comments that name a kernel of 16-bit gradients mean the run without small tiles in both_gradients: the layers are
+# below the sizes at which the library itself chooses these kernels.)
 # the forward pass's small shapes (strides 1..4, non-square windows and capsules, degenerate
 # geometries) plus stride-1 cases that exercise the convolution route on several tiles
 BWD_SHAPES = SMALL_SHAPES + [
@@ -104,7 +115,7 @@ BWD_SHAPES = SMALL_SHAPES + [
     ("wg32n_d12", 2, 5, 5, 3, 3, 2, 2, 2, 0, 1, 12, 12, 12),
     ("wg32n_d3t", 2, 6, 6, 20, 50, 3, 3, 2, 1, 1, 3, 3, 3),
     # large enough for the strided input gradient to run as interleaved phase convolutions
-    # (16-bit): stride 2; stride 3 with a 2x2 window (one phase of pixels no window reaches);
+    # (16-bit, where it is kept off the small-tile kernels): stride 2; stride 3 with a 2x2 window (one phase of pixels no window reaches);
     # a non-square window with padding beyond its reach and a leading capsule index
     ("ph_s2", 3, 80, 80, 4, 8, 3, 3, 2, 1, 1, 8, 8, 8),
     ("ph_s3", 3, 120, 118, 4, 8, 2, 2, 3, 0, 1, 8, 4, 8),
@@ -241,7 +252,7 @@ def test_workspace_too_small_is_refused():
     assert cc.capscaps_conv_bwd_input(p, p, p, *args, p, need_i - 1, st) == cc.EWORKSPACE
     assert cc.capscaps_conv_bwd_kernel(p, p, p, *args, 0, 0, st) == cc.EWORKSPACE
     assert cc.capscaps_conv_bwd_input(0, p, p, *args, p, need_i, st) == cc.EINVAL
-    # a non-square window takes the gather kernel for dI, which needs no scratch
+    # a non-square window takes a small-tile or the gather kernel for dI without scratch
     # (its kernel gradient: capsule widths of 4 elements go through transposed copies)
     nonsq = small("ns", wl.FP16, 2, 6, 6, 4, 4, 3, 2, 1, 1, 1, 8, 8, 4)
     assert cc.capscaps_conv_bwd_input_workspace_bytes(*shape_args(nonsq)) == 0

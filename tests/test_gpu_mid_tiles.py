@@ -1,14 +1,16 @@
 """The small-tile kernels (16-bit forward pass, input gradient in one launch, kernel gradient) at the
 sizes where they can go wrong: tiles of one row and one column and their remainders, K loops shorter than the
 ring of stages, odd channel counts with 4-element rows, every capsule shape's copy layout, leading
-capsule indices, strided phases (with and without pixels no window reaches), non-square windows, splits of
-the K loop; small-integer data, so that every result is exact, and infinities at the image border."""
+capsule indices, strided phases (with and without pixels no window reaches), non-square windows; every layer with
+the library's own choice and with every tile, with and without a split K loop; small-integer data, so that every
+result is exact, and infinities at the image border."""
 import numpy as np
 import pytest
 
 from oracle import capsconv
 from paper_2104_02621_amd import capscaps as cc
 from paper_2104_02621_amd import workloads as wl
+from tests.gpu_util import BWD_INPUT, BWD_KERNEL, FWD, route, run_op, small_tiles
 
 pytestmark = pytest.mark.gpu
 
@@ -25,7 +27,14 @@ SHAPES = [(1, 1, 1, 1, 1, 1, 1, 1, 0, (1, 4, 4, 4)), (1, 3, 3, 1, 2, 3, 3, 1, 1,
           (3, 7, 7, 5, 3, 3, 3, 1, 1, (1, 4, 8, 16)), (2, 12, 5, 3, 2, 6, 6, 2, 3, (1, 4, 8, 16)),
           (2, 6, 5, 3, 2, 3, 3, 1, 1, (2, 8, 8, 8)), (2, 5, 5, 3, 4, 3, 3, 2, 1, (3, 4, 4, 4)),
           (2, 5, 6, 3, 2, 3, 3, 1, 1, (1, 2, 8, 32)), (4, 6, 6, 3, 2, 5, 5, 1, 4, (1, 2, 16, 8)),
-          (1, 20, 20, 64, 2, 3, 3, 1, 1, (1, 8, 8, 8)), (300, 3, 3, 2, 2, 3, 3, 1, 1, (1, 4, 4, 4))]
+          (1, 20, 20, 64, 2, 3, 3, 1, 1, (1, 8, 8, 8)), (300, 3, 3, 2, 2, 3, 3, 1, 1, (1, 4, 4, 4)),
+          # more than 128 rows and columns in every operation, with remainders; without padding a kernel
+          # gradient's 128-row tiles hold rows of two window taps
+          (2, 7, 6, 35, 37, 3, 2, 1, 0, (1, 4, 4, 4)), (2, 7, 6, 18, 19, 2, 2, 1, 0, (1, 8, 8, 8)),
+          (1, 6, 5, 9, 10, 3, 3, 1, 0, (1, 16, 16, 16)), (40, 3, 3, 21, 9, 2, 2, 1, 0, (1, 1, 8, 16)),
+          (21, 4, 3, 9, 19, 3, 3, 1, 1, (1, 2, 16, 8)), (9, 5, 4, 19, 9, 2, 3, 2, 1, (1, 4, 8, 16))]
+# tiles of the forward pass and input gradient, and of the kernel gradient (igemm_mid.hip, wgrad_mid.hip)
+TILES = {FWD: 5, BWD_INPUT: 5, BWD_KERNEL: 4}
 
 
 def _id(s):
@@ -69,6 +78,41 @@ def test_small_tiles_on_integers(shape, dtype):
             assert torch.equal(t.cpu(), want.reshape(t.shape)), (w.name, name, out16)
 
 
+def _can_run(w, op):
+    """Capsules that the small-tile kernels take."""
+    D1, D2, D3 = w.D1, w.D2, w.D3
+    taps = 1 if (w.kh, w.kw, w.pad) == (w.H, w.W, 0) else w.kh * w.kw  # (fully connected: one 1x1 convolution)
+    if op == BWD_INPUT and taps * w.M * D3 <= 24:
+        return False  # (so short a sum takes the wavefront-level path, on a kernel tensor laid out for it)
+    if w.dtype == wl.FP32:
+        return op != FWD and D2 >= 4 and D3 >= 4
+    return (D1, D2, D3) == (4, 4, 4) or D2 >= 8 and D3 >= 8
+
+
+@pytest.mark.parametrize("dtype", [wl.FP32, wl.BF16, wl.FP16], ids=["fp32", "bf16", "fp16"])
+@pytest.mark.parametrize("shape", SHAPES, ids=_id)
+def test_every_tile_and_split_on_integers(shape, dtype):
+    import torch
+    w = _layer(shape, dtype)
+    i32, k32, g32 = _data(w)
+    I, K, G = (_gpu(a, dtype) for a in (i32, k32, g32))
+    refs = {FWD: capsconv.conv_fwd(i32, k32, w.stride, w.pad),
+            BWD_INPUT: capsconv.conv_bwd_input(g32, k32, (w.H, w.W), w.stride, w.pad),
+            BWD_KERNEL: capsconv.conv_bwd_kernel(i32, g32, (w.kh, w.kw), w.stride, w.pad)}
+    operands = {FWD: (I, K), BWD_INPUT: (G, K), BWD_KERNEL: (I, G)}
+    for op in (FWD, BWD_INPUT, BWD_KERNEL):
+        ref = torch.from_numpy(refs[op].astype(np.float32))
+        for tile in range(TILES[op]):
+            for pieces in (1, 3):
+                for out16 in (False, True) if dtype != wl.FP32 and op != BWD_KERNEL else (False,):
+                    ask = small_tiles(tile, pieces)
+                    runs = route(w, op, ask, out16)
+                    assert runs[0] in ((tile,) if _can_run(w, op) else (-1,)), (w.name, op, runs)
+                    got = run_op(w, op, *operands[op], ask, out16)
+                    torch.cuda.synchronize()
+                    assert torch.equal(got.cpu(), ref.to(got.dtype).reshape(got.shape)), (w.name, op, ask, out16)
+
+
 @pytest.mark.parametrize("dtype", [wl.FP32, wl.BF16], ids=["fp32", "bf16"])
 @pytest.mark.parametrize("caps", [(1, 4, 4, 4), (1, 8, 8, 8), (1, 1, 8, 16)], ids=str)
 def test_infinities_stay_with_the_taps_that_meet_them(caps, dtype):
@@ -79,13 +123,18 @@ def test_infinities_stay_with_the_taps_that_meet_them(caps, dtype):
     i32, k32, g32 = _data(w)
     i32 = np.abs(i32) + 1
     g32[0, 0, 0] = np.inf
-    got = cc.conv_bwd_kernel(_gpu(i32, dtype), _gpu(g32, dtype), (3, 3), 1, 1)
-    torch.cuda.synchronize()
-    got = got.cpu().numpy()
+    I, G = _gpu(i32, dtype), _gpu(g32, dtype)
     inside = np.zeros((3, 3), bool)
     inside[1:, 1:] = True
-    assert np.isposinf(got[inside]).all()
-    assert np.isfinite(got[~inside]).all()
+    got = [cc.conv_bwd_kernel(I, G, (3, 3), 1, 1)]
+    for tile in range(TILES[BWD_KERNEL]):  # (tiles of 128 rows: a tap's rows rounded up to whole tiles)
+        assert route(w, BWD_KERNEL, small_tiles(tile))[0] == tile
+        got.append(run_op(w, BWD_KERNEL, I, G, small_tiles(tile)))
+    torch.cuda.synchronize()
+    for dk in got:
+        dk = dk.cpu().numpy()
+        assert np.isposinf(dk[inside]).all()
+        assert np.isfinite(dk[~inside]).all()
 
 
 #                                N  H   W  C  M  kh kw s  p  caps

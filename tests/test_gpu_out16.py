@@ -9,7 +9,7 @@ import pytest
 from oracle import capsconv
 from paper_2104_02621_amd import capscaps as cc
 from paper_2104_02621_amd import workloads as wl
-from tests.gpu_util import run_gpu, shape_args, to_device
+from tests.gpu_util import BY_RULE, FWD, NO_SMALL_TILES, route, run_gpu, run_op, shape_args, to_device
 from tests.test_gpu_parity import SMALL_SHAPES, TUNED_SHAPES, small
 
 pytestmark = pytest.mark.gpu
@@ -48,14 +48,16 @@ def bits_to_f64(bits, dtype):
     return bits.view(np.float16).astype(np.float64)
 
 
-def check_out16(w, ref=None, S=None, sample=None, exact_order=True):
+def check_out16(w, ref=None, S=None, sample=None, exact_order=True, tiles=BY_RULE):
     i_st, k_st, i32, k32 = wl.generate(w)
     i_dev, k_dev = to_device(i_st, w.dtype), to_device(k_st, w.dtype)
-    got_bits = to_bits(run_out16(w, i_dev, k_dev))
+    got_bits = to_bits(run_out16(w, i_dev, k_dev) if tiles == BY_RULE else
+                       run_op(w, FWD, i_dev, k_dev, tiles, out16=True))
     # (1) one rounding of the very same fp32 result.  On large problems the fp32 call may add
     # up the last tiles' K loop in pieces (another summation order, last bits differ): there a
     # few values near a rounding tie may land on the neighbouring 16-bit number.
-    out32 = run_gpu(w, i_dev, k_dev, cc.PATH_AUTO).cpu().numpy()
+    out32 = (run_gpu(w, i_dev, k_dev, cc.PATH_AUTO) if tiles == BY_RULE else
+             run_op(w, FWD, i_dev, k_dev, tiles)).cpu().numpy()
     same = got_bits == round_on_host(out32, w.dtype)
     if not exact_order:
         off = ~same
@@ -102,6 +104,8 @@ def test_small_shapes(shape, dtype):
     if shape in LANE_PER_ROW_SHAPES:
         assert cc.capscaps_select_path(*shape_args(w)) == cc.PATH_MFMA_TUNED32
     check_out16(w)
+    if route(w, FWD, out16=True)[0] >= 0:  # (the path that is reported is that of larger layers)
+        check_out16(w, tiles=NO_SMALL_TILES)
 
 
 @pytest.mark.parametrize("number", [3, 5])
