@@ -117,6 +117,33 @@ __global__ __launch_bounds__(256) void splitk_reduce4_kernel(const float4v* __re
     for (; s < nsplit; ++s) acc += partial[(long long)s * quads + e];
     store4(out, 4 * e, acc, out16);
 }
+// From 64 partial results on: a quarter of them per wave, the four sums added in pairs.  (As one chain, the kernel
+// gradients of two small layers in 200 pieces were 1.3 and 1.5 times as far from exact sums as in 50 and 100.)
+__global__ __launch_bounds__(256) void splitk_reduce4_waves_kernel(const float4v* __restrict__ partial,
+                                                                   float* __restrict__ out,
+                                                                   long long quads, int nsplit, int out16)
+{
+    __shared__ float4v part[4][64];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, each = (nsplit + 3) / 4;
+    const long long e = (long long)blockIdx.x * 64 + lane;
+    const int end = (wave + 1) * each < nsplit ? (wave + 1) * each : nsplit;
+    float4v acc = {};
+    if (e < quads) {
+        int s = wave * each;
+        for (; s + 8 <= end; s += 8) {
+            float4v v[8];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) v[u] = partial[(long long)(s + u) * quads + e];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) acc += v[u];
+        }
+        for (; s < end; ++s) acc += partial[(long long)s * quads + e];
+    }
+    part[wave][lane] = acc;
+    __syncthreads();
+    if (wave == 0 && e < quads)
+        store4(out, 4 * e, (part[0][lane] + part[1][lane]) + (part[2][lane] + part[3][lane]), out16);
+}
 
 // ---------------------------------------------------------------------------------------------
 // VB: bytes the input-side loader moves at a time.  16: a chunk never straddles a capsule row
@@ -791,9 +818,10 @@ hipError_t launch_splitk_reduce(const float* partial, float* out, long long elem
     const bool quads = elems % 4 == 0 && (reinterpret_cast<uintptr_t>(partial) & 15u) == 0 &&
                        (reinterpret_cast<uintptr_t>(out) & 15u) == 0;
     if (quads) {
-        const unsigned blocks = (unsigned)((elems / 4 + 255) / 256);
-        splitk_reduce4_kernel<<<blocks, 256, 0, stream>>>(
-            reinterpret_cast<const float4v*>(partial), out, elems / 4, nsplit, out16);
+        const int each = nsplit >= 64 ? 64 : 256;  // quads per workgroup
+        auto kern = nsplit >= 64 ? splitk_reduce4_waves_kernel : splitk_reduce4_kernel;
+        const unsigned blocks = (unsigned)((elems / 4 + each - 1) / each);
+        kern<<<blocks, 256, 0, stream>>>(reinterpret_cast<const float4v*>(partial), out, elems / 4, nsplit, out16);
     } else {
         const unsigned blocks = (unsigned)((elems + 255) / 256);
         splitk_reduce_kernel<<<blocks, 256, 0, stream>>>(partial, out, elems, nsplit, out16);

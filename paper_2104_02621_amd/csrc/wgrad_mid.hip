@@ -44,8 +44,10 @@ struct WmidParams {
 
 // WIDE: rows and columns come in 16-byte chunks (D2 and D3 multiples of 8, in fp32 of 4), else both are 4 (and
 // D1 = 4).  fp32: a K block is 4 lines, a slot 4 columns of one, and a lane reads its column's 4 values one by one.
+// (LDS holds two or three workgroups per CU.  Left to aim at four waves per SIMD the compiler waits for each K step's
+// reads before it issues the next: kernel gradients of vector capsules took 1.2 times as long.)
 template <typename Tag, int D1, bool WIDE, int RA, int RB, int KBS, int NST>
-__global__ __launch_bounds__(256, 2) void wgrad_mid_kernel(const WmidParams P)
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 3))) void wgrad_mid_kernel(const WmidParams P)
 {
     constexpr int A_BYTES = KBS * RA * 1024, STAGE = KBS * (RA + RB) * 1024;
     constexpr int NKB = KBS / 4, NCOPY = NKB * (RA + RB);
@@ -56,10 +58,9 @@ __global__ __launch_bounds__(256, 2) void wgrad_mid_kernel(const WmidParams P)
     constexpr int PPB = D1 < LINES ? LINES / D1 : 1;    // pixels per K block
     constexpr int HALVES = D1 > LINES ? D1 / LINES : 1;  // K blocks per pixel
     static_assert(HALVES <= 4, "a wave's K blocks are every fourth: always the same part of a pixel");
-    // accumulators: one per K step of a stage (128x128 tiles: one), the larger tiles' added to a second set
-    // every FLUSH stages, so that chains of roundings stay short: K loops are long here
-    constexpr int NACC = RA * RB == 4 ? 1 : KBS / 2, FLUSH = F32 ? 4 : 16;
-    constexpr bool SUM = RA * RB > 1 || std::is_same_v<Tag, f32_tag>;
+    // accumulators: one per K step of a stage (128x128 tiles: one), added to a second set every FLUSH stages, so
+    // that chains of roundings stay short: K loops are long here
+    constexpr int NACC = RA * RB == 4 ? 1 : KBS / 2, FLUSH = F32 ? 4 : RA * RB == 1 ? 32 : 16;
     extern __shared__ char smem[];
 
     int L = blockIdx.x;
@@ -176,7 +177,7 @@ __global__ __launch_bounds__(256, 2) void wgrad_mid_kernel(const WmidParams P)
         }
     };
 
-    float16v acc[NACC][RA][RB] = {}, sum[SUM ? RA : 1][RB] = {};
+    float16v sum[RA][RB] = {};
     int wr_slot = 0, rd_slot = 0;
     const unsigned lds0 = (unsigned)(size_t)(__attribute__((address_space(3))) char*)smem;
 #pragma unroll
@@ -184,55 +185,38 @@ __global__ __launch_bounds__(256, 2) void wgrad_mid_kernel(const WmidParams P)
         issue(i, (int)lds0 + wr_slot);
         wr_slot += STAGE;
     }
-    for (int j = 0; j < last - first; ++j) {
-        // this stage has landed, and nobody reads the slot the next copies go to any more
-        asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"i"(KEEP) : "memory");
-        issue(j + NST - 1, (int)lds0 + wr_slot);
-        wr_slot = wr_slot == (NST - 1) * STAGE ? 0 : wr_slot + STAGE;
+    for (int j = 0; j < last - first;) {
+        float16v acc[NACC][RA][RB] = {};
+        for (const int stop = j + FLUSH < last - first ? j + FLUSH : last - first; j < stop; ++j) {
+            // this stage has landed, and nobody reads the slot the next copies go to any more
+            asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"i"(KEEP) : "memory");
+            issue(j + NST - 1, (int)lds0 + wr_slot);
+            wr_slot = wr_slot == (NST - 1) * STAGE ? 0 : wr_slot + STAGE;
 #pragma unroll
-        for (int k = 0; k < KBS / 2; ++k) {
-            chunk_t fa[RA], fb[RB];
+            for (int k = 0; k < KBS / 2; ++k) {
+                chunk_t fa[RA], fb[RB];
 #pragma unroll
-            for (int i = 0; i < RB; ++i) fb[i] = read_frag(rd_slot + k * 2 * RB * 1024, b_rd[i]);
+                for (int i = 0; i < RB; ++i) fb[i] = read_frag(rd_slot + k * 2 * RB * 1024, b_rd[i]);
 #pragma unroll
-            for (int i = 0; i < RA; ++i) fa[i] = read_frag(rd_slot + k * 2 * RA * 1024, a_rd[i]);
-#pragma unroll
-            for (int i = 0; i < RA; ++i)
-#pragma unroll
-                for (int j2 = 0; j2 < RB; ++j2) Mma<Tag>::run(fb[j2], fa[i], acc[k % NACC][i][j2]);
-        }
-        if constexpr (SUM)
-            if (j % FLUSH == FLUSH - 1) {
+                for (int i = 0; i < RA; ++i) fa[i] = read_frag(rd_slot + k * 2 * RA * 1024, a_rd[i]);
 #pragma unroll
                 for (int i = 0; i < RA; ++i)
 #pragma unroll
-                    for (int j2 = 0; j2 < RB; ++j2) {
-                        sum[i][j2] += NACC == 4 ? (acc[0][i][j2] + acc[NACC / 4][i][j2]) +
-                                                      (acc[NACC / 2][i][j2] + acc[NACC - 1][i][j2])
-                                      : NACC == 2 ? acc[0][i][j2] + acc[NACC - 1][i][j2]
-                                                  : acc[0][i][j2];
-#pragma unroll
-                        for (int a = 0; a < NACC; ++a) acc[a][i][j2] = float16v{};
-                    }
+                    for (int j2 = 0; j2 < RB; ++j2) Mma<Tag>::run(fb[j2], fa[i], acc[k % NACC][i][j2]);
             }
-        rd_slot = rd_slot == (NST - 1) * STAGE ? 0 : rd_slot + STAGE;
-    }
-    // no copy may still be on its way into this workgroup's LDS when it ends
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-    if constexpr (SUM) {
+            rd_slot = rd_slot == (NST - 1) * STAGE ? 0 : rd_slot + STAGE;
+        }
 #pragma unroll
         for (int i = 0; i < RA; ++i)
 #pragma unroll
-            for (int j = 0; j < RB; ++j) acc[0][i][j] += sum[i][j];
+            for (int j2 = 0; j2 < RB; ++j2)
+                sum[i][j2] += NACC == 4   ? (acc[0][i][j2] + acc[NACC / 4][i][j2]) +
+                                                (acc[NACC / 2][i][j2] + acc[NACC - 1][i][j2])
+                              : NACC == 2 ? acc[0][i][j2] + acc[NACC - 1][i][j2]
+                                          : acc[0][i][j2];
     }
-#pragma unroll
-    for (int w = NACC / 2; w > 0; w /= 2)
-#pragma unroll
-        for (int a = 0; a < w; ++a)
-#pragma unroll
-            for (int i = 0; i < RA; ++i)
-#pragma unroll
-                for (int j = 0; j < RB; ++j) acc[a][i][j] += acc[a + w][i][j];
+    // no copy may still be on its way into this workgroup's LDS when it ends
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
 
     // ---- store: a lane holds 4 consecutive columns of a row, four times per 32 columns
     float* out = P.out + (P.nsplit > 1 ? (long long)split * P.out_elems : 0);
@@ -251,7 +235,7 @@ __global__ __launch_bounds__(256, 2) void wgrad_mid_kernel(const WmidParams P)
                 const int col = col0 + wc * 32 * RB + 32 * j + 8 * u + 4 * half;
                 if (col >= P.cols) continue;
                 const int m = col >> P.d3_shift, d3 = col & ((1 << P.d3_shift) - 1);
-                const float16v& d = acc[0][i][j];
+                const float16v& d = sum[i][j];
                 const float4v v = {d[4 * u], d[4 * u + 1], d[4 * u + 2], d[4 * u + 3]};
                 *reinterpret_cast<float4v*>(out + at + (long long)m * P.out_sm + d3) = v;
             }

@@ -163,3 +163,24 @@ def test_infinite_weights_reach_only_their_pixels(shape, dtype):
         torch.cuda.synchronize()
         ref = torch.from_numpy(want.astype(np.float32)).to(got.dtype).reshape(got.shape)
         assert torch.equal(got.cpu().nan_to_num(nan=-1.0, posinf=-2.0), ref.nan_to_num(nan=-1.0, posinf=-2.0)), out16
+
+
+@pytest.mark.parametrize("dtype", [wl.BF16, wl.FP16], ids=["bf16", "fp16"])
+@pytest.mark.parametrize("N,C,M,D,pieces", [(30, 8, 8, 4, 200), (3, 64, 34, 8, 1)], ids=["200_pieces", "one_long_chain"])
+def test_long_sums_have_short_chains_of_roundings(N, C, M, D, pieces, dtype):
+    """A sum of n terms of random sign, one rounding (2.5e-8 of the value, root mean square) per term, is off by
+    2.5e-8 sqrt(n / 2): 1.4e-7 for chains of 64 partial sums, and with as much again for chains of 32 matrix
+    instructions, whose roundings are not all to nearest, below 2e-7.  As one chain, 200 partial sums or the instructions of
+    486 stages are off by 2.5e-7 and 3.9e-7."""
+    import torch
+    H = 36
+    w = wl.Workload("chains", dtype, N, H, H, C, M, 1, 1, 1, 0, 1, D, D, D, "normal", "normal", 1.0, 5, 6)
+    gen = torch.Generator().manual_seed(9)
+    I, G = (torch.randn(s, generator=gen).to({wl.BF16: torch.bfloat16, wl.FP16: torch.float16}[dtype]).cuda()
+            for s in (w.input_shape, w.out_shape))
+    got = run_op(w, BWD_KERNEL, I, G, small_tiles(0, pieces)).double().cpu()
+    rows = lambda t, ch: t.double().cpu().view(-1, ch, D, D).permute(0, 2, 1, 3).reshape(-1, ch * D)
+    ref = (rows(I, C).t() @ rows(G, M)).view(C, D, M, D).permute(0, 2, 1, 3).reshape(got.shape)
+    error = float((got - ref).norm() / ref.norm())
+    print(f"{pieces} pieces: {error:.3e}", flush=True)
+    assert error < 2e-7
