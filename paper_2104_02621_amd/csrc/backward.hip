@@ -370,8 +370,11 @@ bool mid_preferred32(const ConvShape& s, const BwdInputPlan& plan, const ConvSha
 
 // Strided layers, and the windows and paddings that the convolution form does not cover, on the small-tile
 // kernel: always where `dout` would be spread out (16-bit; s^2 times the work) or gathered element by element
-// (40 random layers: 0.2 .. 0.95 times the time), else
-// where one launch is estimated 30 % faster than the phases' launches on the tuned kernels.
+// (220 random layers, none slower), else
+// where one launch is estimated a quarter faster than the phases' launches on the tuned kernels.  These overlap (9 us less than
+// their calls' times), and the phases of one launch each read `dout`, 5.9 TB/s, which the estimate of one convolution
+// leaves out: 37 strided 16-bit layers of four phases 20 % off, 35 % without; 11 of them go, for 0.3 .. 1.0 of the time
+// (without both and at 30 %: 22, of which 16 -> 56 channels of 4x8 . 8x16, N = 101, 34x34, and two others 1.5 times the time).
 // Stride 1 otherwise is a convolution whose kernel the forward pass's rules pick.
 MidPick bwd_input_on_mid(const ConvShape& s, const BwdInputPlan& plan, const ConvShape* f, int n, size_t room)
 {
@@ -382,12 +385,14 @@ MidPick bwd_input_on_mid(const ConvShape& s, const BwdInputPlan& plan, const Con
     } else if (s.dtype == 0 && plan.form != BwdInputPlan::Gather) {
         take = mid_preferred32(s, plan, f, n, e.us);
     } else if (plan.form == BwdInputPlan::Phases) {
-        double other = 0;
+        double other = 9.0, reads = 0;
         for (int i = 0; i < n; ++i) {
             if (f[i].kh * f[i].kw == 0) continue;
-            other += igemm16_tuned_us(f[i], phase_kernel(f[i]) == 16 ? MfmaKernel::Tuned16 : MfmaKernel::Dma32);
+            other += igemm16_tuned_us(f[i], phase_kernel(f[i]) == 16 ? MfmaKernel::Tuned16 : MfmaKernel::Dma32) - 9.0;
+            reads += 1.0;
         }
-        take = e.us < 0.7 * other;
+        const double mb = 2e-6 * (double)s.out_elems(), out_mb = (s.out16 ? 2e-6 : 4e-6) * (double)s.in_elems();
+        take = e.us + 0.17 * reads * mb + 0.03 * out_mb < 0.75 * other;
     }
     return take ? e.pick : MidPick{};
 }

@@ -718,14 +718,18 @@ double igemm16_tuned_us(const ConvShape& s, MfmaKernel which)
     return 11.2 + gflop / 1.01 + 0.13 * (in_mb + out_mb);
 }
 
-// Against the any-shape kernel (three launches) always: 176 random layers, none slower, 0.51 times its
-// time on average.  Against the small-problem kernel (67 layers, 0.56 times) but for one tile or two of a long K
-// loop and next to no work, where that kernel's many short pieces win (2 images, a 5x5 window over 77 channels of
-// 4x4: 11.0 against 9.3 us).  Against the kernels of 256-row tiles where the estimates differ by 30 %
-// (by a tenth: 12 of 200 random layers were 4 .. 21 % slower, by a fifth 7 of 150).
+// Measured with and without this kernel over random layers, 1500 of them 16-bit forward passes and input gradients.
+// Against the any-shape kernel (three launches) always: 800 layers, none slower, 0.5 times its
+// time on average.  Against the small-problem kernel (360 layers, 0.56 times) but for one tile or two of a long K
+// loop and little work, where that kernel's many short pieces win (2 images, a 5x5 window over 77 channels of
+// 4x4: 11.0 against 9.3 us; 3 images, a 7x7 window over 57 of 16x16, 0.14 GFLOP: 16.4 against 13.5).  Against the kernels of
+// 256-row tiles where the estimates differ by 35 % (508 layers, 81 leave, for 0.2 .. 0.9 of the time; by 30 % and without the next sentence
+// 124, three of them 4 .. 22 % slower; by 20 % 179, five).  An input that no cache holds takes its time
+// whatever the tiles, 0.3 us per MB: 198 images of 13x39 with 49 channels at stride 2, 0.63 GB, 184 us, not the
+// estimate's 82; 99 of 36x36 with 16 channels of 16x16, 1.05 GB, 414.
 // fp32 input gradients: against the small-problem and the any-shape kernel, which read the kernel tensor
 // through strides or after a repack pass, from 24 columns on, but for a few tiles of a long K loop (28 random layers 0.41 .. 0.85 times the time, one
-// of 5.6 us 0.3 us slower; 8 and 16 columns 1.13 and 1.2 times); against the kernel on bf16 instructions where
+// of 5.6 us 0.3 us slower; at 24 columns five 0.63 .. 1.06; 8 and 16 columns 1.13 and 1.2 times); against the kernel on bf16 instructions where
 // the estimates differ by a quarter.
 MidPick igemm_mid_choice(const ConvShape& s, MfmaKernel otherwise, size_t room)
 {
@@ -739,9 +743,9 @@ MidPick igemm_mid_choice(const ConvShape& s, MfmaKernel otherwise, size_t room)
     if (s.dtype == 0)
         take = tuned ? e.us < 0.75 * igemm32_us(s, otherwise) : flops >= 1e8 || e.us < 12;
     else if (tuned)
-        take = e.us < 0.7 * igemm16_tuned_us(s, otherwise);
+        take = std::max(e.us, 6e-7 * (double)s.in_elems()) < 0.65 * igemm16_tuned_us(s, otherwise);
     else
-        take = otherwise == MfmaKernel::Generic || e.us <= 9.5 || flops >= 3e7;
+        take = otherwise == MfmaKernel::Generic || e.us <= 9.5 || (flops >= 3e7 && e.us <= 13.0) || flops >= 1.7e8;
     return take ? e.pick : MidPick{};
 }
 

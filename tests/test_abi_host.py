@@ -8,6 +8,7 @@ import pytest
 
 from paper_2104_02621_amd import capscaps as cc
 from paper_2104_02621_amd import workloads as wl
+from tests.gpu_util import BWD_INPUT, BWD_KERNEL, BY_RULE, FWD, route, shape_args
 
 ROOT = Path(__file__).resolve().parent.parent
 
@@ -273,3 +274,33 @@ def test_fp32_layers_that_split_bf16_terms_do_not_pay_for():
     # at most 8 columns and rows of 3: the wavefront-level path below 5e8 FLOPs, 20 times slower above
     assert path(4, 29, 29, 16, 2, 5, 5, 1, 2, 3, 3, 3, 3) == cc.PATH_DIRECT
     assert path(8, 29, 29, 16, 2, 5, 5, 1, 2, 3, 3, 3, 3) == cc.PATH_MFMA_TUNED32
+
+
+def on_small_tiles(op, dtype, out16, *shape):
+    w = wl.Workload("rule", dtype, *shape, "normal", "normal", 1.0, 1, 2)
+    need = (cc.capscaps_conv_fwd_workspace_bytes, cc.capscaps_conv_bwd_input_workspace_bytes,
+            cc.capscaps_conv_bwd_kernel_workspace_bytes)[op](*shape_args(w))
+    return route(w, op, BY_RULE, out16, need)[0] >= 0
+
+
+def test_small_tiles_leave_layers_that_the_other_kernels_run_faster():
+    """Measured without and with the small-tile kernels, us: large strided input gradients, inputs that no cache
+    holds, a few tiles of a very long K loop."""
+    # 297 without, 470 with; 404, 600; 304, 463; 187, 279
+    assert not on_small_tiles(BWD_INPUT, wl.BF16, False, 101, 34, 34, 16, 56, 3, 3, 2, 0, 1, 4, 8, 16)
+    assert not on_small_tiles(BWD_INPUT, wl.FP16, False, 101, 34, 34, 24, 41, 3, 3, 2, 1, 1, 4, 8, 16)
+    assert not on_small_tiles(BWD_INPUT, wl.FP16, False, 90, 26, 39, 7, 86, 3, 3, 2, 1, 1, 8, 8, 8)
+    assert not on_small_tiles(BWD_INPUT, wl.FP16, False, 90, 18, 37, 69, 78, 3, 3, 2, 0, 1, 4, 4, 4)
+    # 81 without, 24 with; 98, 71
+    assert on_small_tiles(BWD_INPUT, wl.BF16, False, 12, 40, 40, 8, 8, 6, 6, 2, 3, 1, 8, 8, 8)
+    assert on_small_tiles(BWD_INPUT, wl.BF16, False, 14, 36, 36, 16, 16, 5, 5, 2, 2, 1, 8, 8, 8)
+    # forward: 150 without, 184 with; 311, 382; 13.5, 16.4
+    assert not on_small_tiles(FWD, wl.FP16, True, 198, 13, 39, 49, 3, 3, 3, 2, 0, 1, 8, 8, 8)
+    assert not on_small_tiles(FWD, wl.FP16, False, 99, 36, 36, 16, 8, 3, 3, 2, 0, 1, 16, 16, 16)
+    assert not on_small_tiles(FWD, wl.BF16, False, 3, 7, 7, 57, 2, 7, 7, 1, 0, 1, 16, 16, 16)
+    # 68, 76; 100, 109; input gradient 610, 667
+    assert not on_small_tiles(FWD, wl.BF16, False, 52, 29, 29, 8, 8, 3, 3, 2, 0, 1, 16, 16, 16)
+    assert not on_small_tiles(FWD, wl.BF16, True, 218, 28, 27, 19, 4, 3, 3, 2, 0, 1, 8, 8, 8)
+    assert not on_small_tiles(BWD_INPUT, wl.BF16, False, 28, 40, 29, 8, 72, 3, 3, 2, 0, 1, 16, 16, 16)
+    # 26 without, 13 with
+    assert on_small_tiles(FWD, wl.BF16, False, 5, 6, 6, 48, 80, 6, 6, 1, 0, 1, 1, 8, 16)
