@@ -417,9 +417,27 @@ bool wgrad_mid_eligible(const ConvShape& s)
     return blocks * ceil_div((long long)s.M * s.D3, 64) * s.D0 < (1LL << 24);
 }
 
-// Against wgrad16_kernel where it is estimated a fifth faster (that kernel: 21 us and its 256 x 256 tiles' FLOPs
-// at 1.23 PFLOP/s, fitted over the same layers, 26 % root mean square; 57 of the 70 layers leave it, for 0.15 ..
-// 0.9 of its time).  Against the kernel gradient as a convolution always.
+namespace {
+// part of the output pixels that a window tap reaches, on average, in one dimension
+double reached(int extent, int out, int k, int stride, int pad)
+{
+    if (pad == 0) return 1.0;
+    long long n = 0;
+    for (int t = 0; t < k; ++t) {
+        const int lo = t < pad ? (pad - t + stride - 1) / stride : 0, top = extent - 1 + pad - t;
+        const int hi = top < 0 ? -1 : top / stride < out ? top / stride : out - 1;
+        if (hi >= lo) n += hi - lo + 1;
+    }
+    return (double)n / ((double)out * k);
+}
+}  // namespace
+
+// Against wgrad16_kernel, which walks only the pixels that a tap reaches (estimated: 21 us and its 256 x 256 tiles' FLOPs at
+// 1.23 PFLOP/s, 27 % root mean square), where this one takes at most 0.8 of the 21 us and 0.66 of the FLOPs' part, with 0.2 us per
+// MB beyond the 60 that the caches hold between two taps: of 1667 random layers 1417 leave, none slower by more than 3 %, 0.44 times the
+// time on average.  (By 0.8 of both and all pixels: 3 x 3, 15 -> 3 channels of 16x16, 0.5 GB, 571 -> 658 us; 6 x 6, 28 -> 5 channels
+// of 8x8 on 6x6 images with padding 3, 52 -> 73; 6 x 6, 48 -> 8 channels of 1x8 . 8x16, 231 -> 334.)  Against the kernel
+// gradient as a convolution always.
 MidPick wgrad_mid_choice(const ConvShape& s, size_t room)
 {
     if (!wgrad_mid_eligible(s)) return {};
@@ -435,7 +453,9 @@ MidPick wgrad_mid_choice(const ConvShape& s, size_t room)
     const int rows = s.C * s.D2, cols = s.M * s.D3, nt = rows > 128 ? 1 : rows > 64 ? 2 : 4;
     const double gflop = 2e-9 * (double)(s.pixels() * s.D1) * ceil_div(s.kh * s.kw, nt) * s.D0 *
                          (256.0 * ceil_div(rows, 256)) * (256.0 * ceil_div(cols, 256));
-    return e.us < 0.8 * (21.0 + gflop / 1.23) ? e.pick : MidPick{};
+    const double part = reached(s.H, s.Ho, s.kh, s.stride, s.pad) * reached(s.W, s.Wo, s.kw, s.stride, s.pad);
+    const double mb = 2e-6 * (double)(s.in_elems() + s.out_elems());
+    return e.us + 0.2 * std::max(mb - 60.0, 0.0) < 0.8 * 21.0 + 0.66 / 1.23 * gflop * part ? e.pick : MidPick{};
 }
 
 hipError_t launch_wgrad_mid(const ConvShape& s, MidPick pick, const void* input, const void* dout, float* dkernel,

@@ -304,3 +304,16 @@ def test_small_tiles_leave_layers_that_the_other_kernels_run_faster():
     assert not on_small_tiles(BWD_INPUT, wl.BF16, False, 28, 40, 29, 8, 72, 3, 3, 2, 0, 1, 16, 16, 16)
     # 26 without, 13 with
     assert on_small_tiles(FWD, wl.BF16, False, 5, 6, 6, 48, 80, 6, 6, 1, 0, 1, 1, 8, 16)
+
+
+def test_small_tiles_leave_kernel_gradients_that_the_larger_tiles_run_faster():
+    """Measured without and with the small-tile kernel, us: tensors beyond the caches, images that are mostly
+    padding (whose pixels the other kernel skips), estimates that differ by less than a third."""
+    # 571 without, 658 with; 52, 73; 231, 334; 344, 377; 355, 390
+    assert not on_small_tiles(BWD_KERNEL, wl.BF16, False, 138, 20, 20, 15, 3, 3, 3, 1, 1, 1, 16, 16, 16)
+    assert not on_small_tiles(BWD_KERNEL, wl.BF16, False, 225, 6, 6, 28, 5, 6, 6, 2, 3, 1, 8, 8, 8)
+    assert not on_small_tiles(BWD_KERNEL, wl.FP16, False, 186, 30, 30, 48, 8, 6, 6, 2, 0, 1, 1, 8, 16)
+    assert not on_small_tiles(BWD_KERNEL, wl.FP16, False, 166, 31, 31, 8, 16, 3, 3, 1, 1, 1, 8, 8, 8)
+    assert not on_small_tiles(BWD_KERNEL, wl.BF16, False, 83, 19, 20, 16, 9, 6, 6, 1, 3, 1, 8, 8, 8)
+    # 24 without, 8 with
+    assert on_small_tiles(BWD_KERNEL, wl.BF16, True, 10, 16, 16, 8, 8, 1, 1, 1, 0, 1, 4, 4, 4)
