@@ -316,4 +316,4 @@ def test_small_tiles_leave_kernel_gradients_that_the_larger_tiles_run_faster():
     assert not on_small_tiles(BWD_KERNEL, wl.FP16, False, 166, 31, 31, 8, 16, 3, 3, 1, 1, 1, 8, 8, 8)
     assert not on_small_tiles(BWD_KERNEL, wl.BF16, False, 83, 19, 20, 16, 9, 6, 6, 1, 3, 1, 8, 8, 8)
     # 24 without, 8 with
-    assert on_small_tiles(BWD_KERNEL, wl.BF16, True, 10, 16, 16, 8, 8, 1, 1, 1, 0, 1, 4, 4, 4)
+    assert on_small_tiles(BWD_KERNEL, wl.BF16, False, 10, 16, 16, 8, 8, 1, 1, 1, 0, 1, 4, 4, 4)
