@@ -372,11 +372,26 @@ def bench_net5(args):
     print(json.dumps(result), flush=True)
 
 
+def on_small_tiles(w, op):
+    """Do the small-tile kernels (fp32 matrix instructions for fp32) run this gradient?"""
+    import ctypes
+    from paper_2104_02621_amd import capscaps as cc
+    ints = lambda values: (ctypes.c_int * len(values))(*values)
+    shape = (w.N, w.H, w.W, w.C, w.M, w.kh, w.kw, w.stride, w.pad, w.D0, w.D1, w.D2, w.D3, w.dtype)
+    need = (cc.capscaps_conv_bwd_input_workspace_bytes if op == "bwd_input" else
+            cc.capscaps_conv_bwd_kernel_workspace_bytes)(*shape)
+    info = ints([-1, 0, 0])
+    fn = cc._load().capscaps_testing_route
+    fn.argtypes = [ctypes.c_int, ctypes.c_void_p, ctypes.c_int, ctypes.c_void_p, ctypes.c_size_t, ctypes.c_void_p]
+    return fn(1 if op == "bwd_input" else 2, ints(shape), 0, ints([0, -1, 0]), need, info) == cc.OK and info[0] >= 0
+
+
 def on_bf16_instructions(w, op, path):
     """Does this fp32 call take six bf16 matrix products for one fp32 product?  Forward: the lane-per-row
-    kernel, also on the written-out copy of the input (reported as PATH_MFMA).  Input gradient: the route of
+    kernel, also on the written-out copy of the input (reported as PATH_MFMA).  Gradients: not on the small-tile
+    kernels; else the input gradient by the route of
     the convolution it is (of the output gradient spread out to stride 1, or of the fully-connected
-    layer's 1x1 window).  Kernel gradient: capsule heights of 3 or 4 times 1, 2 or 4, but for
+    layer's 1x1 window), the kernel gradient for capsule heights of 3 or 4 times 1, 2 or 4, but for
     layers of at most 32 columns that are not square."""
     from paper_2104_02621_amd import capscaps as cc
     from paper_2104_02621_amd import workloads as wl
@@ -388,6 +403,8 @@ def on_bf16_instructions(w, op, path):
             return path == cc.PATH_MFMA_TUNED32
         return cc.capscaps_select_path(w.N, w.H, w.W, w.C, w.M, w.kh, w.kw, w.stride, w.pad, w.D0, w.D1,
                                        w.D2, w.D3, w.dtype) in split
+    if op in ("bwd_input", "bwd_kernel") and on_small_tiles(w, op):
+        return False
     if op == "bwd_input":
         if w.pad == 0 and (w.kh, w.kw) == (w.H, w.W):
             conv = (w.N, 1, 1, w.M, w.kh * w.kw * w.C, 1, 1, 1, 0)

@@ -527,7 +527,7 @@ int capscaps_mfma_yardstick(const void* seed, void* sink, int dtype, int blocks,
                                                  iters, static_cast<hipStream_t>(stream)));
 }
 
-// For the tests only (not in the header): a forward pass (op 0), input (1) or kernel gradient (2) with or without the
+// For the tests and bench.py only (not in the header): a forward pass (op 0), input (1) or kernel gradient (2) with or without the
 // small-tile kernels, and which kernels would run.  `shape`: N, H, W, C, M, kh, kw, stride, pad, D0, D1, D2, D3,
 // dtype; `small_tiles`: ConvShape::mid_use, mid_tile, mid_split; `info`: RouteInfo (forward: form = the path).
 namespace {

@@ -317,3 +317,11 @@ def test_small_tiles_leave_kernel_gradients_that_the_larger_tiles_run_faster():
     assert not on_small_tiles(BWD_KERNEL, wl.BF16, False, 83, 19, 20, 16, 9, 6, 6, 1, 3, 1, 8, 8, 8)
     # 24 without, 8 with
     assert on_small_tiles(BWD_KERNEL, wl.BF16, False, 10, 16, 16, 8, 8, 1, 1, 1, 0, 1, 4, 4, 4)
+
+
+def test_bench_rates_fp32_gradients_by_the_instructions_they_run_on():
+    import bench
+    runs = lambda number, op: bench.on_bf16_instructions(wl.config(number), op, cc.PATH_AUTO)
+    assert runs(2, "bwd_input") and runs(2, "bwd_kernel")
+    # the fully-connected layer's gradients: small tiles on the fp32 instructions
+    assert not runs(4, "bwd_input") and not runs(4, "bwd_kernel")
