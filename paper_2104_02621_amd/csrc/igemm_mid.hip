@@ -723,8 +723,10 @@ double igemm16_tuned_us(const ConvShape& s, MfmaKernel which)
 // Measured with and without this kernel over random layers, 1500 of them 16-bit forward passes and input gradients.
 // Against the any-shape kernel (three launches) always: 800 layers, none slower, 0.5 times its
 // time on average.  Against the small-problem kernel (360 layers, 0.56 times) but for one tile or two of a long K
-// loop and little work, where that kernel's many short pieces win (2 images, a 5x5 window over 77 channels of
-// 4x4: 11.0 against 9.3 us; 3 images, a 7x7 window over 57 of 16x16, 0.14 GFLOP: 16.4 against 13.5).  Against the kernels of
+// loop and next to no work, where that kernel's many short pieces win (2 images, a 5x5 window over 77 channels of
+// 4x4: 11.0 against 9.3 us; the fully-connected layer over 8x8 images of 64 channels of 8x8, 0.04 GFLOP, too when called again
+// and again, 12.4 against 10.8, but behind four other layers, its kernel tensor in no L2, this one: the stack on two images
+// 96.9 against 98.9, on four 139 against 143).  Against the kernels of
 // 256-row tiles where the estimates differ by 35 % (508 layers, 81 leave, for 0.2 .. 0.9 of the time; by 30 % and without the next sentence
 // 124, three of them 4 .. 22 % slower; by 20 % 179, five).  An input that no cache holds takes its time
 // whatever the tiles, 0.3 us per MB: 198 images of 13x39 with 49 channels at stride 2, 0.63 GB, 184 us, not the
@@ -747,7 +749,7 @@ MidPick igemm_mid_choice(const ConvShape& s, MfmaKernel otherwise, size_t room)
     else if (tuned)
         take = std::max(e.us, 6e-7 * (double)s.in_elems()) < 0.65 * igemm16_tuned_us(s, otherwise);
     else
-        take = otherwise == MfmaKernel::Generic || e.us <= 9.5 || (flops >= 3e7 && e.us <= 13.0) || flops >= 1.7e8;
+        take = otherwise == MfmaKernel::Generic || e.us <= 9.5 || flops >= 3e7;
     return take ? e.pick : MidPick{};
 }
 
