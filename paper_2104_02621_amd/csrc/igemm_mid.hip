@@ -726,7 +726,10 @@ double igemm16_tuned_us(const ConvShape& s, MfmaKernel which)
 // loop and next to no work, where that kernel's many short pieces win (2 images, a 5x5 window over 77 channels of
 // 4x4: 11.0 against 9.3 us; the fully-connected layer over 8x8 images of 64 channels of 8x8, 0.04 GFLOP, too when called again
 // and again, 12.4 against 10.8, but behind four other layers, its kernel tensor in no L2, this one: the stack on two images
-// 96.9 against 98.9, on four 139 against 143).  Against the kernels of
+// 96.9 against 98.9, on four 139 against 143), and rows of 4 of one channel or two under few columns, whose K blocks (pairs of two
+// channels) and 64-column tiles are mostly padding: 300 layers of 4x4 of 0.05 MFLOP and more, called again and again / with
+// cold caches, 85 stay there, which take 1.14 / 1.06 times the time here (one channel, a 5x5 window, 12 columns: 5.6 against
+// 3.7 / 4.2 us; 3x3, 8 columns: 4.0 against 3.1 / 3.3); of the others none loses more than 3 % with cold caches.  Against the kernels of
 // 256-row tiles where the estimates differ by 35 % (508 layers, 81 leave, for 0.2 .. 0.9 of the time; by 30 % and without the next sentence
 // 124, three of them 4 .. 22 % slower; by 20 % 179, five).  An input that no cache holds takes its time
 // whatever the tiles, 0.3 us per MB: 198 images of 13x39 with 49 channels at stride 2, 0.63 GB, 184 us, not the
@@ -742,6 +745,9 @@ MidPick igemm_mid_choice(const ConvShape& s, MfmaKernel otherwise, size_t room)
     const double flops = 2.0 * (double)s.out_elems() * s.kh * s.kw * s.C * s.D2;
     const bool tuned = otherwise != MfmaKernel::Generic && otherwise != MfmaKernel::Small;
     if (s.dtype == 0 && (tuned ? otherwise != MfmaKernel::Dma32 : (long long)s.M * s.D3 < 24)) return {};
+    if (otherwise == MfmaKernel::Small && !s.in_gradient && s.D2 == 4 && s.C <= 2 && s.C * s.M * s.D3 <= 48 &&
+        s.kh * s.kw * s.C * s.D2 <= 200)
+        return {};
     const MidEstimate e = igemm_mid_best(&s, 1, room);
     bool take;
     if (s.dtype == 0)

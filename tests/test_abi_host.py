@@ -305,6 +305,19 @@ def test_small_tiles_leave_layers_that_the_other_kernels_run_faster():
     assert on_small_tiles(FWD, wl.BF16, False, 5, 6, 6, 48, 80, 6, 6, 1, 0, 1, 1, 8, 16)
 
 
+def test_small_tiles_leave_4x4_layers_that_they_would_mostly_pad():
+    """Forward passes over one or two channels of 4x4, few columns, measured without and with the small-tile kernel, us."""
+    small_problem = lambda *shape: cc.capscaps_select_path(*shape, wl.BF16) == cc.PATH_MFMA_SMALL
+    # 3.7, 5.6; 3.1, 4.0; 4.3, 5.6; 3.7, 4.4 (two channels)
+    for shape in ((14, 8, 8, 1, 3, 5, 5, 1, 0, 1, 4, 4, 4), (46, 3, 3, 1, 2, 3, 3, 2, 1, 1, 4, 4, 4),
+                  (116, 5, 5, 1, 5, 5, 5, 1, 0, 1, 4, 4, 4), (74, 4, 4, 2, 3, 4, 4, 1, 0, 1, 4, 4, 4)):
+        assert small_problem(*shape)
+        assert not on_small_tiles(FWD, wl.BF16, False, *shape) and not on_small_tiles(FWD, wl.FP16, True, *shape)
+    # 5.5, 4.3; 8.4, 4.5
+    for shape in ((23, 18, 18, 1, 18, 3, 3, 2, 0, 1, 4, 4, 4), (95, 8, 8, 2, 15, 2, 2, 1, 0, 1, 4, 4, 4)):
+        assert small_problem(*shape) and on_small_tiles(FWD, wl.BF16, False, *shape)
+
+
 def test_small_tiles_leave_kernel_gradients_that_the_larger_tiles_run_faster():
     """Measured without and with the small-tile kernel, us: tensors beyond the caches, images that are mostly
     padding (whose pixels the other kernel skips), estimates that differ by less than a third."""
