@@ -24,14 +24,20 @@ __device__ __forceinline__ unsigned round_pair(float lo, float hi)
 }
 __device__ __forceinline__ float low_half(unsigned w) { return __builtin_bit_cast(float, w << 16); }
 __device__ __forceinline__ float high_half(unsigned w) { return __builtin_bit_cast(float, w & 0xffff0000u); }
+// x minus one of the two values of `pair`, exact here.  Two forms: v_dot2_f32_bf16 with a pair of factors 0 and -1 is one
+// instruction, but shares the matrix cores' pipe, whichever wave of the SIMD it comes from: a 32x32x16 matrix
+// instruction with two of them behind it takes 56 cycles, with four 63, and 37 alone or with six
+// multiplications or conversions.  Unpacking and subtracting are two instructions that run beside it.  Where
+// two waves of a SIMD hide each other's issue the latter is faster (igemm32_split.hip: 543 -> 523 us), where one
+// wave's issue is the limit, the former (wgrad32.hip: 672 against 680 us).
+__device__ __forceinline__ float minus_low(float x, unsigned pair) { return x - low_half(pair); }
+__device__ __forceinline__ float minus_high(float x, unsigned pair) { return x - high_half(pair); }
 // The operands of minus_bf16 for the lower and the upper value of a pair, opaque to the compiler
 // (a packed inline constant would be the same value in both halves).
 struct MinusOne {
     unsigned lo = 0x0000bf80u, hi = 0xbf800000u;
     __device__ __forceinline__ MinusOne() { asm volatile("" : "+s"(lo), "+s"(hi)); }
 };
-// one of the two values of `pair` times -1, plus x: exact here, and one instruction where
-// unpacking the value and subtracting it are two
 __device__ __forceinline__ float minus_bf16(float x, unsigned pair, unsigned minus_one)
 {
     return __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2v, pair),

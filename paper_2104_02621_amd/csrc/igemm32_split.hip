@@ -17,7 +17,8 @@
 // -6e-8, -4.9e-7, -2.3e-6, -4.8e-6 in one direction).
 //
 // Measured (N = 64, 32x32, 3x3, 32 -> 32 channels): 3x3x3 capsules 0.776 ms on the fp32
-// instructions, 0.546 ms here (error against 64-bit sums 5.2e-7 and 4.4e-7), 4x4 capsules 0.664
+// instructions, 0.524 ms here (error against 64-bit sums 5.2e-7 and 4.4e-7; 0.549 before the splitting left the
+// matrix cores' pipe alone, see minus_low, and kept to its gaps), 4x4 capsules 0.664
 // and 0.41 ms, 8x8 capsules 4.37 and 2.81 ms (211 TFLOP/s).  The long K loops run at the clock the
 // power limit leaves (1.5 .. 1.6 GHz); 3-float chunks also at the rate of the L1 lookups (57 per
 // copy, 16 where 4-float rows lie side by side).
@@ -32,7 +33,7 @@
 // a 16-byte lane stride.  A stage of the K loop is 4 slots of every row.  The lower half wave
 // takes slots 0 and 1 of its row, the upper half slots 2 and 3: 8 values (CW = 4), the K extent of
 // one bf16 instruction, or 6 (CW = 3), so that four stages make three instructions' worth.  The
-// values are split in registers (4.5 vector instructions each, under the matrix instructions of the
+// values are split in registers (6.5 vector instructions each, under the matrix instructions of the
 // SIMD's other wave); the kernel tensor is split once per call, by the repack pass.
 //
 // Tile: 64*NW rows x 32*TN columns; wave w copies and contracts rows 64w..64w+63 (two MFMA row
@@ -70,6 +71,12 @@ constexpr int kernel_ring(int tn) { return tn == 4 ? 2 : 3; }
 // order of the matrix instruction: 8g + 4h + i in registers 4g + i.
 constexpr int column_runs(int tn) { return 16 * tn / 3; }
 constexpr int tile_columns(bool triple, int tn) { return triple ? 6 * column_runs(tn) : 32 * tn; }
+
+// Keeps an operation in its place: the value is final here, and its uses come after.  (Arithmetic has no order to
+// the compiler: the splitting steps dealt out over the gaps were gathered in a few of them, in front of the
+// first matrix instruction above all.)
+template <typename T>
+__device__ __forceinline__ void pin(T& x) { asm volatile("" : "+v"(x)); }
 
 template <int CW, int TN, int NW, bool TRIPLE>
 __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(NW == 4 ? 2 : 1)))
@@ -192,8 +199,9 @@ void igemm32_split_kernel(const Dma32Params P)
     // input copies of the next stage into the ring slot at LDS address `slot`: this lane's row ...
     unsigned a_voff;
     auto begin_a = [&]() {
-        const bool ok = issued < my_stages && ((tap_ok >> tap) & 1ull) != 0;
-        a_voff = ok ? (unsigned)row_off : (unsigned)OOB;
+        // (no branch: it would cut the stage's one basic block, and with it the deal of the side operations)
+        const unsigned live = issued < my_stages ? 1u : 0u;
+        a_voff = ((unsigned)(tap_ok >> tap) & live) != 0 ? (unsigned)row_off : (unsigned)OOB;
     };
     // ... its slot q
     auto copy_a = [&](unsigned slot, int q) {
@@ -244,7 +252,6 @@ void igemm32_split_kernel(const Dma32Params P)
 
     // ---- the K loop on the split values
     {
-        const MinusOne one;
         constexpr int FLIP = 96;  // stages; a multiple of both periods
         // of the input values being split; the ranges of a split K loop begin with either sign
         unsigned in_scale = __builtin_bit_cast(unsigned, SPLIT_SCALE) | (unsigned)split << 31;
@@ -255,16 +262,23 @@ void igemm32_split_kernel(const Dma32Params P)
         auto split_step = [&](int p, int k, int pos) {
             unsigned(&w)[3][WORDS] = iv[p / CW];
             const int at = pos * CW + p % CW, t = (k - 2) / 3;
-            if (k == 0)
+            if (k == 0) {
+                pin(lo[p]);
                 lo[p] *= __builtin_bit_cast(float, in_scale);
-            else if (k == 1)
+            } else if (k == 1) {
+                pin(hi[p]);
                 hi[p] *= __builtin_bit_cast(float, in_scale);
-            else if (k % 3 == 2)
+            } else if (k % 3 == 2) {
+                pin(lo[p]);
+                pin(hi[p]);
                 w[t][at] = round_pair(lo[p], hi[p]);
-            else if (k % 3 == 0)
-                lo[p] = minus_bf16(lo[p], w[t][at], one.lo);
-            else
-                hi[p] = minus_bf16(hi[p], w[t][at], one.hi);
+            } else if (k % 3 == 0) {
+                pin(w[t][at]);
+                lo[p] = minus_low(lo[p], w[t][at]);
+            } else {
+                pin(hi[p]);
+                hi[p] = minus_high(hi[p], w[t][at]);
+            }
         };
         auto take_input = [&](const char* slot) {
             float4v raw[TM][2];
@@ -391,8 +405,8 @@ void igemm32_split_kernel(const Dma32Params P)
                 }
                 // all of this wave's copies but those of the input stage three ahead have landed,
                 // its reads are done; after the barrier both hold for every wave
-                __builtin_amdgcn_s_waitcnt((0x0F70 | SLOTS) & 0xF0FF);
-                __syncthreads();
+                constexpr int KEPT = AHEAD && has_step(next) ? 3 : 0;
+                asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(%1)\n\ts_barrier" ::"i"(SLOTS), "i"(KEPT) : "memory");
                 a_cur = a_next;
                 a_next = a_next + A_BYTES == NBA * A_BYTES ? 0 : a_next + A_BYTES;
                 b_cur = b_next;
