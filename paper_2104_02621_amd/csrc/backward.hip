@@ -245,14 +245,28 @@ int phase_kernel(const ConvShape& f)
 // kernel read the output gradient with its channels paired; it is paired once for all of them
 bool phases_pair_dout(const ConvShape& s) { return s.dtype != 0 && s.D3 == 4 && s.M % 2 == 0; }
 
+// a phase's kernel tensor read in place: the convolution's input channels are the layer's output
+// channels, its contracted capsule index the layer's d3
+void view_phase_kernel(const ConvShape& s, const PhaseDim& ph, const PhaseDim& pw, int a, int b, ConvShape& f)
+{
+    const long long sD0 = (long long)s.D2 * s.D3, sM = sD0 * s.D0, sC = sM * s.M, sQ = sC * s.C, sP = sQ * s.kw;
+    f.kernel_view = true;
+    f.k_base = (long long)(a + s.stride * (ph.taps - 1)) * sP + (long long)(b + s.stride * (pw.taps - 1)) * sQ;
+    f.k_sp = -s.stride * sP;
+    f.k_sq = -s.stride * sQ;
+    f.k_sc = sM;
+    f.k_sm = sC;
+    f.k_sd0 = sD0;
+    f.k_sd2 = 1;
+    f.k_sd3 = s.D3;
+}
+
 // The input gradient as phases in one launch of the small-tile kernel (any window, padding and
 // stride up to 4; a stride of 1 is one phase).  Returns their number, 0 if there are too many.
 constexpr int kMaxPhases = 16;
 int bwd_input_phases(const ConvShape& s, ConvShape (&f)[kMaxPhases])
 {
     if (s.stride > 4) return 0;
-    const long long sD2 = s.D3, sD0 = (long long)s.D2 * s.D3, sM = sD0 * s.D0, sC = sM * s.M,
-                    sQ = sC * s.C, sP = sQ * s.kw;
     int n = 0;
     for (int a = 0; a < s.stride; ++a)
         for (int b = 0; b < s.stride; ++b) {
@@ -261,16 +275,7 @@ int bwd_input_phases(const ConvShape& s, ConvShape (&f)[kMaxPhases])
             if (ph.count == 0 || pw.count == 0) continue;
             ConvShape& g = f[n++];
             g = bwd_input_phase_shape(s, ph, pw, a, b);
-            g.kernel_view = true;
-            g.k_base = (long long)(a + s.stride * (ph.taps - 1)) * sP +
-                       (long long)(b + s.stride * (pw.taps - 1)) * sQ;
-            g.k_sp = -s.stride * sP;
-            g.k_sq = -s.stride * sQ;
-            g.k_sc = sM;
-            g.k_sm = sC;
-            g.k_sd0 = sD0;
-            g.k_sd2 = 1;
-            g.k_sd3 = sD2;
+            view_phase_kernel(s, ph, pw, a, b, g);
         }
     return n;
 }
@@ -524,7 +529,7 @@ int launch_bwd_input(const ConvShape& s, const BwdInputPlan& plan, const void* d
         char* ws = static_cast<char*>(workspace);
         const size_t kbytes = align256(s.kernel_elems() * eb);
         const long long pix = (long long)s.C * s.D0 * s.D1 * s.D2;
-        size_t used = kbytes;
+        size_t used = 0;
         const void* dout_paired = nullptr;
         if (phases_pair_dout(s)) {
             void* dst = ws + used;
@@ -534,6 +539,9 @@ int launch_bwd_input(const ConvShape& s, const BwdInputPlan& plan, const void* d
             if (err != hipSuccess) return status_from_hip(err);
             dout_paired = dst;
         }
+        ConvShape f[kMaxPhases];
+        MfmaKernel which[kMaxPhases];
+        int n = 0;
         for (int a = 0; a < s.stride; ++a)
             for (int b = 0; b < s.stride; ++b) {
                 const PhaseDim ph = phase_dim(s.H, s.kh, s.stride, s.pad, a);
@@ -559,26 +567,39 @@ int launch_bwd_input(const ConvShape& s, const BwdInputPlan& plan, const void* d
                 // the phase's kernel Kab[i'][j'][m][c][d0][d3][d2] =
                 // K[a + s*(taps_h-1-i')][b + s*(taps_w-1-j')][c][m][d0][d2][d3] is read in place:
                 // the repack pass of the convolution takes it through strides
-                ConvShape f = bwd_input_phase_shape(s, ph, pw, a, b);
-                f.kernel_view = true;
-                f.k_base = (long long)(a + s.stride * (ph.taps - 1)) * sP +
-                           (long long)(b + s.stride * (pw.taps - 1)) * sQ;
-                f.k_sp = -s.stride * sP;
-                f.k_sq = -s.stride * sQ;
-                f.k_sc = sM;   // the convolution's input channels are the layer's output channels
-                f.k_sm = sC;
-                f.k_sd0 = sD0;
-                f.k_sd2 = sD3;  // ... and its contracted capsule index the layer's d3
-                f.k_sd3 = sD2;
-                const bool lane_per_row = phase_kernel(f) == 32;
-                f.in_paired = lane_per_row && dout_paired != nullptr;
-                const int rc = lane_per_row
-                                   ? forward_tuned32(f, f.in_paired ? dout_paired : dout, kernel, din,
-                                                     ws + used, workspace_bytes - used, stream)
-                                   : forward_tuned16(f, dout, kernel, din, ws + used,
-                                                     workspace_bytes - used, stream);
-                if (rc != 0) return rc;
+                f[n] = bwd_input_phase_shape(s, ph, pw, a, b);
+                view_phase_kernel(s, ph, pw, a, b, f[n]);
+                const bool lane_per_row = phase_kernel(f[n]) == 32;
+                f[n].in_paired = lane_per_row && dout_paired != nullptr;
+                which[n++] = lane_per_row ? MfmaKernel::Dma32 : MfmaKernel::Tuned16;
             }
+        // one repack launch for all phases of a 16-bit layer where their kernels fit the scratch together (it holds the
+        // largest and a whole kernel tensor: nearly always; not where few columns are padded to twice their number),
+        // else each phase's before it.  With both gradients: 128 images of 28x28, 64 -> 64 channels of 8x8,
+        // 1696 -> 1685 us; a five-layer stack with two such layers, trained, 2362 -> 2339
+        size_t at = used;
+        void* kp[kMaxPhases];
+        bool together = n > 1;
+        for (int i = 0; i < n && together; ++i) {
+            const size_t bytes = align256(mfma_repacked_bytes(f[i], which[i]));
+            together = bytes != 0 && bytes <= plan.bytes - at;
+            kp[i] = ws + at;
+            at += bytes;
+        }
+        if (together) {
+            const hipError_t err = launch_repack_views(f, which, kp, n, kernel, stream);
+            if (err != hipSuccess) return status_from_hip(err);
+        }
+        const size_t own = workspace_bytes > used + kbytes ? used + kbytes : workspace_bytes;
+        for (int i = 0; i < n; ++i) {
+            const void* g = f[i].in_paired ? dout_paired : dout;
+            const int rc =
+                together ? status_from_hip(launch_mfma_repacked(f[i], g, kp[i], din, stream, which[i]))
+                : which[i] == MfmaKernel::Dma32
+                    ? forward_tuned32(f[i], g, kernel, din, ws + own, workspace_bytes - own, stream)
+                    : forward_tuned16(f[i], g, kernel, din, ws + own, workspace_bytes - own, stream);
+            if (rc != 0) return rc;
+        }
         return 0;
     }
     if (plan.form == BwdInputPlan::Convolution) {

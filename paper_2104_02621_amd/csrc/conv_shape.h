@@ -93,6 +93,15 @@ hipError_t launch_wave_conv(const ConvShape& s, const void* in, const void* kern
 // small problems, split-reduction partial sums).
 // Rechunk: fp32 layers whose rows are written out in runs of four K values first (igemm_conv.hip).
 enum class MfmaKernel { Auto, Generic, Tuned16, Dma32, Small, Rechunk };
+// Several 16-bit convolutions whose kernels are views of one tensor (equal but for the window and k_base), on the
+// tuned kernels: one repack launch for all, then each by itself.  mfma_repacked_bytes: what one's repacked kernel
+// takes; 0 = it needs more scratch than that, or is not for this.
+constexpr int MAX_REPACK_VIEWS = 16;
+size_t mfma_repacked_bytes(const ConvShape& s, MfmaKernel which);
+hipError_t launch_repack_views(const ConvShape* f, const MfmaKernel* which, void* const* kp, int n,
+                               const void* kernel, hipStream_t stream);
+hipError_t launch_mfma_repacked(const ConvShape& s, const void* in, void* kp, float* out, hipStream_t stream,
+                                MfmaKernel which);
 bool mfma_supported(const ConvShape& s);
 MfmaKernel mfma_auto_kernel(const ConvShape& s);  // what Auto resolves to (never Auto)
 bool mfma_tuned16_supported(const ConvShape& s);

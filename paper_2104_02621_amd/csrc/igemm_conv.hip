@@ -44,14 +44,12 @@ struct KernelStrides {
 // one set of them per chunk (with 64-bit ones and a division per element this pass took 13 us for
 // 4.7 MB of kernel, as long as the contraction of a small layer; one image through a stack of five
 // layers, a repack each: 140 -> 125 us).
-template <typename E, int CH, typename I>
-__global__ __launch_bounds__(256) void repack_kernel(const E* __restrict__ kernel,
-                                                     E* __restrict__ kp, int ntaps, int kw, int D2,
-                                                     int D3, int KT, int KQP, int cols, int colsp,
-                                                     int kgroup, KernelStrides ks, I total_chunks)
+// RUN (see repack_reads_runs): the chunk's elements lie side by side, one 16-byte load.
+template <typename E, int CH, bool RUN, typename I>
+__device__ __forceinline__ chunk_t repack_chunk(const E* __restrict__ kernel, I id, int ntaps, int kw, int D2,
+                                                int D3, int KT, int KQP, int cols, int colsp, int kgroup,
+                                                const KernelStrides& ks, long long base)
 {
-    const I id = (I)blockIdx.x * 256 + threadIdx.x;
-    if (id >= total_chunks) return;
     I r = id / (I)colsp;
     const int j = (int)(id - r * (I)colsp);
     int kq, tap, d0;
@@ -70,20 +68,61 @@ __global__ __launch_bounds__(256) void repack_kernel(const E* __restrict__ kerne
     }
     const int k0 = kq * CH, m = j / D3, d3 = j - m * D3, p = tap / kw, q = tap - p * kw;
     int d2 = k0 - k0 / D2 * D2;
-    const E* src = kernel + ks.base + p * ks.sp + q * ks.sq + (long long)(k0 / D2) * ks.sc + m * ks.sm +
+    const E* src = kernel + base + p * ks.sp + q * ks.sq + (long long)(k0 / D2) * ks.sc + m * ks.sm +
                    d0 * ks.sd0 + d2 * ks.sd2 + d3 * ks.sd3;
-    const long long wrap = ks.sc - (D2 - 1) * ks.sd2;  // last row of a channel -> first of the next
-    E v[CH];
+    chunk_t out{};
+    if constexpr (RUN) {
+        if (k0 < KT && j < cols) out = *reinterpret_cast<const chunk_t*>(src);
+    } else {
+        const long long wrap = ks.sc - (D2 - 1) * ks.sd2;  // last row of a channel -> first of the next
+        E v[CH];
 #pragma unroll
-    for (int e = 0; e < CH; ++e) {
-        v[e] = k0 + e < KT && j < cols ? *src : (E)0;
-        const bool last = ++d2 == D2;
-        src += last ? wrap : ks.sd2;
-        d2 = last ? 0 : d2;
+        for (int e = 0; e < CH; ++e) {
+            v[e] = k0 + e < KT && j < cols ? *src : (E)0;
+            const bool last = ++d2 == D2;
+            src += last ? wrap : ks.sd2;
+            d2 = last ? 0 : d2;
+        }
+        __builtin_memcpy(&out, v, 16);
     }
-    chunk_t out;
-    __builtin_memcpy(&out, v, 16);
-    reinterpret_cast<chunk_t*>(kp)[id] = out;
+    return out;
+}
+
+template <typename E, int CH, bool RUN, typename I>
+__global__ __launch_bounds__(256) void repack_kernel(const E* __restrict__ kernel,
+                                                     E* __restrict__ kp, int ntaps, int kw, int D2,
+                                                     int D3, int KT, int KQP, int cols, int colsp,
+                                                     int kgroup, KernelStrides ks, I total_chunks)
+{
+    const I id = (I)blockIdx.x * 256 + threadIdx.x;
+    if (id >= total_chunks) return;
+    reinterpret_cast<chunk_t*>(kp)[id] = repack_chunk<E, CH, RUN, I>(kernel, id, ntaps, kw, D2, D3, KT, KQP, cols,
+                                                                     colsp, kgroup, ks, ks.base);
+}
+
+// The same for several convolutions at once that read views of one 16-bit kernel tensor and differ in their taps and
+// in where these begin (the phases of a strided input gradient): part i is workgroups first_block[i] up to the next
+// part's first.
+struct RepackViews {
+    KernelStrides ks;
+    int n, D2, D3, KT, cols;
+    chunk_t* kp[MAX_REPACK_VIEWS];
+    long long base[MAX_REPACK_VIEWS];
+    int ntaps[MAX_REPACK_VIEWS], kw[MAX_REPACK_VIEWS], KQP[MAX_REPACK_VIEWS], colsp[MAX_REPACK_VIEWS],
+        kgroup[MAX_REPACK_VIEWS];
+    unsigned chunks[MAX_REPACK_VIEWS], first_block[MAX_REPACK_VIEWS];
+};
+template <bool RUN>
+__global__ __launch_bounds__(256) void repack_views_kernel(const unsigned short* __restrict__ kernel,
+                                                           const RepackViews V)
+{
+    int i = 0;
+    while (i + 1 < V.n && blockIdx.x >= V.first_block[i + 1]) ++i;
+    const unsigned id = (blockIdx.x - V.first_block[i]) * 256 + threadIdx.x;
+    if (id >= V.chunks[i]) return;
+    V.kp[i][id] = repack_chunk<unsigned short, 8, RUN, unsigned>(kernel, id, V.ntaps[i], V.kw[i], V.D2, V.D3, V.KT,
+                                                                 V.KQP[i], V.cols, V.colsp[i], V.kgroup[i], V.ks,
+                                                                 V.base[i]);
 }
 
 // Deterministic split-K reduction: out[e] = partial[0][e] + partial[1][e] + ... in that order.
@@ -699,6 +738,7 @@ hipError_t launch_rechunked(const ConvShape& s, const RechunkPlan& rp, const voi
     return hipSuccess;
 }
 
+// (here and in launch_dma32: without a kernel tensor, `workspace` begins with the repacked one)
 hipError_t launch_igemm(const ConvShape& s, const void* in, const void* kernel, float* out,
                         void* workspace, hipStream_t stream, MfmaKernel which)
 {
@@ -713,7 +753,8 @@ hipError_t launch_igemm(const ConvShape& s, const void* in, const void* kernel, 
 
     const size_t chunks = pl.repack_bytes / 16;
     const int kgroup = pl.fast ? igemm16_fast_kgroup(s) : 0;
-    hipError_t err = launch_repack(s, kernel, kp, pl.P.KQP, pl.P.colsp, kgroup, chunks, stream);
+    hipError_t err = kernel == nullptr ? hipSuccess
+                                       : launch_repack(s, kernel, kp, pl.P.KQP, pl.P.colsp, kgroup, chunks, stream);
     if (err != hipSuccess) return err;
 
     if (pl.fast) {
@@ -762,9 +803,10 @@ hipError_t launch_dma32(const ConvShape& s, const void* in, const void* kernel, 
         if (err != hipSuccess) return err;
         pl.P.in = paired;
     }
-    err = s.dtype == 0 ? launch_repack_split(s, pl, kernel, ws, stream)
-                       : launch_repack(s, kernel, ws, pl.kqp, pl.P.colsp, pl.P.kch,
-                                       pl.repack_bytes / 16, stream);
+    if (kernel != nullptr)
+        err = s.dtype == 0 ? launch_repack_split(s, pl, kernel, ws, stream)
+                           : launch_repack(s, kernel, ws, pl.kqp, pl.P.colsp, pl.P.kch,
+                                           pl.repack_bytes / 16, stream);
     if (err != hipSuccess) return err;
     err = launch_igemm32_dma(pl, stream);
     if (err != hipSuccess) return err;
@@ -775,24 +817,40 @@ hipError_t launch_dma32(const ConvShape& s, const void* in, const void* kernel, 
 
 }  // namespace
 
+namespace {
+
+KernelStrides kernel_strides(const ConvShape& s)
+{
+    if (s.kernel_view) return {s.k_base, s.k_sp, s.k_sq, s.k_sc, s.k_sm, s.k_sd0, s.k_sd2, s.k_sd3};
+    KernelStrides ks;  // dense [kh][kw][C][M][D0][D2][D3]
+    ks.base = 0;
+    ks.sd3 = 1;
+    ks.sd2 = s.D3;
+    ks.sd0 = (long long)s.D2 * s.D3;
+    ks.sm = ks.sd0 * s.D0;
+    ks.sc = ks.sm * s.M;
+    ks.sq = ks.sc * s.C;
+    ks.sp = ks.sq * s.kw;
+    return ks;
+}
+
+// Whether every chunk of 8 halves lies side by side in the kernel tensor, on a 16-byte boundary: the kernel read
+// transposed (input gradients), capsule rows of whole chunks.  One load in the place of 8, half the instructions.
+bool repack_reads_runs(const ConvShape& s, const KernelStrides& ks, const void* kernel)
+{
+    return s.dtype != 0 && s.D2 % 8 == 0 && ks.sd2 == 1 &&
+           (ks.base | ks.sp | ks.sq | ks.sc | ks.sm | ks.sd0 | ks.sd3) % 8 == 0 &&
+           (reinterpret_cast<uintptr_t>(kernel) & 15u) == 0;
+}
+
+}  // namespace
+
 hipError_t launch_repack(const ConvShape& s, const void* kernel, void* kp, int KQP,
                          int colsp, int kgroup, size_t chunks, hipStream_t stream)
 {
     const unsigned rblocks = (unsigned)((chunks + 255) / 256);
     const int ntaps = s.kh * s.kw, KT = s.C * s.D2, cols = s.M * s.D3;
-    KernelStrides ks;
-    if (s.kernel_view) {
-        ks = {s.k_base, s.k_sp, s.k_sq, s.k_sc, s.k_sm, s.k_sd0, s.k_sd2, s.k_sd3};
-    } else {  // dense [kh][kw][C][M][D0][D2][D3]
-        ks.base = 0;
-        ks.sd3 = 1;
-        ks.sd2 = s.D3;
-        ks.sd0 = (long long)s.D2 * s.D3;
-        ks.sm = ks.sd0 * s.D0;
-        ks.sc = ks.sm * s.M;
-        ks.sq = ks.sc * s.C;
-        ks.sp = ks.sq * s.kw;
-    }
+    const KernelStrides ks = kernel_strides(s);
     const auto launch = [&](auto kern, auto count, const auto* src, auto* dst) {
         kern<<<rblocks, 256, 0, stream>>>(src, dst, ntaps, s.kw, s.D2, s.D3, KT, KQP, cols, colsp, kgroup,
                                           ks, count);
@@ -801,15 +859,83 @@ hipError_t launch_repack(const ConvShape& s, const void* kernel, void* kp, int K
     if (s.dtype == 0) {
         const float* src = static_cast<const float*>(kernel);
         float* dst = static_cast<float*>(kp);
-        narrow ? launch(repack_kernel<float, 4, unsigned>, (unsigned)chunks, src, dst)
-               : launch(repack_kernel<float, 4, size_t>, chunks, src, dst);
+        narrow ? launch(repack_kernel<float, 4, false, unsigned>, (unsigned)chunks, src, dst)
+               : launch(repack_kernel<float, 4, false, size_t>, chunks, src, dst);
     } else {
         const unsigned short* src = static_cast<const unsigned short*>(kernel);
         unsigned short* dst = static_cast<unsigned short*>(kp);
-        narrow ? launch(repack_kernel<unsigned short, 8, unsigned>, (unsigned)chunks, src, dst)
-               : launch(repack_kernel<unsigned short, 8, size_t>, chunks, src, dst);
+        if (narrow && repack_reads_runs(s, ks, kernel))
+            launch(repack_kernel<unsigned short, 8, true, unsigned>, (unsigned)chunks, src, dst);
+        else
+            narrow ? launch(repack_kernel<unsigned short, 8, false, unsigned>, (unsigned)chunks, src, dst)
+                   : launch(repack_kernel<unsigned short, 8, false, size_t>, chunks, src, dst);
     }
     return hipGetLastError();
+}
+
+size_t mfma_repacked_bytes(const ConvShape& s, MfmaKernel which)
+{
+    if (s.dtype == 0) return 0;
+    if (which == MfmaKernel::Dma32) {
+        const Dma32Plan pl = igemm32_dma_plan(s);
+        return pl.partial_bytes == 0 && pl.pair_bytes == 0 ? pl.repack_bytes : 0;
+    }
+    const Plan pl = make_plan(s, which);
+    return pl.fast && pl.partial_bytes == 0 ? pl.repack_bytes : 0;
+}
+
+hipError_t launch_repack_views(const ConvShape* f, const MfmaKernel* which, void* const* kp, int n,
+                               const void* kernel, hipStream_t stream)
+{
+    if (n < 1 || n > MAX_REPACK_VIEWS) return hipErrorInvalidValue;
+    RepackViews V{};
+    V.ks = kernel_strides(f[0]);
+    V.n = n;
+    V.D2 = f[0].D2;
+    V.D3 = f[0].D3;
+    V.KT = f[0].C * f[0].D2;
+    V.cols = f[0].M * f[0].D3;
+    bool runs = true;
+    unsigned long long blocks = 0;
+    for (int i = 0; i < n; ++i) {
+        V.kp[i] = static_cast<chunk_t*>(kp[i]);
+        V.base[i] = f[i].k_base;
+        V.ntaps[i] = f[i].kh * f[i].kw;
+        V.kw[i] = f[i].kw;
+        size_t bytes;
+        if (which[i] == MfmaKernel::Dma32) {
+            const Dma32Plan pl = igemm32_dma_plan(f[i]);
+            V.KQP[i] = pl.kqp;
+            V.colsp[i] = pl.P.colsp;
+            V.kgroup[i] = pl.P.kch;
+            bytes = pl.repack_bytes;
+        } else {
+            const Plan pl = make_plan(f[i], which[i]);
+            V.KQP[i] = pl.P.KQP;
+            V.colsp[i] = pl.P.colsp;
+            V.kgroup[i] = igemm16_fast_kgroup(f[i]);
+            bytes = pl.repack_bytes;
+        }
+        if (bytes / 16 >= 0xffffff00u) return hipErrorInvalidValue;
+        V.chunks[i] = (unsigned)(bytes / 16);
+        V.first_block[i] = (unsigned)blocks;
+        blocks += (V.chunks[i] + 255u) / 256u;
+        runs = runs && repack_reads_runs(f[i], kernel_strides(f[i]), kernel);
+    }
+    if (blocks > 0x7fffffffULL) return hipErrorInvalidValue;
+    const unsigned short* src = static_cast<const unsigned short*>(kernel);
+    if (runs)
+        repack_views_kernel<true><<<(unsigned)blocks, 256, 0, stream>>>(src, V);
+    else
+        repack_views_kernel<false><<<(unsigned)blocks, 256, 0, stream>>>(src, V);
+    return hipGetLastError();
+}
+
+hipError_t launch_mfma_repacked(const ConvShape& s, const void* in, void* kp, float* out, hipStream_t stream,
+                                MfmaKernel which)
+{
+    return which == MfmaKernel::Dma32 ? launch_dma32(s, in, nullptr, out, kp, stream)
+                                      : launch_igemm(s, in, nullptr, out, kp, stream, which);
 }
 
 hipError_t launch_splitk_reduce(const float* partial, float* out, long long elems, int nsplit,
