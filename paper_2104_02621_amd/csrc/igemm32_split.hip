@@ -568,25 +568,31 @@ void igemm32_split_kernel(const Dma32Params P)
 }
 
 // Kernel repack: Kp[d0][column tile][K step][term of the split][half wave][column][8 bf16], in the
-// K order the contraction walks.  One thread per (K step, half wave, column): 8 values, split.
+// K order the contraction walks.
 struct SplitRepackParams {
     const float* kernel;
     chunk_t* kp;
     int ntaps, kw, D2, D3, KT, cols, bn, col_tiles, ksteps, nstages, cw;
     int triple, tile_cols;  // column order, see tile_columns
     long long k_base, k_sp, k_sq, k_sc, k_sm, k_sd0, k_sd2, k_sd3;
-    size_t total;  // threads
+    unsigned total;  // threads
 };
+// One thread per pair of values, which share the stage and are neighbours in K: index arithmetic bounds this pass, and
+// with a thread per 8 values (a set of divisions each, 64-bit ones for the place) the few waves of a kernel tensor
+// ran it one after the other.  1.0 MB of kernel (32 -> 32 channels of 3x3x3, 3x3 window): 9.8 -> 6.1 us; a forward pass
+// of it over 16 images of 16x16 59.2 -> 54.8, of 4x4 capsules 42.9 -> 39.5.
 __global__ __launch_bounds__(256) void repack_split_kernel(const SplitRepackParams P)
 {
-    const size_t id = (size_t)blockIdx.x * 256 + threadIdx.x;
+    const unsigned id = blockIdx.x * 256 + threadIdx.x;
     if (id >= P.total) return;
-    size_t r = id;
-    const int jl = (int)(r % P.bn); r /= P.bn;
-    const int h = (int)(r & 1);     r >>= 1;
-    const int ks = (int)(r % P.ksteps); r /= P.ksteps;
-    const int col_tile = (int)(r % P.col_tiles);
-    const int d0 = (int)(r / P.col_tiles);
+    const unsigned pair = id & 3;
+    unsigned r = id >> 2, next = r / (unsigned)P.bn;
+    const int jl = (int)(r - next * (unsigned)P.bn);
+    const int h = (int)(next & 1);
+    r = next >> 1;
+    const unsigned tile = r / (unsigned)P.ksteps;
+    const int ks = (int)(r - tile * (unsigned)P.ksteps);
+    const int d0 = (int)(tile / (unsigned)P.col_tiles), col_tile = (int)tile - d0 * P.col_tiles;
     // column of the tile at place jl of the matrix instructions' order
     int j = jl;
     if (P.triple) {
@@ -594,38 +600,33 @@ __global__ __launch_bounds__(256) void repack_split_kernel(const SplitRepackPara
         j = reg < P.tile_cols / 2 ? hw * (P.tile_cols / 2) + reg : P.cols;  // (past the last run: none)
     }
     j += col_tile * P.tile_cols;
-    const int m = j / P.D3, d3 = j - m * P.D3;
-    unsigned short w[3][8];
-#pragma unroll
-    for (int e = 0; e < 8; ++e) {
-        // stage and value (of the half wave's 2 slots) that the contraction has at this place
-        int stage = ks, v = e;
-        if (P.cw == 3) {
-            const int dword = 4 * (ks % 3) + e / 2;
-            stage = ks / 3 * 4 + dword / 3;
-            v = 2 * (dword % 3) + (e & 1);
-        }
-        const int grp = stage / P.ntaps, tap = stage - grp * P.ntaps;
-        const int k = (grp * SLOTS + 2 * h + v / P.cw) * P.cw + v % P.cw;
-        float x = 0.f;
-        if (stage < P.nstages && k < P.KT && j < P.cols) {
-            const int c = k / P.D2, d2 = k - c * P.D2;
-            const int p = tap / P.kw, q = tap - p * P.kw;
-            x = P.kernel[P.k_base + p * P.k_sp + q * P.k_sq + c * P.k_sc + m * P.k_sm + d0 * P.k_sd0 +
-                         d2 * P.k_sd2 + d3 * P.k_sd3];
-        }
-        unsigned short t[3];
-        split_kernel_value(x, t);
-#pragma unroll
-        for (int i = 0; i < 3; ++i) w[i][e] = t[i];
+    // stage, and first value of the pair among those of the half wave's 2 slots, that the contraction has here
+    unsigned stage = (unsigned)ks, v = 2 * pair;
+    if (P.cw == 3) {
+        const unsigned dword = 4 * (stage % 3) + pair, quarter = dword / 3;
+        stage = stage / 3 * 4 + quarter;
+        v = 2 * (dword - 3 * quarter);
     }
-    const size_t step = ((size_t)d0 * P.col_tiles + col_tile) * P.ksteps + ks;
-#pragma unroll
-    for (int t = 0; t < 3; ++t) {
-        chunk_t c;
-        __builtin_memcpy(&c, w[t], 16);
-        P.kp[((step * 3 + t) * 2 + h) * P.bn + jl] = c;
+    const unsigned grp = stage / (unsigned)P.ntaps, tap = stage - grp * (unsigned)P.ntaps;
+    const int k = ((int)grp * SLOTS + 2 * h) * P.cw + (int)v;
+    float x[2] = {0.f, 0.f};
+    if ((int)stage < P.nstages && k < P.KT && j < P.cols) {
+        const int c = (int)((unsigned)k / (unsigned)P.D2), d2 = k - c * P.D2;
+        const int p = (int)(tap / (unsigned)P.kw), q = (int)tap - p * P.kw;
+        const int m = (int)((unsigned)j / (unsigned)P.D3), d3 = j - m * P.D3;
+        const float* src = P.kernel + (P.k_base + p * P.k_sp + q * P.k_sq + c * P.k_sc + m * P.k_sm + d0 * P.k_sd0 +
+                                       d2 * P.k_sd2 + d3 * P.k_sd3);
+        x[0] = *src;
+        if (k + 1 < P.KT) x[1] = src[d2 + 1 < P.D2 ? P.k_sd2 : P.k_sc - d2 * P.k_sd2];
     }
+    unsigned short t[2][3];
+    split_kernel_value(x[0], t[0]);
+    split_kernel_value(x[1], t[1]);
+    const size_t step = (size_t)tile * P.ksteps + ks;
+    unsigned* kp = reinterpret_cast<unsigned*>(P.kp);
+#pragma unroll
+    for (int i = 0; i < 3; ++i)
+        kp[(((step * 3 + i) * 2 + h) * P.bn + jl) * 4 + pair] = t[0][i] | (unsigned)t[1][i] << 16;
 }
 
 template <int CW, int TN, int NW, bool TRIPLE>
@@ -699,9 +700,10 @@ hipError_t launch_repack_split(const ConvShape& s, const Dma32Plan& pl, const vo
         R.k_sq = R.k_sc * s.C;
         R.k_sp = R.k_sq * s.kw;
     }
-    R.total = pl.repack_bytes / 48;
-    const size_t blocks = (R.total + 255) / 256;
-    if (blocks == 0 || blocks > 0x7fffffffULL) return hipErrorInvalidValue;
+    const size_t total = pl.repack_bytes / 12;
+    if (total == 0 || total > 0x7fffff00ULL) return hipErrorInvalidValue;
+    R.total = (unsigned)total;
+    const size_t blocks = (total + 255) / 256;
     repack_split_kernel<<<(unsigned)blocks, 256, 0, stream>>>(R);
     return hipGetLastError();
 }
