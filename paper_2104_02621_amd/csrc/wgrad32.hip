@@ -115,18 +115,39 @@ struct Item {
     }
 };
 
-// dst[x][b][a] = src[x][a][b] for matrices of A x B floats.  One thread per element.
+// dst[x][b][a] = src[x][a][b] for matrices of A x B floats.  One thread per 4 neighbours of dst (on a 16-byte boundary).
+// Index arithmetic bounds it, not the two passes over memory: one set of divisions per 4 values, 32-bit ones where the
+// count fits (I).  Against a thread and two 64-bit divisions per value, the whole call: 20 images of 31x27, 20 -> 14
+// channels of 6x5 . 5x4, 5x5 window, trained, 736 -> 715 us; both gradients of 32 images of 20x20, 32 -> 24 channels of
+// 4x8 . 8x4, 346 -> 325.
+template <typename I>
 __global__ __launch_bounds__(256) void transpose_caps32_kernel(const float* __restrict__ src,
                                                                float* __restrict__ dst, int A,
-                                                               int B, size_t total)
+                                                               int B, I total)
 {
-    const size_t id = (size_t)blockIdx.x * 256 + threadIdx.x;
+    const I id = ((I)blockIdx.x * 256 + threadIdx.x) * 4;
     if (id >= total) return;
-    const int a = (int)(id % A);
-    const size_t rest = id / A;
-    const int b = (int)(rest % B);
-    const size_t mat = rest / B;
-    dst[id] = src[(mat * A + a) * B + b];
+    const I rest = id / (I)A, mat = rest / (I)B;
+    int a = (int)(id - rest * (I)A), b = (int)(rest - mat * (I)B);
+    const float* p = src + (size_t)mat * A * B;
+    const int n = total - id < 4 ? (int)(total - id) : 4;
+    float4v v = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        if (e < n) v[e] = p[a * B + b];
+        if (++a == A) {
+            a = 0;
+            if (++b == B) {
+                b = 0;
+                p += A * B;
+            }
+        }
+    }
+    if (n == 4) {
+        *reinterpret_cast<float4v*>(dst + id) = v;
+    } else {
+        for (int e = 0; e < n; ++e) dst[id + e] = v[e];
+    }
 }
 
 // NAT = 0: the operands are the capsule-transposed copies.  NAT = 1 (one chunk per capsule column)
@@ -924,10 +945,14 @@ hipError_t launch_transpose32(const void* src, void* dst, size_t nmat, int A, in
                               hipStream_t stream)
 {
     const size_t total = nmat * (size_t)A * B;
-    const size_t blocks = (total + 255) / 256;
+    const size_t blocks = (total + 1023) / 1024;
     if (blocks == 0 || blocks > 0x7fffffffULL) return hipErrorInvalidValue;
-    transpose_caps32_kernel<<<(unsigned)blocks, 256, 0, stream>>>(
-        static_cast<const float*>(src), static_cast<float*>(dst), A, B, total);
+    const float* from = static_cast<const float*>(src);
+    float* to = static_cast<float*>(dst);
+    if (total < 0xfffff000u)  // (the last threads' places too)
+        transpose_caps32_kernel<unsigned><<<(unsigned)blocks, 256, 0, stream>>>(from, to, A, B, (unsigned)total);
+    else
+        transpose_caps32_kernel<size_t><<<(unsigned)blocks, 256, 0, stream>>>(from, to, A, B, total);
     return hipGetLastError();
 }
 
