@@ -405,8 +405,8 @@ void igemm32_split_kernel(const Dma32Params P)
                 }
                 // all of this wave's copies but those of the input stage three ahead have landed,
                 // its reads are done; after the barrier both hold for every wave
-                constexpr int KEPT = AHEAD && has_step(next) ? 3 : 0;
-                asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(%1)\n\ts_barrier" ::"i"(SLOTS), "i"(KEPT) : "memory");
+                __builtin_amdgcn_s_waitcnt((0x0F70 | SLOTS) & 0xF0FF);
+                __syncthreads();
                 a_cur = a_next;
                 a_next = a_next + A_BYTES == NBA * A_BYTES ? 0 : a_next + A_BYTES;
                 b_cur = b_next;
