@@ -28,8 +28,9 @@ __device__ __forceinline__ float high_half(unsigned w) { return __builtin_bit_ca
 // instruction, but shares the matrix cores' pipe, whichever wave of the SIMD it comes from: a 32x32x16 matrix
 // instruction with two of them behind it takes 56 cycles, with four 63, and 37 alone or with six
 // multiplications or conversions.  Unpacking and subtracting are two instructions that run beside it.  Where
-// two waves of a SIMD hide each other's issue the latter is faster (igemm32_split.hip: 543 -> 523 us), where one
-// wave's issue is the limit, the former (wgrad32.hip: 672 against 680 us).
+// two waves of a SIMD hide each other's issue the latter is faster (igemm32_split.hip: 543 -> 522 us), where one
+// wave's issue is the limit, the former (wgrad32.hip: 672 against 680 us).  (The multiplication by SPLIT_SCALE before
+// them is exact, so contracting it with the subtraction changes no bit.)
 __device__ __forceinline__ float minus_low(float x, unsigned pair) { return x - low_half(pair); }
 __device__ __forceinline__ float minus_high(float x, unsigned pair) { return x - high_half(pair); }
 // The operands of minus_bf16 for the lower and the upper value of a pair, opaque to the compiler

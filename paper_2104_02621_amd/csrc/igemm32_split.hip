@@ -17,9 +17,9 @@
 // -6e-8, -4.9e-7, -2.3e-6, -4.8e-6 in one direction).
 //
 // Measured (N = 64, 32x32, 3x3, 32 -> 32 channels): 3x3x3 capsules 0.776 ms on the fp32
-// instructions, 0.524 ms here (error against 64-bit sums 5.2e-7 and 4.4e-7; 0.549 before the splitting left the
-// matrix cores' pipe alone, see minus_low, and kept to its gaps), 4x4 capsules 0.664
-// and 0.41 ms, 8x8 capsules 4.37 and 2.81 ms (211 TFLOP/s).  The long K loops run at the clock the
+// instructions, 0.522 ms here (error against 64-bit sums 5.2e-7 and 4.4e-7), 4x4 capsules 0.664
+// and 0.333 ms, 8x8 capsules 4.37 and 2.55 ms (232 TFLOP/s).  With the splitting on the matrix cores' pipe (minus_bf16
+// in the place of minus_low) 0.543, 0.348 and 2.68 ms.  The long K loops run at the clock the
 // power limit leaves (1.5 .. 1.6 GHz); 3-float chunks also at the rate of the L1 lookups (57 per
 // copy, 16 where 4-float rows lie side by side).
 //
@@ -71,12 +71,6 @@ constexpr int kernel_ring(int tn) { return tn == 4 ? 2 : 3; }
 // order of the matrix instruction: 8g + 4h + i in registers 4g + i.
 constexpr int column_runs(int tn) { return 16 * tn / 3; }
 constexpr int tile_columns(bool triple, int tn) { return triple ? 6 * column_runs(tn) : 32 * tn; }
-
-// Keeps an operation in its place: the value is final here, and its uses come after.  (Arithmetic has no order to
-// the compiler: the splitting steps dealt out over the gaps were gathered in a few of them, in front of the
-// first matrix instruction above all.)
-template <typename T>
-__device__ __forceinline__ void pin(T& x) { asm volatile("" : "+v"(x)); }
 
 template <int CW, int TN, int NW, bool TRIPLE>
 __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(NW == 4 ? 2 : 1)))
@@ -199,7 +193,8 @@ void igemm32_split_kernel(const Dma32Params P)
     // input copies of the next stage into the ring slot at LDS address `slot`: this lane's row ...
     unsigned a_voff;
     auto begin_a = [&]() {
-        // (no branch: it would cut the stage's one basic block, and with it the deal of the side operations)
+        // (no branch: it would cut the stage's one basic block; 5x5 window, 20 images of 31x27, 20 -> 14 channels of
+        // 6x5 . 5x4, 211.4 -> 209.0 us, its input gradient 196.7 -> 193.9; 3x3x3 layers 524.8 -> 522.1)
         const unsigned live = issued < my_stages ? 1u : 0u;
         a_voff = ((unsigned)(tap_ok >> tap) & live) != 0 ? (unsigned)row_off : (unsigned)OOB;
     };
@@ -262,23 +257,16 @@ void igemm32_split_kernel(const Dma32Params P)
         auto split_step = [&](int p, int k, int pos) {
             unsigned(&w)[3][WORDS] = iv[p / CW];
             const int at = pos * CW + p % CW, t = (k - 2) / 3;
-            if (k == 0) {
-                pin(lo[p]);
+            if (k == 0)
                 lo[p] *= __builtin_bit_cast(float, in_scale);
-            } else if (k == 1) {
-                pin(hi[p]);
+            else if (k == 1)
                 hi[p] *= __builtin_bit_cast(float, in_scale);
-            } else if (k % 3 == 2) {
-                pin(lo[p]);
-                pin(hi[p]);
+            else if (k % 3 == 2)
                 w[t][at] = round_pair(lo[p], hi[p]);
-            } else if (k % 3 == 0) {
-                pin(w[t][at]);
+            else if (k % 3 == 0)
                 lo[p] = minus_low(lo[p], w[t][at]);
-            } else {
-                pin(hi[p]);
+            else
                 hi[p] = minus_high(hi[p], w[t][at]);
-            }
         };
         auto take_input = [&](const char* slot) {
             float4v raw[TM][2];
