@@ -264,6 +264,7 @@ void view_phase_kernel(const ConvShape& s, const PhaseDim& ph, const PhaseDim& p
 // The input gradient as phases in one launch of the small-tile kernel (any window, padding and
 // stride up to 4; a stride of 1 is one phase).  Returns their number, 0 if there are too many.
 constexpr int kMaxPhases = 16;
+static_assert(kMaxPhases <= MAX_REPACK_VIEWS);
 int bwd_input_phases(const ConvShape& s, ConvShape (&f)[kMaxPhases])
 {
     if (s.stride > 4) return 0;
@@ -293,6 +294,50 @@ bool bwd_input_as_phases(const ConvShape& s)
             if (phase_kernel(f) == 0) return false;
         }
     return true;
+}
+
+// The phases that have both pixels and taps, for the tuned kernels, and where in the scratch their repacked kernels lie
+// when one launch packs them all (`together`: those of a 16-bit layer that fit the scratch side by side; nearly always,
+// not where few columns are padded to twice their number), else each phase's lies at `paired`, packed before it.
+// One launch against one per phase: 18 random layers 0.85 .. 0.99 of the time, 0.95 on average (108 images of 22x22,
+// 5 -> 3 channels of 8x8 capsules, 49.2 -> 41.8 us); 128 images of 28x28, 64 -> 64 channels of 8x8, 1014 -> 1007.
+struct PhaseRun {
+    int n;
+    ConvShape f[kMaxPhases];
+    MfmaKernel which[kMaxPhases];
+    RepackLayout layout[kMaxPhases];
+    size_t at[kMaxPhases];
+    size_t paired;  // bytes of the output gradient with its channels paired, at the scratch's start
+    bool together;
+};
+void bwd_input_phase_run(const ConvShape& s, size_t scratch_bytes, PhaseRun& r)
+{
+    r.paired = phases_pair_dout(s) ? align256(s.out_elems() * elem_bytes(s)) : 0;
+    r.n = 0;
+    for (int a = 0; a < s.stride; ++a)
+        for (int b = 0; b < s.stride; ++b) {
+            const PhaseDim ph = phase_dim(s.H, s.kh, s.stride, s.pad, a);
+            const PhaseDim pw = phase_dim(s.W, s.kw, s.stride, s.pad, b);
+            if (ph.count == 0 || pw.count == 0 || ph.taps == 0 || pw.taps == 0) continue;
+            // the phase's kernel Kab[i'][j'][m][c][d0][d3][d2] =
+            // K[a + s*(taps_h-1-i')][b + s*(taps_w-1-j')][c][m][d0][d2][d3] is read in place:
+            // the repack pass of the convolution takes it through strides
+            ConvShape& f = r.f[r.n];
+            f = bwd_input_phase_shape(s, ph, pw, a, b);
+            view_phase_kernel(s, ph, pw, a, b, f);
+            const bool lane_per_row = phase_kernel(f) == 32;
+            f.in_paired = lane_per_row && r.paired > 0;
+            r.which[r.n++] = lane_per_row ? MfmaKernel::Dma32 : MfmaKernel::Tuned16;
+        }
+    size_t at = r.paired;
+    r.together = r.n > 1;
+    for (int i = 0; i < r.n && r.together; ++i) {
+        r.layout[i] = mfma_repack_layout(r.f[i], r.which[i]);
+        r.at[i] = at;
+        const size_t bytes = align256(r.layout[i].bytes);
+        r.together = bytes != 0 && bytes <= scratch_bytes - at;
+        at += bytes;
+    }
 }
 
 // zero the pixels (n, h0 + i*sh, w0 + j*sw), i < nh, j < nw, of a tensor [N][H][W][pix] of fp32
@@ -446,7 +491,8 @@ BwdInputPlan bwd_input_plan(const ConvShape& s)
                 const size_t need = mfma_workspace_bytes(f);
                 if (need > fwd) fwd = need;
             }
-        // the phases' sub-kernels together are one kernel tensor
+        // (the kernel tensor's size and the largest phase's scratch: room for all phases' repacked kernels side by
+        // side, padding apart)
         plan.bytes = kbytes + fwd + (phases_pair_dout(s) ? align256(s.out_elems() * elem_bytes(s)) : 0);
     } else if (bwd_input_as_conv(s)) {
         const ConvShape f = bwd_input_conv_shape(s);
@@ -485,6 +531,14 @@ RouteInfo bwd_input_route(const ConvShape& s, const BwdInputPlan& plan, size_t w
         pick = forward_small_tiles(f, plan.fwd, workspace_bytes > used ? workspace_bytes - used : 0);
     }
     return {pick.tile, pick.nsplit, plan.form};
+}
+
+bool bwd_input_repacks_together(const ConvShape& s, const BwdInputPlan& plan)
+{
+    if (plan.form != BwdInputPlan::Phases || bwd_input_route(s, plan, plan.bytes).tile >= 0) return false;
+    PhaseRun r;
+    bwd_input_phase_run(s, plan.bytes, r);
+    return r.together;
 }
 
 RouteInfo bwd_kernel_route(const ConvShape& s, size_t need, size_t workspace_bytes)
@@ -527,77 +581,50 @@ int launch_bwd_input(const ConvShape& s, const BwdInputPlan& plan, const void* d
     }
     if (plan.form == BwdInputPlan::Phases) {
         char* ws = static_cast<char*>(workspace);
-        const size_t kbytes = align256(s.kernel_elems() * eb);
         const long long pix = (long long)s.C * s.D0 * s.D1 * s.D2;
-        size_t used = 0;
-        const void* dout_paired = nullptr;
-        if (phases_pair_dout(s)) {
-            void* dst = ws + used;
-            used += align256(s.out_elems() * eb);
-            const hipError_t err = launch_pair_channels(dout, dst, (size_t)s.N * s.Ho * s.Wo, s.M,
+        PhaseRun r;
+        bwd_input_phase_run(s, plan.bytes, r);
+        if (r.paired > 0) {
+            const hipError_t err = launch_pair_channels(dout, ws, (size_t)s.N * s.Ho * s.Wo, s.M,
                                                         s.D0 * s.D1, stream);
             if (err != hipSuccess) return status_from_hip(err);
-            dout_paired = dst;
         }
-        ConvShape f[kMaxPhases];
-        MfmaKernel which[kMaxPhases];
-        int n = 0;
         for (int a = 0; a < s.stride; ++a)
             for (int b = 0; b < s.stride; ++b) {
                 const PhaseDim ph = phase_dim(s.H, s.kh, s.stride, s.pad, a);
                 const PhaseDim pw = phase_dim(s.W, s.kw, s.stride, s.pad, b);
                 if (ph.count == 0 || pw.count == 0) continue;  // no pixel of dI in this phase
+                if (ph.taps > 0 && pw.taps > 0) continue;
+                // pixels no window reaches
                 const int h0 = s.stride * ph.lo + a - s.pad, w0 = s.stride * pw.lo + b - s.pad;
-                if (ph.taps == 0 || pw.taps == 0) {  // pixels no window reaches
-                    const size_t total = (size_t)s.N * ph.count * pw.count * pix;
-                    const size_t blocks = (total + 255) / 256;
-                    if (blocks > 0x7fffffffULL) return status_from_hip(hipErrorInvalidValue);
-                    if (s.out16 != 0)
-                        zero_pixels_kernel<unsigned short><<<(unsigned)blocks, 256, 0, stream>>>(
-                            reinterpret_cast<unsigned short*>(din), s.H, s.W, pix, h0, s.stride,
-                            ph.count, w0, s.stride, pw.count, total);
-                    else
-                        zero_pixels_kernel<float><<<(unsigned)blocks, 256, 0, stream>>>(
-                            din, s.H, s.W, pix, h0, s.stride, ph.count, w0, s.stride, pw.count,
-                            total);
-                    const hipError_t err = hipGetLastError();
-                    if (err != hipSuccess) return status_from_hip(err);
-                    continue;
-                }
-                // the phase's kernel Kab[i'][j'][m][c][d0][d3][d2] =
-                // K[a + s*(taps_h-1-i')][b + s*(taps_w-1-j')][c][m][d0][d2][d3] is read in place:
-                // the repack pass of the convolution takes it through strides
-                f[n] = bwd_input_phase_shape(s, ph, pw, a, b);
-                view_phase_kernel(s, ph, pw, a, b, f[n]);
-                const bool lane_per_row = phase_kernel(f[n]) == 32;
-                f[n].in_paired = lane_per_row && dout_paired != nullptr;
-                which[n++] = lane_per_row ? MfmaKernel::Dma32 : MfmaKernel::Tuned16;
+                const size_t total = (size_t)s.N * ph.count * pw.count * pix;
+                const size_t blocks = (total + 255) / 256;
+                if (blocks > 0x7fffffffULL) return status_from_hip(hipErrorInvalidValue);
+                if (s.out16 != 0)
+                    zero_pixels_kernel<unsigned short><<<(unsigned)blocks, 256, 0, stream>>>(
+                        reinterpret_cast<unsigned short*>(din), s.H, s.W, pix, h0, s.stride,
+                        ph.count, w0, s.stride, pw.count, total);
+                else
+                    zero_pixels_kernel<float><<<(unsigned)blocks, 256, 0, stream>>>(
+                        din, s.H, s.W, pix, h0, s.stride, ph.count, w0, s.stride, pw.count,
+                        total);
+                const hipError_t err = hipGetLastError();
+                if (err != hipSuccess) return status_from_hip(err);
             }
-        // one repack launch for all phases of a 16-bit layer where their kernels fit the scratch together (it holds the
-        // largest and a whole kernel tensor: nearly always; not where few columns are padded to twice their number),
-        // else each phase's before it.  With both gradients: 128 images of 28x28, 64 -> 64 channels of 8x8,
-        // 1696 -> 1685 us; a five-layer stack with two such layers, trained, 2362 -> 2339
-        size_t at = used;
-        void* kp[kMaxPhases];
-        bool together = n > 1;
-        for (int i = 0; i < n && together; ++i) {
-            const size_t bytes = align256(mfma_repacked_bytes(f[i], which[i]));
-            together = bytes != 0 && bytes <= plan.bytes - at;
-            kp[i] = ws + at;
-            at += bytes;
-        }
-        if (together) {
-            const hipError_t err = launch_repack_views(f, which, kp, n, kernel, stream);
+        if (r.together) {
+            void* kp[kMaxPhases];
+            for (int i = 0; i < r.n; ++i) kp[i] = ws + r.at[i];
+            const hipError_t err = launch_repack_views(r.f, r.layout, kp, r.n, kernel, stream);
             if (err != hipSuccess) return status_from_hip(err);
         }
-        const size_t own = workspace_bytes > used + kbytes ? used + kbytes : workspace_bytes;
-        for (int i = 0; i < n; ++i) {
-            const void* g = f[i].in_paired ? dout_paired : dout;
+        for (int i = 0; i < r.n; ++i) {
+            const void* g = r.f[i].in_paired ? ws : dout;
+            char* own = ws + r.paired;
+            const size_t own_bytes = workspace_bytes - r.paired;
             const int rc =
-                together ? status_from_hip(launch_mfma_repacked(f[i], g, kp[i], din, stream, which[i]))
-                : which[i] == MfmaKernel::Dma32
-                    ? forward_tuned32(f[i], g, kernel, din, ws + own, workspace_bytes - own, stream)
-                    : forward_tuned16(f[i], g, kernel, din, ws + own, workspace_bytes - own, stream);
+                r.together ? status_from_hip(launch_mfma_repacked(r.f[i], g, ws + r.at[i], din, stream, r.which[i]))
+                : r.which[i] == MfmaKernel::Dma32 ? forward_tuned32(r.f[i], g, kernel, din, own, own_bytes, stream)
+                                                  : forward_tuned16(r.f[i], g, kernel, din, own, own_bytes, stream);
             if (rc != 0) return rc;
         }
         return 0;

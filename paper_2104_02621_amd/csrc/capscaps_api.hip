@@ -581,6 +581,14 @@ int capscaps_testing_route(int op, const int* shape, int out16, const int* small
     return CAPSCAPS_OK;
 }
 
+// 1: one launch repacks the kernels of this input gradient's phases; 0: there is none, or a launch for each
+int capscaps_testing_repacks_together(const int* shape, int out16, const int* small_tiles)
+{
+    ConvShape s;
+    if (testing_shape(s, shape, out16, small_tiles) != CAPSCAPS_OK) return 0;
+    return capscaps::bwd_input_repacks_together(s, capscaps::bwd_input_plan(s));
+}
+
 const char* capscaps_last_hip_error(void) { return hipGetErrorString(g_last_hip_error); }
 
 const char* capscaps_strerror(int status)

@@ -94,11 +94,15 @@ hipError_t launch_wave_conv(const ConvShape& s, const void* in, const void* kern
 // Rechunk: fp32 layers whose rows are written out in runs of four K values first (igemm_conv.hip).
 enum class MfmaKernel { Auto, Generic, Tuned16, Dma32, Small, Rechunk };
 // Several 16-bit convolutions whose kernels are views of one tensor (equal but for the window and k_base), on the
-// tuned kernels: one repack launch for all, then each by itself.  mfma_repacked_bytes: what one's repacked kernel
-// takes; 0 = it needs more scratch than that, or is not for this.
+// tuned kernels: one repack launch for all, then each by itself.  RepackLayout: the bytes of one's repacked kernel and
+// its order; 0 bytes = it needs more scratch than that, or is not for this.
 constexpr int MAX_REPACK_VIEWS = 16;
-size_t mfma_repacked_bytes(const ConvShape& s, MfmaKernel which);
-hipError_t launch_repack_views(const ConvShape* f, const MfmaKernel* which, void* const* kp, int n,
+struct RepackLayout {
+    size_t bytes;
+    int KQP, colsp, kgroup;
+};
+RepackLayout mfma_repack_layout(const ConvShape& s, MfmaKernel which);
+hipError_t launch_repack_views(const ConvShape* f, const RepackLayout* layout, void* const* kp, int n,
                                const void* kernel, hipStream_t stream);
 hipError_t launch_mfma_repacked(const ConvShape& s, const void* in, void* kp, float* out, hipStream_t stream,
                                 MfmaKernel which);
@@ -155,6 +159,7 @@ struct RouteInfo {
 };
 RouteInfo bwd_input_route(const ConvShape& s, const BwdInputPlan& plan, size_t workspace_bytes);
 RouteInfo bwd_kernel_route(const ConvShape& s, size_t need, size_t workspace_bytes);
+bool bwd_input_repacks_together(const ConvShape& s, const BwdInputPlan& plan);  // (for tests) its phases' kernels
 size_t bwd_kernel_workspace_bytes(const ConvShape& s);
 // Return a status code of the C ABI; the caller has checked the scratch (`need`: of the kernel gradient).
 int launch_bwd_input(const ConvShape& s, const BwdInputPlan& plan, const void* dout, const void* kernel,

@@ -88,6 +88,13 @@ def route(w: wl.Workload, op, tiles=BY_RULE, out16=False, workspace_bytes=1 << 4
     return tuple(info)
 
 
+def repacks_together(w: wl.Workload, tiles=BY_RULE, out16=False):
+    """Does one launch repack the kernels of this input gradient's phases?"""
+    fn = cc._load().capscaps_testing_repacks_together
+    fn.argtypes = [ctypes.c_void_p, ctypes.c_int, ctypes.c_void_p]
+    return bool(fn(_ints(shape_args(w)), int(out16), _ints(tiles)))
+
+
 def run_op(w: wl.Workload, op, a_dev, b_dev, tiles=BY_RULE, out16=False):
     """A forward pass or gradient with the given use of the small-tile kernels -> device tensor."""
     import torch
