@@ -25,12 +25,12 @@ __device__ __forceinline__ unsigned round_pair(float lo, float hi)
 __device__ __forceinline__ float low_half(unsigned w) { return __builtin_bit_cast(float, w << 16); }
 __device__ __forceinline__ float high_half(unsigned w) { return __builtin_bit_cast(float, w & 0xffff0000u); }
 // x minus one of the two values of `pair`, exact here.  Two forms: v_dot2_f32_bf16 with a pair of factors 0 and -1 is one
-// instruction, but shares the matrix cores' pipe, whichever wave of the SIMD it comes from: a 32x32x16 matrix
-// instruction with two of them behind it takes 56 cycles, with four 63, and 37 alone or with six
-// multiplications or conversions.  Unpacking and subtracting are two instructions that run beside it.  Where
+// instruction, but shares the matrix cores' pipe, whichever wave of the SIMD it comes from: with two waves per SIMD a
+// 32x32x16 matrix instruction with two of them behind it takes 54 cycles, with four 63; alone 33, with six
+// multiplications 36, six conversions 39.  Unpacking and subtracting are two instructions that run beside it.  Where
 // two waves of a SIMD hide each other's issue the latter is faster (igemm32_split.hip: 543 -> 522 us), where one
 // wave's issue is the limit, the former (wgrad32.hip: 672 against 680 us).  (The multiplication by SPLIT_SCALE before
-// them is exact, so contracting it with the subtraction changes no bit.)
+// them is exact below 2^104, so contracting it with the subtraction changes no bit; above, the sums are taken again.)
 __device__ __forceinline__ float minus_low(float x, unsigned pair) { return x - low_half(pair); }
 __device__ __forceinline__ float minus_high(float x, unsigned pair) { return x - high_half(pair); }
 // The operands of minus_bf16 for the lower and the upper value of a pair, opaque to the compiler
@@ -51,9 +51,9 @@ constexpr float SPLIT_UNSCALE = 0x1p-46f;  // ... and of the sums of their produ
 // Sums over split values that have to be taken again on the fp32 instructions: those that are not
 // finite (an infinity, a NaN, a value or a sum that the scale factors take out of range).  A workgroup
 // takes all of its sums again, one stage at a time, which is the one case where the time of a call
-// depends on its data: 32 -> 32 channels of 3x3x3 capsules, N = 64, 32x32, with a NaN in every tile 1.5
-// instead of 0.57 ms forward, 1.6 instead of 0.67 ms kernel gradient; one infinity in the input reaches a
-// few tiles (forward 0.57 ms) but a whole range of every tap's pixels (kernel gradient 0.86 ms).
+// depends on its data: 32 -> 32 channels of 3x3x3 capsules, N = 64, 32x32, with a NaN in every tile 1.43
+// instead of 0.54 ms forward, 1.67 instead of 0.68 ms kernel gradient; one infinity in the input reaches a
+// few tiles (forward 0.53 ms) but a whole range of every tap's pixels (kernel gradient 0.85 ms).
 // Values of 1e-37: no difference.
 struct SplitCheck {
     float poison = 0.f;

@@ -511,7 +511,9 @@ namespace {
 
 // Estimated times of an fp32 layer, us, least-squares fits over 730 random layers of 0.3 .. 8 GFLOP (most
 // within 15 % of the measured time): three launches, the stages of the rounds of tiles, partial sums and the
-// packed kernel written and read ...
+// packed kernel written and read ...  (Fitted before the splitting left the matrix cores' pipe and the packing took a
+// thread per pair: 15 random layers of up to 8 GFLOP since take 0.87 of the time, so that layers near the line may stay on
+// the other kernels.)
 double split_us(const Dma32Plan& pl)
 {
     const double rounds = ceil((double)pl.blocks / (pl.nw == 4 ? 512 : 1024));

@@ -688,11 +688,8 @@ hipError_t launch_repack_split(const ConvShape& s, const Dma32Plan& pl, const vo
         R.k_sq = R.k_sc * s.C;
         R.k_sp = R.k_sq * s.kw;
     }
-    const size_t total = pl.repack_bytes / 12;
-    if (total == 0 || total > 0x7fffff00ULL) return hipErrorInvalidValue;
-    R.total = (unsigned)total;
-    const size_t blocks = (total + 255) / 256;
-    repack_split_kernel<<<(unsigned)blocks, 256, 0, stream>>>(R);
+    R.total = (unsigned)(pl.repack_bytes / 12);  // (igemm32_dma_eligible keeps the packed kernel below 2 GiB)
+    repack_split_kernel<<<(R.total + 255) / 256, 256, 0, stream>>>(R);
     return hipGetLastError();
 }
 

@@ -980,7 +980,7 @@ bool wgrad32_eligible(const ConvShape& s)
 
 // A fit over 47 random layers of square capsules, 0.001 .. 38 GFLOP, 16 % root mean square: launches, the tiles'
 // estimate (its scale is that of six layers of 576 rows and columns), and the partial sums of as many ranges as
-// the reduction is worth.
+// the reduction is worth.  The transposed copies of unequal capsules are not in it.
 double wgrad32_us(const ConvShape& s)
 {
     Wgrad32Params P{};
