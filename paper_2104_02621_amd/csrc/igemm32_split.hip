@@ -248,6 +248,13 @@ void igemm32_split_kernel(const Dma32Params P)
     // ---- the K loop on the split values
     {
         constexpr int FLIP = 96;  // stages; a multiple of both periods
+        // One-wave workgroups are at most one per SIMD (Dma32Plan::nw): with one column tile, splitting as many values for
+        // the fewest matrix instructions, their wave's issue is the limit, and dot products take the remainders.  10
+        // random layers 0.94 .. 0.98 of the time of subtractions (47 -> 5 channels of 4x8 . 8x4, 19 images of 29x29, 106.6 ->
+        // 100.2 us); with two column tiles 0.99 .. 1.03 (11 layers), with three and four 1.01 .. 1.09 (20), four-wave
+        // workgroups 0.98 .. 1.10 (119).
+        constexpr bool DOT = NW == 1 && TN == 1;
+        const MinusOne one;
         // of the input values being split; the ranges of a split K loop begin with either sign
         unsigned in_scale = __builtin_bit_cast(unsigned, SPLIT_SCALE) | (unsigned)split << 31;
         // K values of one period, split: pairs per row tile and term
@@ -264,9 +271,9 @@ void igemm32_split_kernel(const Dma32Params P)
             else if (k % 3 == 2)
                 w[t][at] = round_pair(lo[p], hi[p]);
             else if (k % 3 == 0)
-                lo[p] = minus_low(lo[p], w[t][at]);
+                lo[p] = DOT ? minus_bf16(lo[p], w[t][at], one.lo) : minus_low(lo[p], w[t][at]);
             else
-                hi[p] = minus_high(hi[p], w[t][at]);
+                hi[p] = DOT ? minus_bf16(hi[p], w[t][at], one.hi) : minus_high(hi[p], w[t][at]);
         };
         auto take_input = [&](const char* slot) {
             float4v raw[TM][2];

@@ -29,6 +29,8 @@ SHAPES = [
     (1, 5, 5, 1, 1, 3, 3, 1, 0, 1, 1, 4, 4),     # a single row tile, nearly empty
     (20, 24, 24, 3, 6, 3, 3, 1, 1, 1, 4, 3, 5),  # more than 560 tiles of 64 rows: one-wave tiles
     (70, 33, 32, 2, 4, 3, 3, 1, 1, 1, 1, 4, 4),  # more than 256 tiles of 256 rows
+    (20, 24, 24, 3, 8, 3, 3, 1, 1, 1, 4, 4, 4),  # one-wave tiles of one column tile, 4-float chunks ...
+    (24, 24, 24, 2, 10, 3, 3, 1, 1, 1, 3, 3, 3),  # ... and stored by runs of three
 ]
 
 
